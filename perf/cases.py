@@ -159,6 +159,7 @@ def prepare(case, seed):
             who = _liars(g, mask, beta, A)
             lie.scatter_(1, who[:, :, None].expand(-1, -1, C), 10.0 * torch.randn((G, A, C), generator=g, device=DEVICE))
         lie = lie.view(G * N, C)
+        s["weight"], s["lie"] = weight, lie
         s["model"] = lambda coded: torch.addmm(lie, coded, weight)
         return s
     G = case["G"]
@@ -238,3 +239,89 @@ def tolerance(case):
     if case["op"] == "serve":
         return {"rel": 1e-6, "max": 1e-5, "differ": 1e-3}
     return {"rel": 1e-7, "max": 4e-7, "differ": 1e-4}
+
+
+# ---- the same results in 64 bits, in plain torch -----------------------------------------------------------------------
+def _chebyshev(K, N):
+    return (np.cos((2.0 * np.arange(K) + 1.0) * math.pi / (2.0 * K)), np.cos(np.arange(N) * math.pi / (N - 1.0)))
+
+
+def _exact_decode(preds, mask, K, sign):
+    """[G, K, C] float64: the decoder over the workers of each mask."""
+    alpha, beta = (torch.from_numpy(x).to(preds.device) for x in _chebyshev(K, mask.shape[1]))
+    m = mask.double()
+    parity = (m.cumsum(1) - 1.0) if sign else torch.arange(mask.shape[1], device=preds.device).expand_as(m)
+    d = alpha[:, None] - beta[None, :]                        # [K, N]
+    t = (m * (1.0 - 2.0 * (parity % 2)))[:, None, :] / torch.where(d == 0, torch.ones_like(d), d)
+    w = t / t.sum(2, keepdim=True)
+    hit = (d == 0)[None] & (mask[:, None, :] != 0)            # a query node that is a surviving worker's: its own row
+    w = torch.where(hit.any(2, keepdim=True), hit.double(), w)
+    return torch.matmul(w, torch.where(mask[:, :, None] != 0, preds.double(), 0.0))
+
+
+def _exact_located(preds, mask, n, K, A, homogeneous):
+    """(int64 [G, A] ascending, uint8 mask without them): Algorithm 2, or Algorithm 1, per class, and the vote."""
+    G, N, C = preds.shape
+    M = K + A
+    _, beta = _chebyshev(K, N)
+    avail = (mask.cpu() == 0).to(torch.int8).argsort(dim=1, stable=True)[:, :n]                  
+    x = torch.from_numpy(beta)[avail]                                                        # [G, n]
+    y = preds.cpu().double().gather(1, avail[:, :, None].expand(-1, -1, C)).transpose(1, 2)  # [G, C, n]
+    V = x[:, :, None] ** torch.arange(M)
+    votes = torch.zeros((G, N), dtype=torch.int64)
+    step = max(1, 20000 // C)
+    for g in range(0, G, step):
+        v, yy = V[g:g + step], y[g:g + step]
+        if homogeneous:
+            h = torch.cat([v[:, None].expand(-1, C, -1, -1), yy[..., None] * v[:, None]], dim=3)
+            q = torch.linalg.svd(h, full_matrices=False).Vh[..., -1, M:]
+        else:
+            u = torch.linalg.qr(v, mode="complete").Q[:, :, M:].transpose(1, 2)              # [., n - M, n]
+            b = u[:, None] @ (yy[..., None] * v[:, None])
+            q = torch.linalg.lstsq(b[..., 1:], -b[..., :1]).solution[..., 0]
+            q = torch.cat([torch.ones_like(q[..., :1]), q], dim=-1)
+        a = (v[:, None] @ q[..., None])[..., 0].abs()
+        pick = a.argsort(dim=2, stable=True)[..., :A].flatten(1)                                 # [., C A] positions
+        votes[g:g + step].scatter_add_(1, avail[g:g + step].gather(1, pick), torch.ones_like(pick))
+    adv = (-votes).argsort(dim=1, stable=True)[:, :A].sort(1).values
+    return adv, mask.scatter(1, adv.to(mask.device), 0)
+
+
+def exact(case, seed):
+    if case.get("A", 0) and case["op"] != "serve" and case["G"] * case["C"] > 100000:
+        return None                                           # the fits, on the host, would take too long
+    s = prepare(case, seed)
+    K, N, S, A, op = case["K"], case["N"], case["S"], case["A"], case["op"]
+    alpha, beta = _chebyshev(K, N)
+    w = torch.from_numpy(_interpolation(alpha, beta)).to(DEVICE)
+    if op == "encode":
+        q = s["queries"]
+        if 8.0 * q.shape[0] * N * q.shape[2] > 1.4e10:
+            return None
+        return torch.stack([torch.matmul(w, x.double()) for x in q])
+    if op == "serve":
+        x = s["stream"].double()
+        G = -(-case["Q"] // K)
+        x = torch.cat([x, x[-1:].expand(G * K - case["Q"], -1)]).view(G, K, -1)
+        coded = torch.matmul(w, x)
+        preds = torch.matmul(coded.view(G * N, -1), s["weight"].double()).add_(s["lie"].double()).view(G, N, -1)
+        rank = s["arrival"].argsort(dim=1, stable=True).argsort(1)
+        mask = (rank < N - S).to(torch.uint8)
+    else:
+        preds, mask, G = s["preds"], s["mask"], case["G"]
+    left = mask
+    if A:
+        adv, left = _exact_located(preds, mask, N - S, K, A, op == "homogeneous")
+        adv = adv.to(DEVICE, torch.int32)
+    out = _exact_decode(preds, left, K, case["sign"])
+    status = torch.zeros((G,), device=DEVICE, dtype=torch.int32)
+    score, top1 = out.max(2)
+    top1 = top1.to(torch.int32)
+    if op == "decode":
+        return out, status
+    if op == "top1":
+        return top1, score, status
+    if op != "serve":
+        return out, adv, status
+    whole = [coded, preds, mask, top1.view(-1)[:case["Q"]], status]
+    return whole + [out.view(G * K, -1)[:case["Q"]], adv] if A else whole
