@@ -173,9 +173,7 @@ template <int LANE>
 __device__ __forceinline__ double row_bcast(double v) {   // lane LANE of every 16-lane row, to the whole row
     // all rows and banks enabled and every source lane exists: the 'old' operand is never used, and with
     // bound_ctrl set the compiler knows it and does not materialise it
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + LANE, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + LANE, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + LANE, 0xF, 0xF, true);
 }
 
 // The same for a lane index that is only known after unrolling.
@@ -307,7 +305,149 @@ __device__ __forceinline__ void shared_complement_basis(const double *Pw, int n,
     }
 }
 
-// ---- per class: Householder QR of the projected system, in registers ----------------------------
+// ---- broadcast multiply-adds along a 16-lane row -------------------------------------------------
+// v_fmac_f64 takes its first factor from one lane of the row by itself (row_newbcast), at the rate of a plain
+// v_fmac_f64 (4 cycles per wave measured for either); the compiler spends a 64-bit move per broadcast instead.  The
+// passes over a column are therefore written out:
+//     row_dot:   d0, d1 += bcast(a[r]) * b[r]     (even and odd r: two chains)
+//     row_axpy:  a[r]   += bcast(b[r]) * f
+// A DPP operand must not be read within two wait states of the VALU instruction that wrote it, and the compiler does
+// not see into a block: each opens with s_nop 1, and inside no instruction reads what an earlier one wrote as its
+// DPP operand.  `b` may be `a` itself: every element is read before it is written, once.
+// Results of matrix instructions must pass matrix_results_settled() first (the same blindness, up to 19 wait states).
+#define APX_DPP " row_newbcast:%[l] row_mask:0xf bank_mask:0xf\n"
+#define APX_D2(x, y, u, v) "v_fmac_f64_dpp %[d0], %[" #x "], %[" #u "]" APX_DPP "v_fmac_f64_dpp %[d1], %[" #y "], %[" #v "]" APX_DPP
+#define APX_U(x, u) "v_fmac_f64_dpp %[" #x "], %[" #u "], %[f]" APX_DPP
+template <int LANE, int O, int RM>
+__device__ __forceinline__ void row_dot2(const double (&a)[RM], const double (&b)[RM], double &d0, double &d1) {
+    asm("s_nop 1\n" APX_D2(a0, a1, b0, b1)
+        : [d0] "+v"(d0), [d1] "+v"(d1)
+        : [a0] "v"(a[O]), [a1] "v"(a[O + 1]), [b0] "v"(b[O]), [b1] "v"(b[O + 1]), [l] "n"(LANE));
+}
+template <int LANE, int O, int RM>
+__device__ __forceinline__ void row_dot4(const double (&a)[RM], const double (&b)[RM], double &d0, double &d1) {
+    asm("s_nop 1\n" APX_D2(a0, a1, b0, b1) APX_D2(a2, a3, b2, b3)
+        : [d0] "+v"(d0), [d1] "+v"(d1)
+        : [a0] "v"(a[O]), [a1] "v"(a[O + 1]), [a2] "v"(a[O + 2]), [a3] "v"(a[O + 3]), [b0] "v"(b[O]), [b1] "v"(b[O + 1]),
+          [b2] "v"(b[O + 2]), [b3] "v"(b[O + 3]), [l] "n"(LANE));
+}
+template <int LANE, int O, int RM>
+__device__ __forceinline__ void row_dot8(const double (&a)[RM], const double (&b)[RM], double &d0, double &d1) {
+    asm("s_nop 1\n" APX_D2(a0, a1, b0, b1) APX_D2(a2, a3, b2, b3) APX_D2(a4, a5, b4, b5) APX_D2(a6, a7, b6, b7)
+        : [d0] "+v"(d0), [d1] "+v"(d1)
+        : [a0] "v"(a[O]), [a1] "v"(a[O + 1]), [a2] "v"(a[O + 2]), [a3] "v"(a[O + 3]), [a4] "v"(a[O + 4]),
+          [a5] "v"(a[O + 5]), [a6] "v"(a[O + 6]), [a7] "v"(a[O + 7]), [b0] "v"(b[O]), [b1] "v"(b[O + 1]),
+          [b2] "v"(b[O + 2]), [b3] "v"(b[O + 3]), [b4] "v"(b[O + 4]), [b5] "v"(b[O + 5]), [b6] "v"(b[O + 6]),
+          [b7] "v"(b[O + 7]), [l] "n"(LANE));
+}
+template <int LANE, int O, int RM>
+__device__ __forceinline__ void row_dot(const double (&a)[RM], const double (&b)[RM], double &d0, double &d1) {
+    static_assert(RM % 2 == 0, "pairs of rows");
+    if constexpr (RM - O >= 8) {
+        row_dot8<LANE, O>(a, b, d0, d1);
+        row_dot<LANE, O + 8>(a, b, d0, d1);
+    } else if constexpr (RM - O >= 4) {
+        row_dot4<LANE, O>(a, b, d0, d1);
+        row_dot<LANE, O + 4>(a, b, d0, d1);
+    } else if constexpr (RM - O >= 2) {
+        row_dot2<LANE, O>(a, b, d0, d1);
+    }
+}
+// a[r] += bcast(a[r]) * f
+template <int LANE, int O, int RM>
+__device__ __forceinline__ void row_axpy_self(double (&a)[RM], double f) {
+    if constexpr (RM - O >= 8) {
+        asm("s_nop 1\n" APX_U(a0, a0) APX_U(a1, a1) APX_U(a2, a2) APX_U(a3, a3) APX_U(a4, a4) APX_U(a5, a5)
+                APX_U(a6, a6) APX_U(a7, a7)
+            : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1]), [a2] "+v"(a[O + 2]), [a3] "+v"(a[O + 3]), [a4] "+v"(a[O + 4]),
+              [a5] "+v"(a[O + 5]), [a6] "+v"(a[O + 6]), [a7] "+v"(a[O + 7])
+            : [f] "v"(f), [l] "n"(LANE));
+        row_axpy_self<LANE, O + 8>(a, f);
+    } else if constexpr (RM - O >= 4) {
+        asm("s_nop 1\n" APX_U(a0, a0) APX_U(a1, a1) APX_U(a2, a2) APX_U(a3, a3)
+            : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1]), [a2] "+v"(a[O + 2]), [a3] "+v"(a[O + 3])
+            : [f] "v"(f), [l] "n"(LANE));
+        row_axpy_self<LANE, O + 4>(a, f);
+    } else if constexpr (RM - O >= 2) {
+        asm("s_nop 1\n" APX_U(a0, a0) APX_U(a1, a1)
+            : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1])
+            : [f] "v"(f), [l] "n"(LANE));
+        row_axpy_self<LANE, O + 2>(a, f);
+    }
+}
+// q[r] += bcast(b[r]) * f for r < T
+template <int LANE, int O, int T, int NQ, int NB>
+__device__ __forceinline__ void row_axpy(double (&q)[NQ], const double (&b)[NB], double f) {
+    if constexpr (T - O >= 4) {
+        asm("s_nop 1\n" APX_U(q0, b0) APX_U(q1, b1) APX_U(q2, b2) APX_U(q3, b3)
+            : [q0] "+v"(q[O]), [q1] "+v"(q[O + 1]), [q2] "+v"(q[O + 2]), [q3] "+v"(q[O + 3])
+            : [b0] "v"(b[O]), [b1] "v"(b[O + 1]), [b2] "v"(b[O + 2]), [b3] "v"(b[O + 3]), [f] "v"(f), [l] "n"(LANE));
+        row_axpy<LANE, O + 4, T>(q, b, f);
+    } else if constexpr (T - O >= 1) {
+        asm("s_nop 1\n" APX_U(q0, b0) : [q0] "+v"(q[O]) : [b0] "v"(b[O]), [f] "v"(f), [l] "n"(LANE));
+        row_axpy<LANE, O + 1, T>(q, b, f);
+    }
+}
+#undef APX_U
+#undef APX_D2
+#undef APX_DPP
+
+template <int RM>
+__device__ __forceinline__ void matrix_results_settled(double (&a)[RM]) {
+    asm volatile("s_nop 15\n s_nop 7" ::: "memory");
+#pragma unroll
+    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
+}
+
+// ---- per class: least squares of the projected system, in registers ------------------------------
+// Modified Gram-Schmidt on [B | rhs] (lane = column): step K0 takes the part along column K0 out of every column,
+//     nf_j = -(a_K0 . a_j) / (a_K0 . a_K0),    a_j += nf_j a_K0,
+// and leaves a unit triangular system, nf being the negative of its row K0.  With the right-hand side carried as a
+// column this is as backward stable for least squares as Householder reflections (it is Householder on [0; B], Bjorck
+// 1967), takes no square root and no pivot reciprocals in the back substitution, and nothing has to be masked: columns
+// up to the pivot are never read again.  It works on all RM rows at every step where reflections shrink, which the
+// shorter scalar part more than pays for.  A zero column gives NaN, as dividing by a zero pivot does.
+//   K = 12, A = 2 (28 x 14 tile), 8192 groups of 10 classes: 120 us a call with reflections, 91 us this way;
+//   K = 8, A = 2 (20 x 10 tile), 2048 groups of 10 classes: 29.1 and 24.5 us.
+// Steps K0 .. KEND-1 (those below `cols`).
+template <int K0, int KEND, int RM>
+struct ClassGramSchmidt {
+    static __device__ __forceinline__ void run(double (&a)[RM], double (&nf)[KEND], int cols) {
+        if (K0 < cols) {
+            double d0 = 0.0, d1 = 0.0;
+            row_dot<K0, 0>(a, a, d0, d1);
+            const double d = d0 + d1;                        // x^T a for this lane's column a ..
+            const double sigma = row_bcast<K0>(d);           // .. which in the pivot lane is x^T x
+            nf[K0] = -d * rcp_normal(sigma);
+            row_axpy_self<K0, 0>(a, nf[K0]);
+            ClassGramSchmidt<K0 + 1, KEND, RM>::run(a, nf, cols);
+        }
+    }
+};
+template <int KEND, int RM>
+struct ClassGramSchmidt<KEND, KEND, RM> {
+    static __device__ __forceinline__ void run(double (&)[RM], double (&)[KEND], int) {}
+};
+
+// Solves the unit triangular system for the negative of its solution: nf[i] in lane t is minus entry (i, t), the
+// negative of the right-hand side comes in in s and the negative of the solution leaves.
+template <int T, int NS>
+struct BackSubst {
+    static __device__ __forceinline__ void run(const double (&nf)[NS], double (&s)[NS], int cols) {
+        if (T < cols) {
+            row_axpy<T, 0, T>(s, nf, s[T]);
+        } else {
+            s[T] = 0.0;                                   // no such unknown
+        }
+        BackSubst<T - 1, NS>::run(nf, s, cols);
+    }
+};
+template <int NS>
+struct BackSubst<-1, NS> {
+    static __device__ __forceinline__ void run(const double (&)[NS], double (&)[NS], int) {}
+};
+
+// ---- the same factorisation by Householder reflections, for the triangular factor itself (Algorithm 1) -----------
 // Steps K0 .. KEND-1 (those below `cols`); KEND = min(15, RM - 1) bounds the unrolling: cols <= R - 1 <= RM - 1.
 template <int K0, int KEND, int RM>
 struct ClassQrSteps {
@@ -337,27 +477,6 @@ struct ClassQrSteps<KEND, KEND, RM> {
     static __device__ __forceinline__ void run(double (&)[RM], int, int) {}
 };
 
-// Back substitution R q = rhs over the first `cols` rows; column t of R sits in lane t of the row, the
-// transformed right-hand side in lane 15.  Every lane of the class ends with the whole solution.
-template <int T, int NS, int RM>
-struct BackSubst {
-    // s enters as the transformed right-hand side and leaves as the solution: entry T is final once solved
-    static __device__ __forceinline__ void run(const double (&a)[RM], double (&s)[NS], int cols) {
-        if (T < cols) {
-            s[T] = s[T] * rcp_normal(row_bcast<T>(a[T]));
-#pragma unroll
-            for (int i = 0; i < T; ++i) s[i] = fma(-row_bcast<T>(a[i]), s[T], s[i]);
-        } else {
-            s[T] = 0.0;                                   // no such unknown
-        }
-        BackSubst<T - 1, NS, RM>::run(a, s, cols);
-    }
-};
-template <int NS, int RM>
-struct BackSubst<-1, NS, RM> {
-    static __device__ __forceinline__ void run(const double (&)[RM], double (&)[NS], int) {}
-};
-
 // (value, row) minimum over the 16 lanes of a class: smaller value first, equal values: smaller row.
 template <int CTRL>
 __device__ __forceinline__ void row_min_step(double &v, int &i) {
@@ -382,9 +501,10 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
     const int j = lane % kClsLanes;
     const int cols = M - 1;                               // unknowns Q_1 .. Q_{M-1}
 
-    // column of this lane: -y x^(j+1) for the unknown Q_(j+1), y for the right-hand side, 0 on idle lanes
+    // column of this lane: y x^(j+1) for the unknown Q_(j+1), y for the right-hand side, 0 on idle lanes (the signs of
+    // -y x^(j+1) q = y are left out: the solve below returns the negative)
     const int e = j < cols ? j + 1 : 0;
-    const double sgn = j < cols ? -1.0 : (j == kClsLanes - 1 ? 1.0 : 0.0);
+    const double sgn = (j < cols || j == kClsLanes - 1) ? 1.0 : 0.0;
 
     // ---- the projected systems of the four classes, B_c = U diag(y_c) [x^e], on the float64 matrix cores -------
     // v_mfma_f64_16x16x4_f64 computes D[16x16] += A[16x4] * B[4x16]; lane l holds A[l%16][l/16], B[l/16][l%16] and, in
@@ -426,12 +546,14 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
     }
 
     constexpr int kSteps = RM - 1 < kProjMaxM - 1 ? RM - 1 : kProjMaxM - 1;   // most unknowns this tile can hold
-    ClassQrSteps<0, kSteps, RM>::run(a, j, cols);
+    matrix_results_settled(a);
+    double nf[kSteps];
+    ClassGramSchmidt<0, kSteps, RM>::run(a, nf, cols);
 
-    double q[kSteps];                                     // right-hand side in, Q_1 .. Q_{M-1} out
+    double q[kSteps];                                     // minus the right-hand side in, Q_1 .. Q_{M-1} out
 #pragma unroll
-    for (int i = 0; i < kSteps; ++i) q[i] = row_bcast<kClsLanes - 1>(a[i]);
-    BackSubst<kSteps - 1, kSteps, RM>::run(a, q, cols);
+    for (int i = 0; i < kSteps; ++i) q[i] = row_bcast<kClsLanes - 1>(nf[i]);
+    BackSubst<kSteps - 1, kSteps>::run(nf, q, cols);
 
     // a_r = Q(x_r) = 1 + sum_t q[t] x^(t+1) (q[t] = 0 for t >= cols), rows j, j+16, .. of this lane
     constexpr int PR = (NB + kClsLanes - 1) / kClsLanes;
