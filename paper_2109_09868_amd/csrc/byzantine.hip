@@ -342,8 +342,12 @@ __device__ __forceinline__ void row_dot8(const double (&a)[RM], const double (&b
 }
 template <int LANE, int O, int RM>
 __device__ __forceinline__ void row_dot(const double (&a)[RM], const double (&b)[RM], double &d0, double &d1) {
-    static_assert(RM % 2 == 0, "pairs of rows");
-    if constexpr (RM - O >= 8) {
+    if constexpr ((RM - O) % 2 == 1) {                    // an odd row first, then whole pairs
+        asm("s_nop 1\n v_fmac_f64_dpp %[d0], %[a0], %[b0]" APX_DPP
+            : [d0] "+v"(d0)
+            : [a0] "v"(a[O]), [b0] "v"(b[O]), [l] "n"(LANE));
+        row_dot<LANE, O + 1>(a, b, d1, d0);
+    } else if constexpr (RM - O >= 8) {
         row_dot8<LANE, O>(a, b, d0, d1);
         row_dot<LANE, O + 8>(a, b, d0, d1);
     } else if constexpr (RM - O >= 4) {
@@ -373,6 +377,8 @@ __device__ __forceinline__ void row_axpy_self(double (&a)[RM], double f) {
             : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1])
             : [f] "v"(f), [l] "n"(LANE));
         row_axpy_self<LANE, O + 2>(a, f);
+    } else if constexpr (RM - O == 1) {
+        asm("s_nop 1\n" APX_U(a0, a0) : [a0] "+v"(a[O]) : [f] "v"(f), [l] "n"(LANE));
     }
 }
 // q[r] += bcast(b[r]) * f for r < T
@@ -394,9 +400,77 @@ __device__ __forceinline__ void row_axpy(double (&q)[NQ], const double (&b)[NB],
 
 template <int RM>
 __device__ __forceinline__ void matrix_results_settled(double (&a)[RM]) {
-    asm volatile("s_nop 15\n s_nop 7" ::: "memory");
 #pragma unroll
-    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
+    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));       // every result is on its way ..
+    asm volatile("s_nop 15\n s_nop 7");
+#pragma unroll
+    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));       // .. and there before anything below reads it
+}
+
+// ---- once per group, four groups to a wave: U = the last n - M columns of Q, transposed ----------------------------
+// Householder reflectors of the group's Vandermonde block V (n x M) in the group's 16-lane row, lane = column, then
+// the reflectors applied, last one first, to the unit vectors e_M .. e_(n-1), one per lane: Q e_(M+i) = H_0 .. H_(M-1)
+// e_(M+i) is row i of U.  Every broadcast rides in a multiply-add (row_dot, row_axpy), so the wave factorises four
+// groups in the issue slots that one took with the pivot column read lane by lane.
+template <int K0, int NB, int MS>
+struct RowReflectors {
+    // lane K0 keeps v_K0 in rows K0.. of its column and 2 / v^T v in `sc`
+    static __device__ __forceinline__ void factor(double (&a)[NB], int j, int M, double &sc) {
+        if constexpr (K0 < MS) {
+            if (K0 < M) {
+                double d0 = 0.0, d1 = 0.0;
+                row_dot<K0, K0>(a, a, d0, d1);
+                const double d = d0 + d1;                    // x^T a for this lane's column a ..
+                const double sigma = row_bcast<K0>(d);       // .. which in the pivot lane is x^T x
+                const double xkk = row_bcast<K0>(a[K0]);
+                const bool zero = !(sigma > 0.0);            // no reflection (empty rows of the wave come here)
+                const double sq = zero ? 1.0 : sigma;
+                const double nrm = sqrt_normal(sq);
+                const double alpha = xkk >= 0.0 ? -nrm : nrm;
+                const double scale = zero ? 0.0 : rcp_normal(fma(-alpha, xkk, sq));
+                const double nf = j > K0 ? -scale * fma(-alpha, a[K0], d) : 0.0;
+                const double v0 = xkk - alpha;
+                a[K0] = j == K0 ? v0 : fma(nf, v0, a[K0]);
+                sc = j == K0 ? scale : sc;
+                row_axpy_self<K0, K0 + 1>(a, nf);            // lanes up to the pivot take the factor 0
+                RowReflectors<K0 + 1, NB, MS>::factor(a, j, M, sc);
+            }
+        }
+    }
+    static __device__ __forceinline__ void apply(const double (&a)[NB], double (&z)[NB], int M, double sc) {
+        if constexpr (K0 < MS) {
+            RowReflectors<K0 + 1, NB, MS>::apply(a, z, M, sc);
+            if (K0 < M) {
+                double d0 = 0.0, d1 = 0.0;
+                row_dot<K0, K0>(a, z, d0, d1);
+                const double nf = -row_bcast<K0>(sc) * (d0 + d1);
+                row_axpy<K0, K0, NB>(z, a, nf);
+            }
+        }
+    }
+};
+
+// One wave; lane row q works on group q: n_q workers avail_q[0..n_q), ascending (n_q = 0: none).  Pw[w][e] = x_w^e by
+// worker.  Writes Ush_q[i * stride + w] = U[i][worker w] for i < n_q - M (the rest of Ush is left as it is: zero).
+template <int NB>
+__device__ __forceinline__ void rows_complement_basis(const double *Pw, const int *avail_q, int n, int M, double *Ush_q,
+                                                      int stride) {
+    constexpr int MS = NB / 2 < kProjMaxM ? NB / 2 : kProjMaxM;       // eq. (3): 2 M <= n <= NB
+    const int j = lane_id() % kClsLanes;
+    double a[NB], z[NB], sc = 0.0;
+#pragma unroll
+    for (int r = 0; r < NB; ++r) {
+        const double p = Pw[(r < n ? avail_q[r] : 0) * kPwStride + j];
+        a[r] = (r < n && j < M) ? p : 0.0;
+        z[r] = r == M + j && r < n ? 1.0 : 0.0;
+    }
+    RowReflectors<0, NB, MS>::factor(a, j, M, sc);
+    RowReflectors<0, NB, MS>::apply(a, z, M, sc);
+    if (M + j < n) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r)
+            if (r < n) Ush_q[j * stride + avail_q[r]] = z[r];
+    }
 }
 
 // ---- per class: least squares of the projected system, in registers ------------------------------
@@ -477,24 +551,48 @@ struct ClassQrSteps<KEND, KEND, RM> {
     static __device__ __forceinline__ void run(double (&)[RM], int, int) {}
 };
 
-// (value, row) minimum over the 16 lanes of a class: smaller value first, equal values: smaller row.
-template <int CTRL>
-__device__ __forceinline__ void row_min_step(double &v, int &i) {
-    const double ov = dpp_exchange<CTRL>(v);
-    const int oi = __builtin_amdgcn_update_dpp(0, i, CTRL, 0xF, 0xF, true);
-    const bool take = ov < v || (ov == v && oi < i);
-    v = take ? ov : v;
-    i = take ? oi : i;
+// The A smallest keys of a class (equal keys: smaller row first) vote.  Lane j of the class's 16-lane row holds the
+// keys of rows j, j + 16, ..: |a_r|, infinity where it is not a number, NaN where there is no such row.  The minimum
+// travels by itself (a NaN loses to any number); a ballot then finds the first row that has it.
+template <int PR>
+__device__ __forceinline__ void vote_smallest(double (&key)[PR], int A, bool live, const int *worker_of_row, int *votes) {
+    const int lane = lane_id();
+    const unsigned long long row_lanes = 0xffffull << (lane & 48);
+    const unsigned long long before = row_lanes & ((1ull << lane) - 1ull);
+    for (int pick = 0; pick < A; ++pick) {
+        double m = key[0];
+#pragma unroll
+        for (int p = 1; p < PR; ++p) m = __builtin_fmin(m, key[p]);
+        m = __builtin_fmin(m, dpp_exchange<kDppQuadXor1>(m));
+        m = __builtin_fmin(m, dpp_exchange<kDppQuadXor2>(m));
+        m = __builtin_fmin(m, dpp_exchange<kDppRowHalfMirror>(m));
+        m = __builtin_fmin(m, dpp_exchange<kDppRowMirror>(m));
+        bool open = true;                                 // no row of this class found yet
+#pragma unroll
+        for (int p = 0; p < PR; ++p) {
+            const bool has = key[p] == m;
+            const unsigned long long who = __ballot(has);
+            if (open && has && (who & before) == 0ull) {
+                const int r = lane % kClsLanes + p * kClsLanes;
+                if (live) atomicAdd(&votes[worker_of_row != nullptr ? worker_of_row[r] : r], 1);
+                key[p] = __builtin_nan("");
+            }
+            open = open && (who & row_lanes) == 0ull;
+        }
+    }
 }
 
 // Algorithm 2, steps 1-5, for four classes at a time, by one wave.
-//   ycol (per lane): the staged predictions of class slot (lane % 16) & 3 of this round, ycol[r * CW] = prediction of
-//   the r-th available worker for that class, float, zero past n (an empty slot points at zeros);
-//   live, votes (per lane): class slot lane / 16 holds a class, and the vote counters of its group;
-//   Ush[ush_rows(RM)][ush_stride(NB)] (zero past row n-M and column n), Pw[NB][16] (rows past n zero), xs[n]: LDS.
+//   ycol, urow (per lane): class slot (lane % 16) & 3 of this round, whose operands this lane feeds to the matrix cores:
+//   ycol[r * CW] = its prediction of row r, float, zero where there is no answer (an empty slot points at zeros);
+//   urow[i * ush_stride(NB) + r] = U[i][r] of its group, zero where there is no such row or column, LDS;
+//   live, rows, votes (per lane): class slot lane / 16, whose system this lane's row then holds: whether it is a class,
+//   bit r: row r is an available worker, and the vote counters of its group, by worker;
+//   Pw[NB][16] = powers of the rows' nodes, LDS: the same rows for all four slots.
+// A row is the r-th available worker, worker_of_row its index, or (worker_of_row null) the worker r itself.
 template <int NB, int RM>
-__device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, bool live, const int *avail,
-                                                    const double *xs, const double *Pw, const double *Ush, int n,
+__device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, const double *urow, bool live,
+                                                    unsigned long long rows, const int *worker_of_row, const double *Pw,
                                                     int M, int A, int *votes) {
     typedef double v4d __attribute__((ext_vector_type(4)));
     const int lane = lane_id();
@@ -512,7 +610,7 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
     //     A[4t + c][k] = U[4b + t][r] * y_{r, class c}      B[k][j] = sgn_j * x_r^{e_j}      (r = 4s + k)
     // summed over the k-steps s, register t of lane (c, j) receives B_c[4b + t][j]: exactly the layout the
     // factorisation below wants (lane = class and column, rows in registers), with no lane exchange at all.
-    // Rows past n of Ysh and Pw and columns past n of Ush are zero, so the k-steps need no bound.
+    // Empty rows are zero in ycol, Pw and urow, so the k-steps need no bound.
     constexpr int kKSteps = NB / 4;
     constexpr int kRowBlocks = ush_rows(RM) / 4;
     static_assert(NB % 4 == 0, "k-steps take four available workers at a time");
@@ -528,7 +626,7 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
     }
     double a[RM];
     {
-        const double *urow = Ush + ((lane % kClsLanes) >> 2) * ush_stride(NB) + lane / kClsLanes;
+        const double *u = urow + ((lane % kClsLanes) >> 2) * ush_stride(NB) + lane / kClsLanes;
         v4d acc[kRowBlocks];
 #pragma unroll
         for (int b = 0; b < kRowBlocks; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
@@ -536,7 +634,7 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
         for (int s = 0; s < kKSteps; ++s)                 // the row blocks are independent accumulation chains
 #pragma unroll
             for (int b = 0; b < kRowBlocks; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(urow[4 * b * ush_stride(NB) + 4 * s] * yop[s], bop[s], acc[b],
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[4 * b * ush_stride(NB) + 4 * s] * yop[s], bop[s], acc[b],
                                                               0, 0, 0);
 #pragma unroll
         for (int b = 0; b < kRowBlocks; ++b)
@@ -557,42 +655,18 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, b
 
     // a_r = Q(x_r) = 1 + sum_t q[t] x^(t+1) (q[t] = 0 for t >= cols), rows j, j+16, .. of this lane
     constexpr int PR = (NB + kClsLanes - 1) / kClsLanes;
-    double kv[PR];
-    int ki[PR];
+    double key[PR];
 #pragma unroll
     for (int p = 0; p < PR; ++p) {
         const int r = j + p * kClsLanes;
-        const double x = xs[r < n ? r : 0];
+        const double x = Pw[(r < NB ? r : 0) * kPwStride + 1];
         double av = 0.0;
 #pragma unroll
         for (int t = kSteps - 1; t >= 0; --t) av = fma(av, x, q[t]);
         av = fma(av, x, 1.0);
-        kv[p] = (r < n && av == av) ? fabs(av) : __builtin_inf();
-        ki[p] = r;
+        key[p] = ((rows >> r) & 1ull) ? (av == av ? fabs(av) : __builtin_inf()) : __builtin_nan("");
     }
-    // the A smallest |a_r| (equal magnitudes: smaller worker index, i.e. smaller row, first) vote
-    for (int pick = 0; pick < A; ++pick) {
-        double bv = kv[0];
-        int bi = ki[0];
-#pragma unroll
-        for (int p = 1; p < PR; ++p) {
-            const bool take = kv[p] < bv || (kv[p] == bv && ki[p] < bi);
-            bv = take ? kv[p] : bv;
-            bi = take ? ki[p] : bi;
-        }
-        row_min_step<kDppQuadXor1>(bv, bi);
-        row_min_step<kDppQuadXor2>(bv, bi);
-        row_min_step<kDppRowHalfMirror>(bv, bi);
-        row_min_step<kDppRowMirror>(bv, bi);
-        if (live && j == 0) atomicAdd(&votes[avail[bi]], 1);   // bi < n: at least A < n rows are real
-#pragma unroll
-        for (int p = 0; p < PR; ++p) {
-            if (ki[p] == bi) {
-                kv[p] = __builtin_inf();
-                ki[p] = 0x7fffffff;
-            }
-        }
-    }
+    vote_smallest<PR>(key, A, live, worker_of_row, votes);
 }
 
 __device__ __forceinline__ void homogeneous_q(double *mat, int LD, double *coef, double *key, int W2, int M, int j,
@@ -813,8 +887,7 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *Ysh, int CW
 #pragma unroll
         for (int k = 0; k < MT; ++k) qk[k] = row_bcast_dyn(qv, k);              // zero from idle lanes
         constexpr int PR = (NB + kClsLanes - 1) / kClsLanes;
-        double kv[PR];
-        int ki[PR];
+        double key[PR];
 #pragma unroll
         for (int pr = 0; pr < PR; ++pr) {
             const int r = j + pr * kClsLanes;
@@ -822,31 +895,9 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *Ysh, int CW
             double av = 0.0;
 #pragma unroll
             for (int k = MT - 1; k >= 0; --k) av = fma(av, x, qk[k]);
-            kv[pr] = (r < n && av == av) ? fabs(av) : __builtin_inf();
-            ki[pr] = r;
+            key[pr] = r < n ? (av == av ? fabs(av) : __builtin_inf()) : __builtin_nan("");
         }
-        for (int pick = 0; pick < A; ++pick) {
-            double bv = kv[0];
-            int bi = ki[0];
-#pragma unroll
-            for (int pr = 1; pr < PR; ++pr) {
-                const bool take = kv[pr] < bv || (kv[pr] == bv && ki[pr] < bi);
-                bv = take ? kv[pr] : bv;
-                bi = take ? ki[pr] : bi;
-            }
-            row_min_step<kDppQuadXor1>(bv, bi);
-            row_min_step<kDppQuadXor2>(bv, bi);
-            row_min_step<kDppRowHalfMirror>(bv, bi);
-            row_min_step<kDppRowMirror>(bv, bi);
-            if (class_live && settled && j == 0) atomicAdd(&votes[avail[bi]], 1);
-#pragma unroll
-            for (int pr = 0; pr < PR; ++pr) {
-                if (ki[pr] == bi) {
-                    kv[pr] = __builtin_inf();
-                    ki[pr] = 0x7fffffff;
-                }
-            }
-        }
+        vote_smallest<PR>(key, A, class_live && settled, avail, votes);
     }
     const unsigned long long open_lanes = __ballot(class_live && !settled);
     if (open_lanes == 0ull) return;
@@ -1018,8 +1069,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
                                                 hom_scratch + static_cast<size_t>(wv) * hom_wave_doubles, hom_wave_doubles,
                                                 votes);
             else
-                locate_classes_proj<NB, RM>(Ysh + c_rel + ((lane_id() % kClsLanes) & 3), CW,
-                                            c_rel + lane_id() / kClsLanes < tile_classes, avail, xs, Pw, Ush, n, M, A, votes);
+                locate_classes_proj<NB, RM>(Ysh + c_rel + ((lane_id() % kClsLanes) & 3), CW, Ush,
+                                            c_rel + lane_id() / kClsLanes < tile_classes, (1ull << n) - 1ull, avail, Pw, M, A,
+                                            votes);
         }
     }
     __syncthreads();
@@ -1049,119 +1101,182 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
     }
 }
 
-// Algorithm 2 for the paper's Byzantine operating points (Section 4.2, "Byzantine-Robustness": no stragglers, ten
-// classes): every group answers in full, so all groups share the factorisation that full_basis_kernel wrote, and
-// nothing ties a wave's four class slots to one group any more.  A workgroup takes GPW consecutive groups and walks
-// their GPW * C classes four at a time: with C = 10 four groups fill ten rounds where each alone needs three (twelve
-// slots for ten classes); nodes, powers and the basis are staged once for all of them.  Per class the arithmetic is
-// that of decode_byzantine_proj_kernel (same functions, same operands in the same order): the outputs are the same bits.
-// Host guarantees: S = 0 (a group whose mask is not full is marked bad and skipped), C <= 16, N <= 48.
-// dynamic LDS (doubles): Ush | Pw[NB*16] | xs[NB] | WdT[GPW][(N-A)*KP] | alpha_s[K] | beta_s[N]
-//               then float Ysh[GPW + 1][NB*16] (the last tile stays zero: empty class slots read it),
-//               then ints: ident[N] | F[GPW][N] | Fpos[GPW][N] | votes[GPW][N] | good[GPW]
-template <int NB, int RM, int GPW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RM <= 16 && NB <= 28 ? 3 : 2))) void decode_byzantine_shared_basis_kernel(
+// Algorithm 2 for groups of at most fifteen classes (the paper's Byzantine operating points, Section 4.2, have ten).
+// A workgroup of up to four waves takes GPW = 1, 2 or 4 consecutive groups and walks their GPW * C classes four at a time, so
+// that class slots are filled across groups (ten classes: four groups fill ten rounds where each alone needs three,
+// twelve slots for ten classes).  Rows are workers, not survivors: the predictions are staged as they lie, with zeros
+// for missing answers, all groups use one table of powers, and a missing worker is a zero column of its group's U.
+// U comes from the call's one factorisation (SHARED: no stragglers, see full_basis_kernel) or from the first wave, which
+// factorises the workgroup's groups side by side, a 16-lane row each.
+// The decode at the end is one product on the float64 matrix cores per group: with T[j][i] = 1 / (alpha_j - beta_i),
+// which depends on the nodes only, and s_i = the alternating sign of worker i, 0 if it does not count,
+//     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i):
+// column 15 of the product carries the denominators (C <= 15).  A query node that is a worker's node has T = 0 there and
+// takes that worker's row as it is, if the worker counts.
+// K = 8, A = 2, 20 of 24 workers, 2048 groups of 10 classes: 24.5 us with a workgroup per group, 20.4 us this way;
+// K = 12, A = 2, 28 workers, 8192 groups: 91.2 us with this packing but decoder weights per group, 70.8 us.
+// NB >= N - S bounds the workers that answer, NW >= N all workers, RM >= N - S - M.
+// dynamic LDS: double Ush[SHARED ? 1 : GPW][ush_rows(RM) * ush_stride(NW)] | Pw[NW][16] | T[16][NW + 1] | sgn[GPW][NW]
+//              | float Ysh[GPW + 1][NW][16] (the last tile stays zero: empty class slots read it)
+//              | int avail[GPW][NW] | votes[GPW][64] | hit[16] | uint64 bits[GPW]
+template <int NB, int RM, int NW>
+constexpr size_t packed_lds_bytes(bool shared, int gpw) {
+    return sizeof(double) * (static_cast<size_t>(shared ? 1 : gpw) * ush_rows(RM) * ush_stride(NW) + NW * kPwStride +
+                             16 * (NW + 1) + gpw * NW + gpw) +
+           sizeof(float) * (static_cast<size_t>(gpw + 1) * NW * kClsLanes) +
+           sizeof(int) * (static_cast<size_t>(gpw) * (NW + kWave) + 16);
+}
+constexpr int kPackedWaves = 4;      // at most
+
+template <int NB, int RM, int NW, bool SHARED>
+__global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_per_eu(NB <= 28 ? 3 : 2))) void decode_byzantine_packed_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
-    int32_t *__restrict__ adv, int32_t *__restrict__ status, int64_t G, int K, int N, int A, int C, int sign_mode,
-    const double *__restrict__ full_basis, const Nodes nodes) {
+    int32_t *__restrict__ adv, int32_t *__restrict__ status, int64_t G, int K, int N, int S, int n_cap, int A, int C,
+    int sign_mode, int gpw, const double *__restrict__ full_basis, const Nodes nodes) {
+    typedef double v4d __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) double lds_d[];
-    constexpr int CW = kClsLanes;                         // staged tile: sixteen class columns per row
-    constexpr int kTile = NB * CW;
-    constexpr int kUshDoubles = basis_doubles<NB, RM, false>();
-    const int KP = round_up4(K);
+    constexpr int CW = kClsLanes;
+    constexpr int kTile = NW * CW;
+    constexpr int kStride = ush_stride(NW);
+    constexpr int kUsh = ush_rows(RM) * kStride;
+    constexpr int TS = NW + 1;                            // odd: the sixteen rows an operand load touches lie in distinct banks
+    const int threads = blockDim.x;                       // at least a wave per group
+    const int nw = threads / kWave;
     const int M = K + A;
-    const int nF = N - A;
-    const int nw = blockDim.x / kWave;
     double *Ush = lds_d;
-    double *Pw = Ush + kUshDoubles;
-    double *xs = Pw + NB * kPwStride;
-    double *WdT = xs + NB;
-    double *alpha_s = WdT + GPW * nF * KP;
-    double *beta_s = alpha_s + K;
-    float *Ysh = reinterpret_cast<float *>(beta_s + N);
-    int *ident = reinterpret_cast<int *>(Ysh + (GPW + 1) * kTile);
-    int *F = ident + N;
-    int *Fpos = F + GPW * N;
-    int *votes = Fpos + GPW * N;
-    int *good_sh = votes + GPW * N;
-    const int64_t g0 = static_cast<int64_t>(blockIdx.x) * GPW;
-    const int here = G - g0 < GPW ? static_cast<int>(G - g0) : GPW;   // groups of this workgroup
+    double *Pw = Ush + (SHARED ? 1 : gpw) * kUsh;
+    double *T = Pw + NW * kPwStride;
+    double *sgn = T + 16 * TS;
+    unsigned long long *bits = reinterpret_cast<unsigned long long *>(sgn + gpw * NW);
+    float *Ysh = reinterpret_cast<float *>(bits + gpw);
+    int *avail = reinterpret_cast<int *>(Ysh + (gpw + 1) * kTile);
+    int *votes = avail + gpw * NW;
+    int *hit = votes + gpw * kWave;
+    const int64_t g0 = static_cast<int64_t>(blockIdx.x) * gpw;
+    const int here = G - g0 < gpw ? static_cast<int>(G - g0) : gpw;   // groups of this workgroup
     const int tid = threadIdx.x;
     const int wv = wave_id();
     const int lane = lane_id();
+    const int c_ld = tid & (CW - 1);
 
-    stage_nodes(nodes, K, N, alpha_s, beta_s);
-    for (int e = tid; e < GPW * nF * KP; e += blockDim.x) WdT[e] = 0.0;
-    for (int e = tid; e < GPW * N; e += blockDim.x) votes[e] = 0;
-    for (int e = tid; e < N; e += blockDim.x) ident[e] = e;
-    for (int e = tid; e < (GPW + 1) * kTile; e += blockDim.x) Ysh[e] = 0.0f;
-    for (int e = tid; e < kUshDoubles; e += blockDim.x) Ush[e] = full_basis[e];
-    for (int q = wv; q < GPW; q += nw) {                  // N <= 48: one ballot counts a mask row
-        bool ok = q < here;
-        if (ok) {
-            const bool b = lane < N && mask[(g0 + q) * N + lane] != 0;
-            ok = static_cast<int>(__popcll(__ballot(b))) == N;
-            if (lane == 0 && status != nullptr) status[g0 + q] = ok ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
-        }
-        if (lane == 0) good_sh[q] = ok ? 1 : 0;
+    // predictions: row slot u of this thread is row tid / 16 + u * (threads / 16) of the stacked [gpw][NW] tiles;
+    // a pass takes four rows per wave and there are gpw waves or more, so NW / 4 passes do
+    const int rows_per_pass = threads / CW;
+    float pf[NW / 4];
+#pragma unroll
+    for (int u = 0; u < NW / 4; ++u) {
+        const int R = tid / CW + u * rows_per_pass;
+        const int q = R / NW, r = R % NW;
+        pf[u] = (q < here && r < N && c_ld < C) ? preds[(static_cast<size_t>(g0 + q) * N + r) * C + c_ld] : 0.0f;
     }
-    __syncthreads();
-    for (int r = tid; r < NB; r += blockDim.x) {
-        const double x = r < N ? beta_s[r] : 0.0;
-        if (r < N) xs[r] = x;
-        double pw = r < N ? 1.0 : 0.0;
+    if (wv < gpw) {                                       // N <= 48: one ballot reads a mask row
+        const int q = wv;
+        const bool b = q < here && lane < N && mask[(g0 + q) * N + lane] != 0;
+        unsigned long long m = __ballot(b);
+        const int n = static_cast<int>(__popcll(m));
+        const bool good = q < here && (S < 0 ? (n >= 2 * M && n <= n_cap) : n == n_cap);
+        if (lane == 0 && q < here && status != nullptr) status[g0 + q] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+        if (!good) m = 0ull;
+        if (lane == 0) bits[q] = m;
+        if (b && good) avail[q * NW + __popcll(m & ((1ull << lane) - 1ull))] = lane;
+        votes[q * kWave + lane] = 0;
+    }
+    if (SHARED) {
+        for (int e = tid; e < kUsh; e += threads) Ush[e] = full_basis[e];
+    } else {
+        for (int e = tid; e < gpw * kUsh; e += threads) Ush[e] = 0.0;
+    }
+    if (tid < NW) {
+        const double x = tid < N ? nodes.beta[tid] : 0.0;
+        double pw = tid < N ? 1.0 : 0.0;
         for (int e = 0; e < kPwStride; ++e) {
-            Pw[r * kPwStride + e] = pw;
+            Pw[tid * kPwStride + e] = pw;
             pw *= x;
         }
     }
-    // the predictions of the workgroup's groups are one contiguous run of here * N * C floats
-    {
-        const float *pg = preds + static_cast<size_t>(g0) * N * C;
-        const int per_group = N * C;
-        for (int idx = tid; idx < here * per_group; idx += blockDim.x) {
-            const int q = idx / per_group, rem = idx - q * per_group;
-            const int r = rem / C, c = rem - r * C;
-            if (good_sh[q] != 0) Ysh[q * kTile + r * CW + c] = pg[idx];
-        }
+    if (tid >= threads - 16) hit[tid - (threads - 16)] = -1;
+    __syncthreads();
+    for (int e = tid; e < 16 * NW; e += threads) {
+        const int j = e / NW, i = e - j * NW;
+        const bool in = j < K && i < N;
+        const double d = in ? nodes.alpha[in ? j : 0] - nodes.beta[in ? i : 0] : 1.0;
+        if (d == 0.0) hit[j] = i;                         // nodes are distinct: at most one
+        T[j * TS + i] = (in && d != 0.0) ? 1.0 / d : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < NW / 4; ++u) {
+        const int R = tid / CW + u * rows_per_pass;
+        const int q = R / NW, r = R % NW;
+        if (q < gpw) Ysh[R * CW + c_ld] = ((bits[q] >> r) & 1ull) ? pf[u] : 0.0f;
+    }
+    for (int e = tid; e < kTile; e += threads) Ysh[gpw * kTile + e] = 0.0f;
+    if (!SHARED && wv == 0) {
+        const int q = lane / kClsLanes < gpw ? lane / kClsLanes : 0;
+        const int n = lane / kClsLanes < gpw ? static_cast<int>(__popcll(bits[q])) : 0;
+        rows_complement_basis<NB>(Pw, avail + q * NW, n, M, Ush + q * kUsh, kStride);
     }
     __syncthreads();
 
-    const int total = GPW * C;
+    const int total = gpw * C;
     for (int c0 = wv * kClsPerWave; c0 < total; c0 += nw * kClsPerWave) {
-        const int s_op = c0 + ((lane % kClsLanes) & 3);   // the slot whose predictions this lane feeds to the matrix cores
-        const int q_op = s_op / C, c_op = s_op - q_op * C;
-        const bool op_ok = s_op < total && good_sh[s_op < total ? q_op : 0] != 0;
+        const int s_op = c0 + (lane & 3);                 // the slot whose operands this lane feeds to the matrix cores
+        const int q_op = s_op < total ? s_op / C : gpw;   // past the last: the zero tile
+        const int c_op = s_op < total ? s_op - q_op * C : 0;
         const int s_res = c0 + lane / kClsLanes;          // the slot whose system this lane's row then holds
         const int q_res = s_res < total ? s_res / C : 0;
-        const bool live = s_res < total && good_sh[q_res] != 0;
-        locate_classes_proj<NB, RM>(Ysh + (op_ok ? q_op * kTile + c_op : GPW * kTile), CW, live, ident, xs, Pw, Ush, N, M,
-                                    A, votes + q_res * N);
+        const unsigned long long rows = bits[q_res];
+        locate_classes_proj<NW, RM>(Ysh + q_op * kTile + c_op, CW, SHARED || q_op == gpw ? Ush : Ush + q_op * kUsh,
+                                    s_res < total && rows != 0ull, rows, nullptr, Pw, M, A, votes + q_res * kWave);
     }
     __syncthreads();
 
-    for (int q = wv; q < here; q += nw)                   // a wave per group
-        if (good_sh[q] != 0)
-            select_adversaries_wave(adv + (g0 + q) * A, ident, N, N, A, votes + q * N, F + q * N, Fpos + q * N);
-    __syncthreads();
-    for (int q = 0; q < here; ++q)
-        if (good_sh[q] != 0) decoder_weights(alpha_s, beta_s, F + q * N, nF, K, KP, sign_mode, WdT + q * nF * KP);
-    __syncthreads();
-    // out[g][j][c] = sum_r WdT[r][j] * Y[F_r][c] straight from the staged tiles
+    if (wv >= here || bits[wv] == 0ull) return;           // a wave per group from here on, no barrier left
     {
-        float *og = out + static_cast<size_t>(g0) * K * C;
-        const int per_group = K * C;
-        for (int o = tid; o < here * per_group; o += blockDim.x) {
-            const int q = o / per_group, rem = o - q * per_group;
-            if (good_sh[q] == 0) continue;
-            const int jq = rem / C, c = rem - jq * C;
-            const double *w = WdT + q * nF * KP + jq;
-            const float *y = Ysh + q * kTile + c;
-            const int *fp = Fpos + q * N;
-            double acc = 0.0;
-#pragma unroll 6
-            for (int r = 0; r < nF; ++r) acc = fma(w[r * KP], static_cast<double>(y[fp[r] << 4]), acc);
-            og[o] = static_cast<float>(acc);
+        const int q = wv;
+        const unsigned long long below = (1ull << lane) - 1ull;
+        // the A most voted workers, equal counts: smaller index first.  Every class gives A distinct workers a vote, so
+        // at least A have one.
+        int key = lane < N ? (votes[q * kWave + lane] << 6) | (kWave - 1 - lane) : -1;
+        unsigned long long drop = 0ull;
+        for (int pick = 0; pick < A; ++pick) {
+            int m = key;
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor1, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor2, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowHalfMirror, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowMirror, 0xF, 0xF, true));
+            m = max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                    max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+            const int w = kWave - 1 - (m & (kWave - 1));
+            drop |= 1ull << w;
+            if (lane == w) key = -1;
+        }
+        if ((drop >> lane) & 1ull) adv[(g0 + q) * A + __popcll(drop & below)] = lane;
+        const unsigned long long left = bits[q] & ~drop;
+        if (lane < NW) {
+            const int odd = sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK ? static_cast<int>(__popcll(left & below)) & 1 : lane & 1;
+            sgn[q * NW + lane] = ((left >> lane) & 1ull) ? (odd ? -1.0 : 1.0) : 0.0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int c = lane & 15, k = lane >> 4;
+        const float *y = Ysh + q * kTile;
+        v4d acc[2] = {v4d{0.0, 0.0, 0.0, 0.0}, v4d{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int s = 0; s < NW / 4; ++s) {
+            const int i = 4 * s + k;
+            const double sg = sgn[q * NW + i];
+            const double v = c == 15 ? 1.0 : static_cast<double>(y[i * CW + c]);
+            acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(T[c * TS + i], sg != 0.0 ? sg * v : 0.0, acc[s & 1], 0, 0, 0);
+        }
+        float *og = out + static_cast<size_t>(g0 + q) * K * C;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int j = 4 * t + k;
+            const double num = acc[0][t] + acc[1][t];
+            const double den = row_bcast<15>(num);
+            double v = num / den;
+            const int h = hit[j];
+            if (h >= 0 && ((left >> h) & 1ull) != 0ull) v = static_cast<double>(y[h * CW + c]);
+            if (j < K && c < C) og[j * C + c] = static_cast<float>(v);
         }
     }
 }
@@ -1756,34 +1871,54 @@ Carved carve_workspace(void *d_workspace, size_t bytes, size_t need_basis, size_
 // kNoFit: the shape does not fit this kernel's LDS (Algorithm 1 with many workers): the caller falls back.
 constexpr int kNoFit = 1;
 
-// Whether decode_byzantine_shared_basis_kernel takes the call: the classes of a group leave class slots empty (C is
-// not a multiple of four), a group is staged in one sixteen-class tile, and there are enough groups to fill the chip
-// four to a workgroup (with fewer, a workgroup per group spreads them over more CUs).  Measured at K = 12, A = 2,
-// 28 workers, 10 classes, 8192 groups (kernel time): one group per workgroup 132 us; 2 groups, 2 waves 137; 4 groups,
-// 4 waves 126; 8 groups, 4 waves 125; one wave per workgroup of 2 / 4 groups 159 / 208.
-constexpr int kSharedBasisGroups = 4;
-bool shared_basis_applies(int64_t G, int64_t C) {
-    if (C > kClsLanes || C % kClsPerWave == 0) return false;
-    return G * ((C + kClsPerWave - 1) / kClsPerWave) >= kFillWaves;
+// Whether decode_byzantine_packed_kernel takes the call: one staged tile of fifteen class columns and the column of the
+// denominators, a row of U per lane of a 16-lane row.
+bool packed_domain(int N, int n, int M, int64_t C) {
+    return C <= kClsLanes - 1 && N <= 48 && M <= kProjMaxM && n - M <= kProjMaxM;
+}
+// Groups per workgroup: one while the chip holds them all at once (five workgroups to each of 256 CUs), where spreading
+// the classes over waves shortens the chain of a group; then as many as keep the launch at one round of workgroups.
+// Measured with 1 / 2 / 4 groups, ten classes: K = 8, A = 2, 20 of 24 workers, 1024 groups 16.9 / 17.5 / 18.2 us, 2048
+// groups 29.1 / 20.4 / 22.3 us, 4096 groups 56 / 37 / 29 us; K = 12, A = 2, 28 workers, 1024 groups 21.7 / 22.6 / 23.7
+// us, 2048 groups 33 / 28 / 30 us, 8192 groups 101 / 81 / 71 us.
+int packed_groups(int64_t G) { return G <= 1280 ? 1 : (G <= 2560 ? 2 : 4); }
+
+template <int NB, int RM, int NW, bool SHARED>
+int run_packed_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
+                     int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
+                     hipStream_t stream) {
+    const int gpw = packed_groups(G);
+    static_assert(packed_lds_bytes<NB, RM, NW>(SHARED, 4) <= 64 * 1024, "fits a workgroup's LDS without an attribute");
+    const int64_t blocks = (G + gpw - 1) / gpw;
+    // a wave per round of four classes, up to four, and one per group (five waves for the ten rounds of four groups
+    // balance better and are slower from 4096 groups on, 100 us against 71 at K = 12, 8192 groups: fewer workgroups fit)
+    int nw = (gpw * C + kClsPerWave - 1) / kClsPerWave;
+    if (nw > kPackedWaves) nw = kPackedWaves;
+    if (nw < gpw) nw = gpw;
+    return launch_status(launch_kernel(decode_byzantine_packed_kernel<NB, RM, NW, SHARED>, dim3(static_cast<unsigned>(blocks)),
+                                       dim3(nw * kWave), packed_lds_bytes<NB, RM, NW>(SHARED, gpw), stream, d_preds,
+                                       d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, sign_mode, gpw, basis, nodes));
 }
 
-template <int NB, int RM, int GPW>
-int run_shared_basis(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status,
-                     int64_t G, int K, int N, int A, int64_t C, const Nodes &nodes, int sign_mode, const double *basis,
-                     hipStream_t stream) {
-    const int KP = (K + 3) & ~3;
-    const int64_t blocks = (G + GPW - 1) / GPW;
-    int nw = static_cast<int>((GPW * C + kClsPerWave - 1) / kClsPerWave);   // a wave per round of four classes, up to four
-    if (nw > 4) nw = 4;
-    const size_t lds = sizeof(double) * (static_cast<size_t>(basis_doubles<NB, RM, false>()) + NB * kPwStride + NB +
-                                         static_cast<size_t>(GPW) * (N - A) * KP + K + N) +
-                       sizeof(float) * (static_cast<size_t>(GPW + 1) * NB * kClsLanes) +
-                       sizeof(int) * (static_cast<size_t>(N) * (1 + 3 * GPW) + GPW);
-    if (lds > 64 * 1024) return kNoFit;                   // the caller goes on with a workgroup per group
-    if (blocks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    return launch_status(launch_kernel(decode_byzantine_shared_basis_kernel<NB, RM, GPW>, dim3(static_cast<unsigned>(blocks)),
-                                       dim3(nw * kWave), lds, stream, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, A,
-                                       static_cast<int>(C), sign_mode, basis, nodes));
+// basis: the call's shared factorisation, for S = 0 only (a group whose mask is not full is bad then); else null.
+template <int NB, int RM>
+int run_packed(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
+               int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
+               hipStream_t stream) {
+    if (basis != nullptr)
+        return run_packed_shape<NB, RM, NB, true>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                  sign_mode, basis, stream);
+    if (N <= NB)
+        return run_packed_shape<NB, RM, NB, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                   sign_mode, nullptr, stream);
+    if constexpr (NB < 48) {
+        if (N <= NB + 4)
+            return run_packed_shape<NB, RM, NB + 4, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                           sign_mode, nullptr, stream);
+        return run_packed_shape<NB, RM, 48, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                   sign_mode, nullptr, stream);
+    }
+    return APPROXIFER_ERR_LIMIT;                          // not inside packed_domain
 }
 
 template <int NB, int RM, bool HOMOG>
@@ -1806,18 +1941,15 @@ int run_proj(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
     const size_t lds = fixed + p.nw * hom_wave;
     if (lds > 64 * 1024) return HOMOG ? kNoFit : APPROXIFER_ERR_LIMIT;   // Algorithm 2: cannot happen inside the domain
     if (G * p.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    if (ws.basis != nullptr) {
+    const bool packed = !HOMOG && RM <= kProjMaxM && packed_domain(N, n_cap, M, C);
+    if (ws.basis != nullptr && !(packed && S != 0)) {
         const hipError_t e = launch_kernel(full_basis_kernel<NB, RM, HOMOG>, dim3(1), dim3(kWave), 0, stream, ws.basis, N, M, nodes);
         if (e != hipSuccess) return APPROXIFER_ERR_LAUNCH;
-        if constexpr (!HOMOG) {
-            // no stragglers by contract (S = 0): every good group shares this factorisation, and groups whose classes
-            // do not fill whole rounds of four are packed several to a workgroup
-            if (S == 0 && shared_basis_applies(G, C)) {
-                const int rc = run_shared_basis<NB, RM, kSharedBasisGroups>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N,
-                                                                            A, C, nodes, sign_mode, ws.basis, stream);
-                if (rc != kNoFit) return rc;
-            }
-        }
+    }
+    if constexpr (!HOMOG && RM <= kProjMaxM) {
+        if (packed)
+            return run_packed<NB, RM>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n_cap, A, static_cast<int>(C), nodes,
+                                      sign_mode, S == 0 ? ws.basis : nullptr, stream);
     }
     if (p.splits > 1) {
         const int rc = clear_workspace(ws.votes, G, N, stream);

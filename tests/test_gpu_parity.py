@@ -749,6 +749,53 @@ def test_byzantine_no_stragglers_groups_share_one_factorisation(gpu, K, A, N, C,
     assert group_err(out[good], ref[good]).max() <= TOL
 
 
+@pytest.mark.parametrize("K,A,S,N,C", [
+    (8, 2, 4, 24, 10),      # the byzantine workload: one row block of workers more than answer
+    (8, 2, 9, 30, 15),      # many more workers than answer; the most classes a staged tile takes
+    (2, 1, 3, 9, 1), (3, 1, 38, 48, 2), (6, 2, 4, 21, 7), (12, 2, 4, 32, 4), (14, 2, 1, 33, 10), (15, 1, 5, 37, 3),
+    (6, 1, 2, 17, 16),      # one class too many for the tile: the workgroup-per-group kernel
+    (6, 2, -1, 24, 10),     # straggler counts read off the masks
+])
+def test_byzantine_groups_packed_into_workgroups(gpu, K, A, S, N, C):
+    # Four, two or one group(s) to a workgroup, by the number of groups: the same bits each way, a bad group in between,
+    # the first groups against the oracle.  Several shapes have a query node that is a worker's node.
+    torch, binding, dev = gpu
+    G, G_ref, mode = 2700, 24, (K + C) % 2
+    rng = np.random.default_rng(77 * K + N)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    Y = (orc.encode(rng.uniform(0, 1, (G, K, 32)), alpha, beta) @ (rng.standard_normal((32, C)) / 6)).astype(np.float32)
+    sd = Y.std()
+    mask = np.zeros((G, N), np.uint8)
+    adv_true = np.zeros((G, A), np.int32)
+    for g in range(G):
+        late = S if S >= 0 else int(rng.integers(0, N - 2 * (K + A) + 1))
+        order = rng.permutation(N)
+        mask[g, order[late:]] = 1
+        adv_true[g] = np.sort([w for w in order[late:] if abs(beta[w]) > 1e-9][:A])
+        Y[g, adv_true[g]] += (10 * sd * rng.standard_normal((A, C))).astype(np.float32)
+        Y[g, mask[g] == 0] = np.nan                      # an answer that did not come is not looked at
+    mask[5] = 0
+    Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
+    res = {}
+    for n_groups in (2700, 1500, 40):
+        out = torch.full((n_groups, K, C), -3.0, dtype=torch.float32, device=dev)
+        adv = torch.full((n_groups, A), -7, dtype=torch.int32, device=dev)
+        got = binding.approxifer_decode_byzantine(Yd[:n_groups], md[:n_groups], alpha, beta, S, A, mode, out=out, adv=adv)
+        res[n_groups] = [t.cpu().numpy() for t in got]
+    for n_groups in (1500, 40):
+        for whole, part in zip(res[2700], res[n_groups]):
+            assert np.array_equal(whole[:n_groups], part)
+    out, adv, st = [x[:G_ref] for x in res[2700]]
+    Yz = np.where(mask[:G_ref, :, None] != 0, Y[:G_ref], 0.0).astype(np.float32)
+    ref, adv_ref, st_ref = orc.decode_byzantine(Yz, mask[:G_ref], alpha, beta, S, A, mode)
+    assert np.array_equal(st, st_ref) and st[5] == 1 and st.sum() == 1
+    assert np.all(out[5] == -3.0) and np.all(adv[5] == -7)
+    good = (st == 0) & np.array([np.array_equal(a, b) for a, b in zip(adv_ref, adv_true[:G_ref])])
+    assert good.sum() >= (G_ref - 1 if C >= 7 else 1)     # one class may hold an answer that is hardly wrong
+    assert np.array_equal(adv[good], adv_ref[good])
+    assert group_err(out[good], ref[good]).max() <= TOL
+
+
 def test_byzantine_nonlinear_model_votes(gpu):
     # softmax outputs are not rational in beta: Algorithm 2's fit is a genuine least-squares problem
     # and single classes may disagree.  The GPU must reproduce the oracle's vote wherever the oracle's
