@@ -160,14 +160,17 @@ __device__ __forceinline__ void pick_and_vote(const double *key, const int *avai
 // ------------------------------------------------------------------------------------------------
 constexpr int kClsLanes = 16;      // lanes per class (one DPP row)
 constexpr int kClsPerWave = 4;
-constexpr int kPwStride = 16;      // powers table row: x^0 .. x^15
+constexpr int kPowers = 16;        // rows of the powers table: x^0 .. x^15
 constexpr int kProjMaxM = 16;      // M - 1 <= 15 unknown columns in lanes 0..14, right-hand side in lane 15
-// U in LDS: rows padded to a multiple of four (the matrix-core tiles below take four rows of U at a time), row
-// stride chosen so that the sixteen (row, column) pairs one operand load touches fall in distinct banks.
+// LDS layouts, all read a run of rows r at a time by lanes that differ in the other index: U[i][r] (rows padded to a
+// multiple of four) and the powers Pw[e][r] = x_r^e with row stride lds_stride, the predictions Y[c][r] with y_stride.
+// The strides keep runs 16-byte aligned and put the lanes of one 128-bit read into different banks.
+constexpr int lds_stride(int NB) { return NB + 2; }                             // doubles: half of it is odd
+constexpr int y_stride(int NB) { return (NB / 4) % 2 == 1 ? NB : NB + 4; }     // floats: a quarter of it is odd
 // Register-array bound of Algorithm 1's locator for a tile of NB rows: eq. (3) gives M <= n / 2 <= NB / 2.
 constexpr int hom_mt(int NB) { return NB / 2 < kProjMaxM ? NB / 2 : kProjMaxM; }
 constexpr int ush_rows(int RM) { return (RM + 3) & ~3; }
-constexpr int ush_stride(int NB) { return NB % 16 == 0 ? NB + 4 : NB; }
+constexpr int basis_stride(int NB) { return NB % 16 == 0 ? NB + 4 : NB; }      // of the basis kept in the workspace
 
 template <int LANE>
 __device__ __forceinline__ double row_bcast(double v) {   // lane LANE of every 16-lane row, to the whole row
@@ -268,7 +271,7 @@ struct SharedQrSteps<kProjMaxM, NB> {
     static __device__ __forceinline__ void run(double (&)[NB], int, int) {}
 };
 
-// Pw[r][e] = x_r^e (LDS), n rows, M <= 16 columns.  Writes Ush[i][r] = U[i][r], i < RM, row stride ush_stride(NB).
+// Pw[e][r] = x_r^e (LDS), n rows, M <= 16 columns.  Writes Ush[i][r] = U[i][r], i < RM, row stride lds_stride(NB).
 // WITH_RANGE (Algorithm 1's locator needs the whole factorisation): also Q1sh[i][r] = row i < M of Q^T (16 rows of
 // the same stride, rows from M on left as they are) and Rv[i][j] = R[i][j], the M x M triangular factor of V (row
 // stride 16, zero below the diagonal).
@@ -281,7 +284,7 @@ __device__ __forceinline__ void shared_complement_basis(const double *Pw, int n,
     const int e = vandermonde ? lane : 0;
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
-        const double p = Pw[(r < n ? r : 0) * kPwStride + e];
+        const double p = Pw[e * lds_stride(NB) + (r < n ? r : 0)];
         col[r] = (r < n) ? (vandermonde ? p : (lane - M == r ? 1.0 : 0.0)) : 0.0;
     }
     SharedQrSteps<0, NB>::run(col, lane, M);
@@ -290,12 +293,12 @@ __device__ __forceinline__ void shared_complement_basis(const double *Pw, int n,
 #pragma unroll
         for (int row = 2; row < NB; ++row) {        // M >= 2 always
             const int i = row - M;
-            if (i >= 0 && i < RM) Ush[i * ush_stride(NB) + r_out] = col[row];
+            if (i >= 0 && i < RM) Ush[i * lds_stride(NB) + r_out] = col[row];
         }
         if (WITH_RANGE) {
 #pragma unroll
             for (int row = 0; row < kProjMaxM && row < NB; ++row)
-                if (row < M) Q1sh[row * ush_stride(NB) + r_out] = col[row];
+                if (row < M) Q1sh[row * lds_stride(NB) + r_out] = col[row];
         }
     }
     if (WITH_RANGE && lane < M) {
@@ -314,7 +317,8 @@ __device__ __forceinline__ void shared_complement_basis(const double *Pw, int n,
 // A DPP operand must not be read within two wait states of the VALU instruction that wrote it, and the compiler does
 // not see into a block: each opens with s_nop 1, and inside no instruction reads what an earlier one wrote as its
 // DPP operand.  `b` may be `a` itself: every element is read before it is written, once.
-// Results of matrix instructions must pass matrix_results_settled() first (the same blindness, up to 19 wait states).
+// Nor may a block read what a matrix instruction wrote (up to 19 wait states that only the compiler inserts): nothing
+// here does.
 #define APX_DPP " row_newbcast:%[l] row_mask:0xf bank_mask:0xf\n"
 #define APX_D2(x, y, u, v) "v_fmac_f64_dpp %[d0], %[" #x "], %[" #u "]" APX_DPP "v_fmac_f64_dpp %[d1], %[" #y "], %[" #v "]" APX_DPP
 #define APX_U(x, u) "v_fmac_f64_dpp %[" #x "], %[" #u "], %[f]" APX_DPP
@@ -394,18 +398,31 @@ __device__ __forceinline__ void row_axpy(double (&q)[NQ], const double (&b)[NB],
         row_axpy<LANE, O + 1, T>(q, b, f);
     }
 }
+// a[O + i] += bcast_i(u) * p: an outer product, lane i of the row holding the first factor of element i
+#define APX_O(x, i) "v_fmac_f64_dpp %[" #x "], %[u], %[p] row_newbcast:%[" #i "] row_mask:0xf bank_mask:0xf\n"
+template <int O, int L, int CNT, int RM>
+__device__ __forceinline__ void row_outer(double (&a)[RM], double u, double p) {
+    if constexpr (CNT >= 8) {
+        asm("s_nop 1\n" APX_O(a0, i0) APX_O(a1, i1) APX_O(a2, i2) APX_O(a3, i3) APX_O(a4, i4) APX_O(a5, i5) APX_O(a6, i6)
+                APX_O(a7, i7)
+            : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1]), [a2] "+v"(a[O + 2]), [a3] "+v"(a[O + 3]), [a4] "+v"(a[O + 4]),
+              [a5] "+v"(a[O + 5]), [a6] "+v"(a[O + 6]), [a7] "+v"(a[O + 7])
+            : [u] "v"(u), [p] "v"(p), [i0] "n"(L), [i1] "n"(L + 1), [i2] "n"(L + 2), [i3] "n"(L + 3), [i4] "n"(L + 4),
+              [i5] "n"(L + 5), [i6] "n"(L + 6), [i7] "n"(L + 7));
+        row_outer<O + 8, L + 8, CNT - 8>(a, u, p);
+    } else if constexpr (CNT >= 2) {
+        asm("s_nop 1\n" APX_O(a0, i0) APX_O(a1, i1)
+            : [a0] "+v"(a[O]), [a1] "+v"(a[O + 1])
+            : [u] "v"(u), [p] "v"(p), [i0] "n"(L), [i1] "n"(L + 1));
+        row_outer<O + 2, L + 2, CNT - 2>(a, u, p);
+    } else if constexpr (CNT == 1) {
+        asm("s_nop 1\n" APX_O(a0, i0) : [a0] "+v"(a[O]) : [u] "v"(u), [p] "v"(p), [i0] "n"(L));
+    }
+}
+#undef APX_O
 #undef APX_U
 #undef APX_D2
 #undef APX_DPP
-
-template <int RM>
-__device__ __forceinline__ void matrix_results_settled(double (&a)[RM]) {
-#pragma unroll
-    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));       // every result is on its way ..
-    asm volatile("s_nop 15\n s_nop 7");
-#pragma unroll
-    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));       // .. and there before anything below reads it
-}
 
 // ---- once per group, four groups to a wave: U = the last n - M columns of Q, transposed ----------------------------
 // Householder reflectors of the group's Vandermonde block V (n x M) in the group's 16-lane row, lane = column, then
@@ -450,8 +467,8 @@ struct RowReflectors {
     }
 };
 
-// One wave; lane row q works on group q: n_q workers avail_q[0..n_q), ascending (n_q = 0: none).  Pw[w][e] = x_w^e by
-// worker.  Writes Ush_q[i * stride + w] = U[i][worker w] for i < n_q - M (the rest of Ush is left as it is: zero).
+// One wave; lane row q works on group q: n_q workers avail_q[0..n_q), ascending (n_q = 0: none).  Pw[e][w] = x_w^e by
+// worker, row stride `stride` as Ush.  Writes Ush_q[i * stride + w] = U[i][worker w] for i < n_q - M (the rest of Ush is left as it is: zero).
 template <int NB>
 __device__ __forceinline__ void rows_complement_basis(const double *Pw, const int *avail_q, int n, int M, double *Ush_q,
                                                       int stride) {
@@ -460,7 +477,7 @@ __device__ __forceinline__ void rows_complement_basis(const double *Pw, const in
     double a[NB], z[NB], sc = 0.0;
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
-        const double p = Pw[(r < n ? avail_q[r] : 0) * kPwStride + j];
+        const double p = Pw[j * stride + (r < n ? avail_q[r] : 0)];
         a[r] = (r < n && j < M) ? p : 0.0;
         z[r] = r == M + j && r < n ? 1.0 : 0.0;
     }
@@ -582,69 +599,70 @@ __device__ __forceinline__ void vote_smallest(double (&key)[PR], int A, bool liv
     }
 }
 
-// Algorithm 2, steps 1-5, for four classes at a time, by one wave.
-//   ycol, urow (per lane): class slot (lane % 16) & 3 of this round, whose operands this lane feeds to the matrix cores:
-//   ycol[r * CW] = its prediction of row r, float, zero where there is no answer (an empty slot points at zeros);
-//   urow[i * ush_stride(NB) + r] = U[i][r] of its group, zero where there is no such row or column, LDS;
-//   live, rows, votes (per lane): class slot lane / 16, whose system this lane's row then holds: whether it is a class,
-//   bit r: row r is an available worker, and the vote counters of its group, by worker;
-//   Pw[NB][16] = powers of the rows' nodes, LDS: the same rows for all four slots.
+// Between a block above and a DPP operand that the compiler schedules itself.
+template <int RM>
+__device__ __forceinline__ void row_results_settled(double (&a)[RM]) {
+#pragma unroll
+    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
+    asm volatile("s_nop 1");
+#pragma unroll
+    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
+}
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+// a[i] += sum_r U[i][r] y_r w_r over the NB rows r, this lane holding row i = lane % 16 of U (`u`), its class's
+// predictions (`y`) and its column's powers (`w`): an outer product per row, whose factor U[i][r] reaches the lanes of
+// the class inside the multiply-add.  On the vector ALUs on purpose: v_mfma_f64_16x16x4_f64 takes four classes' products
+// in the same layout, but at 108 cycles each (measured; 16 % below the rate of plain multiply-adds) it holds the same
+// issue slots and fills fourteen of sixteen columns: K = 12, A = 2, 28 workers, 8192 groups 71 us with it, 69 without;
+// Algorithm 1 at K = 8, A = 2, 2048 groups 67 and 61 us.
+template <int NB, int RM>
+__device__ __forceinline__ void project_column(double (&a)[RM], const double *u, const float *y, const double *w) {
+#pragma unroll
+    for (int r = 0; r < NB; r += 4) {
+        const v4f y4 = *reinterpret_cast<const v4f *>(y + r);
+#pragma unroll
+        for (int h = 0; h < 4; h += 2) {
+            const v2d w2 = *reinterpret_cast<const v2d *>(w + r + h);
+            const v2d u2 = *reinterpret_cast<const v2d *>(u + r + h);
+            const double p0 = static_cast<double>(y4[h]) * w2[0], p1 = static_cast<double>(y4[h + 1]) * w2[1];
+            constexpr int kLow = RM < kClsLanes ? RM : kClsLanes;
+            row_outer<0, 0, kLow>(a, u2[0], p0);
+            row_outer<0, 0, kLow>(a, u2[1], p1);
+            if constexpr (RM > kClsLanes) {               // rows 16.. of U come from a second register of the lanes
+                const v2d v2 = *reinterpret_cast<const v2d *>(u + kClsLanes * lds_stride(NB) + r + h);
+                row_outer<kClsLanes, 0, RM - kClsLanes>(a, v2[0], p0);
+                row_outer<kClsLanes, 0, RM - kClsLanes>(a, v2[1], p1);
+            }
+        }
+    }
+}
+
+// Algorithm 2, steps 1-5, for four classes at a time, by one wave; lane / 16 is the class slot.  Per lane:
+//   y[r] = the class's prediction of row r, float, zero where there is no answer (an empty slot points at zeros); `zeros`
+//   the same number of zeros;  U: its group's U[i][r], zero where there is no such row or column;  live: the slot holds a
+//   class;  bit r of rows: row r is an available worker;  votes: the counters of its group, by worker.
+// Pw[e][r] = powers of the rows' nodes: the same rows for all four slots.  U and Pw in LDS, stride lds_stride(NB).
 // A row is the r-th available worker, worker_of_row its index, or (worker_of_row null) the worker r itself.
 template <int NB, int RM>
-__device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, const double *urow, bool live,
+__device__ __forceinline__ void locate_classes_proj(const float *y, const float *zeros, const double *U, bool live,
                                                     unsigned long long rows, const int *worker_of_row, const double *Pw,
                                                     int M, int A, int *votes) {
-    typedef double v4d __attribute__((ext_vector_type(4)));
     const int lane = lane_id();
     const int j = lane % kClsLanes;
     const int cols = M - 1;                               // unknowns Q_1 .. Q_{M-1}
 
-    // column of this lane: y x^(j+1) for the unknown Q_(j+1), y for the right-hand side, 0 on idle lanes (the signs of
-    // -y x^(j+1) q = y are left out: the solve below returns the negative)
+    // the projected system B_c = U diag(y_c) [x^e]: column of this lane: y x^(j+1) for the unknown Q_(j+1), y for the
+    // right-hand side, 0 on idle lanes (the signs of -y x^(j+1) q = y are left out: the solve below returns the negative)
     const int e = j < cols ? j + 1 : 0;
-    const double sgn = (j < cols || j == kClsLanes - 1) ? 1.0 : 0.0;
-
-    // ---- the projected systems of the four classes, B_c = U diag(y_c) [x^e], on the float64 matrix cores -------
-    // v_mfma_f64_16x16x4_f64 computes D[16x16] += A[16x4] * B[4x16]; lane l holds A[l%16][l/16], B[l/16][l%16] and, in
-    // register t of D, D[4t + l/16][l%16].  With
-    //     A[4t + c][k] = U[4b + t][r] * y_{r, class c}      B[k][j] = sgn_j * x_r^{e_j}      (r = 4s + k)
-    // summed over the k-steps s, register t of lane (c, j) receives B_c[4b + t][j]: exactly the layout the
-    // factorisation below wants (lane = class and column, rows in registers), with no lane exchange at all.
-    // Empty rows are zero in ycol, Pw and urow, so the k-steps need no bound.
-    constexpr int kKSteps = NB / 4;
-    constexpr int kRowBlocks = ush_rows(RM) / 4;
-    static_assert(NB % 4 == 0, "k-steps take four available workers at a time");
-    double bop[kKSteps], yop[kKSteps];
-    {
-        const int k = lane / kClsLanes;
-#pragma unroll
-        for (int s = 0; s < kKSteps; ++s) {
-            const int r = 4 * s + k;
-            bop[s] = sgn * Pw[r * kPwStride + e];
-            yop[s] = static_cast<double>(ycol[r * CW]);
-        }
-    }
     double a[RM];
-    {
-        const double *u = urow + ((lane % kClsLanes) >> 2) * ush_stride(NB) + lane / kClsLanes;
-        v4d acc[kRowBlocks];
 #pragma unroll
-        for (int b = 0; b < kRowBlocks; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int s = 0; s < kKSteps; ++s)                 // the row blocks are independent accumulation chains
-#pragma unroll
-            for (int b = 0; b < kRowBlocks; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[4 * b * ush_stride(NB) + 4 * s] * yop[s], bop[s], acc[b],
-                                                              0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < kRowBlocks; ++b)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (4 * b + t < RM) a[4 * b + t] = acc[b][t];
-    }
+    for (int i = 0; i < RM; ++i) a[i] = 0.0;
+    project_column<NB>(a, U + (j < RM ? j : 0) * lds_stride(NB), j < cols || j == kClsLanes - 1 ? y : zeros,
+                       Pw + e * lds_stride(NB));
 
     constexpr int kSteps = RM - 1 < kProjMaxM - 1 ? RM - 1 : kProjMaxM - 1;   // most unknowns this tile can hold
-    matrix_results_settled(a);
     double nf[kSteps];
     ClassGramSchmidt<0, kSteps, RM>::run(a, nf, cols);
 
@@ -659,7 +677,7 @@ __device__ __forceinline__ void locate_classes_proj(const float *ycol, int CW, c
 #pragma unroll
     for (int p = 0; p < PR; ++p) {
         const int r = j + p * kClsLanes;
-        const double x = Pw[(r < NB ? r : 0) * kPwStride + 1];
+        const double x = Pw[lds_stride(NB) + (r < NB ? r : 0)];
         double av = 0.0;
 #pragma unroll
         for (int t = kSteps - 1; t >= 0; --t) av = fma(av, x, q[t]);
@@ -818,56 +836,29 @@ __device__ __forceinline__ bool singular_vector_rows(const double (&r2c)[MT], co
 //     Q^T H_c = [ R_V   Q1^T diag(y_c) V ]      Q1^T = rows 0..M-1 of Q^T,
 //               [  0     U  diag(y_c) V ]      U    = rows M..n-1,
 // so the 2M x 2M triangular factor of H_c is [[R_V, B1], [0, R2]] with B1 = Q1^T diag(y_c) V (M x M) and
-// R2 the triangular factor of B2 = U diag(y_c) V ((n-M) x M; n - M >= M by eq. (3)).  B1 and B2 come from the
-// float64 matrix cores exactly as the projected system of Algorithm 2 does (Q1 sits in the 16 rows that follow U in
-// LDS), R2 from the same register Householder QR, run over all M columns.  The smallest right singular vector of
+// R2 the triangular factor of B2 = U diag(y_c) V ((n-M) x M; n - M >= M by eq. (3)).  B1 and B2 are
+// formed as the projected system of Algorithm 2 is (Q1 sits in the 16 rows that follow U in LDS), R2 from the same register Householder QR, run over all M columns.  The smallest right singular vector of
 // the assembled factor is found in registers (singular_vector_rows); a class that does not settle there is assembled
 // in this wave's scratch, mat[2M][2M+1] | coef[M] | key[n], and goes through the LDS form (homogeneous_q), as many
 // classes at a time as the scratch holds (one, as the host sizes it).
 template <int NB, int RM>
-__device__ __forceinline__ void locate_classes_hom_proj(const float *Ysh, int CW, int c_rel, int tile_classes,
+__device__ __forceinline__ void locate_classes_hom_proj(const float *y, const float *zeros, int c_rel, int tile_classes,
                                                         const int *avail, const double *xs, const double *Pw,
                                                         const double *Ush, const double *Rv, int n, int M, int A,
                                                         double *scratch, int scratch_doubles, int *votes) {
-    typedef double v4d __attribute__((ext_vector_type(4)));
     const int lane = lane_id();
     const int j = lane % kClsLanes;
-    const int e = j < M ? j : 0;                          // column of this lane: y x^j; idle lanes hold zeros
-    const double sgn = j < M ? 1.0 : 0.0;
     constexpr int MT = hom_mt(NB);
-    constexpr int kKSteps = NB / 4;
-    constexpr int kUBlocks = ush_rows(RM) / 4;
-    constexpr int kBlocks = kUBlocks + (MT + 3) / 4;      // then the rows of Q1 (16 of them in LDS, the first MT used)
-    double bop[kKSteps], yop[kKSteps];
-    {
-        const int k = lane / kClsLanes, cm = (lane % kClsLanes) & 3;
-#pragma unroll
-        for (int s = 0; s < kKSteps; ++s) {
-            const int r = 4 * s + k;
-            bop[s] = sgn * Pw[r * kPwStride + e];
-            yop[s] = static_cast<double>(Ysh[r * CW + c_rel + cm]);
-        }
-    }
     double a[RM], b1[MT];
-    {
-        const double *urow = Ush + ((lane % kClsLanes) >> 2) * ush_stride(NB) + lane / kClsLanes;
-        v4d acc[kBlocks];
 #pragma unroll
-        for (int b = 0; b < kBlocks; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int i = 0; i < RM; ++i) a[i] = 0.0;
 #pragma unroll
-        for (int s = 0; s < kKSteps; ++s)
-#pragma unroll
-            for (int b = 0; b < kBlocks; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(urow[4 * b * ush_stride(NB) + 4 * s] * yop[s], bop[s], acc[b],
-                                                              0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < kUBlocks; ++b)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (4 * b + t < RM) a[4 * b + t] = acc[b][t];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) b1[i] = acc[kUBlocks + i / 4][i % 4];
-    }
+    for (int i = 0; i < MT; ++i) b1[i] = 0.0;
+    const float *yj = j < M ? y : zeros;                  // column of this lane: y x^j; idle lanes hold zeros
+    const double *wj = Pw + (j < M ? j : 0) * lds_stride(NB);
+    project_column<NB>(a, Ush + (j < RM ? j : 0) * lds_stride(NB), yj, wj);
+    project_column<NB>(b1, Ush + (ush_rows(RM) + j) * lds_stride(NB), yj, wj);
+    row_results_settled(a);
 
     // R2: steps 0 .. min(M, RM - 1) - 1; when M == RM the last diagonal entry is the one row that is left
     constexpr int kSteps = RM - 1 < kProjMaxM - 1 ? RM - 1 : kProjMaxM - 1;
@@ -955,16 +946,35 @@ __host__ __device__ constexpr int hom_scratch_doubles(int M, int n_cap, int MT) 
 }
 
 // Doubles of the shared factorisation as the kernel keeps it in LDS (and as full_basis_kernel writes it out):
-// Ush[ush_rows(RM)][ush_stride(NB)], and for Algorithm 1's locator also Q1sh[16][ush_stride(NB)] | Rv[16][16].
+// Ush[ush_rows(RM)][lds_stride(NB)], and for Algorithm 1's locator also Q1sh[16][lds_stride(NB)] | Rv[16][16].
 template <int NB, int RM, bool HOMOG>
 constexpr int basis_doubles() {
-    return ush_rows(RM) * ush_stride(NB) + (HOMOG ? kProjMaxM * ush_stride(NB) + kProjMaxM * kProjMaxM : 0);
+    return (ush_rows(RM) + (HOMOG ? kProjMaxM : 0)) * lds_stride(NB) + (HOMOG ? kProjMaxM * kProjMaxM : 0);
+}
+// The same between LDS and the caller's workspace, where rows have stride basis_stride(NB).
+template <int NB, int RM, bool HOMOG>
+__device__ __forceinline__ void basis_from_workspace(double *Ush, const double *__restrict__ basis) {
+    constexpr int rows = ush_rows(RM) + (HOMOG ? kProjMaxM : 0);
+    for (int e = threadIdx.x; e < rows * NB; e += blockDim.x)
+        Ush[e / NB * lds_stride(NB) + e % NB] = basis[e / NB * basis_stride(NB) + e % NB];
+    if (HOMOG)
+        for (int e = threadIdx.x; e < kProjMaxM * kProjMaxM; e += blockDim.x)
+            Ush[rows * lds_stride(NB) + e] = basis[rows * basis_stride(NB) + e];
+}
+template <int NB, int RM, bool HOMOG>
+__device__ __forceinline__ void basis_to_workspace(const double *Ush, double *__restrict__ basis) {
+    constexpr int rows = ush_rows(RM) + (HOMOG ? kProjMaxM : 0);
+    for (int e = threadIdx.x; e < rows * NB; e += blockDim.x)
+        basis[e / NB * basis_stride(NB) + e % NB] = Ush[e / NB * lds_stride(NB) + e % NB];
+    if (HOMOG)
+        for (int e = threadIdx.x; e < kProjMaxM * kProjMaxM; e += blockDim.x)
+            basis[rows * basis_stride(NB) + e] = Ush[rows * lds_stride(NB) + e];
 }
 
 // HOMOG: Algorithm 1's fit as the per-class locator (locate_classes_hom_proj) instead of Algorithm 2's.
-// dynamic LDS (doubles): basis (see basis_doubles) | Pw[NB*16] | xs[NB] | WdT[(n_cap-A)*KP] | alpha_s[K] | beta_s[N]
-//               | HOMOG: scratch[nw][hom_scratch_doubles(M, n_cap, NB / 2)]
-//               then float Ysh[NB*CW], then ints: avail[N] | F[N] | Fpos[N] | votes[N] | n | flag
+// dynamic LDS (doubles): basis (see basis_doubles) | Pw[16][lds_stride] | xs[NB] | float Ysh[CW + 1][y_stride]
+//               | WdT[(n_cap-A)*KP] | alpha_s[K] | beta_s[N] | HOMOG: scratch[nw][hom_scratch_doubles(M, n_cap, NB / 2)]
+//               then ints: avail[N] | F[N] | Fpos[N] | votes[N] | n | flag
 template <int NB, int RM, bool HOMOG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && RM <= 16 && NB <= 28 ? 3 : 2))) void decode_byzantine_proj_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
@@ -978,17 +988,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
     const int CW = 1 << cw_log2;                          // classes per staged tile (16, 32 or 64)
     double *Ush = lds_d;
     constexpr int kUshDoubles = basis_doubles<NB, RM, HOMOG>();
-    double *Q1sh = Ush + ush_rows(RM) * ush_stride(NB);   // HOMOG only: the 16 rows after U, then R_V
-    double *Rv = Q1sh + kProjMaxM * ush_stride(NB);
+    constexpr int YS = y_stride(NB);
+    double *Q1sh = Ush + ush_rows(RM) * lds_stride(NB);   // HOMOG only: the 16 rows after U, then R_V
+    double *Rv = Q1sh + kProjMaxM * lds_stride(NB);
     double *Pw = Ush + kUshDoubles;
-    double *xs = Pw + NB * kPwStride;
-    double *WdT = xs + NB;
+    double *xs = Pw + kPowers * lds_stride(NB);
+    float *Ysh = reinterpret_cast<float *>(xs + NB);      // [CW + 1][YS], the last row stays zero
+    double *WdT = xs + NB + (CW + 1) * YS / 2;
     double *alpha_s = WdT + (n_cap - A) * KP;
     double *beta_s = alpha_s + K;
     const int hom_wave_doubles = HOMOG ? hom_scratch_doubles(M, n_cap, hom_mt(NB)) : 0;
     double *hom_scratch = beta_s + N;
-    float *Ysh = reinterpret_cast<float *>(hom_scratch + static_cast<size_t>(nw) * hom_wave_doubles);
-    int *avail = reinterpret_cast<int *>(Ysh + NB * CW);
+    int *avail = reinterpret_cast<int *>(hom_scratch + static_cast<size_t>(nw) * hom_wave_doubles);
     int *F = avail + N;
     int *Fpos = F + N;
     int *votes = Fpos + N;
@@ -1016,7 +1027,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
     // A group in which every worker answered has the node set of the whole call: its complement basis was
     // factorised once, ahead of this launch (full_basis_kernel), and is only copied here.
     const bool preloaded = full_basis != nullptr && n == N;
-    for (int e = tid; e < kUshDoubles; e += blockDim.x) Ush[e] = preloaded ? full_basis[e] : 0.0;
+    if (preloaded) basis_from_workspace<NB, RM, HOMOG>(Ush, full_basis);
+    else
+        for (int e = tid; e < kUshDoubles; e += blockDim.x) Ush[e] = 0.0;
+    for (int e = tid; e < YS; e += blockDim.x) Ysh[CW * YS + e] = 0.0f;
 
     // first class tile: the loads are issued now and land in LDS after the shared factorisation
     constexpr int kPrefetch = 8;
@@ -1035,8 +1049,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
         const double x = r < n ? beta_s[avail[r]] : 0.0;
         if (r < n) xs[r] = x;
         double p = r < n ? 1.0 : 0.0;
-        for (int e = 0; e < kPwStride; ++e) {
-            Pw[r * kPwStride + e] = p;
+        for (int e = 0; e < kPowers; ++e) {
+            Pw[e * lds_stride(NB) + r] = p;
             p *= x;
         }
     }
@@ -1048,28 +1062,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
 #pragma unroll
             for (int u = 0; u < kPrefetch; ++u) {
                 const int slot = tid + u * blockDim.x;
-                if (slot < slots) Ysh[slot] = pf[u];
+                if (slot < slots) Ysh[(slot & (CW - 1)) * YS + (slot >> cw_log2)] = pf[u];
             }
             for (int slot = tid + kPrefetch * blockDim.x; slot < slots; slot += blockDim.x) {
                 const int r = slot >> cw_log2, c = slot & (CW - 1);
-                Ysh[slot] = (r < n && cb + c < C) ? pg[static_cast<size_t>(avail[r]) * C + cb + c] : 0.0f;
+                Ysh[c * YS + r] = (r < n && cb + c < C) ? pg[static_cast<size_t>(avail[r]) * C + cb + c] : 0.0f;
             }
         } else {
             __syncthreads();                              // every wave is done with the previous tile
             for (int slot = tid; slot < slots; slot += blockDim.x) {
                 const int r = slot >> cw_log2, c = slot & (CW - 1);
-                Ysh[slot] = (r < n && cb + c < C) ? pg[static_cast<size_t>(avail[r]) * C + cb + c] : 0.0f;
+                Ysh[c * YS + r] = (r < n && cb + c < C) ? pg[static_cast<size_t>(avail[r]) * C + cb + c] : 0.0f;
             }
         }
         __syncthreads();
         const int tile_classes = (C - cb < CW) ? static_cast<int>(C - cb) : CW;
         for (int c_rel = wv * kClsPerWave; c_rel < tile_classes; c_rel += nw * kClsPerWave) {
             if (HOMOG)
-                locate_classes_hom_proj<NB, RM>(Ysh, CW, c_rel, tile_classes, avail, xs, Pw, Ush, Rv, n, M, A,
+                locate_classes_hom_proj<NB, RM>(Ysh + (c_rel + lane_id() / kClsLanes) * YS, Ysh + CW * YS, c_rel, tile_classes,
+                                                avail, xs, Pw, Ush, Rv, n, M, A,
                                                 hom_scratch + static_cast<size_t>(wv) * hom_wave_doubles, hom_wave_doubles,
                                                 votes);
             else
-                locate_classes_proj<NB, RM>(Ysh + c_rel + ((lane_id() % kClsLanes) & 3), CW, Ush,
+                locate_classes_proj<NB, RM>(Ysh + (c_rel + lane_id() / kClsLanes) * YS, Ysh + CW * YS, Ush,
                                             c_rel + lane_id() / kClsLanes < tile_classes, (1ull << n) - 1ull, avail, Pw, M, A,
                                             votes);
         }
@@ -1091,7 +1106,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
             double acc = 0.0;
 #pragma unroll 6
             for (int r = 0; r < nF; ++r)
-                acc = fma(WdT[r * KP + jq], static_cast<double>(Ysh[(Fpos[r] << cw_log2) + c]), acc);
+                acc = fma(WdT[r * KP + jq], static_cast<double>(Ysh[c * YS + Fpos[r]]), acc);
             og[o] = static_cast<float>(acc);
         }
     } else if (vec4) {
@@ -1116,14 +1131,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
 // K = 8, A = 2, 20 of 24 workers, 2048 groups of 10 classes: 24.5 us with a workgroup per group, 20.4 us this way;
 // K = 12, A = 2, 28 workers, 8192 groups: 91.2 us with this packing but decoder weights per group, 70.8 us.
 // NB >= N - S bounds the workers that answer, NW >= N all workers, RM >= N - S - M.
-// dynamic LDS: double Ush[SHARED ? 1 : GPW][ush_rows(RM) * ush_stride(NW)] | Pw[NW][16] | T[16][NW + 1] | sgn[GPW][NW]
-//              | float Ysh[GPW + 1][NW][16] (the last tile stays zero: empty class slots read it)
-//              | int avail[GPW][NW] | votes[GPW][64] | hit[16] | uint64 bits[GPW]
+// dynamic LDS: double Ush[SHARED ? 1 : GPW][ush_rows(RM)][lds_stride(NW)] | Pw[16][lds_stride(NW)] | T[16][NW + 1]
+//              | sgn[GPW][NW] | float Ysh[16 GPW + 1][y_stride(NW)] (the last row stays zero: empty class slots read it)
+//              | uint64 bits[GPW] | int avail[GPW][NW] | votes[GPW][64] | hit[16]
 template <int NB, int RM, int NW>
 constexpr size_t packed_lds_bytes(bool shared, int gpw) {
-    return sizeof(double) * (static_cast<size_t>(shared ? 1 : gpw) * ush_rows(RM) * ush_stride(NW) + NW * kPwStride +
+    return sizeof(double) * ((static_cast<size_t>(shared ? 1 : gpw) * ush_rows(RM) + kPowers) * lds_stride(NW) +
                              16 * (NW + 1) + gpw * NW + gpw) +
-           sizeof(float) * (static_cast<size_t>(gpw + 1) * NW * kClsLanes) +
+           sizeof(float) * (static_cast<size_t>(gpw * kClsLanes + 1) * y_stride(NW)) +
            sizeof(int) * (static_cast<size_t>(gpw) * (NW + kWave) + 16);
 }
 constexpr int kPackedWaves = 4;      // at most
@@ -1136,8 +1151,8 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     typedef double v4d __attribute__((ext_vector_type(4)));
     extern __shared__ __align__(16) double lds_d[];
     constexpr int CW = kClsLanes;
-    constexpr int kTile = NW * CW;
-    constexpr int kStride = ush_stride(NW);
+    constexpr int YS = y_stride(NW);
+    constexpr int kStride = lds_stride(NW);
     constexpr int kUsh = ush_rows(RM) * kStride;
     constexpr int TS = NW + 1;                            // odd: the sixteen rows an operand load touches lie in distinct banks
     const int threads = blockDim.x;                       // at least a wave per group
@@ -1145,11 +1160,12 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     const int M = K + A;
     double *Ush = lds_d;
     double *Pw = Ush + (SHARED ? 1 : gpw) * kUsh;
-    double *T = Pw + NW * kPwStride;
+    double *T = Pw + kPowers * kStride;
     double *sgn = T + 16 * TS;
-    unsigned long long *bits = reinterpret_cast<unsigned long long *>(sgn + gpw * NW);
-    float *Ysh = reinterpret_cast<float *>(bits + gpw);
-    int *avail = reinterpret_cast<int *>(Ysh + (gpw + 1) * kTile);
+    float *Ysh = reinterpret_cast<float *>(sgn + gpw * NW);
+    float *zeros = Ysh + gpw * CW * YS;
+    unsigned long long *bits = reinterpret_cast<unsigned long long *>(zeros + YS);
+    int *avail = reinterpret_cast<int *>(bits + gpw);
     int *votes = avail + gpw * NW;
     int *hit = votes + gpw * kWave;
     const int64_t g0 = static_cast<int64_t>(blockIdx.x) * gpw;
@@ -1182,15 +1198,15 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         votes[q * kWave + lane] = 0;
     }
     if (SHARED) {
-        for (int e = tid; e < kUsh; e += threads) Ush[e] = full_basis[e];
+        basis_from_workspace<NB, RM, false>(Ush, full_basis);
     } else {
         for (int e = tid; e < gpw * kUsh; e += threads) Ush[e] = 0.0;
     }
     if (tid < NW) {
         const double x = tid < N ? nodes.beta[tid] : 0.0;
         double pw = tid < N ? 1.0 : 0.0;
-        for (int e = 0; e < kPwStride; ++e) {
-            Pw[tid * kPwStride + e] = pw;
+        for (int e = 0; e < kPowers; ++e) {
+            Pw[e * kStride + tid] = pw;
             pw *= x;
         }
     }
@@ -1207,9 +1223,9 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     for (int u = 0; u < NW / 4; ++u) {
         const int R = tid / CW + u * rows_per_pass;
         const int q = R / NW, r = R % NW;
-        if (q < gpw) Ysh[R * CW + c_ld] = ((bits[q] >> r) & 1ull) ? pf[u] : 0.0f;
+        if (q < gpw) Ysh[(q * CW + c_ld) * YS + r] = ((bits[q] >> r) & 1ull) ? pf[u] : 0.0f;
     }
-    for (int e = tid; e < kTile; e += threads) Ysh[gpw * kTile + e] = 0.0f;
+    for (int e = tid; e < YS; e += threads) zeros[e] = 0.0f;
     if (!SHARED && wv == 0) {
         const int q = lane / kClsLanes < gpw ? lane / kClsLanes : 0;
         const int n = lane / kClsLanes < gpw ? static_cast<int>(__popcll(bits[q])) : 0;
@@ -1219,14 +1235,12 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
 
     const int total = gpw * C;
     for (int c0 = wv * kClsPerWave; c0 < total; c0 += nw * kClsPerWave) {
-        const int s_op = c0 + (lane & 3);                 // the slot whose operands this lane feeds to the matrix cores
-        const int q_op = s_op < total ? s_op / C : gpw;   // past the last: the zero tile
-        const int c_op = s_op < total ? s_op - q_op * C : 0;
-        const int s_res = c0 + lane / kClsLanes;          // the slot whose system this lane's row then holds
-        const int q_res = s_res < total ? s_res / C : 0;
-        const unsigned long long rows = bits[q_res];
-        locate_classes_proj<NW, RM>(Ysh + q_op * kTile + c_op, CW, SHARED || q_op == gpw ? Ush : Ush + q_op * kUsh,
-                                    s_res < total && rows != 0ull, rows, nullptr, Pw, M, A, votes + q_res * kWave);
+        const int slot = c0 + lane / kClsLanes;           // the class of this lane's row
+        const int q = slot < total ? slot / C : 0;
+        const unsigned long long rows = bits[q];
+        const bool live = slot < total && rows != 0ull;
+        locate_classes_proj<NW, RM>(live ? Ysh + (q * CW + slot - q * C) * YS : zeros, zeros, SHARED ? Ush : Ush + q * kUsh, live,
+                                    rows, nullptr, Pw, M, A, votes + q * kWave);
     }
     __syncthreads();
 
@@ -1258,13 +1272,13 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         }
         __builtin_amdgcn_wave_barrier();
         const int c = lane & 15, k = lane >> 4;
-        const float *y = Ysh + q * kTile;
+        const float *y = Ysh + (q * CW + c) * YS;         // this lane's class column
         v4d acc[2] = {v4d{0.0, 0.0, 0.0, 0.0}, v4d{0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
         for (int s = 0; s < NW / 4; ++s) {
             const int i = 4 * s + k;
             const double sg = sgn[q * NW + i];
-            const double v = c == 15 ? 1.0 : static_cast<double>(y[i * CW + c]);
+            const double v = c == 15 ? 1.0 : static_cast<double>(y[i]);
             acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(T[c * TS + i], sg != 0.0 ? sg * v : 0.0, acc[s & 1], 0, 0, 0);
         }
         float *og = out + static_cast<size_t>(g0 + q) * K * C;
@@ -1275,7 +1289,7 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
             const double den = row_bcast<15>(num);
             double v = num / den;
             const int h = hit[j];
-            if (h >= 0 && ((left >> h) & 1ull) != 0ull) v = static_cast<double>(y[h * CW + c]);
+            if (h >= 0 && ((left >> h) & 1ull) != 0ull) v = static_cast<double>(y[h]);
             if (j < K && c < C) og[j * C + c] = static_cast<float>(v);
         }
     }
@@ -1283,27 +1297,27 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
 
 // The complement basis of the node set of ALL N workers, once per call, for the groups whose mask is full (the
 // paper's Byzantine experiments have no stragglers: every group then shares this one factorisation).  One wave;
-// writes Ush as the kernel above lays it out, ush_rows(RM) * ush_stride(NB) doubles, to `basis`.
+// writes it to `basis`, rows of stride basis_stride(NB).
 template <int NB, int RM, bool HOMOG>
 __global__ __launch_bounds__(kWave) void full_basis_kernel(double *__restrict__ basis, int N, int M, const Nodes nodes) {
     constexpr int kUshDoubles = basis_doubles<NB, RM, HOMOG>();
     __shared__ double Ush[kUshDoubles];
-    __shared__ double Pw[NB * kPwStride];
+    __shared__ double Pw[kPowers * lds_stride(NB)];
     const int tid = threadIdx.x;
     for (int e = tid; e < kUshDoubles; e += kWave) Ush[e] = 0.0;
     for (int r = tid; r < NB; r += kWave) {
         const double x = r < N ? nodes.beta[r] : 0.0;
         double p = r < N ? 1.0 : 0.0;
-        for (int e = 0; e < kPwStride; ++e) {
-            Pw[r * kPwStride + e] = p;
+        for (int e = 0; e < kPowers; ++e) {
+            Pw[e * lds_stride(NB) + r] = p;
             p *= x;
         }
     }
     __syncthreads();
-    shared_complement_basis<NB, RM, HOMOG>(Pw, N, M, Ush, Ush + ush_rows(RM) * ush_stride(NB),
-                                           Ush + (ush_rows(RM) + kProjMaxM) * ush_stride(NB));
+    shared_complement_basis<NB, RM, HOMOG>(Pw, N, M, Ush, Ush + ush_rows(RM) * lds_stride(NB),
+                                           Ush + (ush_rows(RM) + kProjMaxM) * lds_stride(NB));
     __syncthreads();
-    for (int e = tid; e < kUshDoubles; e += kWave) basis[e] = Ush[e];
+    basis_to_workspace<NB, RM, HOMOG>(Ush, basis);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1832,7 +1846,7 @@ int proj_tile(int n, int M) {         // the smallest tile that holds (n, n - M)
     return -1;
 }
 size_t basis_bytes(int tile, bool homogeneous) {
-    const int stride = ush_stride(kProjTiles[tile].nb);
+    const int stride = basis_stride(kProjTiles[tile].nb);
     const size_t b = sizeof(double) * (ush_rows(kProjTiles[tile].rm) * stride +
                                        (homogeneous ? kProjMaxM * stride + kProjMaxM * kProjMaxM : 0));
     return (b + 255) & ~static_cast<size_t>(255);
@@ -1934,9 +1948,9 @@ int run_proj(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
     ProjShape p = proj_shape(G, C, ws.votes != nullptr, HOMOG ? kFillWaves / 2 : kFillWaves);
     const int CW = 1 << p.cw_log2;
     const size_t hom_wave = HOMOG ? sizeof(double) * hom_scratch_doubles(M, n_cap, hom_mt(NB)) : 0;
-    const size_t fixed = sizeof(double) * (static_cast<size_t>(basis_doubles<NB, RM, HOMOG>()) + NB * kPwStride + NB +
+    const size_t fixed = sizeof(double) * (static_cast<size_t>(basis_doubles<NB, RM, HOMOG>()) + kPowers * lds_stride(NB) + NB +
                                            static_cast<size_t>(n_cap - A) * KP + K + N) +
-                         sizeof(float) * (static_cast<size_t>(NB) * CW) + sizeof(int) * (4 * static_cast<size_t>(N) + 2);
+                         sizeof(float) * (static_cast<size_t>(CW + 1) * y_stride(NB)) + sizeof(int) * (4 * static_cast<size_t>(N) + 2);
     while (p.nw > 1 && fixed + p.nw * hom_wave > 64 * 1024) --p.nw;
     const size_t lds = fixed + p.nw * hom_wave;
     if (lds > 64 * 1024) return HOMOG ? kNoFit : APPROXIFER_ERR_LIMIT;   // Algorithm 2: cannot happen inside the domain
