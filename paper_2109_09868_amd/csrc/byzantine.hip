@@ -30,6 +30,7 @@
 // rounds of a DPP arg-min in the projected one) vote in an LDS histogram, the A most voted workers
 // (equal counts: smaller index first) leave the available list, and the workgroup decodes the group
 // over the rest.
+#include <algorithm>
 #include <mutex>
 
 #include "decode_common.h"
@@ -224,6 +225,16 @@ __device__ __forceinline__ double sqrt_normal(double s) {
     return fma(fma(-g, g, s), h, g);
 }
 
+__device__ __forceinline__ double rsqrt_normal(double s) {
+    const double y = __builtin_amdgcn_rsq(s);
+    double g = s * y, h = 0.5 * y;
+    double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    r = fma(-h, g, 0.5);
+    return 2.0 * fma(h, r, h);
+}
+
 // Householder reflector of a pivot column x (rows k..): returns alpha = -sign(x_k) ||x|| and the factor
 // f = 2 v^T a / (v^T v) for a column a, v = x - alpha e_k, given sigma = x^T x, d = x^T a.
 struct Reflector {
@@ -398,6 +409,17 @@ __device__ __forceinline__ void row_axpy(double (&q)[NQ], const double (&b)[NB],
         row_axpy<LANE, O + 1, T>(q, b, f);
     }
 }
+// One step of a triangular sweep: s and t gain their multiples of entry LANE of s, which is final (f is 0 there).
+template <int LANE>
+__device__ __forceinline__ void row_sweep(double &s, double f) {
+    asm("s_nop 1\n v_fmac_f64_dpp %[s], %[s], %[f]" APX_DPP : [s] "+v"(s) : [f] "v"(f), [l] "n"(LANE));
+}
+template <int LANE>
+__device__ __forceinline__ void row_sweep2(double &s, double f, double &t, double b) {
+    asm("s_nop 1\n v_fmac_f64_dpp %[t], %[s], %[b]" APX_DPP "v_fmac_f64_dpp %[s], %[s], %[f]" APX_DPP
+        : [s] "+v"(s), [t] "+v"(t)
+        : [f] "v"(f), [b] "v"(b), [l] "n"(LANE));
+}
 // a[O + i] += bcast_i(u) * p: an outer product, lane i of the row holding the first factor of element i
 #define APX_O(x, i) "v_fmac_f64_dpp %[" #x "], %[u], %[p] row_newbcast:%[" #i "] row_mask:0xf bank_mask:0xf\n"
 template <int O, int L, int CNT, int RM>
@@ -431,8 +453,8 @@ __device__ __forceinline__ void row_outer(double (&a)[RM], double u, double p) {
 // groups in the issue slots that one took with the pivot column read lane by lane.
 template <int K0, int NB, int MS>
 struct RowReflectors {
-    // lane K0 keeps v_K0 in rows K0.. of its column and 2 / v^T v in `sc`
-    static __device__ __forceinline__ void factor(double (&a)[NB], int j, int M, double &sc) {
+    // lane K0 keeps v_K0 in rows K0.. of its column, 2 / v^T v in `sc` and R[K0][K0] in `diag`
+    static __device__ __forceinline__ void factor(double (&a)[NB], int j, int M, double &sc, double &diag) {
         if constexpr (K0 < MS) {
             if (K0 < M) {
                 double d0 = 0.0, d1 = 0.0;
@@ -449,8 +471,9 @@ struct RowReflectors {
                 const double v0 = xkk - alpha;
                 a[K0] = j == K0 ? v0 : fma(nf, v0, a[K0]);
                 sc = j == K0 ? scale : sc;
+                diag = j == K0 ? (zero ? xkk : alpha) : diag;
                 row_axpy_self<K0, K0 + 1>(a, nf);            // lanes up to the pivot take the factor 0
-                RowReflectors<K0 + 1, NB, MS>::factor(a, j, M, sc);
+                RowReflectors<K0 + 1, NB, MS>::factor(a, j, M, sc, diag);
             }
         }
     }
@@ -468,25 +491,41 @@ struct RowReflectors {
 };
 
 // One wave; lane row q works on group q: n_q workers avail_q[0..n_q), ascending (n_q = 0: none).  Pw[e][w] = x_w^e by
-// worker, row stride `stride` as Ush.  Writes Ush_q[i * stride + w] = U[i][worker w] for i < n_q - M (the rest of Ush is left as it is: zero).
-template <int NB>
+// worker, row stride `stride` as Ush.  Writes Ush_q[i * stride + w] = U[i][worker w] for i < n_q - M, and WITH_RANGE
+// (Algorithm 1) Q1_q[i * stride + w], i < M, the same of the first M columns of Q, and Rv_q[16][16] the upper triangle of
+// R; the rest of each is left as it is: zero.
+template <int NB, bool WITH_RANGE>
 __device__ __forceinline__ void rows_complement_basis(const double *Pw, const int *avail_q, int n, int M, double *Ush_q,
-                                                      int stride) {
+                                                      int stride, double *Q1_q, double *Rv_q) {
     constexpr int MS = NB / 2 < kProjMaxM ? NB / 2 : kProjMaxM;       // eq. (3): 2 M <= n <= NB
     const int j = lane_id() % kClsLanes;
-    double a[NB], z[NB], sc = 0.0;
+    double a[NB], z[NB], sc = 0.0, diag = 0.0;
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
         const double p = Pw[j * stride + (r < n ? avail_q[r] : 0)];
         a[r] = (r < n && j < M) ? p : 0.0;
-        z[r] = r == M + j && r < n ? 1.0 : 0.0;
     }
-    RowReflectors<0, NB, MS>::factor(a, j, M, sc);
+    RowReflectors<0, NB, MS>::factor(a, j, M, sc, diag);
+#pragma unroll
+    for (int r = 0; r < NB; ++r) z[r] = r == M + j && r < n ? 1.0 : 0.0;
     RowReflectors<0, NB, MS>::apply(a, z, M, sc);
     if (M + j < n) {
 #pragma unroll
         for (int r = 0; r < NB; ++r)
             if (r < n) Ush_q[j * stride + avail_q[r]] = z[r];
+    }
+    if (WITH_RANGE) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r) z[r] = r == j && j < M && r < n ? 1.0 : 0.0;
+        RowReflectors<0, NB, MS>::apply(a, z, M, sc);
+        if (j < M && n > 0) {
+#pragma unroll
+            for (int r = 0; r < NB; ++r)
+                if (r < n) Q1_q[j * stride + avail_q[r]] = z[r];
+#pragma unroll
+            for (int i = 0; i < MS; ++i)
+                if (i <= j) Rv_q[i * kProjMaxM + j] = i == j ? diag : a[i];
+        }
     }
 }
 
@@ -538,34 +577,29 @@ struct BackSubst<-1, NS> {
     static __device__ __forceinline__ void run(const double (&)[NS], double (&)[NS], int) {}
 };
 
-// ---- the same factorisation by Householder reflections, for the triangular factor itself (Algorithm 1) -----------
-// Steps K0 .. KEND-1 (those below `cols`); KEND = min(15, RM - 1) bounds the unrolling: cols <= R - 1 <= RM - 1.
+// The same elimination for the triangular factor itself (Algorithm 1): r[K0] = row K0 of R in the lanes from K0 on.  A
+// zero column leaves a zero row and takes nothing out of the others.
 template <int K0, int KEND, int RM>
-struct ClassQrSteps {
-    static __device__ __forceinline__ void run(double (&a)[RM], int j, int cols) {
+struct ClassTriangle {
+    static __device__ __forceinline__ void run(double (&a)[RM], double (&r)[KEND], int cols) {
         if (K0 < cols) {
-            double v[RM];
-            double dt[2] = {0.0, 0.0};                       // two partial sums: shorter dependency chains
-#pragma unroll
-            for (int r = K0; r < RM; ++r) {
-                v[r] = row_bcast<K0>(a[r]);
-                dt[(r - K0) & 1] = fma(v[r], a[r], dt[(r - K0) & 1]);
-            }
-            const double d = dt[0] + dt[1];                  // x^T a for this lane's column a ..
+            double d0 = 0.0, d1 = 0.0;
+            row_dot<K0, 0>(a, a, d0, d1);
+            const double d = d0 + d1;                        // x^T a for this lane's column a ..
             const double sigma = row_bcast<K0>(d);           // .. which in the pivot lane is x^T x
-            const Reflector h = reflector(sigma, d, v[K0], a[K0]);
-            const double nf = (!h.degenerate && j > K0) ? -h.f : 0.0;       // no branch: other columns take the factor 0
-            const double akk = fma(nf, v[K0] - h.alpha, a[K0]);
-            a[K0] = (!h.degenerate && j == K0) ? h.alpha : akk;           // R[k][k] in the pivot lane
-#pragma unroll
-            for (int r = K0 + 1; r < RM; ++r) a[r] = fma(nf, v[r], a[r]);
-            ClassQrSteps<K0 + 1, KEND, RM>::run(a, j, cols);
+            const double y = sigma > 0.0 ? rsqrt_normal(sigma) : 0.0;
+            r[K0] = d * y;
+            row_axpy_self<K0, 0>(a, -r[K0] * y);
+            ClassTriangle<K0 + 1, KEND, RM>::run(a, r, cols);
+        } else {
+            r[K0] = 0.0;
+            ClassTriangle<K0 + 1, KEND, RM>::run(a, r, cols);
         }
     }
 };
 template <int KEND, int RM>
-struct ClassQrSteps<KEND, KEND, RM> {
-    static __device__ __forceinline__ void run(double (&)[RM], int, int) {}
+struct ClassTriangle<KEND, KEND, RM> {
+    static __device__ __forceinline__ void run(double (&)[RM], double (&)[KEND], int) {}
 };
 
 // The A smallest keys of a class (equal keys: smaller row first) vote.  Lane j of the class's 16-lane row holds the
@@ -597,16 +631,6 @@ __device__ __forceinline__ void vote_smallest(double (&key)[PR], int A, bool liv
             open = open && (who & row_lanes) == 0ull;
         }
     }
-}
-
-// Between a block above and a DPP operand that the compiler schedules itself.
-template <int RM>
-__device__ __forceinline__ void row_results_settled(double (&a)[RM]) {
-#pragma unroll
-    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
-    asm volatile("s_nop 1");
-#pragma unroll
-    for (int r = 0; r < RM; ++r) asm volatile("" : "+v"(a[r]));
 }
 
 typedef double v2d __attribute__((ext_vector_type(2)));
@@ -694,17 +718,63 @@ constexpr int kInverseRounds = 24;      // inverse-iteration rounds before a cla
 constexpr int kJacobiSweeps = 30;
 constexpr int kRegisterRounds = 64;     // .. and of the register form, whose rounds are cheap next to that fallback
 
+// Sweeps over all entries (or back), f(i) and b(i) being this lane's multipliers of entry i.  Entries from M on are zero
+// and take no branch: the multipliers that come from LDS are then read ahead of the chain.
+template <int I, int MT>
+struct TriangularSweeps {
+    template <class F>
+    static __device__ __forceinline__ void forward(double &s, F f) {
+        row_sweep<I>(s, f(I));
+        if constexpr (I + 1 < MT) TriangularSweeps<I + 1, MT>::forward(s, f);
+    }
+    template <class F, class B>
+    static __device__ __forceinline__ void forward2(double &s, F f, double &t, B b) {
+        row_sweep2<I>(s, f(I), t, b(I));
+        if constexpr (I + 1 < MT) TriangularSweeps<I + 1, MT>::forward2(s, f, t, b);
+    }
+    template <class F>
+    static __device__ __forceinline__ void backward(double &s, F f) {
+        row_sweep<I>(s, f(I));
+        if constexpr (I > 0) TriangularSweeps<I - 1, MT>::backward(s, f);
+    }
+    template <class F, class B>
+    static __device__ __forceinline__ void backward2(double &s, F f, double &t, B b) {
+        row_sweep2<I>(s, f(I), t, b(I));
+        if constexpr (I > 0) TriangularSweeps<I - 1, MT>::backward2(s, f, t, b);
+    }
+};
+
+// What the sweeps over R_V need, once per group, behind R_V itself: fv[i][j] = -R_V[i][j] / R_V[j][j] for i < j (the
+// forward sweep of lane j), gv[k][j] = -R_V[j][k] / R_V[j][j] for k > j (its backward sweep), 1 / R_V[j][j].
+constexpr int kVSquare = kProjMaxM * kProjMaxM;
+constexpr int kVDoubles = 3 * kVSquare + kProjMaxM;      // R_V | fv | gv | reciprocal pivots
+// Entry e of the squares (e < 256), by one thread each.  A pivot below 1e-24 of its column is raised to that.
+__device__ __forceinline__ void sweep_multipliers(double *Rv, int e, int M) {
+    const int i = e / kProjMaxM, j = e % kProjMaxM;
+    double cs = 0.0;
+    for (int t = 0; t < M; ++t) cs = fma(Rv[t * kProjMaxM + j], Rv[t * kProjMaxM + j], cs);
+    double dv = Rv[j * kProjMaxM + j];
+    const double least = 1e-24 * sqrt(cs);
+    if (fabs(dv) < least) dv = dv < 0.0 ? -least : least;
+    const double rdv = j < M ? 1.0 / dv : 0.0;
+    Rv[kVSquare + e] = i < j ? -Rv[e] * rdv : 0.0;
+    Rv[2 * kVSquare + e] = i > j && i < M ? -Rv[j * kProjMaxM + i] * rdv : 0.0;
+    if (i == 0) Rv[3 * kVSquare + j] = rdv;
+}
+
 // Smallest right singular vector of the 2M x 2M factor R = [[R_V, B1], [0, R2]] of one class, by inverse iteration
 // z <- (R^T R)^-1 z, entirely in the registers of the class's 16-lane row (lane j = index j of both halves of
 // z = (p, q), M <= 15).  The four triangular solves of a round,
 //     w1 = R_V^-T p,   w2 = R2^-T (q - B1^T w1),   q' = R2^-1 w2,   p' = R_V^-1 (w1 - B1 q'),
-// are column sweeps: the entry that has just become final is broadcast along the row (DPP) and every lane subtracts
-// its multiple.  The two forward sweeps need the lane's COLUMN of R_V, B1, R2, the two backward ones its ROW; the
-// rows of B1 and R2 come through one transposition in the wave's LDS scratch (T: 4 classes x MT x (MT + 1) doubles), those
-// of R_V from the group's LDS copy.  Start vector, settling rule, extrapolation of a slowly decaying error mode and
+// are column sweeps: the entry that has just become final is broadcast along the row inside the multiply-add with which
+// every lane takes its multiple; the division by the pivot is folded into the multipliers.  The two forward sweeps need
+// the lane's COLUMN of R_V, B1, R2, the two backward ones its ROW: the columns of B1 and R2 and the row of B1 are held
+// in registers, the row of R2 stays in the wave's LDS scratch through which it was transposed (T: 4 classes x MT x
+// (MT + 1) doubles), R_V's multipliers are the group's (sweep_multipliers): with all of it in registers the 28-row tile
+// spills (K = 12, A = 2, 8192 groups, a workgroup each: 427 us, 333 us this way).  Start vector, settling rule, extrapolation of a slowly decaying error mode and
 // the floor under vanishing pivots are those of homogeneous_q (the LDS form, which stays the fallback for a class
 // that has not settled after kRegisterRounds: it also holds the Jacobi iteration).
-//   r2c[i] = R2[i][j] (i <= j), b1c[i] = B1[i][j]: this lane's columns; Rv: LDS, row stride 16.
+//   r2c[i] = R2[i][j] (i <= j), b1c[i] = B1[i][j]: this lane's columns; Rv: LDS, see kVDoubles.
 //   MT >= M bounds the unrolling and the register arrays (the register tile of the kernel bounds M: M <= NB / 2).
 // `live`: the row holds a class.  Returns q_j in `qv` and whether the class settled (the same value in all lanes of
 // the row).
@@ -715,49 +785,43 @@ __device__ __forceinline__ bool singular_vector_rows(const double (&r2c)[MT], co
     constexpr int LDT = MT + 1;
     const bool act = j < M;
     double *Tc = T + cl * MT * LDT;                        // M <= MT: lanes j >= MT hold no column and read no row
-    // rows of R2 and B1 by transposition through LDS
-    double r2r[MT], b1r[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-        if (j < MT) Tc[i * LDT + j] = (act && i < M && i <= j) ? r2c[i] : 0.0;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < MT; ++k) r2r[k] = Tc[(j < MT ? j : 0) * LDT + k];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-        if (j < MT) Tc[i * LDT + j] = (act && i < M) ? b1c[i] : 0.0;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < MT; ++k) b1r[k] = act ? Tc[j * LDT + k] : 0.0;
-    __builtin_amdgcn_wave_barrier();
-    // R_V's column and row are read from the group's LDS copy inside the sweeps (they are the same for the wave's
-    // four classes); Rv is zero below its diagonal and outside M x M.
-    constexpr int LDV = kProjMaxM;
-    const double *rv_col = Rv + j;                         // rv_col[i * LDV] = R_V[i][j]
-    const double *rv_row = Rv + j * LDV;                   // rv_row[k] = R_V[j][k]
-    // reciprocal pivots; a pivot below 1e-24 of its column of R is raised to that (an exactly singular system keeps
-    // its null vector to 1e-24, and the solves stay finite)
-    double csv = 0.0, cs2 = 0.0;
+    // reciprocal pivot; one below 1e-24 of its column of R is raised to that (an exactly singular system keeps its null
+    // vector to 1e-24, and the solves stay finite)
+    double cs2 = 0.0, d2 = 0.0;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        const double rv = rv_col[i * LDV];
-        csv = fma(rv, rv, csv);
-        cs2 = fma(b1c[i], b1c[i], fma((i < M && i <= j) ? r2c[i] : 0.0, (i < M && i <= j) ? r2c[i] : 0.0, cs2));
+        const double r2 = i < M && i <= j ? r2c[i] : 0.0;
+        cs2 = fma(b1c[i], b1c[i], fma(r2, r2, cs2));
+        d2 = i == j ? r2 : d2;
     }
-    double dv = rv_row[j], d2 = 0.0;
+    const double least = 1e-24 * sqrt(cs2);
+    if (fabs(d2) < least) d2 = d2 < 0.0 ? -least : least;
+    const double rdv = Rv[3 * kVSquare + j], rd2 = act ? 1.0 / d2 : 0.0;   // a zero column: inf, the class does not settle
+    // multipliers, zero on idle lanes
+    double fb[MT], f2[MT], gb[MT];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) d2 = (i == j && i < M) ? r2c[i] : d2;
-    const double fv = 1e-24 * sqrt(csv), f2 = 1e-24 * sqrt(cs2);
-    if (fabs(dv) < fv) dv = dv < 0.0 ? -fv : fv;
-    if (fabs(d2) < f2) d2 = d2 < 0.0 ? -f2 : f2;
-    const double rdv = act ? 1.0 / dv : 0.0, rd2 = act ? 1.0 / d2 : 0.0;   // a zero column: inf, the class does not settle
-    // strictly upper parts: the multiples a sweep subtracts
+    for (int i = 0; i < MT; ++i) {
+        fb[i] = -b1c[i];
+        f2[i] = i < j ? -r2c[i] * rd2 : 0.0;
+        if (j < MT) Tc[i * LDT + j] = fb[i];
+    }
+    __builtin_amdgcn_wave_barrier();
+    const double *row = Tc + (j < MT ? j : MT - 1) * LDT;  // the last row of a strict upper triangle is zero
 #pragma unroll
-    for (int i = 0; i < MT; ++i) r2r[i] = (act && i > j) ? r2r[i] : 0.0;
-    double r2u[MT];
+    for (int k = 0; k < MT; ++k) gb[k] = act ? row[k] : 0.0;
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i = 0; i < MT; ++i) r2u[i] = (act && i < M && i < j) ? r2c[i] : 0.0;
+    for (int i = 0; i < MT; ++i) {
+        const double scaled = -row_bcast_dyn(rd2, i) * r2c[i];
+        if (j < MT) Tc[i * LDT + j] = i < j ? scaled : 0.0;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const auto fv_at = [Rv, j](int i) { return Rv[kVSquare + i * kProjMaxM + j]; };
+    const auto gv_at = [Rv, j](int k) { return Rv[2 * kVSquare + k * kProjMaxM + j]; };
+    const auto g2_at = [row](int k) { return row[k]; };
+    const auto fb_at = [&fb](int i) { return fb[i]; };
+    const auto f2_at = [&f2](int i) { return f2[i]; };
+    const auto gb_at = [&gb](int k) { return gb[k]; };
 
     double p = act ? 1.0 + 0.25 * (j % 3) : 0.0;
     double q = act ? 1.0 + 0.25 * ((M + j) % 3) : 0.0;
@@ -765,45 +829,14 @@ __device__ __forceinline__ bool singular_vector_rows(const double (&r2c)[MT], co
     int since_jump = 0;
     bool settled = false;
     for (int round = 0; round < kRegisterRounds; ++round) {
-        // forward: w1 = R_V^-T p, t = q - B1^T w1, then w2 = R2^-T t
-        double s1 = p, t = q;
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (i < M) {
-                const double wi = row_bcast_dyn(s1 * rdv, i);
-                s1 = fma(i < j ? -rv_col[i * LDV] : 0.0, wi, s1);
-                t = fma(-b1c[i], wi, t);
-            }
-        }
-        const double w1 = s1 * rdv;
-        double s2 = t;
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (i < M) {
-                const double wi = row_bcast_dyn(s2 * rd2, i);
-                s2 = fma(-r2u[i], wi, s2);
-            }
-        }
-        // backward: q' = R2^-1 w2, u = w1 - B1 q', then p' = R_V^-1 u
-        double s3 = s2 * rd2, u = w1;
-#pragma unroll
-        for (int k = MT - 1; k >= 0; --k) {
-            if (k < M) {
-                const double qk = row_bcast_dyn(s3 * rd2, k);
-                s3 = fma(-r2r[k], qk, s3);
-                u = fma(-b1r[k], qk, u);
-            }
-        }
-        const double qn_raw = s3 * rd2;
-        double s4 = u;
-#pragma unroll
-        for (int k = MT - 1; k >= 0; --k) {
-            if (k < M) {
-                const double pk = row_bcast_dyn(s4 * rdv, k);
-                s4 = fma(k > j ? -rv_row[k] : 0.0, pk, s4);
-            }
-        }
-        const double pn_raw = s4 * rdv;
+        double w1 = p * rdv, t = q;                       // forward: w1 = R_V^-T p, t = q - B1^T w1, then w2 = R2^-T t
+        TriangularSweeps<0, MT>::forward2(w1, fv_at, t, fb_at);
+        double w2 = t * rd2;
+        TriangularSweeps<0, MT>::forward(w2, f2_at);
+        double qn_raw = w2 * rd2, u = w1;                 // backward: q' = R2^-1 w2, u = w1 - B1 q', then p' = R_V^-1 u
+        TriangularSweeps<MT - 1, MT>::backward2(qn_raw, g2_at, u, gb_at);
+        double pn_raw = u * rdv;
+        TriangularSweeps<MT - 1, MT>::backward(pn_raw, gv_at);
         const double nn = row16_sum(act ? fma(pn_raw, pn_raw, qn_raw * qn_raw) : 0.0);
         const double inv = rcp_normal(sqrt_normal(nn));       // nn = 0, inf or NaN: NaN, the class does not settle
         const double pn = act ? pn_raw * inv : 0.0, qn = act ? qn_raw * inv : 0.0;
@@ -830,25 +863,30 @@ __device__ __forceinline__ bool singular_vector_rows(const double (&r2c)[MT], co
     return settled;
 }
 
-// Algorithm 1 (the homogeneous fit, Q_0 free) for the four classes c_rel..c_rel+3 of the staged tile, by one wave, on
-// the shared factorisation V = Q [R_V; 0] of the group.  With H_c = [V | diag(y_c) V] (the sign of the second block
+// Algorithm 1 (the homogeneous fit, Q_0 free) for four classes at a time, by one wave, on the factorisations
+// V = Q [R_V; 0] of their groups; arguments as for locate_classes_proj, U followed by Q1 and R_V (see kVDoubles).  With H_c = [V | diag(y_c) V] (the sign of the second block
 // only flips the sign of Q),
 //     Q^T H_c = [ R_V   Q1^T diag(y_c) V ]      Q1^T = rows 0..M-1 of Q^T,
 //               [  0     U  diag(y_c) V ]      U    = rows M..n-1,
 // so the 2M x 2M triangular factor of H_c is [[R_V, B1], [0, R2]] with B1 = Q1^T diag(y_c) V (M x M) and
 // R2 the triangular factor of B2 = U diag(y_c) V ((n-M) x M; n - M >= M by eq. (3)).  B1 and B2 are
-// formed as the projected system of Algorithm 2 is (Q1 sits in the 16 rows that follow U in LDS), R2 from the same register Householder QR, run over all M columns.  The smallest right singular vector of
-// the assembled factor is found in registers (singular_vector_rows); a class that does not settle there is assembled
+// formed as the projected system of Algorithm 2 is (Q1 sits in the 16 rows that follow U in LDS), R2 by the same
+// elimination, run over all M columns.  The smallest right singular vector of the assembled factor is found in registers (singular_vector_rows); a class that does not settle there is assembled
 // in this wave's scratch, mat[2M][2M+1] | coef[M] | key[n], and goes through the LDS form (homogeneous_q), as many
-// classes at a time as the scratch holds (one, as the host sizes it).
-template <int NB, int RM>
-__device__ __forceinline__ void locate_classes_hom_proj(const float *y, const float *zeros, int c_rel, int tile_classes,
-                                                        const int *avail, const double *xs, const double *Pw,
-                                                        const double *Ush, const double *Rv, int n, int M, int A,
-                                                        double *scratch, int scratch_doubles, int *votes) {
+// classes at a time as the scratch holds (one, as the host sizes it); slot_of(s) tells about class slot s there.
+struct ClassSlot {
+    int n;                     // available workers, avail[0..n) ascending
+    const int *avail;
+    int *votes;
+};
+template <int NB, int RM, int MT, class SlotOf>
+__device__ __forceinline__ void locate_classes_hom_proj(const float *y, const float *zeros, const double *U, bool class_live,
+                                                        unsigned long long rows, const int *worker_of_row, const double *Pw,
+                                                        int M, int A, int *votes, double *scratch, int scratch_doubles,
+                                                        SlotOf slot_of) {
     const int lane = lane_id();
     const int j = lane % kClsLanes;
-    constexpr int MT = hom_mt(NB);
+    const double *Rv = U + (ush_rows(RM) + kProjMaxM) * lds_stride(NB);
     double a[RM], b1[MT];
 #pragma unroll
     for (int i = 0; i < RM; ++i) a[i] = 0.0;
@@ -856,21 +894,15 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *y, const fl
     for (int i = 0; i < MT; ++i) b1[i] = 0.0;
     const float *yj = j < M ? y : zeros;                  // column of this lane: y x^j; idle lanes hold zeros
     const double *wj = Pw + (j < M ? j : 0) * lds_stride(NB);
-    project_column<NB>(a, Ush + (j < RM ? j : 0) * lds_stride(NB), yj, wj);
-    project_column<NB>(b1, Ush + (ush_rows(RM) + j) * lds_stride(NB), yj, wj);
-    row_results_settled(a);
-
-    // R2: steps 0 .. min(M, RM - 1) - 1; when M == RM the last diagonal entry is the one row that is left
-    constexpr int kSteps = RM - 1 < kProjMaxM - 1 ? RM - 1 : kProjMaxM - 1;
-    ClassQrSteps<0, kSteps, RM>::run(a, j, M);
+    project_column<NB>(a, U + (j < RM ? j : 0) * lds_stride(NB), yj, wj);
+    project_column<NB>(b1, U + (ush_rows(RM) + j) * lds_stride(NB), yj, wj);
+    // R2: the triangular factor of B2 (M <= RM: eq. (3) gives n - M >= M)
+    double r2c[MT];
+    ClassTriangle<0, MT, RM>::run(a, r2c, M);
 
     // ---- the singular vector: in registers; classes that do not settle there go through the LDS form below ---------
     const int cl16 = lane / kClsLanes;                    // class slot of this lane in the register layout
-    double r2c[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) r2c[i] = i < RM ? a[i < RM ? i : 0] : 0.0;
     double qv;
-    const bool class_live = c_rel + cl16 < tile_classes;
     const bool settled = singular_vector_rows<MT>(r2c, b1, Rv, scratch, M, j, cl16, class_live, qv);
     // a_r = Q(x_r) = sum_k q_k x_r^k, rows j, j+16, .. of this lane; the A smallest |a_r| vote
     {
@@ -882,13 +914,13 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *y, const fl
 #pragma unroll
         for (int pr = 0; pr < PR; ++pr) {
             const int r = j + pr * kClsLanes;
-            const double x = xs[r < n ? r : 0];
+            const double x = Pw[lds_stride(NB) + (r < NB ? r : 0)];
             double av = 0.0;
 #pragma unroll
             for (int k = MT - 1; k >= 0; --k) av = fma(av, x, qk[k]);
-            key[pr] = r < n ? (av == av ? fabs(av) : __builtin_inf()) : __builtin_nan("");
+            key[pr] = ((rows >> r) & 1ull) ? (av == av ? fabs(av) : __builtin_inf()) : __builtin_nan("");
         }
-        vote_smallest<PR>(key, A, class_live && settled, avail, votes);
+        vote_smallest<PR>(key, A, class_live && settled, worker_of_row, votes);
     }
     const unsigned long long open_lanes = __ballot(class_live && !settled);
     if (open_lanes == 0ull) return;
@@ -896,7 +928,7 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *y, const fl
     // ---- fallback: assemble the factor in LDS and find the vector there (inverse iteration again, then Jacobi) -----
     const int W2 = 2 * M;
     const int LD = W2 + 1;
-    const int per_class = W2 * LD + M + n;
+    const int per_class = W2 * LD + M + NB;
     const int fit = scratch_doubles / per_class;          // >= 1 (hom_scratch_doubles)
     const int cpw = kWave / W2 < fit ? kWave / W2 : fit;  // classes per pass: what the lanes and the scratch hold
     const int clw = lane / W2, jw = lane - clw * W2;      // the layout of homogeneous_q (lane jw owns row jw)
@@ -921,16 +953,17 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *y, const fl
         double *coef = mat + W2 * LD;
         double *key = coef + M;
         homogeneous_q(mat, LD, coef, key, W2, M, jw, live, true);
+        const ClassSlot slot = slot_of(p0 + (live ? clw : 0));
         if (live) {
-            for (int r = jw; r < n; r += W2) {            // a_r = Q(x_r), Q_k = coef[k]
-                const double x = xs[r];
+            for (int r = jw; r < slot.n; r += W2) {       // a_r = Q(x_r), Q_k = coef[k]
+                const double x = Pw[lds_stride(NB) + (worker_of_row != nullptr ? r : slot.avail[r])];
                 double av = 0.0;
                 for (int t = M - 1; t >= 0; --t) av = fma(av, x, coef[t]);
                 key[r] = (av != av) ? __builtin_inf() : fabs(av);
             }
         }
         __builtin_amdgcn_wave_barrier();
-        if (live) pick_and_vote(key, avail, n, A, jw, W2, votes);
+        if (live) pick_and_vote(key, slot.avail, slot.n, A, jw, W2, slot.votes);
         __builtin_amdgcn_wave_barrier();
     }
 }
@@ -939,10 +972,11 @@ __device__ __forceinline__ void locate_classes_hom_proj(const float *y, const fl
 // (MT + 1)) or, for a class that falls back to homogeneous_q, ONE assembled factor with its coefficient and key
 // arrays.  Kept this small on purpose: LDS, not registers, decides how many groups a CU holds (at K = 8, A = 2 with
 // three factors per wave seven workgroups fitted a CU where eight were due, and the launch took two rounds).
-__host__ __device__ constexpr int hom_scratch_doubles(int M, int n_cap, int MT) {
-    const int fallback = 2 * M * (2 * M + 1) + M + n_cap;
+__host__ __device__ constexpr int hom_scratch_doubles(int M, int rows, int MT) {
+    const int fallback = 2 * M * (2 * M + 1) + M + rows;
     const int transpose = kClsPerWave * MT * (MT + 1);
-    return fallback > transpose ? fallback : transpose;
+    const int most = fallback > transpose ? fallback : transpose;
+    return (most + 1) & ~1;
 }
 
 // Doubles of the shared factorisation as the kernel keeps it in LDS (and as full_basis_kernel writes it out):
@@ -972,8 +1006,8 @@ __device__ __forceinline__ void basis_to_workspace(const double *Ush, double *__
 }
 
 // HOMOG: Algorithm 1's fit as the per-class locator (locate_classes_hom_proj) instead of Algorithm 2's.
-// dynamic LDS (doubles): basis (see basis_doubles) | Pw[16][lds_stride] | xs[NB] | float Ysh[CW + 1][y_stride]
-//               | WdT[(n_cap-A)*KP] | alpha_s[K] | beta_s[N] | HOMOG: scratch[nw][hom_scratch_doubles(M, n_cap, NB / 2)]
+// dynamic LDS (doubles): basis (see basis_doubles; HOMOG: up to kVDoubles) | Pw[16][lds_stride] | xs[NB] | float Ysh[CW + 1][y_stride]
+//               | WdT[(n_cap-A)*KP] | alpha_s[K] | beta_s[N] | HOMOG: scratch[nw][hom_scratch_doubles]
 //               then ints: avail[N] | F[N] | Fpos[N] | votes[N] | n | flag
 template <int NB, int RM, bool HOMOG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && RM <= 16 && NB <= 28 ? 3 : 2))) void decode_byzantine_proj_kernel(
@@ -991,13 +1025,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
     constexpr int YS = y_stride(NB);
     double *Q1sh = Ush + ush_rows(RM) * lds_stride(NB);   // HOMOG only: the 16 rows after U, then R_V
     double *Rv = Q1sh + kProjMaxM * lds_stride(NB);
-    double *Pw = Ush + kUshDoubles;
+    double *Pw = Ush + kUshDoubles + (HOMOG ? kVDoubles - kVSquare : 0);
     double *xs = Pw + kPowers * lds_stride(NB);
     float *Ysh = reinterpret_cast<float *>(xs + NB);      // [CW + 1][YS], the last row stays zero
     double *WdT = xs + NB + (CW + 1) * YS / 2;
     double *alpha_s = WdT + (n_cap - A) * KP;
     double *beta_s = alpha_s + K;
-    const int hom_wave_doubles = HOMOG ? hom_scratch_doubles(M, n_cap, hom_mt(NB)) : 0;
+    const int hom_wave_doubles = HOMOG ? hom_scratch_doubles(M, NB, hom_mt(NB)) : 0;
     double *hom_scratch = beta_s + N;
     int *avail = reinterpret_cast<int *>(hom_scratch + static_cast<size_t>(nw) * hom_wave_doubles);
     int *F = avail + N;
@@ -1056,6 +1090,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
     }
     __syncthreads();
     if (wv == 0 && !preloaded) shared_complement_basis<NB, RM, HOMOG>(Pw, n, M, Ush, Q1sh, Rv);
+    if (HOMOG) {
+        __syncthreads();
+        for (int e = tid; e < kVSquare; e += blockDim.x) sweep_multipliers(Rv, e, M);
+    }
 
     for (int64_t cb = cb_first; cb < C; cb += static_cast<int64_t>(splits) * CW) {   // class tiles of this part
         if (cb == cb_first) {
@@ -1079,10 +1117,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
         const int tile_classes = (C - cb < CW) ? static_cast<int>(C - cb) : CW;
         for (int c_rel = wv * kClsPerWave; c_rel < tile_classes; c_rel += nw * kClsPerWave) {
             if (HOMOG)
-                locate_classes_hom_proj<NB, RM>(Ysh + (c_rel + lane_id() / kClsLanes) * YS, Ysh + CW * YS, c_rel, tile_classes,
-                                                avail, xs, Pw, Ush, Rv, n, M, A,
-                                                hom_scratch + static_cast<size_t>(wv) * hom_wave_doubles, hom_wave_doubles,
-                                                votes);
+                locate_classes_hom_proj<NB, RM, hom_mt(NB)>(Ysh + (c_rel + lane_id() / kClsLanes) * YS, Ysh + CW * YS, Ush,
+                                                c_rel + lane_id() / kClsLanes < tile_classes, (1ull << n) - 1ull, avail, Pw, M, A,
+                                                votes, hom_scratch + static_cast<size_t>(wv) * hom_wave_doubles,
+                                                hom_wave_doubles, [=](int) { return ClassSlot{n, avail, votes}; });
             else
                 locate_classes_proj<NB, RM>(Ysh + (c_rel + lane_id() / kClsLanes) * YS, Ysh + CW * YS, Ush,
                                             c_rel + lane_id() / kClsLanes < tile_classes, (1ull << n) - 1ull, avail, Pw, M, A,
@@ -1131,20 +1169,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
 // K = 8, A = 2, 20 of 24 workers, 2048 groups of 10 classes: 24.5 us with a workgroup per group, 20.4 us this way;
 // K = 12, A = 2, 28 workers, 8192 groups: 91.2 us with this packing but decoder weights per group, 70.8 us.
 // NB >= N - S bounds the workers that answer, NW >= N all workers, RM >= N - S - M.
-// dynamic LDS: double Ush[SHARED ? 1 : GPW][ush_rows(RM)][lds_stride(NW)] | Pw[16][lds_stride(NW)] | T[16][NW + 1]
-//              | sgn[GPW][NW] | float Ysh[16 GPW + 1][y_stride(NW)] (the last row stays zero: empty class slots read it)
+// HOMOG: Algorithm 1's locator instead (locate_classes_hom_proj): K = 8, 2048 groups 61 us with a workgroup per group
+// and the sweeps' broadcasts as moves, 47.5 us; K = 12, 8192 groups 357 and 183 us.
+// dynamic LDS: double basis[SHARED ? 1 : GPW][packed_basis_doubles] | Pw[16][lds_stride(NW)] | T[16][NW + 1] | sgn[GPW][NW]
+//              | HOMOG: scratch[nw][hom_scratch_doubles]
+//              | float Ysh[16 GPW + 1][y_stride(NW)] (the last row stays zero: empty class slots read it)
 //              | uint64 bits[GPW] | int avail[GPW][NW] | votes[GPW][64] | hit[16]
-template <int NB, int RM, int NW>
-constexpr size_t packed_lds_bytes(bool shared, int gpw) {
-    return sizeof(double) * ((static_cast<size_t>(shared ? 1 : gpw) * ush_rows(RM) + kPowers) * lds_stride(NW) +
-                             16 * (NW + 1) + gpw * NW + gpw) +
+template <int NB, int RM, int NW, bool HOMOG>
+constexpr int packed_basis_doubles() {                   // U, and for Algorithm 1 Q1 and what kVDoubles lists
+    return basis_doubles<NW, RM, HOMOG>() + (HOMOG ? kVDoubles - kVSquare : 0);
+}
+template <int NB, int RM, int NW, bool HOMOG>
+constexpr size_t packed_lds_bytes(bool shared, int gpw, int nw, int M) {
+    return sizeof(double) * (static_cast<size_t>(shared ? 1 : gpw) * packed_basis_doubles<NB, RM, NW, HOMOG>() +
+                             kPowers * lds_stride(NW) + 16 * (NW + 1) + gpw * NW + gpw +
+                             (HOMOG ? nw * hom_scratch_doubles(M, NW, hom_mt(NB)) : 0)) +
            sizeof(float) * (static_cast<size_t>(gpw * kClsLanes + 1) * y_stride(NW)) +
            sizeof(int) * (static_cast<size_t>(gpw) * (NW + kWave) + 16);
 }
 constexpr int kPackedWaves = 4;      // at most
 
-template <int NB, int RM, int NW, bool SHARED>
-__global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_per_eu(NB <= 28 ? 3 : 2))) void decode_byzantine_packed_kernel(
+template <int NB, int RM, int NW, bool SHARED, bool HOMOG>
+__global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_per_eu(!HOMOG && NB <= 28 ? 3 : 2))) void decode_byzantine_packed_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
     int32_t *__restrict__ adv, int32_t *__restrict__ status, int64_t G, int K, int N, int S, int n_cap, int A, int C,
     int sign_mode, int gpw, const double *__restrict__ full_basis, const Nodes nodes) {
@@ -1153,16 +1199,20 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     constexpr int CW = kClsLanes;
     constexpr int YS = y_stride(NW);
     constexpr int kStride = lds_stride(NW);
-    constexpr int kUsh = ush_rows(RM) * kStride;
+    constexpr int kQ1 = ush_rows(RM) * kStride;           // inside a basis: U, then Q1, then R_V
+    constexpr int kRv = kQ1 + kProjMaxM * kStride;
+    constexpr int kBasis = packed_basis_doubles<NB, RM, NW, HOMOG>();
     constexpr int TS = NW + 1;                            // odd: the sixteen rows an operand load touches lie in distinct banks
     const int threads = blockDim.x;                       // at least a wave per group
     const int nw = threads / kWave;
     const int M = K + A;
     double *Ush = lds_d;
-    double *Pw = Ush + (SHARED ? 1 : gpw) * kUsh;
+    double *Pw = Ush + (SHARED ? 1 : gpw) * kBasis;
     double *T = Pw + kPowers * kStride;
     double *sgn = T + 16 * TS;
-    float *Ysh = reinterpret_cast<float *>(sgn + gpw * NW);
+    const int hom_doubles = HOMOG ? hom_scratch_doubles(M, NW, hom_mt(NB)) : 0;
+    double *hom_scratch = sgn + gpw * NW;
+    float *Ysh = reinterpret_cast<float *>(hom_scratch + nw * hom_doubles);
     float *zeros = Ysh + gpw * CW * YS;
     unsigned long long *bits = reinterpret_cast<unsigned long long *>(zeros + YS);
     int *avail = reinterpret_cast<int *>(bits + gpw);
@@ -1198,9 +1248,9 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         votes[q * kWave + lane] = 0;
     }
     if (SHARED) {
-        basis_from_workspace<NB, RM, false>(Ush, full_basis);
+        basis_from_workspace<NB, RM, HOMOG>(Ush, full_basis);
     } else {
-        for (int e = tid; e < gpw * kUsh; e += threads) Ush[e] = 0.0;
+        for (int e = tid; e < gpw * kBasis; e += threads) Ush[e] = 0.0;
     }
     if (tid < NW) {
         const double x = tid < N ? nodes.beta[tid] : 0.0;
@@ -1229,9 +1279,15 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     if (!SHARED && wv == 0) {
         const int q = lane / kClsLanes < gpw ? lane / kClsLanes : 0;
         const int n = lane / kClsLanes < gpw ? static_cast<int>(__popcll(bits[q])) : 0;
-        rows_complement_basis<NB>(Pw, avail + q * NW, n, M, Ush + q * kUsh, kStride);
+        double *basis = Ush + q * kBasis;
+        rows_complement_basis<NB, HOMOG>(Pw, avail + q * NW, n, M, basis, kStride, basis + kQ1, basis + kRv);
     }
     __syncthreads();
+    if (HOMOG) {
+        for (int e = tid; e < (SHARED ? 1 : here) * kVSquare; e += threads)
+            sweep_multipliers(Ush + e / kVSquare * kBasis + kRv, e % kVSquare, M);
+        __syncthreads();
+    }
 
     const int total = gpw * C;
     for (int c0 = wv * kClsPerWave; c0 < total; c0 += nw * kClsPerWave) {
@@ -1239,8 +1295,17 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         const int q = slot < total ? slot / C : 0;
         const unsigned long long rows = bits[q];
         const bool live = slot < total && rows != 0ull;
-        locate_classes_proj<NW, RM>(live ? Ysh + (q * CW + slot - q * C) * YS : zeros, zeros, SHARED ? Ush : Ush + q * kUsh, live,
-                                    rows, nullptr, Pw, M, A, votes + q * kWave);
+        const float *y = live ? Ysh + (q * CW + slot - q * C) * YS : zeros;
+        const double *basis = SHARED ? Ush : Ush + q * kBasis;
+        if constexpr (HOMOG)
+            locate_classes_hom_proj<NW, RM, hom_mt(NB)>(
+                y, zeros, basis, live, rows, nullptr, Pw, M, A, votes + q * kWave, hom_scratch + wv * hom_doubles, hom_doubles,
+                [=](int s) {
+                    const int qs = c0 + s < total ? (c0 + s) / C : 0;
+                    return ClassSlot{static_cast<int>(__popcll(bits[qs])), avail + qs * NW, votes + qs * kWave};
+                });
+        else
+            locate_classes_proj<NW, RM>(y, zeros, basis, live, rows, nullptr, Pw, M, A, votes + q * kWave);
     }
     __syncthreads();
 
@@ -1895,42 +1960,54 @@ bool packed_domain(int N, int n, int M, int64_t C) {
 // Measured with 1 / 2 / 4 groups, ten classes: K = 8, A = 2, 20 of 24 workers, 1024 groups 16.9 / 17.5 / 18.2 us, 2048
 // groups 29.1 / 20.4 / 22.3 us, 4096 groups 56 / 37 / 29 us; K = 12, A = 2, 28 workers, 1024 groups 21.7 / 22.6 / 23.7
 // us, 2048 groups 33 / 28 / 30 us, 8192 groups 101 / 81 / 71 us.
-int packed_groups(int64_t G) { return G <= 1280 ? 1 : (G <= 2560 ? 2 : 4); }
+// Algorithm 1's locator runs two waves to a SIMD: K = 8, 500 groups 27 / 32 / 40 us, 1024 groups 48 / 36 / 41 us, 2048
+// groups 91 / 66 / 48 us; K = 12, 28 workers, 8192 groups 289 / 231 / 183 us.
+int packed_groups(int64_t G, bool homogeneous) {
+    if (homogeneous) return G <= 512 ? 1 : (G <= 1024 ? 2 : 4);
+    return G <= 1280 ? 1 : (G <= 2560 ? 2 : 4);
+}
 
-template <int NB, int RM, int NW, bool SHARED>
+template <int NB, int RM, int NW, bool SHARED, bool HOMOG>
 int run_packed_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
                      int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
                      hipStream_t stream) {
-    const int gpw = packed_groups(G);
-    static_assert(packed_lds_bytes<NB, RM, NW>(SHARED, 4) <= 64 * 1024, "fits a workgroup's LDS without an attribute");
-    const int64_t blocks = (G + gpw - 1) / gpw;
+    int gpw = packed_groups(G, HOMOG);
     // a wave per round of four classes, up to four, and one per group (five waves for the ten rounds of four groups
     // balance better and are slower from 4096 groups on, 100 us against 71 at K = 12, 8192 groups: fewer workgroups fit)
-    int nw = (gpw * C + kClsPerWave - 1) / kClsPerWave;
-    if (nw > kPackedWaves) nw = kPackedWaves;
-    if (nw < gpw) nw = gpw;
-    return launch_status(launch_kernel(decode_byzantine_packed_kernel<NB, RM, NW, SHARED>, dim3(static_cast<unsigned>(blocks)),
-                                       dim3(nw * kWave), packed_lds_bytes<NB, RM, NW>(SHARED, gpw), stream, d_preds,
-                                       d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, sign_mode, gpw, basis, nodes));
+    const auto waves = [C](int groups) {
+        const int rounds = (groups * C + kClsPerWave - 1) / kClsPerWave;
+        return std::max(std::min(rounds, kPackedWaves), groups);
+    };
+    // two workgroups to a CU at least
+    while (gpw > 1 && packed_lds_bytes<NB, RM, NW, HOMOG>(SHARED, gpw, waves(gpw), K + A) > kLdsPerCu / 2) gpw /= 2;
+    const int nw = waves(gpw);
+    const size_t lds = packed_lds_bytes<NB, RM, NW, HOMOG>(SHARED, gpw, nw, K + A);
+    const auto kernel = decode_byzantine_packed_kernel<NB, RM, NW, SHARED, HOMOG>;
+    if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
+    return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>((G + gpw - 1) / gpw)), dim3(nw * kWave), lds, stream,
+                                       d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, sign_mode, gpw, basis,
+                                       nodes));
 }
 
 // basis: the call's shared factorisation, for S = 0 only (a group whose mask is not full is bad then); else null.
-template <int NB, int RM>
+template <int NB, int RM, bool HOMOG>
 int run_packed(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
                int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
                hipStream_t stream) {
     if (basis != nullptr)
-        return run_packed_shape<NB, RM, NB, true>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                  sign_mode, basis, stream);
+        return run_packed_shape<NB, RM, NB, true, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                         sign_mode, basis, stream);
     if (N <= NB)
-        return run_packed_shape<NB, RM, NB, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                   sign_mode, nullptr, stream);
+        return run_packed_shape<NB, RM, NB, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                          sign_mode, nullptr, stream);
     if constexpr (NB < 48) {
         if (N <= NB + 4)
-            return run_packed_shape<NB, RM, NB + 4, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                           sign_mode, nullptr, stream);
-        return run_packed_shape<NB, RM, 48, false>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                   sign_mode, nullptr, stream);
+            return run_packed_shape<NB, RM, NB + 4, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C,
+                                                                  nodes, sign_mode, nullptr, stream);
+        return run_packed_shape<NB, RM, 48, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                          sign_mode, nullptr, stream);
     }
     return APPROXIFER_ERR_LIMIT;                          // not inside packed_domain
 }
@@ -1947,28 +2024,34 @@ int run_proj(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
     // Algorithm 1's locator runs two waves to a SIMD (registers): half as many waves fill the chip
     ProjShape p = proj_shape(G, C, ws.votes != nullptr, HOMOG ? kFillWaves / 2 : kFillWaves);
     const int CW = 1 << p.cw_log2;
-    const size_t hom_wave = HOMOG ? sizeof(double) * hom_scratch_doubles(M, n_cap, hom_mt(NB)) : 0;
-    const size_t fixed = sizeof(double) * (static_cast<size_t>(basis_doubles<NB, RM, HOMOG>()) + kPowers * lds_stride(NB) + NB +
+    const size_t hom_wave = HOMOG ? sizeof(double) * hom_scratch_doubles(M, NB, hom_mt(NB)) : 0;
+    const size_t fixed = sizeof(double) * (static_cast<size_t>(basis_doubles<NB, RM, HOMOG>()) + (HOMOG ? kVDoubles - kVSquare : 0) +
+                                           kPowers * lds_stride(NB) + NB +
                                            static_cast<size_t>(n_cap - A) * KP + K + N) +
                          sizeof(float) * (static_cast<size_t>(CW + 1) * y_stride(NB)) + sizeof(int) * (4 * static_cast<size_t>(N) + 2);
-    while (p.nw > 1 && fixed + p.nw * hom_wave > 64 * 1024) --p.nw;
+    constexpr size_t kBudget = kLdsPerCu / 2;              // two workgroups to a CU at least
+    while (p.nw > 1 && fixed + p.nw * hom_wave > kBudget) --p.nw;
     const size_t lds = fixed + p.nw * hom_wave;
-    if (lds > 64 * 1024) return HOMOG ? kNoFit : APPROXIFER_ERR_LIMIT;   // Algorithm 2: cannot happen inside the domain
+    if (lds > kBudget) return HOMOG ? kNoFit : APPROXIFER_ERR_LIMIT;   // Algorithm 2: cannot happen inside the domain
     if (G * p.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    const bool packed = !HOMOG && RM <= kProjMaxM && packed_domain(N, n_cap, M, C);
+    const bool packed = RM <= kProjMaxM && packed_domain(N, n_cap, M, C);
     if (ws.basis != nullptr && !(packed && S != 0)) {
         const hipError_t e = launch_kernel(full_basis_kernel<NB, RM, HOMOG>, dim3(1), dim3(kWave), 0, stream, ws.basis, N, M, nodes);
         if (e != hipSuccess) return APPROXIFER_ERR_LAUNCH;
     }
-    if constexpr (!HOMOG && RM <= kProjMaxM) {
+    if constexpr (RM <= kProjMaxM) {
         if (packed)
-            return run_packed<NB, RM>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n_cap, A, static_cast<int>(C), nodes,
+            return run_packed<NB, RM, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n_cap, A, static_cast<int>(C), nodes,
                                       sign_mode, S == 0 ? ws.basis : nullptr, stream);
     }
     if (p.splits > 1) {
         const int rc = clear_workspace(ws.votes, G, N, stream);
         if (rc != APPROXIFER_OK) return rc;
     }
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(decode_byzantine_proj_kernel<NB, RM, HOMOG>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
     const dim3 grid(static_cast<unsigned>(G * p.splits)), block(p.nw * kWave);
     return launch_status(launch_kernel(decode_byzantine_proj_kernel<NB, RM, HOMOG>, grid, block, lds, stream, d_preds, d_mask, d_out,
                                        d_adv, d_status, K, N, S, A, C, Cv, vec4 ? 1 : 0, sign_mode, n_cap, p.cw_log2,

@@ -13,6 +13,7 @@
 namespace approxifer {
 
 constexpr int kWave = 64;
+constexpr int kLdsPerCu = 160 * 1024;                     // gfx950
 
 // Query and worker nodes travel by value in the kernel-argument segment: the library
 // owns no device memory, and K + N doubles always fit.

@@ -39,7 +39,6 @@ constexpr int kMfmaMinK = 17;   // from this K on the matrix-core variant serves
 constexpr int kMfmaWideMinK = 8;   // .. and from this K on the shapes with N >= 2K + 4
 constexpr int kMfmaBlocksPerCu = 4;   // matrix-core variant (four waves of 64 columns)
 constexpr int kScalarRowsMaxD = 128;   // ragged rows (D % 4 != 0) this short: 64-bit or 4-byte accesses only
-constexpr int kLdsPerCu = 160 * 1024;                // gfx950
 
 // Register type of VEC floats, and the type a lane loads and stores it through.  Rows that are only
 // 4-byte aligned (a row length that is not a multiple of 4 floats, or an offset base pointer) are still

@@ -756,7 +756,8 @@ def test_byzantine_no_stragglers_groups_share_one_factorisation(gpu, K, A, N, C,
     (6, 1, 2, 17, 16),      # one class too many for the tile: the workgroup-per-group kernel
     (6, 2, -1, 24, 10),     # straggler counts read off the masks
 ])
-def test_byzantine_groups_packed_into_workgroups(gpu, K, A, S, N, C):
+@pytest.mark.parametrize("locator", [orc.LOCATOR_ALGORITHM_2, orc.LOCATOR_ALGORITHM_1])
+def test_byzantine_groups_packed_into_workgroups(gpu, K, A, S, N, C, locator):
     # Four, two or one group(s) to a workgroup, by the number of groups: the same bits each way, a bad group in between,
     # the first groups against the oracle.  Several shapes have a query node that is a worker's node.
     torch, binding, dev = gpu
@@ -780,14 +781,15 @@ def test_byzantine_groups_packed_into_workgroups(gpu, K, A, S, N, C):
     for n_groups in (2700, 1500, 40):
         out = torch.full((n_groups, K, C), -3.0, dtype=torch.float32, device=dev)
         adv = torch.full((n_groups, A), -7, dtype=torch.int32, device=dev)
-        got = binding.approxifer_decode_byzantine(Yd[:n_groups], md[:n_groups], alpha, beta, S, A, mode, out=out, adv=adv)
+        decode = binding.approxifer_decode_byzantine if locator == orc.LOCATOR_ALGORITHM_2 else binding.approxifer_decode_byzantine_homogeneous
+        got = decode(Yd[:n_groups], md[:n_groups], alpha, beta, S, A, mode, out=out, adv=adv)
         res[n_groups] = [t.cpu().numpy() for t in got]
     for n_groups in (1500, 40):
         for whole, part in zip(res[2700], res[n_groups]):
             assert np.array_equal(whole[:n_groups], part)
     out, adv, st = [x[:G_ref] for x in res[2700]]
     Yz = np.where(mask[:G_ref, :, None] != 0, Y[:G_ref], 0.0).astype(np.float32)
-    ref, adv_ref, st_ref = orc.decode_byzantine(Yz, mask[:G_ref], alpha, beta, S, A, mode)
+    ref, adv_ref, st_ref = orc.decode_byzantine(Yz, mask[:G_ref], alpha, beta, S, A, mode, locator=locator)
     assert np.array_equal(st, st_ref) and st[5] == 1 and st.sum() == 1
     assert np.all(out[5] == -3.0) and np.all(adv[5] == -7)
     good = (st == 0) & np.array([np.array_equal(a, b) for a, b in zip(adv_ref, adv_true[:G_ref])])
