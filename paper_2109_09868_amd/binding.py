@@ -103,6 +103,26 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+_entries = None
+
+
+def _entry() -> ctypes.CDLL:
+    """The library once more, for the calls below: node arrays go in as plain addresses (here: bytes objects), so that no
+    ctypes pointer object has to be built for them (3 us each, half of what a call took on the host)."""
+    global _entries
+    lib = load()
+    if _entries is None or _entries[0] is not lib:
+        fast = ctypes.CDLL(LIB_PATH)
+        for name in EXPORTS:
+            typed = getattr(lib, name)
+            if typed.argtypes is not None:
+                getattr(fast, name).argtypes = [ctypes.c_void_p if t is ctypes.POINTER(ctypes.c_double) else t
+                                                for t in typed.argtypes]
+            getattr(fast, name).restype = typed.restype
+        _entries = (lib, fast)
+    return _entries[1]
+
+
 def strerror(code: int) -> str:
     return load().approxifer_strerror(int(code)).decode()
 
@@ -113,26 +133,29 @@ def _check(code: int) -> None:
 
 
 def _nodes(a) -> tuple:
-    arr = np.ascontiguousarray(a, dtype=np.float64)
-    return arr, arr.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+    """(number of nodes, their float64 values as bytes, which ctypes passes as a pointer without building one)."""
+    arr = np.asarray(a, dtype=np.float64)
+    return arr.size, arr.tobytes()
 
 
 def _stream_handle(stream) -> int:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        # torch.cuda.current_stream().cuda_stream without the Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return getattr(stream, "cuda_stream", stream)
 
 
 def _dev(t, dtype, shape=None):
+    """Address of a contiguous device tensor of this dtype and, where given, shape (a tuple)."""
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("expected a tensor in device memory")
     if t.dtype != dtype or not t.is_contiguous():
         raise TypeError("expected a contiguous %s tensor, got %s" % (dtype, t.dtype))
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("expected shape %s, got %s" % (tuple(shape), tuple(t.shape)))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def approxifer_chebyshev_nodes(K: int, N: int):
@@ -147,7 +170,7 @@ def approxifer_chebyshev_nodes(K: int, N: int):
 
 def approxifer_group_count(Q: int, K: int) -> int:
     """Number of groups of K consecutive queries that a stream of Q queries forms."""
-    return int(load().approxifer_group_count(int(Q), int(K)))
+    return _entry().approxifer_group_count(int(Q), int(K))
 
 
 def approxifer_pad_last_group(buffer, Q, K, stream=None):
@@ -158,44 +181,42 @@ def approxifer_pad_last_group(buffer, Q, K, stream=None):
     G = approxifer_group_count(Q, K)
     if G < 0 or rows < G * K:
         raise ValueError("the buffer must hold ceil(Q / K) * K rows")
-    _check(load().approxifer_pad_last_group(_dev(buffer, torch.float32), int(Q), int(K), int(D),
-                                            ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_pad_last_group(_dev(buffer, torch.float32), int(Q), int(K), int(D),
+                                              _stream_handle(stream)))
     return buffer[: G * K].view(G, K, D)
 
 
 def approxifer_encode(queries, alpha, beta, coded=None, stream=None):
     """queries [G, K, D] float32 device tensor -> coded [G, N, D]; K = len(alpha), N = len(beta)."""
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    n_alpha, ap = _nodes(alpha)
+    N, bp = _nodes(beta)
     G, K, D = queries.shape
-    N = b.size
-    if K != a.size:
+    if K != n_alpha:
         raise ValueError("queries.shape[1] must equal len(alpha)")
     if coded is None:
         coded = torch.empty((G, N, D), dtype=torch.float32, device=queries.device)
-    _check(load().approxifer_encode(_dev(queries, torch.float32), _dev(coded, torch.float32, (G, N, D)),
-                                    G, K, N, D, ap, bp, ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_encode(_dev(queries, torch.float32), _dev(coded, torch.float32, (G, N, D)),
+                                      G, K, N, D, ap, bp, _stream_handle(stream)))
     return coded
 
 
 def approxifer_decode(preds, mask, alpha, beta, S, sign_mode=SIGN_WORKER_INDEX, out=None, status=None, stream=None):
     """preds [G, N, C] float32, mask [G, N] uint8 -> (out [G, K, C] float32, status [G] int32)."""
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    K, ap = _nodes(alpha)
+    n_beta, bp = _nodes(beta)
     G, N, C = preds.shape
-    K = a.size
-    if N != b.size:
+    if N != n_beta:
         raise ValueError("preds.shape[1] must equal len(beta)")
     if out is None:
         out = torch.zeros((G, K, C), dtype=torch.float32, device=preds.device)
     if status is None:
         status = torch.full((G,), -1, dtype=torch.int32, device=preds.device)
-    _check(load().approxifer_decode(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                    _dev(out, torch.float32, (G, K, C)), _dev(status, torch.int32, (G,)),
-                                    G, K, N, int(S), C, ap, bp, int(sign_mode),
-                                    ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_decode(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                      _dev(out, torch.float32, (G, K, C)), _dev(status, torch.int32, (G,)),
+                                      G, K, N, int(S), C, ap, bp, int(sign_mode),
+                                      _stream_handle(stream)))
     return out, status
 
 
@@ -203,11 +224,10 @@ def approxifer_decode_top1(preds, mask, alpha, beta, S, sign_mode=SIGN_WORKER_IN
                            stream=None, want_score=True):
     """Fused decode + argmax over classes: (top1 [G, K] int32, score [G, K] float32 or None, status [G] int32)."""
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    K, ap = _nodes(alpha)
+    n_beta, bp = _nodes(beta)
     G, N, C = preds.shape
-    K = a.size
-    if N != b.size:
+    if N != n_beta:
         raise ValueError("preds.shape[1] must equal len(beta)")
     if top1 is None:
         top1 = torch.full((G, K), -1, dtype=torch.int32, device=preds.device)
@@ -215,11 +235,11 @@ def approxifer_decode_top1(preds, mask, alpha, beta, S, sign_mode=SIGN_WORKER_IN
         score = torch.zeros((G, K), dtype=torch.float32, device=preds.device)
     if status is None:
         status = torch.full((G,), -1, dtype=torch.int32, device=preds.device)
-    _check(load().approxifer_decode_top1(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                         _dev(top1, torch.int32, (G, K)),
-                                         _dev(score, torch.float32, (G, K)) if score is not None else None,
-                                         _dev(status, torch.int32, (G,)), G, K, N, int(S), C, ap, bp, int(sign_mode),
-                                         ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_decode_top1(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                           _dev(top1, torch.int32, (G, K)),
+                                           _dev(score, torch.float32, (G, K)) if score is not None else None,
+                                           _dev(status, torch.int32, (G,)), G, K, N, int(S), C, ap, bp, int(sign_mode),
+                                           _stream_handle(stream)))
     return top1, score, status
 
 
@@ -233,11 +253,10 @@ NO_WORKSPACE = object()
 
 def _decode_byzantine(entry, preds, mask, alpha, beta, S, A, sign_mode, out, adv, status, stream, workspace):
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    K, ap = _nodes(alpha)
+    n_beta, bp = _nodes(beta)
     G, N, C = preds.shape
-    K = a.size
-    if N != b.size:
+    if N != n_beta:
         raise ValueError("preds.shape[1] must equal len(beta)")
     if out is None:
         out = torch.zeros((G, K, C), dtype=torch.float32, device=preds.device)
@@ -254,12 +273,12 @@ def _decode_byzantine(entry, preds, mask, alpha, beta, S, A, sign_mode, out, adv
     else:
         if not isinstance(workspace, torch.Tensor) or not workspace.is_cuda or not workspace.is_contiguous():
             raise TypeError("workspace must be a contiguous tensor in device memory")
-        ws_ptr, ws_bytes = ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
-    _check(getattr(load(), entry)(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                  _dev(out, torch.float32, (G, K, C)), _dev(adv, torch.int32, (G, int(A))),
-                                  _dev(status, torch.int32, (G,)), G, K, N, int(S), int(A), C, ap, bp,
-                                  int(sign_mode), ws_ptr, ctypes.c_size_t(ws_bytes),
-                                  ctypes.c_void_p(_stream_handle(stream))))
+        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    _check(getattr(_entry(), entry)(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                    _dev(out, torch.float32, (G, K, C)), _dev(adv, torch.int32, (G, int(A))),
+                                    _dev(status, torch.int32, (G,)), G, K, N, int(S), int(A), C, ap, bp,
+                                    int(sign_mode), ws_ptr, ws_bytes,
+                                    _stream_handle(stream)))
     return out, adv, status
 
 
@@ -284,19 +303,18 @@ def approxifer_decode_rational(preds, mask, alpha, beta, S, A, out=None, status=
     """Algorithm 3: out[g, j, c] = P(alpha_j) / Q(alpha_j) with (P, Q) Algorithm 2's fit per class.
     Returns (out [G, K, C] float32, status [G] int32)."""
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    K, ap = _nodes(alpha)
+    n_beta, bp = _nodes(beta)
     G, N, C = preds.shape
-    K = a.size
-    if N != b.size:
+    if N != n_beta:
         raise ValueError("preds.shape[1] must equal len(beta)")
     if out is None:
         out = torch.zeros((G, K, C), dtype=torch.float32, device=preds.device)
     if status is None:
         status = torch.full((G,), -1, dtype=torch.int32, device=preds.device)
-    _check(load().approxifer_decode_rational(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                             _dev(out, torch.float32, (G, K, C)), _dev(status, torch.int32, (G,)),
-                                             G, K, N, int(S), int(A), C, ap, bp, ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_decode_rational(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                               _dev(out, torch.float32, (G, K, C)), _dev(status, torch.int32, (G,)),
+                                               G, K, N, int(S), int(A), C, ap, bp, _stream_handle(stream)))
     return out, status
 
 
@@ -310,9 +328,9 @@ def approxifer_top1(values, top1=None, score=None, stream=None, want_score=True)
         top1 = torch.full(lead, -1, dtype=torch.int32, device=values.device)
     if score is None and want_score:
         score = torch.zeros(lead, dtype=torch.float32, device=values.device)
-    _check(load().approxifer_top1(_dev(values, torch.float32), _dev(top1, torch.int32, lead),
-                                  _dev(score, torch.float32, lead) if score is not None else None, rows, C,
-                                  ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_top1(_dev(values, torch.float32), _dev(top1, torch.int32, lead),
+                                    _dev(score, torch.float32, lead) if score is not None else None, rows, C,
+                                    _stream_handle(stream)))
     return top1, score
 
 
@@ -324,17 +342,16 @@ def approxifer_decode_byzantine_static(preds, mask, alpha, beta, S, A, out, adv,
     """approxifer_decode_byzantine on the library's built-in workspace.  Allocates nothing: every output is the
     caller's.  Raises ApproxiferError(-8) for shapes whose workspace exceeds STATIC_WORKSPACE_BYTES."""
     import torch
-    a, ap = _nodes(alpha)
-    b, bp = _nodes(beta)
+    K, ap = _nodes(alpha)
+    n_beta, bp = _nodes(beta)
     G, N, C = preds.shape
-    K = a.size
-    if N != b.size:
+    if N != n_beta:
         raise ValueError("preds.shape[1] must equal len(beta)")
-    _check(load().approxifer_decode_byzantine_static(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                                     _dev(out, torch.float32, (G, K, C)),
-                                                     _dev(adv, torch.int32, (G, int(A))),
-                                                     _dev(status, torch.int32, (G,)), G, K, N, int(S), int(A), C, ap, bp,
-                                                     int(sign_mode), ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_decode_byzantine_static(_dev(preds, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                                       _dev(out, torch.float32, (G, K, C)),
+                                                       _dev(adv, torch.int32, (G, int(A))),
+                                                       _dev(status, torch.int32, (G,)), G, K, N, int(S), int(A), C, ap, bp,
+                                                       int(sign_mode), _stream_handle(stream)))
     return out, adv, status
 
 
@@ -346,7 +363,7 @@ def approxifer_wait_mask(arrival, wait_for, mask=None, count=None, stream=None):
         mask = torch.zeros((G, N), dtype=torch.uint8, device=arrival.device)
     if count is None:
         count = torch.full((G,), -1, dtype=torch.int32, device=arrival.device)
-    _check(load().approxifer_wait_mask(_dev(arrival, torch.float32), _dev(mask, torch.uint8, (G, N)),
-                                       _dev(count, torch.int32, (G,)), G, N, int(wait_for),
-                                       ctypes.c_void_p(_stream_handle(stream))))
+    _check(_entry().approxifer_wait_mask(_dev(arrival, torch.float32), _dev(mask, torch.uint8, (G, N)),
+                                         _dev(count, torch.int32, (G,)), G, N, int(wait_for),
+                                         _stream_handle(stream)))
     return mask, count

@@ -11,11 +11,18 @@ namespace {
 constexpr double kPi = 3.14159265358979323846264338327950288;
 
 int check_nodes(const double *h, int n) {
+    bool rising = true, falling = true;
     for (int i = 0; i < n; ++i) {
         if (!std::isfinite(h[i])) return APPROXIFER_ERR_BAD_NODES;
+        if (i > 0) {
+            rising = rising && h[i] > h[i - 1];
+            falling = falling && h[i] < h[i - 1];
+        }
+    }
+    if (rising || falling) return APPROXIFER_OK;          // as node generators list them: distinct without comparing pairs
+    for (int i = 0; i < n; ++i)
         for (int k = 0; k < i; ++k)
             if (h[k] == h[i]) return APPROXIFER_ERR_BAD_NODES;
-    }
     return APPROXIFER_OK;
 }
 

@@ -10,6 +10,8 @@ answers.  There is no CPU path here: the binding raises if the HIP library is mi
 """
 from __future__ import annotations
 
+import operator
+
 import numpy as np
 
 from . import binding
@@ -45,6 +47,23 @@ class ServingLoop:
         self.adv = torch.empty((G, max(A, 1)), dtype=torch.int32, device=dev)[:, :A]
         need = binding.approxifer_workspace_bytes(G, K, N, S, A, C) if A > 0 else 0
         self.workspace = torch.empty((need,), dtype=torch.uint8, device=dev) if need else binding.NO_WORKSPACE
+        self._views = None
+
+    def _for_queries(self, Q):
+        """Views of the buffers for a stream of Q queries; those of the last Q are kept (slicing a dozen tensors takes as
+        long on the host as two of the calls below)."""
+        bufs = (self.coded, self.preds, self.mask, self.count, self.out, self.top1, self.status, self.adv)
+        kept = self._views
+        if kept is not None and kept[0] == Q and all(map(operator.is_, kept[1], bufs)):
+            return kept[2]
+        K, N, D, C = self.K, self.N, self.D, self.C
+        G = binding.approxifer_group_count(Q, K)
+        coded, preds, mask, count, out, top1, status, adv = (t[:G] for t in bufs)
+        v = {"G": G, "coded": coded, "coded_rows": coded.view(G * N, D), "preds": preds, "pred_rows": preds.view(G * N, C),
+             "mask": mask, "count": count, "out": out, "top1": top1, "status": status, "adv": adv,
+             "values": out.view(G * K, C)[:Q], "classes": top1.view(G * K)[:Q]}
+        self._views = (Q, bufs, v)
+        return v
 
     def load(self, stream):
         """Copies a [Q, D] float32 stream (host or device tensor) into the query buffer; returns Q."""
@@ -63,32 +82,29 @@ class ServingLoop:
         Returns a dict of views: values [Q, C] (None unless want_values or A > 0), top1 [Q], mask [G, N],
         adv [G, A], status [G] (0: decoded), groups G.
         """
-        K, N, S, A, D, C = self.K, self.N, self.S, self.A, self.D, self.C
-        G = binding.approxifer_group_count(Q, K)
+        K, N, S, A = self.K, self.N, self.S, self.A
+        v = self._for_queries(Q)
+        G, preds, out, top1, status, adv = v["G"], v["preds"], v["out"], v["top1"], v["status"], v["adv"]
         groups = binding.approxifer_pad_last_group(self.queries, Q, K)            # [G, K, D] view, last group completed
-        coded = binding.approxifer_encode(groups, self.alpha, self.beta, coded=self.coded[:G])
-        preds = self.preds[:G]
-        preds.view(G * N, C).copy_(model(coded.view(G * N, D)))
+        coded = binding.approxifer_encode(groups, self.alpha, self.beta, coded=v["coded"])
+        v["pred_rows"].copy_(model(v["coded_rows"]))
         if tamper is not None:
             tamper(preds)
-        mask, count = binding.approxifer_wait_mask(arrival[:G], N - S, mask=self.mask[:G], count=self.count[:G])
-        out, top1, status = self.out[:G], self.top1[:G], self.status[:G]
-        adv = self.adv[:G]
-        values = None
+        mask, _ = binding.approxifer_wait_mask(arrival[:G], N - S, mask=v["mask"], count=v["count"])
+        values = v["values"]
         if A > 0:
             binding.approxifer_decode_byzantine(preds, mask, self.alpha, self.beta, S, A, self.sign_mode, out=out, adv=adv,
                                                 status=status, workspace=self.workspace)
             binding.approxifer_top1(out, top1=top1, want_score=False)
-            values = out
         elif want_values:
             binding.approxifer_decode(preds, mask, self.alpha, self.beta, S, self.sign_mode, out=out, status=status)
             binding.approxifer_top1(out, top1=top1, want_score=False)
-            values = out
         else:
             binding.approxifer_decode_top1(preds, mask, self.alpha, self.beta, S, self.sign_mode, top1=top1, status=status,
                                            want_score=False)
-        return {"values": None if values is None else values.view(G * K, C)[:Q], "top1": top1.view(G * K)[:Q],
-                "mask": mask, "adv": adv, "status": status, "groups": G, "coded": coded, "preds": preds}
+            values = None
+        return {"values": values, "top1": v["classes"], "mask": mask, "adv": adv, "status": status, "groups": G,
+                "coded": coded, "preds": preds}
 
 
 def exponential_arrivals(G, N, seed, device, slow_fraction=0.0):
