@@ -6,9 +6,12 @@
 // reduction) and kept transposed in LDS, and the contraction over F accumulates in float64
 // with the weights broadcast from LDS.  Rows of missing workers are never read.
 #include "decode_common.h"
+#include "rows.h"
 
 namespace approxifer {
 namespace {
+
+constexpr int kRowLanes = 16;
 
 // ------------------------------------------------------------------------------------
 // decoder kernel
@@ -455,126 +458,147 @@ __global__ __launch_bounds__(256) void decode_top1_stream_kernel(const float *__
 }
 
 // ------------------------------------------------------------------------------------
-// packed kernel for the small shapes of the image-classification operating points
+// small classes: a 16-lane row per group
 // ------------------------------------------------------------------------------------
-// K <= KT queries, at most RT surviving workers, C <= 16 classes, (KT, RT) = (16, 16), (16, 32) or (32, 64) (e.g.
-// K = 8..12, one to three stragglers, ten classes; K = 16 with 18 of 24 workers and K = 32 with 36 of 48, two classes).  A group is then a few hundred bytes, and a workgroup per group spends its time on launch
-// and barrier latency.  Here ONE WAVE decodes a group on its own -- four (two for the largest tile) groups per workgroup, the only
-// workgroup barrier is the one after the nodes are staged -- with everything in 16 x 16 tiles in the wave's
-// own LDS: survivors from one ballot, predictions Y[r][c], weights W[j][r] (RT lanes per query node, 64 / RT
-// nodes per pass), then one lane per output (j, c).  TOP1 adds the argmax over classes.
-constexpr int kPk = 16;                 // tile edge for C (and for K in the smaller tiles)
+// K <= 32 queries, N <= 64 workers, C <= 16 classes: the image-classification operating points (K = 8..12, one to three
+// stragglers, ten classes) and the text shapes (two classes).  A group is a few hundred bytes; what its decode took was
+// launch and barrier latency with a workgroup per group, and the issue slots of the weights, two divisions and a
+// reduction per entry, with a wave per group.  Here a group is one 16-lane row, lane = class, sixteen groups to a
+// workgroup, and no weights are formed.  T[i][j] = 1 / (alpha_j - beta_i) depends on the nodes only and is evaluated
+// once per workgroup, while the loads are in flight; with s_i = the alternating sign of worker i, 0 if it did not answer,
+//     out[j][c] = (sum_i T[i][j] s_i y_ic) / (sum_i T[i][j] s_i).
+// Lane j holds T[i][j], from where the numerators of all classes take it inside the multiply-add (row_outer), and sums
+// the denominator of query j.  Every worker's row is loaded, answered or not (S of N more bytes of a run that is mostly
+// read anyway): the loads need not wait for the mask; an answer that did not come is replaced by zero.
+// A query node that is a worker's node has T = 0 there and takes that worker's row as it is, if the worker answered.
+// 16384 groups of K = 8, N = 9, ten classes, top-1: 13.1 us a kernel with a wave per group, 7.2 us this way.
+constexpr int kRowGroups = 16;
+constexpr int kRowChunkSmall = 16;      // prediction rows in flight
 
-template <bool TOP1, int KT, int RT, int GROUPS>
-__global__ __launch_bounds__(GROUPS *kWave) void decode_packed_kernel(
+template <bool TOP1, int KP>
+__global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
     int32_t *__restrict__ top1, float *__restrict__ score, int32_t *__restrict__ status, int64_t G, int K, int N,
     int S, int C, int sign_mode, const Nodes nodes) {
-    static_assert((KT == 16 && (RT == 16 || RT == 32)) || (KT == 32 && RT == 64), "tile");
-    __shared__ double alpha_s[KT];
-    __shared__ double beta_s[kWave];
-    __shared__ double W_s[GROUPS][KT * RT];            // W[j][r]
-    __shared__ double O_s[TOP1 ? GROUPS : 1][KT * kPk];
-    __shared__ float Y_s[GROUPS][RT * kPk];            // Y[r][c]
-    __shared__ int F_s[GROUPS][RT];
+    constexpr int kRegs = (KP + kRowLanes - 1) / kRowLanes;  // T and denominators of query lane + 16 h in register h
+    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit
+    int *hit = reinterpret_cast<int *>(T + N * KP);
+    const int c = threadIdx.x % kRowLanes;
+    const int row = threadIdx.x / kRowLanes;
+    const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * kRowGroups + row;
+    const bool here = g_raw < G;
+    const int64_t g = here ? g_raw : G - 1;                 // rows past the last group work on it and store nothing
 
-    const int lane = lane_id();
-    const int wv = wave_id();
-    for (int t = threadIdx.x; t < K + N; t += blockDim.x) {
-        if (t < K) alpha_s[t] = nodes.alpha[t];
-        else beta_s[t - K] = nodes.beta[t - K];
+    // every load first: the mask row by sixteens, the first predictions
+    bool answered[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) answered[p] = p * kRowLanes + c < N && mask[g * N + p * kRowLanes + c] != 0;
+    const float *pg = preds + static_cast<size_t>(g) * N * C + (c < C ? c : 0);
+    float y[kRowChunkSmall];
+#pragma unroll
+    for (int u = 0; u < kRowChunkSmall; ++u) y[u] = u < N ? pg[u * C] : 0.0f;
+
+    if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
+    __syncthreads();
+    for (int e = threadIdx.x; e < N * KP; e += kRowGroups * kRowLanes) {
+        const int i = e / KP, j = e % KP;
+        const double d = nodes.alpha[j < K ? j : 0] - nodes.beta[i];
+        const bool same = j < K && d == 0.0;
+        if (same) {                                         // nodes are distinct: one worker at most
+            hit[j] = i;
+            hit[KP] = 1;
+        }
+        T[e] = (j < K && !same) ? 1.0 / d : 0.0;
+    }
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        m |= ((__ballot(answered[p]) >> (lane_id() & 48)) & 0xffffull) << (p * kRowLanes);
+    const int nF = static_cast<int>(__popcll(m));
+    const bool good = S < 0 ? nF >= 1 : nF == N - S;
+    if (c == 0 && here && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    unsigned long long minus = 0xaaaaaaaaaaaaaaaaull;       // workers with an odd index ..
+    if (sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK) {       // .. or with an odd number of survivors before them
+        minus = m;
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) minus ^= minus << s;
+        minus = ~minus;                                     // (for a survivor: an even number up to and including it)
     }
     __syncthreads();
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * GROUPS + wv;
-    if (g >= G) return;
 
-    double *W = W_s[wv];
-    float *Y = Y_s[wv];
-    int *F = F_s[wv];
-
-    // survivors: N <= 64, one ballot
-    const bool mine = lane < N && mask[g * N + lane] != 0;
-    const unsigned long long m = __ballot(mine);
-    const int nF = __popcll(m);
-    const bool good = S < 0 ? (nF >= 1 && nF <= RT) : nF == N - S;
-    if (lane == 0 && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
-    if (!good) return;
-    if (mine) F[__popcll(m & ((1ull << lane) - 1ull))] = lane;
-    __builtin_amdgcn_wave_barrier();
-
-    // predictions of the survivors: slot (r, c) = (slot / 16, slot % 16), RT / 4 slots per lane
-    constexpr int kYSlots = RT / 4;
-    const float *pg = preds + static_cast<size_t>(g) * N * C;
-    float yv[kYSlots];
+    double acc[KP], den[kRegs];
 #pragma unroll
-    for (int u = 0; u < kYSlots; ++u) {
-        const int slot = lane + u * kWave;
-        const int r = slot / kPk, c = slot % kPk;
-        yv[u] = (r < nF && c < C) ? pg[static_cast<size_t>(F[r]) * C + c] : 0.0f;
-    }
-
-    // weights, Section 3 "ApproxIFER Decoding" step 2: lanes (jsub, r) = (lane / RT, lane % RT)
-    {
-        constexpr int kRowsPerPass = kWave / RT;
-        const int r = lane % RT, jsub = lane / RT;
-        const bool valid = r < nF;
-        const int i = valid ? F[r] : 0;
-        const double xb = beta_s[i];
-        const int parity = (sign_mode == APPROXIFER_SIGN_WORKER_INDEX) ? (i & 1) : (r & 1);
-        const double sign = parity ? -1.0 : 1.0;
-        const unsigned long long group_mask = RT == 64 ? ~0ull : (RT == 16 ? 0xFFFFull : 0xFFFFFFFFull) << (jsub * (RT & 63));
+    for (int j = 0; j < KP; ++j) acc[j] = 0.0;
 #pragma unroll
-        for (int p = 0; p < KT / kRowsPerPass; ++p) {
-            if (kRowsPerPass * p < K) {
-                const int j = kRowsPerPass * p + jsub;
-                const bool row = j < K;
-                const BerrutTerm bt = berrut_term(alpha_s[row ? j : 0], xb, sign, valid && row);
-                const double rden = 1.0 / group_sum<RT>(bt.t);
-                const bool any_hit = (__ballot(bt.hit) & group_mask) != 0ull;
-                W[j * RT + r] = (valid && row) ? (any_hit ? (bt.hit ? 1.0 : 0.0) : bt.t * rden) : 0.0;
+    for (int h = 0; h < kRegs; ++h) den[h] = 0.0;
+    for (int i0 = 0; i0 < N; i0 += kRowChunkSmall) {
+        if (i0 > 0) {
+#pragma unroll
+            for (int u = 0; u < kRowChunkSmall; ++u) y[u] = i0 + u < N ? pg[(i0 + u) * C] : 0.0f;
+        }
+        const uint32_t m16 = static_cast<uint32_t>(m >> i0), minus16 = static_cast<uint32_t>(minus >> i0);
+#pragma unroll
+        for (int u = 0; u < kRowChunkSmall; ++u) {
+            if (i0 + u < N) {
+                const uint32_t there = 0u - ((m16 >> u) & 1u);              // all ones, or zero
+                const uint32_t flip = ((minus16 >> u) & 1u) << 31;
+                const double sy = static_cast<double>(__uint_as_float((__float_as_uint(y[u]) ^ flip) & there));
+                const double s = __hiloint2double(static_cast<int>((0x3ff00000u ^ flip) & there), 0);
+                double t[kRegs];
+#pragma unroll
+                for (int h = 0; h < kRegs; ++h) {
+                    const int j = h * kRowLanes + c;
+                    t[h] = T[(i0 + u) * KP + (j < KP ? j : 0)];
+                    den[h] = fma(s, t[h], den[h]);
+                }
+                row_outer<0, 0, (KP < kRowLanes ? KP : kRowLanes)>(acc, t[0], sy);
+                if constexpr (kRegs > 1) row_outer<kRowLanes, 0, KP - kRowLanes>(acc, t[1], sy);
             }
         }
     }
 #pragma unroll
-    for (int u = 0; u < kYSlots; ++u) Y[lane + u * kWave] = yv[u];
-    __builtin_amdgcn_wave_barrier();
-
-    // one lane per output (j, c) = (slot / 16, slot % 16); float64 accumulation, one rounding
-    const int nF4 = (nF + 3) & ~3;                       // rows nF.. of W and Y are zero
-    float *og = out + static_cast<size_t>(g) * K * C;
+    for (int h = 0; h < kRegs; ++h) den[h] = 1.0 / den[h];
 #pragma unroll
-    for (int u = 0; u < KT / 4; ++u) {
-        if (u * 4 < K) {
-            const int slot = lane + u * kWave;
-            const int j = slot / kPk, c = slot % kPk;
-            double acc = 0.0;
+    for (int j = 0; j < KP; ++j) acc[j] *= row_bcast_dyn(den[j / kRowLanes], j % kRowLanes);
+    if (hit[KP] != 0) {
 #pragma unroll
-            for (int r0 = 0; r0 < RT; r0 += 4) {
-                if (r0 < nF4) {
-#pragma unroll
-                    for (int r = r0; r < r0 + 4; ++r)
-                        acc = fma(W[j * RT + r], static_cast<double>(Y[r * kPk + c]), acc);
-                }
-            }
-            if (TOP1) O_s[TOP1 ? wv : 0][slot] = acc;
-            else if (j < K && c < C) og[j * C + c] = static_cast<float>(acc);
+        for (int j = 0; j < KP; ++j) {
+            const int h = hit[j];
+            if (h >= 0 && ((m >> h) & 1ull) != 0ull) acc[j] = static_cast<double>(pg[h * C]);
         }
     }
-    if (TOP1) {
-        __builtin_amdgcn_wave_barrier();
-        if (lane < K) {                                   // largest value, smallest class on equal values
-            const double *o = O_s[TOP1 ? wv : 0] + lane * kPk;
-            double bv = o[0];
-            int bi = 0;
-            for (int c = 1; c < C; ++c) {
-                const double v = o[c];
-                if (v > bv) {
-                    bv = v;
-                    bi = c;
-                }
-            }
-            top1[g * K + lane] = bi;
-            if (score != nullptr) score[g * K + lane] = static_cast<float>(bv);
+    if (!TOP1) {
+        float *og = out + static_cast<size_t>(g) * K * C + c;
+        if (here && good && c < C) {
+#pragma unroll
+            for (int j = 0; j < KP; ++j)
+                if (j < K) og[j * C] = static_cast<float>(acc[j]);
+        }
+        return;
+    }
+    // largest value of each query, smallest class on equal values, kept by the lane of the query
+    int best_c[kRegs];
+    double best_v[kRegs];
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+        const double v = c < C ? acc[j] : -__builtin_inf();
+        double b = v;
+        b = __builtin_fmax(b, dpp_exchange<kDppQuadXor1>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppQuadXor2>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppRowHalfMirror>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppRowMirror>(b));
+        const uint32_t who = static_cast<uint32_t>(__ballot(v == b) >> (lane_id() & 48)) & 0xffffu;
+        if (c == j % kRowLanes) {
+            best_v[j / kRowLanes] = b;
+            best_c[j / kRowLanes] = who != 0u ? __ffs(who) - 1 : 0;         // nothing but NaN: class 0
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < kRegs; ++h) {
+        const int j = h * kRowLanes + c;
+        if (here && good && j < K) {
+            top1[g * K + j] = best_c[h];
+            if (score != nullptr) score[g * K + j] = static_cast<float>(best_v[h]);
         }
     }
 }
@@ -671,40 +695,36 @@ __global__ __launch_bounds__(kArgmaxWaves *kWave) void argmax_rows_kernel(const 
     }
 }
 
-bool packed_shape(int K, int N, int64_t C) {
-    return K <= 32 && N <= kWave && C <= kPk;             // N <= 64: the survivors fit the largest tile
-}
+bool rows_shape(int K, int N, int64_t C) { return K <= 32 && N <= kWave && C <= kRowLanes; }
 
-int run_packed(bool top1_variant, const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1,
-               float *d_score, int32_t *d_status, int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes,
-               int sign_mode, hipStream_t stream) {
-    const int most_survivors = S < 0 ? N : N - S;
-    // the smallest tile (queries, survivors) that holds the shape; the largest takes two groups per workgroup
-    const int tile = (K <= 16 && most_survivors <= 16) ? 0 : ((K <= 16 && most_survivors <= 32) ? 1 : 2);
-    const int groups = tile == 2 ? 2 : 4;
-    const int64_t blocks = (G + groups - 1) / groups;
+template <bool TOP1>
+int run_rows(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1, float *d_score, int32_t *d_status,
+             int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
+    const int64_t blocks = (G + kRowGroups - 1) / kRowGroups;
     if (blocks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    const dim3 grid(static_cast<unsigned>(blocks)), block(groups * kWave);
-#define APPROXIFER_PACKED(TOP1, KT, RT, GROUPS)                                                                        \
-    launch_status(launch_kernel(decode_packed_kernel<TOP1, KT, RT, GROUPS>, grid, block, 0, stream, d_preds, d_mask,     \
-                                d_out, d_top1, d_score, d_status, G, K, N, S, static_cast<int>(C), sign_mode, nodes))
-    if (top1_variant) {
-        if (tile == 0) return APPROXIFER_PACKED(true, 16, 16, 4);
-        if (tile == 1) return APPROXIFER_PACKED(true, 16, 32, 4);
-        return APPROXIFER_PACKED(true, 32, 64, 2);
+    const dim3 grid(static_cast<unsigned>(blocks)), block(kRowGroups * kRowLanes);
+#define APPROXIFER_ROWS(KP)                                                                                            \
+    launch_status(launch_kernel(decode_rows_kernel<TOP1, KP>, grid, block,                                              \
+                                sizeof(double) * N * KP + sizeof(int) * (KP + 1), stream, d_preds, d_mask, d_out, d_top1,  \
+                                d_score, d_status, G, K, N, S, static_cast<int>(C), sign_mode, nodes))
+    switch ((K + 3) / 4) {
+        case 1: return APPROXIFER_ROWS(4);
+        case 2: return APPROXIFER_ROWS(8);
+        case 3: return APPROXIFER_ROWS(12);
+        case 4: return APPROXIFER_ROWS(16);
+        case 5:
+        case 6: return APPROXIFER_ROWS(24);
+        default: return APPROXIFER_ROWS(32);
     }
-    if (tile == 0) return APPROXIFER_PACKED(false, 16, 16, 4);
-    if (tile == 1) return APPROXIFER_PACKED(false, 16, 32, 4);
-    return APPROXIFER_PACKED(false, 32, 64, 2);
-#undef APPROXIFER_PACKED
+#undef APPROXIFER_ROWS
 }
 
 }  // namespace
 
 int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K,
                   int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
-    if (packed_shape(K, N, C))
-        return run_packed(false, d_preds, d_mask, d_out, nullptr, nullptr, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+    if (rows_shape(K, N, C))
+        return run_rows<false>(d_preds, d_mask, d_out, nullptr, nullptr, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     const int KP = (K + 3) & ~3;
     const bool vec4 = (C % 4 == 0) && aligned16(d_preds) && aligned16(d_out);
     const int64_t Cv = vec4 ? C / 4 : C;
@@ -747,8 +767,8 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
 int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_top1, float *d_score,
                        int32_t *d_status, int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes,
                        int sign_mode, hipStream_t stream) {
-    if (packed_shape(K, N, C))
-        return run_packed(true, d_preds, d_mask, nullptr, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+    if (rows_shape(K, N, C))
+        return run_rows<true>(d_preds, d_mask, nullptr, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     const int KP = (K + 3) & ~3;
     const bool vec4 = (C % 4 == 0) && aligned16(d_preds);
     const int64_t Cv = vec4 ? C / 4 : C;

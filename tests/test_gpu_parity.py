@@ -749,6 +749,43 @@ def test_byzantine_no_stragglers_groups_share_one_factorisation(gpu, K, A, N, C,
     assert group_err(out[good], ref[good]).max() <= TOL
 
 
+@pytest.mark.parametrize("K,N,S,C,G", [
+    (1, 2, 0, 1, 1), (4, 16, 3, 16, 17), (5, 17, 4, 3, 33), (6, 9, 2, 10, 16), (8, 9, 1, 10, 257), (12, 28, 9, 15, 5),
+    (16, 33, 15, 2, 31), (17, 48, 12, 5, 18), (24, 64, 30, 16, 3), (32, 64, 0, 7, 15), (32, 48, 12, 2, 40), (9, 32, -1, 10, 50),
+])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_decode_small_classes_sixteen_groups_to_a_workgroup(gpu, K, N, S, C, G, mode):
+    # Edges of the row kernel: register counts of K, chunks of sixteen workers, the last workgroup partly filled, query
+    # nodes that are worker nodes (6 of 9, 5 of 17, ..), answers that did not come hold NaN; decode and fused top-1.
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(91 * K + N + C)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    Y = rng.standard_normal((G, N, C)).astype(np.float32)
+    mask = np.zeros((G, N), np.uint8)
+    for g in range(G):
+        late = S if S >= 0 else int(rng.integers(0, N - 1))
+        mask[g, rng.permutation(N)[late:]] = 1
+    if G > 2:
+        mask[1] = 0                                       # bad: nobody answered
+    poisoned = np.where(mask[:, :, None] != 0, Y, np.float32(np.nan))
+    Yd, md = torch.from_numpy(poisoned).to(dev), torch.from_numpy(mask).to(dev)
+    out = torch.full((G, K, C), -3.0, dtype=torch.float32, device=dev)
+    out, st = binding.approxifer_decode(Yd, md, alpha, beta, S, mode, out=out)
+    top1, score, st1 = binding.approxifer_decode_top1(Yd, md, alpha, beta, S, mode)
+    out, st, top1, score, st1 = (t.cpu().numpy() for t in (out, st, top1, score, st1))
+    ref, st_ref = orc.decode(Y, mask, alpha, beta, S, mode)
+    assert np.array_equal(st, st_ref) and np.array_equal(st1, st_ref)
+    good = st == 0
+    assert np.all(out[~good] == -3.0) and np.all(top1[~good] == -1)
+    ok = good & np.isfinite(ref).all(axis=(1, 2)) & (np.abs(ref).max(axis=(1, 2)) < 1e6)   # printed signs can meet a pole
+    assert ok.sum() >= good.sum() // 2
+    assert group_err(out[ok], ref[ok]).max() <= TOL
+    assert np.array_equal(score[ok], out[ok].max(-1))
+    srt = np.sort(ref, axis=-1)
+    clear = ok[:, None] & (np.ones((G, K), bool) if C == 1 else srt[..., -1] - srt[..., -2] > 1e-9 * np.abs(srt).max(-1))
+    assert np.array_equal(top1[clear], ref.argmax(-1)[clear])
+
+
 @pytest.mark.parametrize("K,A,S,N,C", [
     (8, 2, 4, 24, 10),      # the byzantine workload: one row block of workers more than answer
     (8, 2, 9, 30, 15),      # many more workers than answer; the most classes a staged tile takes
