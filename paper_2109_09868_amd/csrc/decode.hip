@@ -458,6 +458,57 @@ __global__ __launch_bounds__(256) void decode_top1_stream_kernel(const float *__
 }
 
 // ------------------------------------------------------------------------------------
+// what the row kernels below share: a 16-lane row works on one group, N <= 64
+// ------------------------------------------------------------------------------------
+// T[i][j] = 1 / (alpha_j - beta_i), row stride KP, zero for j >= K and where the two nodes are one; hit[j] = the worker
+// whose node is query node j, or -1, hit[KP] = whether there is one.  By the whole workgroup; ends with a barrier.
+template <int KP>
+__device__ __forceinline__ void node_table(const Nodes &nodes, int K, int N, double *T, int *hit) {
+    if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
+    __syncthreads();
+    for (int e = threadIdx.x; e < N * KP; e += blockDim.x) {
+        const int i = e / KP, j = e % KP;
+        const double d = nodes.alpha[j < K ? j : 0] - nodes.beta[i];
+        const bool same = j < K && d == 0.0;
+        if (same) {                                         // nodes are distinct: one worker at most
+            hit[j] = i;
+            hit[KP] = 1;
+        }
+        T[e] = (j < K && !same) ? 1.0 / d : 0.0;
+    }
+    __syncthreads();
+}
+// The mask row of this lane's group, byte lane % 16 + 16 p in b[p]; lanes past N load byte 0 (four loads that nothing
+// waits for, instead of four branches with a load in each).
+struct MaskBytes {
+    uint8_t b[4];
+};
+__device__ __forceinline__ MaskBytes load_mask_row(const uint8_t *__restrict__ mask_row, int N) {
+    MaskBytes r;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int i = p * kRowLanes + static_cast<int>(threadIdx.x % kRowLanes);
+        r.b[p] = mask_row[i < N ? i : 0];
+    }
+    return r;
+}
+// Bit i of the result: worker i of this lane's group answered.
+__device__ __forceinline__ unsigned long long row_survivors(const MaskBytes &r, int N) {
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        m |= ((__ballot(r.b[p] != 0) >> (lane_id() & 48)) & 0xffffull) << (p * kRowLanes);
+    return N < 64 ? m & ((1ull << N) - 1ull) : m;
+}
+// Bit i, for a survivor i: its term of the decoder carries a minus sign.
+__device__ __forceinline__ unsigned long long minus_signs(unsigned long long m, int sign_mode) {
+    if (sign_mode != APPROXIFER_SIGN_SURVIVOR_RANK) return 0xaaaaaaaaaaaaaaaaull;       // an odd index
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) m ^= m << s;           // bit i: an odd number of survivors up to and including i
+    return ~m;
+}
+
+// ------------------------------------------------------------------------------------
 // small classes: a 16-lane row per group
 // ------------------------------------------------------------------------------------
 // K <= 32 queries, N <= 64 workers, C <= 16 classes: the image-classification operating points (K = 8..12, one to three
@@ -490,41 +541,17 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
     const int64_t g = here ? g_raw : G - 1;                 // rows past the last group work on it and store nothing
 
     // every load first: the mask row by sixteens, the first predictions
-    bool answered[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) answered[p] = p * kRowLanes + c < N && mask[g * N + p * kRowLanes + c] != 0;
+    const MaskBytes answered = load_mask_row(mask + g * N, N);
     const float *pg = preds + static_cast<size_t>(g) * N * C + (c < C ? c : 0);
     float y[kRowChunkSmall];
 #pragma unroll
     for (int u = 0; u < kRowChunkSmall; ++u) y[u] = u < N ? pg[u * C] : 0.0f;
 
-    if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
-    __syncthreads();
-    for (int e = threadIdx.x; e < N * KP; e += kRowGroups * kRowLanes) {
-        const int i = e / KP, j = e % KP;
-        const double d = nodes.alpha[j < K ? j : 0] - nodes.beta[i];
-        const bool same = j < K && d == 0.0;
-        if (same) {                                         // nodes are distinct: one worker at most
-            hit[j] = i;
-            hit[KP] = 1;
-        }
-        T[e] = (j < K && !same) ? 1.0 / d : 0.0;
-    }
-    unsigned long long m = 0ull;
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-        m |= ((__ballot(answered[p]) >> (lane_id() & 48)) & 0xffffull) << (p * kRowLanes);
+    node_table<KP>(nodes, K, N, T, hit);
+    const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
     if (c == 0 && here && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
-    unsigned long long minus = 0xaaaaaaaaaaaaaaaaull;       // workers with an odd index ..
-    if (sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK) {       // .. or with an odd number of survivors before them
-        minus = m;
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) minus ^= minus << s;
-        minus = ~minus;                                     // (for a survivor: an even number up to and including it)
-    }
-    __syncthreads();
 
     double acc[KP], den[kRegs];
 #pragma unroll
@@ -600,6 +627,248 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
             top1[g * K + j] = best_c[h];
             if (score != nullptr) score[g * K + j] = static_cast<float>(best_v[h]);
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// more classes: a 16-lane row per (group, sixteen vectors of four classes)
+// ------------------------------------------------------------------------------------
+// The same for K <= 16, N <= 64 and more than sixteen classes: a lane owns four neighbouring classes, a tile is 64 classes
+// of a group, and a workgroup takes sixteen consecutive tiles of the batch, so that a row end leaves at most fifteen
+// lanes idle where a wave per (group, 256 classes) left up to 63 (100 classes: 7 of 32 against 39 of 64).  Here the rows
+// of missing workers are not read: the survivors' indices go through LDS (one row each), a lane has kTileChunk rows in
+// flight, and everything else, T above all, is evaluated while the mask is on its way.
+// UNAL: rows are only 4-byte aligned; the lane with a row's last partial vector moves it float by float.
+// 4096 groups of K = 8, 8 of 12 workers, 100 classes: 8.6 us with a wave per 256 classes, 7.1 us this way; 65536 groups
+// of 40 classes 88 and 40 us; 512 groups of K = 12, 12 of 20 workers, 1000 classes 13.4 and 11.3 us.
+// K = 9..12 with twelve rows in flight (two waves to a SIMD) is faster while one round of workgroups holds the launch
+// (8192 tiles), slower after that: 512 groups of 1000 classes 11.1 us against 12.9 with eight rows (three waves),
+// 1024 groups of 4000 classes 76.8 against 71.7.
+constexpr int64_t kTilesOneRound = 8192;
+
+// acc[e][j] = sum over the survivors i of T[i][j] s_i y_ie, this lane's four classes e of the row at pg + class; den: in
+// lane j the denominator of query j.  rows: the most survivors that any row of the wave may have.  A row past its last
+// survivor repeats it (S < 0: with factor 0); a bad row reads worker 0 and its values are not used.
+template <int KP, int CHUNK, bool UNAL>
+__device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t C, int floats, const uint8_t *F, int nF, bool good,
+                                          int rows, bool varies, unsigned long long minus, const double *T, double (&acc)[4][KP],
+                                          double &den) {
+    const int c = threadIdx.x % kRowLanes;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < KP; ++j) acc[e][j] = 0.0;
+    den = 0.0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < rows; r0 += CHUNK) {
+        v4f y[CHUNK];
+        int w[CHUNK];
+#pragma unroll
+        for (int u = 0; u < CHUNK; ++u) {
+            const int r = r0 + u < nF ? r0 + u : nF - 1;
+            const int f = F[r > 0 ? r : 0];
+            w[u] = good ? f : 0;
+            y[u] = load_pred_vector<UNAL>(pg + static_cast<size_t>(w[u]) * C, floats);
+        }
+#pragma unroll
+        for (int u = 0; u < CHUNK; ++u) {
+            if (r0 + u < rows) {
+                const uint32_t flip = (static_cast<uint32_t>(minus >> w[u]) & 1u) << 31;
+                double s = __hiloint2double(static_cast<int>(0x3ff00000u ^ flip), 0);
+                if (varies && r0 + u >= nF) {
+                    s = 0.0;
+                    y[u] = v4f(0.0f);
+                }
+                const double t = T[w[u] * KP + (c < KP ? c : 0)];
+                den = fma(s, t, den);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    row_outer<0, 0, KP>(acc[e], t, static_cast<double>(__uint_as_float(__float_as_uint(y[u][e]) ^ flip)));
+            }
+        }
+    }
+}
+// The survivors of this row's group, ascending, to F[64]; visible to the row after the wave barrier at the end.
+__device__ __forceinline__ void list_survivors(unsigned long long m, uint8_t *F) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int i = p * kRowLanes + static_cast<int>(threadIdx.x % kRowLanes);
+        if ((m >> i) & 1ull) F[__popcll(m & ((1ull << i) - 1ull))] = static_cast<uint8_t>(i);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int KP, int CHUNK, bool UNAL>
+__global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
+    const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
+    int32_t *__restrict__ status, int64_t tiles, uint32_t chunks, int K, int N, int S, int64_t C, int sign_mode,
+    const Nodes nodes) {
+    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit | uint8 F[16][64]
+    int *hit = reinterpret_cast<int *>(T + N * KP);
+    const int c = threadIdx.x % kRowLanes;
+    const int row = threadIdx.x / kRowLanes;
+    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 1) + row * kWave;
+    const int64_t tile_raw = static_cast<int64_t>(blockIdx.x) * kRowGroups + row;
+    const bool here = tile_raw < tiles;
+    const int64_t tile = here ? tile_raw : tiles - 1;
+    const int64_t g = tiles <= 0xffffffffLL ? static_cast<uint32_t>(tile) / chunks : tile / chunks;
+    const uint32_t chunk = static_cast<uint32_t>(tile - g * chunks);
+
+    const MaskBytes answered = load_mask_row(mask + g * N, N);
+    node_table<KP>(nodes, K, N, T, hit);
+    const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
+    const int nF = static_cast<int>(__popcll(m));
+    const bool good = S < 0 ? nF >= 1 : nF == N - S;
+    if (c == 0 && here && chunk == 0 && status != nullptr)
+        status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    list_survivors(m, F);
+
+    const int64_t col = (static_cast<int64_t>(chunk) * kRowLanes + c) * 4;
+    const bool ok = col < C;
+    const int floats = UNAL && ok && C - col < 4 ? static_cast<int>(C - col) : 4;
+    const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
+    double acc[4][KP], den;
+    tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, good, S < 0 ? N : N - S, S < 0, minus, T, acc, den);
+    den = 1.0 / den;
+    float *og = out + static_cast<size_t>(g) * K * C + col;
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+        const double d = row_bcast_dyn(den, j);
+        double v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[e][j] * d;
+        if (hit[KP] != 0) {
+            const int h = hit[j];
+            if (good && h >= 0 && ((m >> h) & 1ull) != 0ull) {
+                const v4f yh = load_pred_vector<UNAL>(pg + static_cast<size_t>(h) * C, floats);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = static_cast<double>(yh[e]);   // waits here: behind the branch it would
+            }                                                                    // wait for the stores of every query
+        }
+        v4f f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = static_cast<float>(v[e]);
+        if (here && good && ok && j < K) {
+            float *dst = og + static_cast<size_t>(j) * C;
+            if (!UNAL) {
+                __builtin_nontemporal_store(f, reinterpret_cast<v4f *>(dst));
+            } else if (floats >= 4) {
+                __builtin_nontemporal_store(static_cast<v4f_dword_aligned>(f), reinterpret_cast<v4f_dword_aligned *>(dst));
+            } else {
+                dst[0] = f[0];
+                if (floats > 1) dst[1] = f[1];
+                if (floats > 2) dst[2] = f[2];
+            }
+        }
+    }
+}
+
+// The class decision over the same tiles: R = 1, 2, 4, 8 or 16 rows of a workgroup share a group, row q taking the tiles
+// q, q + R, ..; a lane keeps the best (value, class) of every query over its tiles, the lanes of a row meet by DPP, the
+// rows of a group in LDS.  4096 groups of 100 classes (K = 8, 8 of 12 workers): 18.0 us with a workgroup per group, 7.9 us
+// this way; 512 groups of 1000 classes (K = 12): 16.5 and 12.9 us; 16384 groups of 40: 53 and 12.
+template <int KP, int CHUNK, bool UNAL>
+__global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kernel(
+    const float *__restrict__ preds, const uint8_t *__restrict__ mask, int32_t *__restrict__ top1,
+    float *__restrict__ score, int32_t *__restrict__ status, int64_t G, uint32_t chunks, int R, int K, int N, int S,
+    int64_t C, int sign_mode, const Nodes nodes) {
+    extern __shared__ double T[];                           // [N][KP] | best values [16][KP] | int best classes [16][KP]
+    double *best_v = T + N * KP;                            // | int hit[KP] | int any_hit | uint8 F[16][64]
+    int *best_c = reinterpret_cast<int *>(best_v + kRowGroups * KP);
+    int *hit = best_c + kRowGroups * KP;
+    const int c = threadIdx.x % kRowLanes;
+    const int row = threadIdx.x / kRowLanes;
+    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 1) + row * kWave;
+    const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * (kRowGroups / R) + row / R;
+    const bool here = g_raw < G;
+    const int64_t g = here ? g_raw : G - 1;
+
+    const MaskBytes answered = load_mask_row(mask + g * N, N);
+    node_table<KP>(nodes, K, N, T, hit);
+    const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
+    const int nF = static_cast<int>(__popcll(m));
+    const bool good = S < 0 ? nF >= 1 : nF == N - S;
+    if (c == 0 && here && row % R == 0 && status != nullptr)
+        status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    list_survivors(m, F);
+
+    double bv[KP];
+    int bc[KP];
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+        bv[j] = -__builtin_inf();
+        bc[j] = 0x7fffffff;
+    }
+#pragma unroll 1
+    for (uint32_t base = 0; base < chunks; base += R) {     // every row goes round as often as the others
+        const int64_t col = (static_cast<int64_t>(base + row % R) * kRowLanes + c) * 4;
+        const bool ok = col < C;
+        const int floats = ok ? (C - col < 4 ? static_cast<int>(C - col) : 4) : 0;
+        const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
+        double acc[4][KP], den;
+        tile_sums<KP, CHUNK, UNAL>(pg, C, UNAL && ok ? floats : 4, F, nF, good, S < 0 ? N : N - S, S < 0, minus, T, acc, den);
+        den = 1.0 / den;
+#pragma unroll
+        for (int j = 0; j < KP; ++j) {
+            const double d = row_bcast_dyn(den, j);
+            double v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[e][j] * d;
+            if (hit[KP] != 0) {
+                const int h = hit[j];
+                if (good && h >= 0 && ((m >> h) & 1ull) != 0ull) {
+                    const v4f yh = load_pred_vector<UNAL>(pg + static_cast<size_t>(h) * C, UNAL && ok ? floats : 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = static_cast<double>(yh[e]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {                   // ascending classes: the first of equal values stays
+                const bool take = e < floats && v[e] > bv[j];
+                bv[j] = take ? v[e] : bv[j];
+                bc[j] = take ? static_cast<int>(col) + e : bc[j];
+            }
+        }
+    }
+    // largest value of the row, smallest class on equal values; lane j keeps query j's
+    double mine_v = -__builtin_inf();
+    int mine_c = 0x7fffffff;
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
+        double b = bv[j];
+        b = __builtin_fmax(b, dpp_exchange<kDppQuadXor1>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppQuadXor2>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppRowHalfMirror>(b));
+        b = __builtin_fmax(b, dpp_exchange<kDppRowMirror>(b));
+        int i = bv[j] == b ? bc[j] : 0x7fffffff;
+        i = min(i, __builtin_amdgcn_update_dpp(0, i, kDppQuadXor1, 0xF, 0xF, true));
+        i = min(i, __builtin_amdgcn_update_dpp(0, i, kDppQuadXor2, 0xF, 0xF, true));
+        i = min(i, __builtin_amdgcn_update_dpp(0, i, kDppRowHalfMirror, 0xF, 0xF, true));
+        i = min(i, __builtin_amdgcn_update_dpp(0, i, kDppRowMirror, 0xF, 0xF, true));
+        if (c == j) {
+            mine_v = b;
+            mine_c = i;
+        }
+    }
+    if (R > 1) {
+        if (c < KP) {
+            best_v[row * KP + c] = mine_v;
+            best_c[row * KP + c] = mine_c;
+        }
+        __syncthreads();
+        if (row % R != 0) return;
+        for (int q = 1; q < R && c < KP; ++q) {
+            const double v = best_v[(row + q) * KP + c];
+            const int i = best_c[(row + q) * KP + c];
+            if (v > mine_v || (v == mine_v && i < mine_c)) {
+                mine_v = v;
+                mine_c = i;
+            }
+        }
+    }
+    if (here && good && c < K) {
+        top1[g * K + c] = mine_c == 0x7fffffff ? 0 : mine_c;             // nothing above -inf: class 0
+        if (score != nullptr) score[g * K + c] = static_cast<float>(mine_v);
     }
 }
 
@@ -734,8 +1003,31 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
     int waves = KP / 4;
     if (waves > 4) waves = 4;
     const size_t lds = sizeof(double) * (static_cast<size_t>(S < 0 ? N : N - S) * KP + K + N) + sizeof(int) * (static_cast<size_t>(N) + 2);
-    // K <= 16, up to 64 survivors: one wave per tile with all K accumulator rows (faster at every size measured, 26 MB
-    // to 1.1 GB; capping its residency as in the encoder changes nothing: 4 to 12 waves per CU +-3 %)
+    const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
+    const int64_t tiles = G * chunks;
+    // .. but for K = 9..12 and long aligned rows beyond one round of workgroups the wave per 256 classes is a little
+    // faster (1024 groups of 4000 classes: 71.3 against 73.3 us; K = 16, 300 groups of 4096: 35.6 against 35.4)
+    const bool long_rows = KP == 12 && vec4 && C >= 2048 && tiles > kTilesOneRound;
+    if (K <= 16 && N <= kWave && !long_rows) {
+        const int64_t tblocks = (tiles + kRowGroups - 1) / kRowGroups;
+        if (tblocks > 0x7fffffffLL || chunks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+        const dim3 tgrid(static_cast<unsigned>(tblocks)), tblock(kRowGroups * kRowLanes);
+#define APPROXIFER_TILES(KPV, CHUNK, UNAL)                                                                             \
+    launch_status(launch_kernel(decode_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                                   \
+                                sizeof(double) * N * KPV + sizeof(int) * (KPV + 1) + kRowGroups * kWave, stream, d_preds,  \
+                                d_mask, d_out, d_status, tiles, static_cast<uint32_t>(chunks), K, N, S, C, sign_mode, nodes))
+        switch (KP / 4) {
+            case 1: return vec4 ? APPROXIFER_TILES(4, 8, false) : APPROXIFER_TILES(4, 8, true);
+            case 2: return vec4 ? APPROXIFER_TILES(8, 8, false) : APPROXIFER_TILES(8, 8, true);
+            case 3:
+                if (tiles <= kTilesOneRound) return vec4 ? APPROXIFER_TILES(12, 12, false) : APPROXIFER_TILES(12, 12, true);
+                return vec4 ? APPROXIFER_TILES(12, 8, false) : APPROXIFER_TILES(12, 8, true);
+            default: return vec4 ? APPROXIFER_TILES(16, 8, false) : APPROXIFER_TILES(16, 8, true);
+        }
+#undef APPROXIFER_TILES
+    }
+    // the same with up to 64 of more than 64 workers: one wave per 256 classes with all K accumulator rows (capping its
+    // residency as in the encoder changes nothing: 4 to 12 waves per CU +-3 %)
     const int most_survivors = S < 0 ? N : N - S;
     if (K <= 16 && most_survivors <= 64 && C >= 4) {
         const int64_t sCv = (C + 3) / 4;                  // counts a partial last vector
@@ -774,9 +1066,29 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     const int64_t Cv = vec4 ? C / 4 : C;
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const int KQ = KP / 4;
+    const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;     // .. with very many classes: the split below
+    if (K <= 16 && N <= kWave && !few_groups) {
+        const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
+        int R = 1;
+        while (R < kRowGroups && R < chunks) R *= 2;
+        const dim3 tgrid(static_cast<unsigned>((G + kRowGroups / R - 1) / (kRowGroups / R))), tblock(kRowGroups * kRowLanes);
+#define APPROXIFER_TOP1_TILES(KPV, CHUNK, UNAL)                                                                        \
+    launch_status(launch_kernel(decode_top1_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                              \
+                                sizeof(double) * (N + kRowGroups) * KPV + sizeof(int) * (kRowGroups * KPV + KPV + 1) +   \
+                                    kRowGroups * kWave,                                                                 \
+                                stream, d_preds, d_mask, d_top1, d_score, d_status, G, static_cast<uint32_t>(chunks), R, K, \
+                                N, S, C, sign_mode, nodes))
+        switch (KQ) {
+            case 1: return vec4 ? APPROXIFER_TOP1_TILES(4, 8, false) : APPROXIFER_TOP1_TILES(4, 8, true);
+            case 2: return vec4 ? APPROXIFER_TOP1_TILES(8, 8, false) : APPROXIFER_TOP1_TILES(8, 8, true);
+            case 3: return vec4 ? APPROXIFER_TOP1_TILES(12, 8, false) : APPROXIFER_TOP1_TILES(12, 8, true);
+            default: return vec4 ? APPROXIFER_TOP1_TILES(16, 8, false) : APPROXIFER_TOP1_TILES(16, 8, true);
+        }
+#undef APPROXIFER_TOP1_TILES
+    }
     // K <= 16, up to 64 survivors, enough groups to fill the chip: a workgroup per group whose waves keep all K
     // accumulator rows (few groups with very many classes stay with the quad-per-workgroup split below)
-    if (K <= 16 && (S < 0 ? N : N - S) <= 64 && C >= 4 && !(G * KQ <= 512 && (C + 3) / 4 >= 64 * 16)) {
+    if (K <= 16 && (S < 0 ? N : N - S) <= 64 && C >= 4 && !few_groups) {
         const int64_t sCv = (C + 3) / 4;
         const int64_t stiles = (sCv + kColsPerTile - 1) / kColsPerTile;
         const int nwaves = stiles < 4 ? static_cast<int>(stiles) : 4;
