@@ -2,8 +2,8 @@
 //
 //   coded[g][i][d] = sum_j l_j(beta_i) * queries[g][j][d]
 //
-// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16,
-// four waves (256 columns) above; short ragged rows are tiled over the flattened (group, column)
+// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16 and 16-byte
+// rows, four waves (256 columns) otherwise; short ragged rows are tiled over the flattened (group, column)
 // index instead, so that no lane idles at a row end.  Each lane first issues the loads of its vector column of
 // all K queries (they stay in registers), and while those are in flight the workgroup
 // evaluates the N x K matrix l_j(beta_i) -- it depends on the nodes only -- in float64 (one
@@ -314,16 +314,23 @@ int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, in
     return run_encode_mfma_shape<KS, UNAL, false>(d_queries, d_coded, G * chunks, chunks, K, N, D, Dv, nodes, stream);
 }
 
+// Workgroup size.  K <= 16: one wave, but four for rows that are only 4-byte aligned.  There every wave's row segment
+// begins and ends inside a 128-byte line that the neighbouring wave's shares; in one workgroup the two meet in one L2
+// instead of two, and three of four such lines are moved once (K = 8, N = 12, 3 x 299 x 299 floats, 64 groups: 279 ->
+// 268 us; K = 4, N = 6, 50001 floats: 198 -> 174 us; K = 16, N = 24, 100001 floats: 225 -> 206 us).
+constexpr int encode_threads(int K, bool UNAL) { return K <= 16 && !UNAL ? 64 : 256; }
+
 template <int K, int VEC, bool FLAT, bool UNAL>
 int run_encode_shape(const float *d_queries, float *d_coded, int64_t tiles, int64_t chunks, int N, int64_t D,
                      int64_t Dv, int64_t col0, const Nodes &nodes, hipStream_t stream) {
     constexpr int KP = (K + 3) & ~3;
-    constexpr int THREADS = K <= 16 ? 64 : 256;
+    constexpr int THREADS = encode_threads(K, UNAL);
     int per_cu = kBlocksPerCuLargeK;
     if (K <= 16) {
         per_cu = (kLoadKbPerCu + K - 1) / K;     // K loads of 1 KB per wave
         if (per_cu < kWavesPerCuMin) per_cu = kWavesPerCuMin;
         if (per_cu > 24) per_cu = 24;
+        if (THREADS > 64) per_cu = (per_cu + THREADS / 64 - 1) / (THREADS / 64);   // as many waves
         if (VEC == 1) per_cu = 7;       // 4-byte accesses (the last D % 4 columns, or D < 4): a sliver of the work
     }
     if (tiles > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
@@ -343,7 +350,7 @@ int run_encode_shape(const float *d_queries, float *d_coded, int64_t tiles, int6
 template <int K, int VEC, bool UNAL>
 int run_encode(const float *d_queries, float *d_coded, int64_t G, int N, int64_t D, int64_t Dv, int64_t col0,
                const Nodes &nodes, hipStream_t stream) {
-    constexpr int THREADS = K <= 16 ? 64 : 256;
+    constexpr int THREADS = encode_threads(K, UNAL);
     const int64_t chunks = (Dv + THREADS - 1) / THREADS;
     // lanes left idle at the row ends by the per-group tiling; above 3 % the flattened numbering pays for its
     // per-lane division and addresses
