@@ -15,10 +15,10 @@
 //    that leaves U = the last n-M rows of Q^T, an orthonormal basis of range(V)'s complement, in
 //    LDS.  Eliminating p exactly, class c only has to solve the (n-M) x (M-1) problem
 //        min_q || U C_c q - U y_c ||,
-//    so a class needs 16 lanes (lane = column, 15 = right-hand side), four classes share a wave, the
-//    four projected systems are formed by the float64 matrix cores (operands read from LDS, result
-//    directly in the lane layout of the factorisation), and the Householder QR runs entirely in
-//    registers: the pivot column reaches the other lanes of the class through DPP row broadcasts.
+//    so a class needs 16 lanes (lane = column, 15 = right-hand side), four classes share a wave, and
+//    the systems are formed and solved entirely in registers: what the other lanes of the class need of
+//    a column reaches them inside the multiply-adds (see rows.h).  Up to fifteen classes:
+//    decode_byzantine_packed_kernel, several groups to a workgroup.
 //    No LDS traffic and no barrier inside either factorisation.
 //
 //  * decode_byzantine_general_kernel (everything else up to 64 available workers).  A class owns
