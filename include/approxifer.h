@@ -267,7 +267,8 @@ int approxifer_decode_rational(const float *d_preds, const uint8_t *d_mask, floa
  *     d_top1[g][j]  = argmax_c r_g(alpha_j)[c]      (equal values: the smallest c)
  *     d_score[g][j] = that largest decoded value, rounded to float32 (d_score may be NULL)
  * The [G][K][C] prediction tensor is never written.  The argmax is taken on the float64
- * accumulators, before any rounding.
+ * accumulators, before any rounding.  NaN never wins against a number; a query whose values are all NaN gets class 0,
+ * and one that has nothing above -inf a class all the same: 0 <= d_top1 < C, with a score that is NaN or -inf.
  *
  *   d_top1    [G][K] int32, device, written
  *   d_score   [G][K] float32, device, written, or NULL

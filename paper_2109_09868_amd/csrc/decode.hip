@@ -603,7 +603,9 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
         }
         return;
     }
-    // largest value of each query, smallest class on equal values, kept by the lane of the query
+    // largest value of each query, smallest class on equal values, kept by the lane of the query.  NaN loses to any number;
+    // a query without any value above -inf gets class 0 and that class's value.  Lanes past the last class hold -inf too,
+    // so that they win nothing.
     int best_c[kRegs];
     double best_v[kRegs];
 #pragma unroll
@@ -614,10 +616,11 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
         b = __builtin_fmax(b, dpp_exchange<kDppQuadXor2>(b));
         b = __builtin_fmax(b, dpp_exchange<kDppRowHalfMirror>(b));
         b = __builtin_fmax(b, dpp_exchange<kDppRowMirror>(b));
-        const uint32_t who = static_cast<uint32_t>(__ballot(v == b) >> (lane_id() & 48)) & 0xffffu;
+        const uint32_t who = static_cast<uint32_t>(__ballot(v == b && v > -__builtin_inf()) >> (lane_id() & 48)) & 0xffffu;
+        const double first = row_bcast<0>(v);
         if (c == j % kRowLanes) {
-            best_v[j / kRowLanes] = b;
-            best_c[j / kRowLanes] = who != 0u ? __ffs(who) - 1 : 0;         // nothing but NaN: class 0
+            best_v[j / kRowLanes] = who != 0u ? b : first;
+            best_c[j / kRowLanes] = who != 0u ? __ffs(who) - 1 : 0;
         }
     }
 #pragma unroll

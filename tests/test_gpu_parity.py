@@ -507,6 +507,67 @@ def test_decode_top1_exact_ties_take_smallest_class(gpu):
     assert set(np.unique(top1)) <= {0, 7}
 
 
+@pytest.mark.parametrize("K,N,S,C,exact", [
+    (8, 9, 1, 1, True), (8, 9, 1, 2, True), (12, 28, 2, 10, True), (17, 33, -1, 15, True), (4, 12, 4, 16, True),
+    (8, 12, 4, 17, True), (12, 20, 8, 100, True), (16, 24, -1, 1283, True),
+    (8, 70, 10, 40, False), (20, 30, 2, 40, False),       # the kernels for more workers or more queries
+])
+def test_decode_top1_of_predictions_that_are_not_numbers(gpu, K, N, S, C, exact):
+    # A worker that answered may return NaN or infinities, in every class or in some: the answer is a class all the same.
+    # NaN never wins; a query without any value above -inf gets class 0.  The rule is applied to what approxifer_decode
+    # makes of the same predictions (`exact` off: a row of NaN and -inf only may also give the first -inf).
+    torch, binding, dev = gpu
+    G = 48
+    rng = np.random.default_rng(1000 * K + C)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    Y = rng.standard_normal((G, N, C)).astype(np.float32)
+    mask = np.zeros((G, N), np.uint8)
+    for g in range(G):
+        late = S if S >= 0 else int(rng.integers(0, N - 1))
+        order = rng.permutation(N)
+        mask[g, order[late:]] = 1
+        w = order[late]                                   # it answered
+        kind = g % 8
+        some = rng.permutation(C)[: (C + 1) // 2]
+        if kind == 0:
+            Y[g, w] = np.nan
+        elif kind == 1:
+            Y[g, w, some] = np.nan
+        elif kind == 2:
+            Y[g, w] = -np.inf
+        elif kind == 3:
+            Y[g, w] = np.inf
+        elif kind == 4:
+            Y[g, w], Y[g, w, some] = -np.inf, np.nan
+        elif kind == 5:
+            Y[g, w], Y[g, w, some] = np.inf, np.nan
+        elif kind == 6:
+            Y[g, w, some] = -np.inf
+        else:
+            Y[g, w, 0] = np.nan
+    Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
+    out, st = binding.approxifer_decode(Yd, md, alpha, beta, S, 1)
+    top1, score, st1 = binding.approxifer_decode_top1(Yd, md, alpha, beta, S, 1)
+    out, st, top1, score, st1 = (t.cpu().numpy() for t in (out, st, top1, score, st1))
+    assert np.all(st == 0) and np.all(st1 == 0)
+    assert np.all((top1 >= 0) & (top1 < C))
+    above = out > -np.inf                                 # False for NaN
+    none = ~above.any(-1)
+    assert none.any() and (C == 1 or (~none).any())
+    ranked = np.where(above, out.astype(np.float64), -np.inf)
+    best = ranked.argmax(-1)
+    srt = np.sort(ranked, axis=-1)
+    with np.errstate(invalid="ignore"):
+        clear = np.ones(none.shape, bool) if C == 1 else ~(srt[..., -1] - srt[..., -2] <= 1e-6 * np.abs(srt[..., -1]))
+    clear |= np.isinf(srt[..., -1])                       # equal infinities: the first
+    pick = clear & ~none
+    assert np.array_equal(top1[pick], best[pick])
+    assert np.array_equal(score[pick], ranked.max(-1)[pick].astype(np.float32))
+    only_nan = np.isnan(out).all(-1)
+    assert np.all(top1[none if exact else only_nan] == 0)
+    assert not np.any(score[none] > -np.inf)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
