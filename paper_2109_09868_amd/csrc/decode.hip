@@ -7,6 +7,7 @@
 // with the weights broadcast from LDS.  Rows of missing workers are never read.
 #include "decode_common.h"
 #include "rows.h"
+#include "survivors.h"
 
 namespace approxifer {
 namespace {
@@ -508,6 +509,21 @@ __device__ __forceinline__ unsigned long long minus_signs(unsigned long long m, 
     return ~m;
 }
 
+// Lists the survivors of this row's group, visible to the row after the wave barrier at the end: F[0 .. nF) ascending, and
+// every entry behind them names the first survivor, so that a pass over the list never names a worker that did not
+// answer.  (No survivor: zeros, which nobody may follow.)
+__device__ __forceinline__ void list_survivors(unsigned long long m, uint8_t *F) {
+    const int lane = static_cast<int>(threadIdx.x % kRowLanes);
+    list_first(m, F, lane);
+    list_ranks(m, F, lane);
+    __builtin_amdgcn_wave_barrier();
+}
+// The most survivors that any row of this wave has.
+__device__ __forceinline__ int most_survivors_of_wave(int nF) {
+    return max(max(__builtin_amdgcn_readlane(nF, 0), __builtin_amdgcn_readlane(nF, 16)),
+               max(__builtin_amdgcn_readlane(nF, 32), __builtin_amdgcn_readlane(nF, 48)));
+}
+
 // ------------------------------------------------------------------------------------
 // small classes: a 16-lane row per group
 // ------------------------------------------------------------------------------------
@@ -519,12 +535,13 @@ __device__ __forceinline__ unsigned long long minus_signs(unsigned long long m, 
 // once per workgroup, while the loads are in flight; with s_i = the alternating sign of worker i, 0 if it did not answer,
 //     out[j][c] = (sum_i T[i][j] s_i y_ic) / (sum_i T[i][j] s_i).
 // Lane j holds T[i][j], from where the numerators of all classes take it inside the multiply-add (row_outer), and sums
-// the denominator of query j.  Every worker's row is loaded, answered or not (S of N more bytes of a run that is mostly
-// read anyway): the loads need not wait for the mask; an answer that did not come is replaced by zero.
+// the denominator of query j.  The pass goes over the list of survivors: rows of missing workers are not read, and the
+// predictions wait for the mask.
 // A query node that is a worker's node has T = 0 there and takes that worker's row as it is, if the worker answered.
 // 16384 groups of K = 8, N = 9, ten classes, top-1: 13.1 us a kernel with a wave per group, 7.2 us this way.
 constexpr int kRowGroups = 16;
 constexpr int kRowChunkSmall = 16;      // prediction rows in flight
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 template <bool TOP1, int KP>
 __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
@@ -532,50 +549,56 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
     int32_t *__restrict__ top1, float *__restrict__ score, int32_t *__restrict__ status, int64_t G, int K, int N,
     int S, int C, int sign_mode, const Nodes nodes) {
     constexpr int kRegs = (KP + kRowLanes - 1) / kRowLanes;  // T and denominators of query lane + 16 h in register h
-    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit
+    extern __shared__ __align__(16) double T[];             // [N][KP] | int hit[KP] | int any_hit | pad | uint8 F[16][80]
     int *hit = reinterpret_cast<int *>(T + N * KP);
     const int c = threadIdx.x % kRowLanes;
     const int row = threadIdx.x / kRowLanes;
+    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 4) + row * kListBytes;
     const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * kRowGroups + row;
     const bool here = g_raw < G;
     const int64_t g = here ? g_raw : G - 1;                 // rows past the last group work on it and store nothing
 
-    // every load first: the mask row by sixteens, the first predictions
     const MaskBytes answered = load_mask_row(mask + g * N, N);
-    const float *pg = preds + static_cast<size_t>(g) * N * C + (c < C ? c : 0);
-    float y[kRowChunkSmall];
-#pragma unroll
-    for (int u = 0; u < kRowChunkSmall; ++u) y[u] = u < N ? pg[u * C] : 0.0f;
-
-    node_table<KP>(nodes, K, N, T, hit);
-    const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
+    node_table<KP>(nodes, K, N, T, hit);                    // while the mask is on its way
+    const unsigned long long m = row_survivors(answered, N);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
     if (c == 0 && here && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    list_survivors(m, F);
+    const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
+    const uint32_t by_index = sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK ? 0u : 1u;
+    const float *pg = preds + static_cast<size_t>(g) * N * C + (c < C ? c : 0);
 
     double acc[KP], den[kRegs];
 #pragma unroll
     for (int j = 0; j < KP; ++j) acc[j] = 0.0;
 #pragma unroll
     for (int h = 0; h < kRegs; ++h) den[h] = 0.0;
-    for (int i0 = 0; i0 < N; i0 += kRowChunkSmall) {
-        if (i0 > 0) {
+    for (int r0 = 0; r0 < rows; r0 += kRowChunkSmall) {
+        const v4u f = *reinterpret_cast<const v4u *>(F + r0);
+        float y[kRowChunkSmall];
 #pragma unroll
-            for (int u = 0; u < kRowChunkSmall; ++u) y[u] = i0 + u < N ? pg[(i0 + u) * C] : 0.0f;
+        for (int u = 0; u < kRowChunkSmall; ++u) y[u] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kRowChunkSmall; q += 4) {
+            if (r0 + q < rows && nF > 0) {
+#pragma unroll
+                for (int u = q; u < q + 4; ++u) y[u] = pg[static_cast<int>((f[u / 4] >> (8 * (u % 4))) & 0xffu) * C];
+            }
         }
-        const uint32_t m16 = static_cast<uint32_t>(m >> i0), minus16 = static_cast<uint32_t>(minus >> i0);
 #pragma unroll
         for (int u = 0; u < kRowChunkSmall; ++u) {
-            if (i0 + u < N) {
-                const uint32_t there = 0u - ((m16 >> u) & 1u);              // all ones, or zero
-                const uint32_t flip = ((minus16 >> u) & 1u) << 31;
+            if (r0 + u < rows) {
+                const uint32_t w = (f[u / 4] >> (8 * (u % 4))) & 0xffu;
+                const uint32_t there = r0 + u < nF ? ~0u : 0u;              // rows of the wave may differ in nF
+                const uint32_t flip = ((w & by_index) | (u & 1u & ~by_index)) << 31;
                 const double sy = static_cast<double>(__uint_as_float((__float_as_uint(y[u]) ^ flip) & there));
                 const double s = __hiloint2double(static_cast<int>((0x3ff00000u ^ flip) & there), 0);
                 double t[kRegs];
 #pragma unroll
                 for (int h = 0; h < kRegs; ++h) {
                     const int j = h * kRowLanes + c;
-                    t[h] = T[(i0 + u) * KP + (j < KP ? j : 0)];
+                    t[h] = T[w * KP + (j < KP ? j : 0)];
                     den[h] = fma(s, t[h], den[h]);
                 }
                 row_outer<0, 0, (KP < kRowLanes ? KP : kRowLanes)>(acc, t[0], sy);
@@ -651,9 +674,10 @@ constexpr int64_t kTilesOneRound = 8192;
 
 // acc[e][j] = sum over the survivors i of T[i][j] s_i y_ie, this lane's four classes e of the row at pg + class; den: in
 // lane j the denominator of query j.  rows: the most survivors that any row of the wave may have.  A row past its last
-// survivor repeats it (S < 0: with factor 0); a bad row reads worker 0 and its values are not used.
+// survivor repeats its first (S < 0: with factor 0); the values of a bad row are not used, and one without survivors
+// reads nothing.
 template <int KP, int CHUNK, bool UNAL>
-__device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t C, int floats, const uint8_t *F, int nF, bool good,
+__device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t C, int floats, const uint8_t *F, int nF,
                                           int rows, bool varies, unsigned long long minus, const double *T, double (&acc)[4][KP],
                                           double &den) {
     const int c = threadIdx.x % kRowLanes;
@@ -668,10 +692,12 @@ __device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t 
         int w[CHUNK];
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u) {
-            const int r = r0 + u < nF ? r0 + u : nF - 1;
-            const int f = F[r > 0 ? r : 0];
-            w[u] = good ? f : 0;
-            y[u] = load_pred_vector<UNAL>(pg + static_cast<size_t>(w[u]) * C, floats);
+            w[u] = F[r0 + u];
+            y[u] = v4f(0.0f);
+        }
+        if (nF > 0) {
+#pragma unroll
+            for (int u = 0; u < CHUNK; ++u) y[u] = load_pred_vector<UNAL>(pg + static_cast<size_t>(w[u]) * C, floats);
         }
 #pragma unroll
         for (int u = 0; u < CHUNK; ++u) {
@@ -691,26 +717,16 @@ __device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t 
         }
     }
 }
-// The survivors of this row's group, ascending, to F[64]; visible to the row after the wave barrier at the end.
-__device__ __forceinline__ void list_survivors(unsigned long long m, uint8_t *F) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int i = p * kRowLanes + static_cast<int>(threadIdx.x % kRowLanes);
-        if ((m >> i) & 1ull) F[__popcll(m & ((1ull << i) - 1ull))] = static_cast<uint8_t>(i);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int KP, int CHUNK, bool UNAL>
 __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
     int32_t *__restrict__ status, int64_t tiles, uint32_t chunks, int K, int N, int S, int64_t C, int sign_mode,
     const Nodes nodes) {
-    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit | uint8 F[16][64]
+    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit | pad | uint8 F[16][80]
     int *hit = reinterpret_cast<int *>(T + N * KP);
     const int c = threadIdx.x % kRowLanes;
     const int row = threadIdx.x / kRowLanes;
-    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 1) + row * kWave;
+    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 4) + row * kListBytes;
     const int64_t tile_raw = static_cast<int64_t>(blockIdx.x) * kRowGroups + row;
     const bool here = tile_raw < tiles;
     const int64_t tile = here ? tile_raw : tiles - 1;
@@ -725,13 +741,14 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     if (c == 0 && here && chunk == 0 && status != nullptr)
         status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
     list_survivors(m, F);
+    const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
 
     const int64_t col = (static_cast<int64_t>(chunk) * kRowLanes + c) * 4;
     const bool ok = col < C;
     const int floats = UNAL && ok && C - col < 4 ? static_cast<int>(C - col) : 4;
     const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
     double acc[4][KP], den;
-    tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, good, S < 0 ? N : N - S, S < 0, minus, T, acc, den);
+    tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, rows, S < 0, minus, T, acc, den);
     den = 1.0 / den;
     float *og = out + static_cast<size_t>(g) * K * C + col;
 #pragma unroll
@@ -776,12 +793,12 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
     float *__restrict__ score, int32_t *__restrict__ status, int64_t G, uint32_t chunks, int R, int K, int N, int S,
     int64_t C, int sign_mode, const Nodes nodes) {
     extern __shared__ double T[];                           // [N][KP] | best values [16][KP] | int best classes [16][KP]
-    double *best_v = T + N * KP;                            // | int hit[KP] | int any_hit | uint8 F[16][64]
+    double *best_v = T + N * KP;                            // | int hit[KP] | int any_hit | pad | uint8 F[16][80]
     int *best_c = reinterpret_cast<int *>(best_v + kRowGroups * KP);
     int *hit = best_c + kRowGroups * KP;
     const int c = threadIdx.x % kRowLanes;
     const int row = threadIdx.x / kRowLanes;
-    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 1) + row * kWave;
+    uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 4) + row * kListBytes;
     const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * (kRowGroups / R) + row / R;
     const bool here = g_raw < G;
     const int64_t g = here ? g_raw : G - 1;
@@ -794,6 +811,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
     if (c == 0 && here && row % R == 0 && status != nullptr)
         status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
     list_survivors(m, F);
+    const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
 
     double bv[KP];
     int bc[KP];
@@ -809,7 +827,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
         const int floats = ok ? (C - col < 4 ? static_cast<int>(C - col) : 4) : 0;
         const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
         double acc[4][KP], den;
-        tile_sums<KP, CHUNK, UNAL>(pg, C, UNAL && ok ? floats : 4, F, nF, good, S < 0 ? N : N - S, S < 0, minus, T, acc, den);
+        tile_sums<KP, CHUNK, UNAL>(pg, C, UNAL && ok ? floats : 4, F, nF, rows, S < 0, minus, T, acc, den);
         den = 1.0 / den;
 #pragma unroll
         for (int j = 0; j < KP; ++j) {
@@ -977,7 +995,7 @@ int run_rows(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
     const dim3 grid(static_cast<unsigned>(blocks)), block(kRowGroups * kRowLanes);
 #define APPROXIFER_ROWS(KP)                                                                                            \
     launch_status(launch_kernel(decode_rows_kernel<TOP1, KP>, grid, block,                                              \
-                                sizeof(double) * N * KP + sizeof(int) * (KP + 1), stream, d_preds, d_mask, d_out, d_top1,  \
+                                sizeof(double) * N * KP + sizeof(int) * (KP + 4) + kRowGroups * kListBytes, stream, d_preds, d_mask, d_out, d_top1,  \
                                 d_score, d_status, G, K, N, S, static_cast<int>(C), sign_mode, nodes))
     switch ((K + 3) / 4) {
         case 1: return APPROXIFER_ROWS(4);
@@ -1017,7 +1035,7 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
         const dim3 tgrid(static_cast<unsigned>(tblocks)), tblock(kRowGroups * kRowLanes);
 #define APPROXIFER_TILES(KPV, CHUNK, UNAL)                                                                             \
     launch_status(launch_kernel(decode_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                                   \
-                                sizeof(double) * N * KPV + sizeof(int) * (KPV + 1) + kRowGroups * kWave, stream, d_preds,  \
+                                sizeof(double) * N * KPV + sizeof(int) * (KPV + 4) + kRowGroups * kListBytes, stream, d_preds,  \
                                 d_mask, d_out, d_status, tiles, static_cast<uint32_t>(chunks), K, N, S, C, sign_mode, nodes))
         switch (KP / 4) {
             case 1: return vec4 ? APPROXIFER_TILES(4, 8, false) : APPROXIFER_TILES(4, 8, true);
@@ -1077,8 +1095,8 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
         const dim3 tgrid(static_cast<unsigned>((G + kRowGroups / R - 1) / (kRowGroups / R))), tblock(kRowGroups * kRowLanes);
 #define APPROXIFER_TOP1_TILES(KPV, CHUNK, UNAL)                                                                        \
     launch_status(launch_kernel(decode_top1_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                              \
-                                sizeof(double) * (N + kRowGroups) * KPV + sizeof(int) * (kRowGroups * KPV + KPV + 1) +   \
-                                    kRowGroups * kWave,                                                                 \
+                                sizeof(double) * (N + kRowGroups) * KPV + sizeof(int) * (kRowGroups * KPV + KPV + 4) +   \
+                                    kRowGroups * kListBytes,                                                                 \
                                 stream, d_preds, d_mask, d_top1, d_score, d_status, G, static_cast<uint32_t>(chunks), R, K, \
                                 N, S, C, sign_mode, nodes))
         switch (KQ) {
