@@ -1168,16 +1168,6 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     const int lane = lane_id();
     const int c_ld = tid & (CW - 1);
 
-    // predictions: row slot u of this thread is row tid / 16 + u * (threads / 16) of the stacked [gpw][NW] tiles;
-    // a pass takes four rows per wave and there are gpw waves or more, so NW / 4 passes do
-    const int rows_per_pass = threads / CW;
-    float pf[NW / 4];
-#pragma unroll
-    for (int u = 0; u < NW / 4; ++u) {
-        const int R = tid / CW + u * rows_per_pass;
-        const int q = R / NW, r = R % NW;
-        pf[u] = (q < here && r < N && c_ld < C) ? preds[(static_cast<size_t>(g0 + q) * N + r) * C + c_ld] : 0.0f;
-    }
     if (wv < gpw) {                                       // N <= 48: one ballot reads a mask row
         const int q = wv;
         const bool b = q < here && lane < N && mask[(g0 + q) * N + lane] != 0;
@@ -1205,6 +1195,20 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     }
     if (tid >= threads - 16) hit[tid - (threads - 16)] = -1;
     __syncthreads();
+    // predictions: row slot u of this thread is row tid / 16 + u * (threads / 16) of the stacked [gpw][NW] tiles;
+    // a pass takes four rows per wave and there are gpw waves or more, so NW / 4 passes do.  Only rows of workers that
+    // answered are read; T is evaluated while they are on their way.  (Kept in registers until the first wave has
+    // factorised they cost it 16 to 45 registers; a mask byte per lane and row, to load ahead of the barrier: 20.4 us at
+    // K = 8, 2048 groups, and 69.6 at K = 12, 8192 groups, against 19.9 and 68.2 this way.)
+    const int rows_per_pass = threads / CW;
+    float pf[NW / 4];
+#pragma unroll
+    for (int u = 0; u < NW / 4; ++u) {
+        const int R = tid / CW + u * rows_per_pass;
+        const int q = R / NW, r = R % NW;
+        const bool there = q < gpw && ((bits[q] >> r) & 1ull) != 0ull;
+        pf[u] = (there && c_ld < C) ? preds[(static_cast<size_t>(g0 + q) * N + r) * C + c_ld] : 0.0f;
+    }
     for (int e = tid; e < 16 * NW; e += threads) {
         const int j = e / NW, i = e - j * NW;
         const bool in = j < K && i < N;
@@ -1216,7 +1220,7 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
     for (int u = 0; u < NW / 4; ++u) {
         const int R = tid / CW + u * rows_per_pass;
         const int q = R / NW, r = R % NW;
-        if (q < gpw) Ysh[(q * CW + c_ld) * YS + r] = ((bits[q] >> r) & 1ull) ? pf[u] : 0.0f;
+        if (q < gpw) Ysh[(q * CW + c_ld) * YS + r] = pf[u];
     }
     for (int e = tid; e < YS; e += threads) zeros[e] = 0.0f;
     if (!SHARED && wv == 0) {
