@@ -47,23 +47,21 @@ class ServingLoop:
         self.adv = torch.empty((G, max(A, 1)), dtype=torch.int32, device=dev)[:, :A]
         need = binding.approxifer_workspace_bytes(G, K, N, S, A, C) if A > 0 else 0
         self.workspace = torch.empty((need,), dtype=torch.uint8, device=dev) if need else binding.NO_WORKSPACE
-        self._views = None
+        self._kept = None
 
-    def _for_queries(self, Q):
-        """Views of the buffers for a stream of Q queries; those of the last Q are kept (slicing a dozen tensors takes as
-        long on the host as two of the calls below)."""
+    def _views(self, G):
+        """The first G groups of every buffer, for the calls of step() alone: what leaves step() is an object of its own, so
+        that a caller may do with it what tensors allow.  Those of the last G are kept (to build all of them takes a
+        sixth of a step on the host)."""
         bufs = (self.coded, self.preds, self.mask, self.count, self.out, self.top1, self.status, self.adv)
-        kept = self._views
-        if kept is not None and kept[0] == Q and all(map(operator.is_, kept[1], bufs)):
+        kept = self._kept
+        if kept is not None and kept[0] == G and all(map(operator.is_, kept[1], bufs)):
             return kept[2]
-        K, N, D, C = self.K, self.N, self.D, self.C
-        G = binding.approxifer_group_count(Q, K)
         coded, preds, mask, count, out, top1, status, adv = (t[:G] for t in bufs)
-        v = {"G": G, "coded": coded, "coded_rows": coded.view(G * N, D), "preds": preds, "pred_rows": preds.view(G * N, C),
-             "mask": mask, "count": count, "out": out, "top1": top1, "status": status, "adv": adv,
-             "values": out.view(G * K, C)[:Q], "classes": top1.view(G * K)[:Q]}
-        self._views = (Q, bufs, v)
-        return v
+        views = (coded, coded.view(G * self.N, self.D), preds, preds.view(G * self.N, self.C), mask, count,
+                 out, out.view(G * self.K, self.C), top1, top1.view(G * self.K), status, adv)
+        self._kept = (G, bufs, views)
+        return views
 
     def load(self, stream):
         """Copies a [Q, D] float32 stream (host or device tensor) into the query buffer; returns Q."""
@@ -83,15 +81,14 @@ class ServingLoop:
         adv [G, A], status [G] (0: decoded), groups G.
         """
         K, N, S, A = self.K, self.N, self.S, self.A
-        v = self._for_queries(Q)
-        G, preds, out, top1, status, adv = v["G"], v["preds"], v["out"], v["top1"], v["status"], v["adv"]
+        G = binding.approxifer_group_count(Q, K)
         groups = binding.approxifer_pad_last_group(self.queries, Q, K)            # [G, K, D] view, last group completed
-        coded = binding.approxifer_encode(groups, self.alpha, self.beta, coded=v["coded"])
-        v["pred_rows"].copy_(model(v["coded_rows"]))
+        coded, coded_rows, preds, pred_rows, mask, count, out, out_rows, top1, top1_rows, status, adv = self._views(G)
+        binding.approxifer_encode(groups, self.alpha, self.beta, coded=coded)
+        pred_rows.copy_(model(coded_rows.detach()))
         if tamper is not None:
-            tamper(preds)
-        mask, _ = binding.approxifer_wait_mask(arrival[:G], N - S, mask=v["mask"], count=v["count"])
-        values = v["values"]
+            tamper(preds.detach())
+        binding.approxifer_wait_mask(arrival[:G], N - S, mask=mask, count=count)
         if A > 0:
             binding.approxifer_decode_byzantine(preds, mask, self.alpha, self.beta, S, A, self.sign_mode, out=out, adv=adv,
                                                 status=status, workspace=self.workspace)
@@ -102,9 +99,9 @@ class ServingLoop:
         else:
             binding.approxifer_decode_top1(preds, mask, self.alpha, self.beta, S, self.sign_mode, top1=top1, status=status,
                                            want_score=False)
-            values = None
-        return {"values": values, "top1": v["classes"], "mask": mask, "adv": adv, "status": status, "groups": G,
-                "coded": coded, "preds": preds}
+        return {"values": out_rows[:Q] if A > 0 or want_values else None, "top1": top1_rows[:Q], "mask": mask.detach(),
+                "adv": adv.detach(), "status": status.detach(), "groups": G, "coded": coded.detach(),
+                "preds": preds.detach()}
 
 
 def exponential_arrivals(G, N, seed, device, slow_fraction=0.0):
