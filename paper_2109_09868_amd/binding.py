@@ -141,8 +141,10 @@ def _nodes(a) -> tuple:
 def _stream_handle(stream) -> int:
     if stream is None:
         import torch
-        # torch.cuda.current_stream().cuda_stream without the Stream object around it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # torch.cuda.current_stream().cuda_stream without the Stream object around it; not a documented name, so the
+        # documented way is there where it is missing
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
     return getattr(stream, "cuda_stream", stream)
 
 

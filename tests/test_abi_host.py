@@ -233,3 +233,18 @@ def test_header_is_plain_c_and_a_c_program_links_against_the_library(lib, tmp_pa
     text, ws = out[1].rsplit(None, 1)
     assert text == binding.strerror(-5)
     assert int(ws) == binding.approxifer_workspace_bytes(5, 8, 24, 4, 2, 1000)
+
+
+@pytest.mark.parametrize("short_cut", [True, False])
+def test_the_current_stream_is_found_with_and_without_torchs_undocumented_call(monkeypatch, short_cut):
+    import types
+    import torch
+    from paper_2109_09868_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4096))
+    if short_cut:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 4096 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._stream_handle(None) == (4099 if short_cut else 4096)
+    assert binding._stream_handle(17) == 17
