@@ -661,15 +661,14 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
 // ------------------------------------------------------------------------------------
 // The same for K <= 16, N <= 64 and more than sixteen classes: a lane owns four neighbouring classes, a tile is 64 classes
 // of a group, and a workgroup takes sixteen consecutive tiles of the batch, so that a row end leaves at most fifteen
-// lanes idle where a wave per (group, 256 classes) left up to 63 (100 classes: 7 of 32 against 39 of 64).  Here the rows
-// of missing workers are not read: the survivors' indices go through LDS (one row each), a lane has kTileChunk rows in
-// flight, and everything else, T above all, is evaluated while the mask is on its way.
+// lanes idle where a wave per (group, 256 classes) left up to 63 (100 classes: 7 of 32 against 39 of 64).  A lane has CHUNK
+// rows in flight; everything else, T above all, is evaluated while the mask is on its way.
 // UNAL: rows are only 4-byte aligned; the lane with a row's last partial vector moves it float by float.
 // 4096 groups of K = 8, 8 of 12 workers, 100 classes: 8.6 us with a wave per 256 classes, 7.1 us this way; 65536 groups
 // of 40 classes 88 and 40 us; 512 groups of K = 12, 12 of 20 workers, 1000 classes 13.4 and 11.3 us.
-// K = 9..12 with twelve rows in flight (two waves to a SIMD) is faster while one round of workgroups holds the launch
-// (8192 tiles), slower after that: 512 groups of 1000 classes 11.1 us against 12.9 with eight rows (three waves),
-// 1024 groups of 4000 classes 76.8 against 71.7.
+// Which calls come here: tiles_shape.  K = 9..12 with twelve rows in flight (two waves to a SIMD) is faster while one
+// round of workgroups holds the launch (8192 tiles), slower after that: 512 groups of 1000 classes 11.1 us against 12.9
+// with eight rows (three waves), 1024 groups of 4000 classes 76.8 against 71.7.
 constexpr int64_t kTilesOneRound = 8192;
 
 // acc[e][j] = sum over the survivors i of T[i][j] s_i y_ie, this lane's four classes e of the row at pg + class; den: in
@@ -750,24 +749,29 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     double acc[4][KP], den;
     tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, rows, S < 0, minus, T, acc, den);
     den = 1.0 / den;
-    float *og = out + static_cast<size_t>(g) * K * C + col;
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
         const double d = row_bcast_dyn(den, j);
-        double v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[e][j] * d;
-        if (hit[KP] != 0) {
+        for (int e = 0; e < 4; ++e) acc[e][j] *= d;
+    }
+    if (hit[KP] != 0) {                                     // before the first store: a load behind it waits for it too
+#pragma unroll
+        for (int j = 0; j < KP; ++j) {
             const int h = hit[j];
             if (good && h >= 0 && ((m >> h) & 1ull) != 0ull) {
                 const v4f yh = load_pred_vector<UNAL>(pg + static_cast<size_t>(h) * C, floats);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = static_cast<double>(yh[e]);   // waits here: behind the branch it would
-            }                                                                    // wait for the stores of every query
+                for (int e = 0; e < 4; ++e) acc[e][j] = static_cast<double>(yh[e]);
+            }
         }
+    }
+    float *og = out + static_cast<size_t>(g) * K * C + col;
+#pragma unroll
+    for (int j = 0; j < KP; ++j) {
         v4f f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = static_cast<float>(v[e]);
+        for (int e = 0; e < 4; ++e) f[e] = static_cast<float>(acc[e][j]);
         if (here && good && ok && j < K) {
             float *dst = og + static_cast<size_t>(j) * C;
             if (!UNAL) {
@@ -987,6 +991,30 @@ __global__ __launch_bounds__(kArgmaxWaves *kWave) void argmax_rows_kernel(const 
 
 bool rows_shape(int K, int N, int64_t C) { return K <= 32 && N <= kWave && C <= kRowLanes; }
 
+// Whether decode_tiles_kernel decodes the call (K <= 16, N <= 64).  Over 1900 shapes of 2 to 16 queries and 17 to 32000
+// classes, inputs in rotation, it was 2 to 11 % slower than a wave per 256 classes where it took them all; it gains
+//  - where most of that wave's lanes lie past the end of the row and groups abound: up to 100 classes, from 2048 groups
+//    (K = 8, 4096 groups of 100 classes 8.7 -> 7.2 us; 65536 groups of 40 classes 88 -> 40 us);
+//  - for K = 9..16 and a known number of survivors while one round of workgroups holds the launch (512 groups of K = 12,
+//    1000 classes 13.4 -> 10.7 us): 5 % on average from 1024 tiles on, where it loses 9 % beyond 8192 (84 groups of K = 9,
+//    16000 classes 21.4 and 26.7 us);
+//  - rows that are only 4-byte aligned are loaded float by float at their ends, by every sixteenth lane instead of every
+//    64th: worth it for up to 80 classes and many groups only (K = 4, 1024 groups of 1003 classes 10.1 and 14.5 us).
+bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
+    if (K > 16 || N > kWave) return false;
+    const int64_t vectors = (C + 3) / 4;
+    if (!vec4) return vectors <= 20 && G * K >= 32768;
+    const int64_t tiles = G * ((vectors + kRowLanes - 1) / kRowLanes);
+    return (vectors <= 25 && G >= 2048) || (K > 8 && S >= 0 && tiles >= 1024 && tiles <= kTilesOneRound);
+}
+// Whether decode_top1_tiles_kernel decides the call: all of them (0.76 of the time of a workgroup per group over 1600
+// shapes), but for long rows that are only 4-byte aligned with few queries to make up for their ends (K = 3, 7900 groups of
+// 750 classes 48.8 and 79.5 us; K = 8 from 4096 groups on 3 to 8 % slower).
+bool top1_tiles_shape(int K, int N, int64_t C, int64_t G, bool vec4) {
+    if (K > 16 || N > kWave) return false;
+    return vec4 || C <= 128 || K > 8 || (K > 4 && G < 4096);
+}
+
 template <bool TOP1>
 int run_rows(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1, float *d_score, int32_t *d_status,
              int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
@@ -1024,12 +1052,9 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
     int waves = KP / 4;
     if (waves > 4) waves = 4;
     const size_t lds = sizeof(double) * (static_cast<size_t>(S < 0 ? N : N - S) * KP + K + N) + sizeof(int) * (static_cast<size_t>(N) + 2);
-    const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
-    const int64_t tiles = G * chunks;
-    // .. but for K = 9..12 and long aligned rows beyond one round of workgroups the wave per 256 classes is a little
-    // faster (1024 groups of 4000 classes: 71.3 against 73.3 us; K = 16, 300 groups of 4096: 35.6 against 35.4)
-    const bool long_rows = KP == 12 && vec4 && C >= 2048 && tiles > kTilesOneRound;
-    if (K <= 16 && N <= kWave && !long_rows) {
+    if (tiles_shape(K, N, S, C, G, vec4)) {
+        const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
+        const int64_t tiles = G * chunks;
         const int64_t tblocks = (tiles + kRowGroups - 1) / kRowGroups;
         if (tblocks > 0x7fffffffLL || chunks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
         const dim3 tgrid(static_cast<unsigned>(tblocks)), tblock(kRowGroups * kRowLanes);
@@ -1041,14 +1066,14 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
             case 1: return vec4 ? APPROXIFER_TILES(4, 8, false) : APPROXIFER_TILES(4, 8, true);
             case 2: return vec4 ? APPROXIFER_TILES(8, 8, false) : APPROXIFER_TILES(8, 8, true);
             case 3:
-                if (tiles <= kTilesOneRound) return vec4 ? APPROXIFER_TILES(12, 12, false) : APPROXIFER_TILES(12, 12, true);
-                return vec4 ? APPROXIFER_TILES(12, 8, false) : APPROXIFER_TILES(12, 8, true);
+                if (!vec4) return APPROXIFER_TILES(12, 8, true);
+                return tiles <= kTilesOneRound ? APPROXIFER_TILES(12, 12, false) : APPROXIFER_TILES(12, 8, false);
             default: return vec4 ? APPROXIFER_TILES(16, 8, false) : APPROXIFER_TILES(16, 8, true);
         }
 #undef APPROXIFER_TILES
     }
-    // the same with up to 64 of more than 64 workers: one wave per 256 classes with all K accumulator rows (capping its
-    // residency as in the encoder changes nothing: 4 to 12 waves per CU +-3 %)
+    // all other calls of up to 16 queries and 64 survivors: one wave per 256 classes with all K accumulator rows (capping
+    // its residency as in the encoder changes nothing: 4 to 12 waves per CU +-3 %)
     const int most_survivors = S < 0 ? N : N - S;
     if (K <= 16 && most_survivors <= 64 && C >= 4) {
         const int64_t sCv = (C + 3) / 4;                  // counts a partial last vector
@@ -1088,7 +1113,7 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const int KQ = KP / 4;
     const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;     // .. with very many classes: the split below
-    if (K <= 16 && N <= kWave && !few_groups) {
+    if (top1_tiles_shape(K, N, C, G, vec4) && !few_groups) {
         const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
         int R = 1;
         while (R < kRowGroups && R < chunks) R *= 2;

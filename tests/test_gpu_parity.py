@@ -568,6 +568,63 @@ def test_decode_top1_of_predictions_that_are_not_numbers(gpu, K, N, S, C, exact)
     assert not np.any(score[none] > -np.inf)
 
 
+@pytest.mark.parametrize("K,N,S,C,G", [
+    (8, 12, 4, 100, 2048), (8, 12, 4, 100, 2047), (8, 12, 4, 104, 2048),     # short rows: from 2048 groups on
+    (16, 24, -1, 40, 2050), (6, 9, 2, 20, 2100),
+    (4, 7, 1, 77, 8192), (6, 9, -1, 78, 5462), (8, 9, 1, 79, 4095),          # rows that are only 4-byte aligned
+    (10, 17, 7, 256, 256), (10, 17, 7, 256, 255), (15, 21, 6, 192, 400),     # K = 9..16: from 1024 tiles on
+    (12, 20, 8, 1000, 512), (12, 20, 8, 1000, 513), (14, 25, 11, 108, 600),  # .. up to 8192
+])
+def test_decode_tiles_on_both_sides_of_their_rule(gpu, K, N, S, C, G):
+    # Query nodes that are worker nodes (6 of 9, 10 of 17, 15 of 21, ..), straggler counts off the masks, groups without
+    # any answer and with one too many; answers that did not come hold NaN.  Forty groups and the last against the oracle.
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(7 * K + C + G)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    order = rng.random((G, N)).argsort(1).argsort(1)
+    late = np.full((G, 1), S) if S >= 0 else rng.integers(0, N - 1, (G, 1))
+    mask = (order >= late).astype(np.uint8)
+    mask[1] = 0
+    if S > 0:
+        mask[2] = 1
+    Y = rng.standard_normal((G, N, C)).astype(np.float32)
+    poisoned = np.where(mask[:, :, None] != 0, Y, np.float32(np.nan))
+    out = torch.full((G, K, C), -3.0, dtype=torch.float32, device=dev)
+    out, st = binding.approxifer_decode(torch.from_numpy(poisoned).to(dev), torch.from_numpy(mask).to(dev), alpha, beta, S, 1, out=out)
+    out, st = out.cpu().numpy(), st.cpu().numpy()
+    some = np.unique(np.concatenate([[0, 1, 2, 3, G - 1], rng.integers(0, G, 36)]))
+    ref, st_ref = orc.decode(Y[some], mask[some], alpha, beta, S, 1)
+    assert np.array_equal(st[some], st_ref) and st[1] == 1 and (S <= 0 or st[2] == 1)
+    good = st_ref == 0
+    assert np.all(out[some][~good] == -3.0) and np.isfinite(out[st == 0]).all()
+    assert group_err(out[some][good], ref[good]).max() <= TOL
+
+
+@pytest.mark.parametrize("K,N,S,C,G", [
+    (8, 12, 4, 1100, 40), (10, 17, 7, 1283, 33), (16, 24, -1, 1283, 21),     # tiles: a second pass over the columns
+    (15, 21, 6, 68, 70), (6, 9, -1, 19, 90), (3, 6, 1, 126, 50),
+    (4, 7, 1, 130, 60), (4, 7, 1, 132, 60), (3, 5, 2, 750, 90),              # K <= 4: 4-byte rows longer than 128 leave the tiles
+    (7, 13, 6, 133, 4095), (7, 13, 6, 133, 4096),
+])
+def test_decode_top1_tiles_on_both_sides_of_their_rule(gpu, K, N, S, C, G):
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(11 * K + C + G)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    order = rng.random((G, N)).argsort(1).argsort(1)
+    late = np.full((G, 1), S) if S >= 0 else rng.integers(0, N - 1, (G, 1))
+    mask = (order >= late).astype(np.uint8)
+    mask[1] = 0
+    Y = rng.standard_normal((G, N, C)).astype(np.float32)
+    Y[0, mask[0].nonzero()[0], C - 1] += 50.0             # the last class wins: every survivor says so
+    poisoned = np.where(mask[:, :, None] != 0, Y, np.float32(np.nan))
+    top1, score, st = binding.approxifer_decode_top1(torch.from_numpy(poisoned).to(dev), torch.from_numpy(mask).to(dev), alpha, beta, S, 1)
+    top1, score, st = (t.cpu().numpy() for t in (top1, score, st))
+    some = np.unique(np.concatenate([[0, 1, 2, G - 1], rng.integers(0, G, 36)]))
+    ref = orc.decode_top1(Y[some], mask[some], alpha, beta, S, 1)
+    assert st[1] == 1 and np.all(top1[1] == -1) and np.all(top1[0] == C - 1)
+    _assert_top1(Y[some], mask[some], alpha, beta, S, 1, top1[some], score[some], st[some], *ref)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
