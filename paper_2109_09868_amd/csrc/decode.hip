@@ -462,23 +462,36 @@ __global__ __launch_bounds__(256) void decode_top1_stream_kernel(const float *__
 // what the row kernels below share: a 16-lane row works on one group, N <= 64
 // ------------------------------------------------------------------------------------
 // T[i][j] = 1 / (alpha_j - beta_i), row stride KP, zero for j >= K and where the two nodes are one; hit[j] = the worker
-// whose node is query node j, or -1, hit[KP] = whether there is one.  By the whole workgroup; ends with a barrier.
+// whose node is query node j, or -1, hit[KP] = whether there is one.  By the whole workgroup, one entry per thread from
+// nodes that begin() has sent for; ends with a barrier.
 template <int KP>
-__device__ __forceinline__ void node_table(const Nodes &nodes, int K, int N, double *T, int *hit) {
-    if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
-    __syncthreads();
-    for (int e = threadIdx.x; e < N * KP; e += blockDim.x) {
-        const int i = e / KP, j = e % KP;
-        const double d = nodes.alpha[j < K ? j : 0] - nodes.beta[i];
-        const bool same = j < K && d == 0.0;
-        if (same) {                                         // nodes are distinct: one worker at most
-            hit[j] = i;
-            hit[KP] = 1;
-        }
-        T[e] = (j < K && !same) ? 1.0 / d : 0.0;
+struct NodeTable {
+    double alpha, beta;                                     // of entry threadIdx.x
+    __device__ __forceinline__ void begin(const Nodes &nodes, int K, int N, int *hit) {
+        const int e = threadIdx.x < N * KP ? threadIdx.x : 0;
+        alpha = nodes.alpha[e % KP < K ? e % KP : 0];
+        beta = nodes.beta[e / KP];
+        if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
     }
-    __syncthreads();
-}
+    __device__ __forceinline__ void finish(const Nodes &nodes, int K, int N, double *T, int *hit) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < N * KP; e += blockDim.x) {
+            const int i = e / KP, j = e % KP;
+            if (e >= static_cast<int>(blockDim.x)) {
+                alpha = nodes.alpha[j < K ? j : 0];
+                beta = nodes.beta[i];
+            }
+            const double d = alpha - beta;
+            const bool same = j < K && d == 0.0;
+            if (same) {                                     // nodes are distinct: one worker at most
+                hit[j] = i;
+                hit[KP] = 1;
+            }
+            T[e] = (j < K && !same) ? 1.0 / d : 0.0;
+        }
+        __syncthreads();
+    }
+};
 // The mask row of this lane's group, byte lane % 16 + 16 p in b[p]; lanes past N load byte 0 (four loads that nothing
 // waits for, instead of four branches with a load in each).
 struct MaskBytes {
@@ -541,42 +554,42 @@ __device__ __forceinline__ int most_survivors_of_wave(int nF) {
 // 16384 groups of K = 8, N = 9, ten classes, top-1: 13.1 us a kernel with a wave per group, 7.2 us this way.
 constexpr int kRowGroups = 16;
 constexpr int kRowChunkSmall = 16;      // prediction rows in flight
+constexpr int64_t kRowsSplitGroups = 2048;
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-template <bool TOP1, int KP>
+template <bool TOP1, int KP, int QS>
 __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
     int32_t *__restrict__ top1, float *__restrict__ score, int32_t *__restrict__ status, int64_t G, int K, int N,
     int S, int C, int sign_mode, const Nodes nodes) {
-    constexpr int kRegs = (KP + kRowLanes - 1) / kRowLanes;  // T and denominators of query lane + 16 h in register h
+    constexpr int KQ = KP / QS;                              // queries of a row: j0 ..
+    constexpr int kRegs = (KQ + kRowLanes - 1) / kRowLanes;  // T and denominators of query j0 + lane + 16 h in register h
     extern __shared__ __align__(16) double T[];             // [N][KP] | int hit[KP] | int any_hit | pad | uint8 F[16][80]
     int *hit = reinterpret_cast<int *>(T + N * KP);
     const int c = threadIdx.x % kRowLanes;
     const int row = threadIdx.x / kRowLanes;
     uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 4) + row * kListBytes;
-    const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * kRowGroups + row;
+    const int64_t g_raw = static_cast<int64_t>(blockIdx.x) * (kRowGroups / QS) + row / QS;
+    const int j0 = row % QS * KQ;
     const bool here = g_raw < G;
     const int64_t g = here ? g_raw : G - 1;                 // rows past the last group work on it and store nothing
 
     const MaskBytes answered = load_mask_row(mask + g * N, N);
-    node_table<KP>(nodes, K, N, T, hit);                    // while the mask is on its way
+    NodeTable<KP> table;
+    table.begin(nodes, K, N, hit);
     const unsigned long long m = row_survivors(answered, N);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
-    if (c == 0 && here && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    if (c == 0 && row % QS == 0 && here && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
     list_survivors(m, F);
     const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
     const uint32_t by_index = sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK ? 0u : 1u;
     const float *pg = preds + static_cast<size_t>(g) * N * C + (c < C ? c : 0);
 
-    double acc[KP], den[kRegs];
-#pragma unroll
-    for (int j = 0; j < KP; ++j) acc[j] = 0.0;
-#pragma unroll
-    for (int h = 0; h < kRegs; ++h) den[h] = 0.0;
-    for (int r0 = 0; r0 < rows; r0 += kRowChunkSmall) {
-        const v4u f = *reinterpret_cast<const v4u *>(F + r0);
-        float y[kRowChunkSmall];
+    v4u f;
+    float y[kRowChunkSmall];
+    const auto load_chunk = [&](int r0) {
+        f = *reinterpret_cast<const v4u *>(F + r0);
 #pragma unroll
         for (int u = 0; u < kRowChunkSmall; ++u) y[u] = 0.0f;
 #pragma unroll
@@ -586,6 +599,17 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
                 for (int u = q; u < q + 4; ++u) y[u] = pg[static_cast<int>((f[u / 4] >> (8 * (u % 4))) & 0xffu) * C];
             }
         }
+    };
+    load_chunk(0);
+    table.finish(nodes, K, N, T, hit);                      // while the first predictions are on their way
+
+    double acc[KQ], den[kRegs];
+#pragma unroll
+    for (int j = 0; j < KQ; ++j) acc[j] = 0.0;
+#pragma unroll
+    for (int h = 0; h < kRegs; ++h) den[h] = 0.0;
+    for (int r0 = 0; r0 < rows; r0 += kRowChunkSmall) {
+        if (r0 > 0) load_chunk(r0);
 #pragma unroll
         for (int u = 0; u < kRowChunkSmall; ++u) {
             if (r0 + u < rows) {
@@ -598,22 +622,22 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
 #pragma unroll
                 for (int h = 0; h < kRegs; ++h) {
                     const int j = h * kRowLanes + c;
-                    t[h] = T[w * KP + (j < KP ? j : 0)];
+                    t[h] = T[w * KP + j0 + (j < KQ ? j : 0)];
                     den[h] = fma(s, t[h], den[h]);
                 }
-                row_outer<0, 0, (KP < kRowLanes ? KP : kRowLanes)>(acc, t[0], sy);
-                if constexpr (kRegs > 1) row_outer<kRowLanes, 0, KP - kRowLanes>(acc, t[1], sy);
+                row_outer<0, 0, (KQ < kRowLanes ? KQ : kRowLanes)>(acc, t[0], sy);
+                if constexpr (kRegs > 1) row_outer<kRowLanes, 0, KQ - kRowLanes>(acc, t[1], sy);
             }
         }
     }
 #pragma unroll
     for (int h = 0; h < kRegs; ++h) den[h] = 1.0 / den[h];
 #pragma unroll
-    for (int j = 0; j < KP; ++j) acc[j] *= row_bcast_dyn(den[j / kRowLanes], j % kRowLanes);
+    for (int j = 0; j < KQ; ++j) acc[j] *= row_bcast_dyn(den[j / kRowLanes], j % kRowLanes);
     if (hit[KP] != 0) {
 #pragma unroll
-        for (int j = 0; j < KP; ++j) {
-            const int h = hit[j];
+        for (int j = 0; j < KQ; ++j) {
+            const int h = hit[j0 + j];
             if (h >= 0 && ((m >> h) & 1ull) != 0ull) acc[j] = static_cast<double>(pg[h * C]);
         }
     }
@@ -621,8 +645,8 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
         float *og = out + static_cast<size_t>(g) * K * C + c;
         if (here && good && c < C) {
 #pragma unroll
-            for (int j = 0; j < KP; ++j)
-                if (j < K) og[j * C] = static_cast<float>(acc[j]);
+            for (int j = 0; j < KQ; ++j)
+                if (j0 + j < K) og[(j0 + j) * C] = static_cast<float>(acc[j]);
         }
         return;
     }
@@ -632,7 +656,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
     int best_c[kRegs];
     double best_v[kRegs];
 #pragma unroll
-    for (int j = 0; j < KP; ++j) {
+    for (int j = 0; j < KQ; ++j) {
         const double v = c < C ? acc[j] : -__builtin_inf();
         double b = v;
         b = __builtin_fmax(b, dpp_exchange<kDppQuadXor1>(b));
@@ -649,9 +673,9 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
 #pragma unroll
     for (int h = 0; h < kRegs; ++h) {
         const int j = h * kRowLanes + c;
-        if (here && good && j < K) {
-            top1[g * K + j] = best_c[h];
-            if (score != nullptr) score[g * K + j] = static_cast<float>(best_v[h]);
+        if (here && good && j < KQ && j0 + j < K) {
+            top1[g * K + j0 + j] = best_c[h];
+            if (score != nullptr) score[g * K + j0 + j] = static_cast<float>(best_v[h]);
         }
     }
 }
@@ -733,7 +757,9 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     const uint32_t chunk = static_cast<uint32_t>(tile - g * chunks);
 
     const MaskBytes answered = load_mask_row(mask + g * N, N);
-    node_table<KP>(nodes, K, N, T, hit);
+    NodeTable<KP> table;
+    table.begin(nodes, K, N, hit);
+    table.finish(nodes, K, N, T, hit);
     const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
@@ -808,7 +834,9 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
     const int64_t g = here ? g_raw : G - 1;
 
     const MaskBytes answered = load_mask_row(mask + g * N, N);
-    node_table<KP>(nodes, K, N, T, hit);
+    NodeTable<KP> table;
+    table.begin(nodes, K, N, hit);
+    table.finish(nodes, K, N, T, hit);
     const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
@@ -1015,16 +1043,28 @@ bool top1_tiles_shape(int K, int N, int64_t C, int64_t G, bool vec4) {
     return vec4 || C <= 128 || K > 8 || (K > 4 && G < 4096);
 }
 
+template <bool TOP1, int KP, int QS>
+int run_rows_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1, float *d_score,
+                   int32_t *d_status, int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode,
+                   hipStream_t stream) {
+    constexpr int kGroups = kRowGroups / QS;
+    const int64_t blocks = (G + kGroups - 1) / kGroups;
+    if (blocks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    return launch_status(launch_kernel(decode_rows_kernel<TOP1, KP, QS>, dim3(static_cast<unsigned>(blocks)),
+                                       dim3(kRowGroups * kRowLanes),
+                                       sizeof(double) * N * KP + sizeof(int) * (KP + 4) + kRowGroups * kListBytes, stream, d_preds,
+                                       d_mask, d_out, d_top1, d_score, d_status, G, K, N, S, static_cast<int>(C), sign_mode,
+                                       nodes));
+}
+
 template <bool TOP1>
 int run_rows(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1, float *d_score, int32_t *d_status,
              int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
-    const int64_t blocks = (G + kRowGroups - 1) / kRowGroups;
-    if (blocks > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kRowGroups * kRowLanes);
 #define APPROXIFER_ROWS(KP)                                                                                            \
-    launch_status(launch_kernel(decode_rows_kernel<TOP1, KP>, grid, block,                                              \
-                                sizeof(double) * N * KP + sizeof(int) * (KP + 4) + kRowGroups * kListBytes, stream, d_preds, d_mask, d_out, d_top1,  \
-                                d_score, d_status, G, K, N, S, static_cast<int>(C), sign_mode, nodes))
+    (G <= kRowsSplitGroups ? run_rows_shape<TOP1, KP, 4>(d_preds, d_mask, d_out, d_top1, d_score, d_status, G, K, N, S, C,    \
+                                                         nodes, sign_mode, stream)                                      \
+                           : run_rows_shape<TOP1, KP, 1>(d_preds, d_mask, d_out, d_top1, d_score, d_status, G, K, N, S, C,    \
+                                                         nodes, sign_mode, stream))
     switch ((K + 3) / 4) {
         case 1: return APPROXIFER_ROWS(4);
         case 2: return APPROXIFER_ROWS(8);

@@ -625,6 +625,28 @@ def test_decode_top1_tiles_on_both_sides_of_their_rule(gpu, K, N, S, C, G):
     _assert_top1(Y[some], mask[some], alpha, beta, S, 1, top1[some], score[some], st[some], *ref)
 
 
+@pytest.mark.parametrize("K,N,S,C", [(2, 3, 1, 10), (4, 7, 1, 16), (7, 13, 3, 1), (8, 9, 1, 10), (10, 17, -1, 10), (12, 28, 4, 3),
+                                     (16, 33, 0, 2), (20, 41, 21, 5), (32, 64, 12, 2)])
+def test_decode_small_classes_four_rows_or_one_to_a_group(gpu, K, N, S, C):
+    # Up to 2048 groups a group's queries are split over four rows of lanes: the same bits either way.
+    torch, binding, dev = gpu
+    G = 2300
+    rng = np.random.default_rng(K * N + C)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    order = rng.random((G, N)).argsort(1).argsort(1)
+    late = np.full((G, 1), S) if S >= 0 else rng.integers(0, N - 1, (G, 1))
+    mask = (order >= late).astype(np.uint8)
+    mask[3] = 0
+    Y = np.where(mask[:, :, None] != 0, rng.standard_normal((G, N, C)), np.nan).astype(np.float32)
+    Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
+    whole = binding.approxifer_decode(Yd, md, alpha, beta, S, 1) + binding.approxifer_decode_top1(Yd, md, alpha, beta, S, 1)
+    for n in (1, 2048):
+        part = binding.approxifer_decode(Yd[:n], md[:n], alpha, beta, S, 1) + binding.approxifer_decode_top1(Yd[:n], md[:n], alpha, beta, S, 1)
+        for a, b in zip(whole, part):
+            assert np.array_equal(a[:n].cpu().numpy(), b.cpu().numpy())
+    assert whole[1][3] == 1 and torch.all(whole[1][torch.arange(G, device=dev) != 3] == 0)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
