@@ -1004,8 +1004,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
 // that class slots are filled across groups (ten classes: four groups fill ten rounds where each alone needs three,
 // twelve slots for ten classes).  Rows are workers, not survivors: the predictions are staged as they lie, with zeros
 // for missing answers, all groups use one table of powers, and a missing worker is a zero column of its group's U.
-// U comes from the call's one factorisation (SHARED: no stragglers, see full_basis_kernel) or from the first wave, which
-// factorises the workgroup's groups side by side, a 16-lane row each.
+// U comes from the call's one factorisation (SHARED: no stragglers, see full_basis_kernel; without a workspace the first
+// wave forms the same one, bit for bit) or from the first wave, which factorises the workgroup's groups side by side, a
+// 16-lane row each.
 // The decode at the end is one product on the float64 matrix cores per group: with T[j][i] = 1 / (alpha_j - beta_i),
 // which depends on the nodes only, and s_i = the alternating sign of worker i, 0 if it does not count,
 //     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i):
@@ -1082,10 +1083,10 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         if (b && good) avail[q * NW + __popcll(m & ((1ull << lane) - 1ull))] = lane;
         votes[q * kWave + lane] = 0;
     }
-    if (SHARED) {
+    if (SHARED && full_basis != nullptr) {
         basis_from_workspace<NB, RM, HOMOG>(Ush, full_basis);
     } else {
-        for (int e = tid; e < gpw * kBasis; e += threads) Ush[e] = 0.0;
+        for (int e = tid; e < (SHARED ? 1 : gpw) * kBasis; e += threads) Ush[e] = 0.0;
     }
     if (tid < NW) {
         const double x = tid < N ? nodes.beta[tid] : 0.0;
@@ -1125,6 +1126,9 @@ __global__ __launch_bounds__(kPackedWaves * kWave) __attribute__((amdgpu_waves_p
         if (q < gpw) Ysh[(q * CW + c_ld) * YS + r] = pf[u];
     }
     for (int e = tid; e < YS; e += threads) zeros[e] = 0.0f;
+    if (SHARED && full_basis == nullptr && wv == 0) {
+        if constexpr (NB == NW) shared_complement_basis<NB, RM, HOMOG>(Pw, N, M, Ush, Ush + kQ1, Ush + kRv);
+    }
     if (!SHARED && wv == 0) {
         const int q = lane / kClsLanes < gpw ? lane / kClsLanes : 0;
         const int n = lane / kClsLanes < gpw ? static_cast<int>(__popcll(bits[q])) : 0;
@@ -1840,12 +1844,13 @@ int run_packed_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, 
                                        nodes));
 }
 
-// basis: the call's shared factorisation, for S = 0 only (a group whose mask is not full is bad then); else null.
+// basis: the call's shared factorisation, or null.  S = 0 (a group whose mask is not full is bad then): all groups have it,
+// whether it comes from the workspace or not, so that a workspace changes no bit.
 template <int NB, int RM, bool HOMOG>
 int run_packed(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
                int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
                hipStream_t stream) {
-    if (basis != nullptr)
+    if (S == 0)
         return run_packed_shape<NB, RM, NB, true, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
                                                          sign_mode, basis, stream);
     if (N <= NB)

@@ -889,6 +889,30 @@ def test_byzantine_no_stragglers_groups_share_one_factorisation(gpu, K, A, N, C,
     assert group_err(out[good], ref[good]).max() <= TOL
 
 
+@pytest.mark.parametrize("K,A,N,C", [(12, 2, 28, 10), (8, 2, 20, 10), (6, 2, 18, 3), (12, 3, 32, 15), (13, 3, 33, 10), (15, 1, 40, 10),
+                                     (6, 2, 32, 7), (8, 2, 20, 16), (12, 2, 28, 40)])
+@pytest.mark.parametrize("entry", ["approxifer_decode_byzantine", "approxifer_decode_byzantine_homogeneous"])
+def test_byzantine_same_bits_with_and_without_workspace_where_picks_hang_on_rounding(gpu, K, A, N, C, entry):
+    # Fewer liars than A, none at all, softmax answers: which innocent workers go is decided by the last bits of the fits,
+    # so that a factorisation that differs in rounding between the two ways shows up as another located set.
+    torch, binding, dev = gpu
+    decode = getattr(binding, entry)
+    G = 300 if entry == "approxifer_decode_byzantine" else 60
+    rng = np.random.default_rng(K + C)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    Y = orc.encode(rng.uniform(0, 1, (G, K, 32)), alpha, beta) @ (rng.standard_normal((32, C)) / 6)
+    one = Y.copy()
+    one[:, 0] += 5 * rng.standard_normal((G, C))
+    soft = np.exp(3 * Y) / np.exp(3 * Y).sum(-1, keepdims=True)
+    md = torch.ones((G, N), dtype=torch.uint8, device=dev)
+    for data in (Y, one, soft, rng.standard_normal(Y.shape)):
+        Yd = torch.from_numpy(data.astype(np.float32)).to(dev)
+        with_ws = decode(Yd, md, alpha, beta, 0, A, 1)
+        without = decode(Yd, md, alpha, beta, 0, A, 1, workspace=binding.NO_WORKSPACE)
+        for a, b in zip(with_ws, without):
+            assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
 @pytest.mark.parametrize("K,N,S,C,G", [
     (1, 2, 0, 1, 1), (4, 16, 3, 16, 17), (5, 17, 4, 3, 33), (6, 9, 2, 10, 16), (8, 9, 1, 10, 257), (12, 28, 9, 15, 5),
     (16, 33, 15, 2, 31), (17, 48, 12, 5, 18), (24, 64, 30, 16, 3), (32, 64, 0, 7, 15), (32, 48, 12, 2, 40), (9, 32, -1, 10, 50),
