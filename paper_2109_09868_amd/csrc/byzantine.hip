@@ -1804,9 +1804,16 @@ Carved carve_workspace(void *d_workspace, size_t bytes, size_t need_basis, size_
 constexpr int kNoFit = 1;
 
 // Whether decode_byzantine_packed_kernel takes the call: one staged tile of fifteen class columns and the column of the
-// denominators, a row of U per lane of a 16-lane row.
-bool packed_domain(int N, int n, int M, int64_t C) {
-    return C <= kClsLanes - 1 && N <= 48 && M <= kProjMaxM && n - M <= kProjMaxM;
+// denominators, and a factorisation of the workgroup's groups side by side (a row of U per lane of a 16-lane row) or, without
+// stragglers, of one node set for all of them.  Its rows are workers, so that it works on rows of missing workers too: up
+// to four more than the tile has it is the faster one throughout; with more, only Algorithm 2 from 2048 groups and tiles of
+// 24 rows on (against a workgroup per group; K = 12, 28 of 46 workers, 4096 groups of 12 classes 69 and 86 us, Algorithm 1
+// never: K = 10, 24 of 33, 650 and 577 us; K = 2, 6 of 26, 4096 groups, Algorithm 2: 36 and 25 us).
+bool packed_domain(int NB, int RM, bool homogeneous, int64_t G, int N, int S, int M, int64_t C) {
+    if (C > kClsLanes - 1 || M > kProjMaxM) return false;
+    if (S == 0 && N <= NB && !homogeneous) return true;
+    if (RM > kProjMaxM || N > 48) return false;
+    return N <= NB + 4 || (!homogeneous && NB >= 24 && G > 2048);
 }
 // Groups per workgroup: one while the chip holds them all at once (five workgroups to each of 256 CUs), where spreading
 // the classes over waves shortens the chain of a group; then as many as keep the launch at one round of workgroups.
@@ -1853,15 +1860,18 @@ int run_packed(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
     if (S == 0)
         return run_packed_shape<NB, RM, NB, true, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
                                                          sign_mode, basis, stream);
-    if (N <= NB)
-        return run_packed_shape<NB, RM, NB, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                          sign_mode, nullptr, stream);
-    if constexpr (NB < 48) {
-        if (N <= NB + 4)
-            return run_packed_shape<NB, RM, NB + 4, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C,
-                                                                  nodes, sign_mode, nullptr, stream);
-        return run_packed_shape<NB, RM, 48, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
-                                                          sign_mode, nullptr, stream);
+    if constexpr (RM <= kProjMaxM) {
+        if (N <= NB)
+            return run_packed_shape<NB, RM, NB, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, nodes,
+                                                              sign_mode, nullptr, stream);
+        if constexpr (NB < 48) {
+            if (N <= NB + 4)
+                return run_packed_shape<NB, RM, NB + 4, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A,
+                                                                      C, nodes, sign_mode, nullptr, stream);
+        }
+        if constexpr (NB >= 24 && NB < 48 && !HOMOG)
+            return run_packed_shape<NB, RM, 48, false, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C,
+                                                              nodes, sign_mode, nullptr, stream);
     }
     return APPROXIFER_ERR_LIMIT;                          // not inside packed_domain
 }
@@ -1888,12 +1898,12 @@ int run_proj(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
     const size_t lds = fixed + p.nw * hom_wave;
     if (lds > kBudget) return HOMOG ? kNoFit : APPROXIFER_ERR_LIMIT;   // Algorithm 2: cannot happen inside the domain
     if (G * p.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    const bool packed = RM <= kProjMaxM && packed_domain(N, n_cap, M, C);
+    const bool packed = packed_domain(NB, RM, HOMOG, G, N, S, M, C);
     if (ws.basis != nullptr && !(packed && S != 0)) {
         const hipError_t e = launch_kernel(full_basis_kernel<NB, RM, HOMOG>, dim3(1), dim3(kWave), 0, stream, ws.basis, N, M, nodes);
         if (e != hipSuccess) return APPROXIFER_ERR_LAUNCH;
     }
-    if constexpr (RM <= kProjMaxM) {
+    if constexpr (RM <= kProjMaxM || !HOMOG) {
         if (packed)
             return run_packed<NB, RM, HOMOG>(d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n_cap, A, static_cast<int>(C), nodes,
                                       sign_mode, S == 0 ? ws.basis : nullptr, stream);

@@ -955,6 +955,8 @@ def test_decode_small_classes_sixteen_groups_to_a_workgroup(gpu, K, N, S, C, G, 
     (8, 2, 9, 30, 15),      # many more workers than answer; the most classes a staged tile takes
     (2, 1, 3, 9, 1), (3, 1, 38, 48, 2), (6, 2, 4, 21, 7), (12, 2, 4, 32, 4), (14, 2, 1, 33, 10), (15, 1, 5, 37, 3),
     (6, 1, 2, 17, 16),      # one class too many for the tile: the workgroup-per-group kernel
+    (2, 1, 20, 26, 12), (8, 2, 19, 44, 10), (12, 2, 12, 40, 10),     # many more workers than answer: by rule one or the other
+    (15, 1, 0, 40, 10), (4, 2, 0, 30, 7),                            # no stragglers, more rows of U than a row of lanes
     (6, 2, -1, 24, 10),     # straggler counts read off the masks
 ])
 @pytest.mark.parametrize("locator", [orc.LOCATOR_ALGORITHM_2, orc.LOCATOR_ALGORITHM_1])
