@@ -144,7 +144,7 @@ int approxifer_decode(const float *d_preds, const uint8_t *d_mask, float *d_out,
  * Location, per class c = 0..C-1 (Algorithm 2): with M = K + A and x_i = beta_i,
  * y_i = d_preds[g][i][c] for the available i, find P (degree M-1) and
  * Q = 1 + Q_1 x + .. + Q_{M-1} x^{M-1} minimising sum_i (P(x_i) - y_i Q(x_i))^2
- * (ordinary least squares, float64 Householder QR), set a_i = Q(x_i), and note the A
+ * (ordinary least squares, orthogonal elimination in float64), set a_i = Q(x_i), and note the A
  * workers of smallest |a_i| (equal magnitudes: smaller worker index first).  The A workers
  * noted most often over the C classes (equal counts: smaller worker index first) are the
  * adversaries.
@@ -224,7 +224,7 @@ int approxifer_decode_byzantine_static(const float *d_preds, const uint8_t *d_ma
  * M = K + A, P and Q both of degree M-1, the coefficient vector (P_0..P_{M-1}, Q_0..Q_{M-1})
  * is the unit vector minimising sum_i (P(x_i) - y_i Q(x_i))^2 over the available workers: the
  * right singular vector of the smallest singular value of the n x 2M matrix of the
- * homogeneous system (float64 Householder QR, then inverse iteration on the triangular
+ * homogeneous system (orthogonal elimination in float64, then inverse iteration on the triangular
  * factor and, for a class whose iteration does not settle, one-sided Jacobi rotations
  * until every pair of its columns is orthogonal to rounding).  a_i = Q(x_i) is
  * defined up to one factor, which the order of the |a_i| does not see.  Unlike Algorithm 2

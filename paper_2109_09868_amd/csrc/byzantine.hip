@@ -1,5 +1,5 @@
 // ApproxIFER Byzantine decoder for gfx950: Algorithm 2 (error locator) followed by the decoder of
-// Section 3, "ApproxIFER Decoding", one workgroup per group.
+// Section 3, "ApproxIFER Decoding".
 //
 // Algorithm 2 fits, per class c, polynomials P (degree M-1) and Q (degree M-1, Q_0 = 1), M = K+A, to
 //     P(x_r) - y_rc Q(x_r) = 0        over the n available workers (x_r their nodes),
@@ -7,29 +7,30 @@
 // returns the A most voted workers.  The system is  V p + C_c q = y_c  with V the n x M Vandermonde
 // matrix of the nodes and C_c = -diag(y_c) V[:, 1:].
 //
-// Two kernels compute the same thing:
+// Three kernels compute the same thing:
 //
-//  * decode_byzantine_proj_kernel (K+A <= 16, at most 48 available workers, n-M <= 32).  V is the
-//    same for every class of a group, so its Householder QR is done ONCE per group, by one wave
-//    with one lane per column of [V | I] held in registers (pivot columns travel by v_readlane):
-//    that leaves U = the last n-M rows of Q^T, an orthonormal basis of range(V)'s complement, in
-//    LDS.  Eliminating p exactly, class c only has to solve the (n-M) x (M-1) problem
+//  * decode_byzantine_proj_kernel (K+A <= 16, at most 48 available workers, n-M <= 32), one workgroup per
+//    group.  V is the same for every class of a group, so its Householder QR is done ONCE per group,
+//    by one wave with one lane per column of [V | I] held in registers (pivot columns travel by
+//    v_readlane): that leaves U = the last n-M rows of Q^T, an orthonormal basis of range(V)'s
+//    complement, in LDS.  Eliminating p exactly, class c only has to solve the (n-M) x (M-1) problem
 //        min_q || U C_c q - U y_c ||,
 //    so a class needs 16 lanes (lane = column, 15 = right-hand side), four classes share a wave, and
-//    the systems are formed and solved entirely in registers: what the other lanes of the class need of
-//    a column reaches them inside the multiply-adds (see rows.h).  Up to fifteen classes:
-//    decode_byzantine_packed_kernel, several groups to a workgroup.
+//    the systems are formed and solved entirely in registers, by modified Gram-Schmidt: what the other
+//    lanes of the class need of a column reaches them inside the multiply-adds (see rows.h).
 //    No LDS traffic and no barrier inside either factorisation.
+//
+//  * decode_byzantine_packed_kernel (the same for up to fifteen classes, see packed_domain): one to four
+//    groups to a workgroup, factorised side by side, decoded by one matrix product each.
 //
 //  * decode_byzantine_general_kernel (everything else up to 64 available workers).  A class owns
 //    2M neighbouring lanes, lane j owns COLUMN j of the full n x (2M-1) system, which sits in LDS
 //    row-major; a Householder step walks down the pivot column (an LDS broadcast).
 //
-// Both finish the same way: Q by back substitution, a_r = Q(x_r) by Horner's rule, the A smallest
+// All finish the same way: Q by back substitution, a_r = Q(x_r) by Horner's rule, the A smallest
 // |a_r| (equal magnitudes: smaller worker index first; by counting ranks in the general kernel, by A
-// rounds of a DPP arg-min in the projected one) vote in an LDS histogram, the A most voted workers
-// (equal counts: smaller index first) leave the available list, and the workgroup decodes the group
-// over the rest.
+// rounds of a DPP minimum in the others) vote in an LDS histogram, the A most voted workers (equal
+// counts: smaller index first) leave the available list, and the group is decoded over the rest.
 #include <algorithm>
 #include <mutex>
 
@@ -1012,8 +1013,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!HOMOG && R
 //     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i):
 // column 15 of the product carries the denominators (C <= 15).  A query node that is a worker's node has T = 0 there and
 // takes that worker's row as it is, if the worker counts.
-// K = 8, A = 2, 20 of 24 workers, 2048 groups of 10 classes: 24.5 us with a workgroup per group, 20.4 us this way;
-// K = 12, A = 2, 28 workers, 8192 groups: 91.2 us with this packing but decoder weights per group, 70.8 us.
+// K = 8, A = 2, 20 of 24 workers, 2048 groups of 10 classes: 24.5 us with a workgroup per group, 19.9 us this way;
+// K = 12, A = 2, 28 workers, 8192 groups: 91.2 us with this packing but decoder weights per group, 68.3 us.
 // NB >= N - S bounds the workers that answer, NW >= N all workers, RM >= N - S - M.
 // HOMOG: Algorithm 1's locator instead (locate_classes_hom_proj): K = 8, 2048 groups 61 us with a workgroup per group
 // and the sweeps' broadcasts as moves, 47.5 us; K = 12, 8192 groups 357 and 183 us.
@@ -1770,9 +1771,9 @@ size_t basis_bytes(int tile, bool homogeneous) {
     return (b + 255) & ~static_cast<size_t>(255);
 }
 // Algorithm 1 on the shared factorisation: the register QR runs min(M, RM - 1) <= 15 steps.  Below K + A = 6 the LDS
-// kernel, which packs 64 / 2M classes into a wave, is the faster one (measured, 10 classes, 4096 groups: K + A = 3:
-// 33 us against 77; K + A = 6: 105 against 101; K + A = 10: 233 against 124; K + A = 12: 830 against 214;
-// K + A = 14, 8192 groups: 2651 against 548).
+// kernel, which packs 64 / 2M classes into a wave, is the faster one for many classes (measured, LDS / registers, 4096
+// groups of 10 classes | 64 groups of 100: K + A = 3: 25 / 60 | 37 / 51 us; 5: 67 / 63 | 33 / 54; 6: 81 / 66 | 39 / 57;
+// 8: 188 / 73 | 57 / 62; 10: 346 / 76 | 94 / 69; 14: 1275 / 111 | 201 / 97).
 bool hom_proj_domain(int M, int n) { return proj_domain(M, n) && M >= 6 && M <= kProjMaxM - 1; }
 size_t votes_bytes(int64_t G, int N) {
     return (sizeof(int32_t) * static_cast<size_t>(G) * (N + 1) + 255) & ~static_cast<size_t>(255);
@@ -1817,11 +1818,13 @@ bool packed_domain(int NB, int RM, bool homogeneous, int64_t G, int N, int S, in
 }
 // Groups per workgroup: one while the chip holds them all at once (five workgroups to each of 256 CUs), where spreading
 // the classes over waves shortens the chain of a group; then as many as keep the launch at one round of workgroups.
-// Measured with 1 / 2 / 4 groups, ten classes: K = 8, A = 2, 20 of 24 workers, 1024 groups 16.9 / 17.5 / 18.2 us, 2048
-// groups 29.1 / 20.4 / 22.3 us, 4096 groups 56 / 37 / 29 us; K = 12, A = 2, 28 workers, 1024 groups 21.7 / 22.6 / 23.7
-// us, 2048 groups 33 / 28 / 30 us, 8192 groups 101 / 81 / 71 us.
-// Algorithm 1's locator runs two waves to a SIMD: K = 8, 500 groups 27 / 32 / 40 us, 1024 groups 48 / 36 / 41 us, 2048
-// groups 91 / 66 / 48 us; K = 12, 28 workers, 8192 groups 289 / 231 / 183 us.
+// Measured with 1 / 2 / 4 groups, ten classes: K = 8, A = 2, 20 of 24 workers, 1024 groups 17.4 / 18.3 / 19.9 us, 2048
+// groups 30.3 / 21.5 / 23.1 us, 4096 groups 52 / 37 / 30 us; K = 12, A = 2, 28 workers, 1024 groups 22.6 / 23.4 / 25.3
+// us, 2048 groups 33 / 28 / 31 us, 8192 groups 87 / 74 / 68 us.  The lines lie right for 2, 5 and 15 classes too, but that
+// two and five classes up to 1024 groups would be up to 13 % faster with two or four (K = 8, 2 classes, 1024 groups
+// 15.4 / 15.0 / 14.0 us; 15 classes, 2048 groups 32 / 26 / 26).
+// Algorithm 1's locator runs two waves to a SIMD: K = 8, 512 groups 31 / 33 / 43 us, 1024 groups 53 / 38 / 42 us, 2048
+// groups 96 / 72 / 51 us; K = 12, 28 workers, 8192 groups 289 / 231 / 183 us.
 int packed_groups(int64_t G, bool homogeneous) {
     if (homogeneous) return G <= 512 ? 1 : (G <= 1024 ? 2 : 4);
     return G <= 1280 ? 1 : (G <= 2560 ? 2 : 4);

@@ -1,10 +1,13 @@
 // ApproxIFER decoder and fused decoder + top-1 for gfx950 (Section 3, "ApproxIFER Decoding").
 //
-// One workgroup per (group, tile of prediction columns).  The group's mask is turned into the
-// ascending survivor list F with wavefront ballots, the K x |F| matrix of basis functions is
-// evaluated in float64 (a group of lanes per query node, the denominator by a wavefront
-// reduction) and kept transposed in LDS, and the contraction over F accumulates in float64
-// with the weights broadcast from LDS.  Rows of missing workers are never read.
+// The group's mask is turned into the ascending survivor list F with wavefront ballots; rows of
+// missing workers are never read.  Two forms of the contraction, float64 in both:
+//  * weights: the K x |F| matrix of basis functions is evaluated (a group of lanes per query node,
+//    the denominator by a wavefront reduction), kept transposed in LDS and broadcast from there.
+//    A workgroup per (group, tile of prediction columns), or per group for the class decision.
+//  * node table: T[i][j] = 1 / (alpha_j - beta_i), the same for all groups, is evaluated once per
+//    workgroup; numerators and denominators are summed over F and divided at the end.  A 16-lane
+//    row per group (up to sixteen classes) or per (group, 64 classes).
 #include "decode_common.h"
 #include "rows.h"
 #include "survivors.h"
@@ -552,9 +555,13 @@ __device__ __forceinline__ int most_survivors_of_wave(int nF) {
 // predictions wait for the mask.
 // A query node that is a worker's node has T = 0 there and takes that worker's row as it is, if the worker answered.
 // 16384 groups of K = 8, N = 9, ten classes, top-1: 13.1 us a kernel with a wave per group, 7.2 us this way.
+// QS = 4: four rows share a group, a quarter of its queries each.  While the launch does not fill the chip it takes as
+// long as one row's chain (K <= 8, up to 1024 groups: 2.9 us split, 3.2 unsplit, 2.9 with a wave per group that forms
+// weights; K = 9..16 3.7, 4.5 and 4.0 us); beyond, the unsplit rows do more with what they load (K <= 8, 4096 to 8191
+// groups 3.6 us, 5.1 split).
+constexpr int64_t kRowsSplitGroups = 2048;
 constexpr int kRowGroups = 16;
 constexpr int kRowChunkSmall = 16;      // prediction rows in flight
-constexpr int64_t kRowsSplitGroups = 2048;
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 template <bool TOP1, int KP, int QS>
@@ -1152,7 +1159,9 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     const int64_t Cv = vec4 ? C / 4 : C;
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const int KQ = KP / 4;
-    const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;     // .. with very many classes: the split below
+    // few groups with very many classes: the split below (K = 12, one group of 21844 classes 32 us, 92 with tiles; K = 4,
+    // 4096 classes 10.5 and 9.3; K = 16, 128 groups of 50256 classes 269 and 307)
+    const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;
     if (top1_tiles_shape(K, N, C, G, vec4) && !few_groups) {
         const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
         int R = 1;
