@@ -143,8 +143,10 @@ def _stream_handle(stream) -> int:
         import torch
         # torch.cuda.current_stream().cuda_stream without the Stream object around it; not a documented name, so the
         # documented way is there where it is missing
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 
 

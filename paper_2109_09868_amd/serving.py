@@ -81,8 +81,8 @@ class ServingLoop:
         adv [G, A], status [G] (0: decoded), groups G.
         """
         K, N, S, A = self.K, self.N, self.S, self.A
-        G = binding.approxifer_group_count(Q, K)
         groups = binding.approxifer_pad_last_group(self.queries, Q, K)            # [G, K, D] view, last group completed
+        G = groups.shape[0]
         coded, coded_rows, preds, pred_rows, mask, count, out, out_rows, top1, top1_rows, status, adv = self._views(G)
         binding.approxifer_encode(groups, self.alpha, self.beta, coded=coded)
         pred_rows.copy_(model(coded_rows.detach()))
