@@ -476,7 +476,8 @@ struct NodeTable {
         beta = nodes.beta[e / KP];
         if (threadIdx.x <= KP) hit[threadIdx.x] = threadIdx.x < KP ? -1 : 0;
     }
-    __device__ __forceinline__ void finish(const Nodes &nodes, int K, int N, double *T, int *hit) {
+    // unit: also T[N + i][j] = 1 where the two nodes are one, else 0
+    __device__ __forceinline__ void finish(const Nodes &nodes, int K, int N, double *T, int *hit, bool unit) {
         __syncthreads();
         for (int e = threadIdx.x; e < N * KP; e += blockDim.x) {
             const int i = e / KP, j = e % KP;
@@ -491,6 +492,7 @@ struct NodeTable {
                 hit[KP] = 1;
             }
             T[e] = (j < K && !same) ? 1.0 / d : 0.0;
+            if (unit) T[N * KP + e] = same ? 1.0 : 0.0;
         }
         __syncthreads();
     }
@@ -553,7 +555,7 @@ __device__ __forceinline__ int most_survivors_of_wave(int nF) {
 // Lane j holds T[i][j], from where the numerators of all classes take it inside the multiply-add (row_outer), and sums
 // the denominator of query j.  The pass goes over the list of survivors: rows of missing workers are not read, and the
 // predictions wait for the mask.
-// A query node that is a worker's node has T = 0 there and takes that worker's row as it is, if the worker answered.
+// A query node that is a worker's node has T = 0 there; if the worker answered, the query takes its row as it is.
 // 16384 groups of K = 8, N = 9, ten classes, top-1: 13.1 us a kernel with a wave per group, 7.2 us this way.
 // QS = 4: four rows share a group, a quarter of its queries each.  While the launch does not fill the chip it takes as
 // long as one row's chain (K <= 8, up to 1024 groups: 2.9 us split, 3.2 unsplit, 2.9 with a wave per group that forms
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
         }
     };
     load_chunk(0);
-    table.finish(nodes, K, N, T, hit);                      // while the first predictions are on their way
+    table.finish(nodes, K, N, T, hit, false);               // while the first predictions are on their way
 
     double acc[KQ], den[kRegs];
 #pragma unroll
@@ -702,15 +704,25 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_rows_kernel(
 // with eight rows (three waves), 1024 groups of 4000 classes 76.8 against 71.7.
 constexpr int64_t kTilesOneRound = 8192;
 
+// The worker whose node is a query node (hit[]), if it answered, else -1.
+__device__ __forceinline__ int own_worker(int h, unsigned long long m) { return h >= 0 && ((m >> h) & 1ull) != 0ull ? h : -1; }
+// This lane's query's column of the table.  A query whose node is that of a worker that answered takes the worker's row as it
+// is: its column is the unit vector kept behind T.  (To load the row again at the end cost a round trip to memory for each
+// such query: K = 13, 16 of 27 workers, three such queries, 317 groups of 808 classes 18.9 us, 13.0 this way.)
+template <int KP>
+__device__ __forceinline__ const double *query_column(const double *T, const int *hit, int N, unsigned long long m) {
+    const int c = threadIdx.x % kRowLanes < KP ? threadIdx.x % kRowLanes : 0;
+    return T + c + (own_worker(hit[c], m) >= 0 ? N * KP : 0);
+}
+
 // acc[e][j] = sum over the survivors i of T[i][j] s_i y_ie, this lane's four classes e of the row at pg + class; den: in
 // lane j the denominator of query j.  rows: the most survivors that any row of the wave may have.  A row past its last
 // survivor repeats its first (S < 0: with factor 0); the values of a bad row are not used, and one without survivors
 // reads nothing.
 template <int KP, int CHUNK, bool UNAL>
 __device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t C, int floats, const uint8_t *F, int nF,
-                                          int rows, bool varies, unsigned long long minus, const double *T, double (&acc)[4][KP],
-                                          double &den) {
-    const int c = threadIdx.x % kRowLanes;
+                                          int rows, bool varies, unsigned long long minus, const double *column,
+                                          double (&acc)[4][KP], double &den) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -738,7 +750,7 @@ __device__ __forceinline__ void tile_sums(const float *__restrict__ pg, int64_t 
                     s = 0.0;
                     y[u] = v4f(0.0f);
                 }
-                const double t = T[w[u] * KP + (c < KP ? c : 0)];
+                const double t = column[w[u] * KP];
                 den = fma(s, t, den);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -752,8 +764,8 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out,
     int32_t *__restrict__ status, int64_t tiles, uint32_t chunks, int K, int N, int S, int64_t C, int sign_mode,
     const Nodes nodes) {
-    extern __shared__ double T[];                           // [N][KP] | int hit[KP] | int any_hit | pad | uint8 F[16][80]
-    int *hit = reinterpret_cast<int *>(T + N * KP);
+    extern __shared__ double T[];                           // [2 N][KP] | int hit[KP] | int any_hit | pad | uint8 F[16][80]
+    int *hit = reinterpret_cast<int *>(T + 2 * N * KP);
     const int c = threadIdx.x % kRowLanes;
     const int row = threadIdx.x / kRowLanes;
     uint8_t *F = reinterpret_cast<uint8_t *>(hit + KP + 4) + row * kListBytes;
@@ -766,7 +778,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
     const MaskBytes answered = load_mask_row(mask + g * N, N);
     NodeTable<KP> table;
     table.begin(nodes, K, N, hit);
-    table.finish(nodes, K, N, T, hit);
+    table.finish(nodes, K, N, T, hit, true);
     const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
@@ -774,13 +786,14 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
         status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
     list_survivors(m, F);
     const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
+    const double *column = query_column<KP>(T, hit, N, m);
 
     const int64_t col = (static_cast<int64_t>(chunk) * kRowLanes + c) * 4;
     const bool ok = col < C;
     const int floats = UNAL && ok && C - col < 4 ? static_cast<int>(C - col) : 4;
     const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
     double acc[4][KP], den;
-    tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, rows, S < 0, minus, T, acc, den);
+    tile_sums<KP, CHUNK, UNAL>(pg, C, floats, F, nF, rows, S < 0, minus, column, acc, den);
     den = 1.0 / den;
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
@@ -788,11 +801,12 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_tiles_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e][j] *= d;
     }
-    if (hit[KP] != 0) {                                     // before the first store: a load behind it waits for it too
+    if (hit[KP] != 0) {                                          // another worker's NaN or infinity does not reach such a query
 #pragma unroll
         for (int j = 0; j < KP; ++j) {
-            const int h = hit[j];
-            if (good && h >= 0 && ((m >> h) & 1ull) != 0ull) {
+            const int h = own_worker(hit[j], m);
+            const double sum = (acc[0][j] + acc[1][j]) + (acc[2][j] + acc[3][j]);
+            if (good && h >= 0 && !(__builtin_fabs(sum) < __builtin_inf())) {
                 const v4f yh = load_pred_vector<UNAL>(pg + static_cast<size_t>(h) * C, floats);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[e][j] = static_cast<double>(yh[e]);
@@ -829,8 +843,8 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
     const float *__restrict__ preds, const uint8_t *__restrict__ mask, int32_t *__restrict__ top1,
     float *__restrict__ score, int32_t *__restrict__ status, int64_t G, uint32_t chunks, int R, int K, int N, int S,
     int64_t C, int sign_mode, const Nodes nodes) {
-    extern __shared__ double T[];                           // [N][KP] | best values [16][KP] | int best classes [16][KP]
-    double *best_v = T + N * KP;                            // | int hit[KP] | int any_hit | pad | uint8 F[16][80]
+    extern __shared__ double T[];                           // [2 N][KP] | best values [16][KP] | int best classes [16][KP]
+    double *best_v = T + 2 * N * KP;                            // | int hit[KP] | int any_hit | pad | uint8 F[16][80]
     int *best_c = reinterpret_cast<int *>(best_v + kRowGroups * KP);
     int *hit = best_c + kRowGroups * KP;
     const int c = threadIdx.x % kRowLanes;
@@ -843,7 +857,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
     const MaskBytes answered = load_mask_row(mask + g * N, N);
     NodeTable<KP> table;
     table.begin(nodes, K, N, hit);
-    table.finish(nodes, K, N, T, hit);
+    table.finish(nodes, K, N, T, hit, true);
     const unsigned long long m = row_survivors(answered, N), minus = minus_signs(m, sign_mode);
     const int nF = static_cast<int>(__popcll(m));
     const bool good = S < 0 ? nF >= 1 : nF == N - S;
@@ -851,6 +865,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
         status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
     list_survivors(m, F);
     const int rows = S < 0 ? most_survivors_of_wave(nF) : N - S;
+    const double *column = query_column<KP>(T, hit, N, m);
 
     double bv[KP];
     int bc[KP];
@@ -866,7 +881,7 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
         const int floats = ok ? (C - col < 4 ? static_cast<int>(C - col) : 4) : 0;
         const float *pg = preds + static_cast<size_t>(g) * N * C + (ok ? col : 0);
         double acc[4][KP], den;
-        tile_sums<KP, CHUNK, UNAL>(pg, C, UNAL && ok ? floats : 4, F, nF, rows, S < 0, minus, T, acc, den);
+        tile_sums<KP, CHUNK, UNAL>(pg, C, UNAL && ok ? floats : 4, F, nF, rows, S < 0, minus, column, acc, den);
         den = 1.0 / den;
 #pragma unroll
         for (int j = 0; j < KP; ++j) {
@@ -874,9 +889,10 @@ __global__ __launch_bounds__(kRowGroups *kRowLanes) void decode_top1_tiles_kerne
             double v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = acc[e][j] * d;
-            if (hit[KP] != 0) {
-                const int h = hit[j];
-                if (good && h >= 0 && ((m >> h) & 1ull) != 0ull) {
+            if (hit[KP] != 0) {                                  // another worker's NaN or infinity does not reach such a query
+                const int h = own_worker(hit[j], m);
+                const double sum = (v[0] + v[1]) + (v[2] + v[3]);
+                if (good && h >= 0 && !(__builtin_fabs(sum) < __builtin_inf())) {
                     const v4f yh = load_pred_vector<UNAL>(pg + static_cast<size_t>(h) * C, UNAL && ok ? floats : 4);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = static_cast<double>(yh[e]);
@@ -1032,7 +1048,7 @@ bool rows_shape(int K, int N, int64_t C) { return K <= 32 && N <= kWave && C <= 
 //    (K = 8, 4096 groups of 100 classes 8.7 -> 7.2 us; 65536 groups of 40 classes 88 -> 40 us);
 //  - for K = 9..16 and a known number of survivors while one round of workgroups holds the launch (512 groups of K = 12,
 //    1000 classes 13.4 -> 10.7 us): 5 % on average from 1024 tiles on, where it loses 9 % beyond 8192 (84 groups of K = 9,
-//    16000 classes 21.4 and 26.7 us);
+//    16000 classes 21.4 and 26.7 us); up to K = 12 for up to twelve survivors, which one pass takes (13 to 16: 13 % slower);
 //  - rows that are only 4-byte aligned are loaded float by float at their ends, by every sixteenth lane instead of every
 //    64th: worth it for up to 80 classes and many groups only (K = 4, 1024 groups of 1003 classes 10.1 and 14.5 us).
 bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
@@ -1040,7 +1056,8 @@ bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
     const int64_t vectors = (C + 3) / 4;
     if (!vec4) return vectors <= 20 && G * K >= 32768;
     const int64_t tiles = G * ((vectors + kRowLanes - 1) / kRowLanes);
-    return (vectors <= 25 && G >= 2048) || (K > 8 && S >= 0 && tiles >= 1024 && tiles <= kTilesOneRound);
+    if (vectors <= 25 && G >= 2048) return true;
+    return K > 8 && S >= 0 && (K > 12 || N - S <= 12) && tiles >= 1024 && tiles <= kTilesOneRound;
 }
 // Whether decode_top1_tiles_kernel decides the call: all of them (0.76 of the time of a workgroup per group over 1600
 // shapes), but for long rows that are only 4-byte aligned with few queries to make up for their ends (K = 3, 7900 groups of
@@ -1107,7 +1124,7 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
         const dim3 tgrid(static_cast<unsigned>(tblocks)), tblock(kRowGroups * kRowLanes);
 #define APPROXIFER_TILES(KPV, CHUNK, UNAL)                                                                             \
     launch_status(launch_kernel(decode_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                                   \
-                                sizeof(double) * N * KPV + sizeof(int) * (KPV + 4) + kRowGroups * kListBytes, stream, d_preds,  \
+                                sizeof(double) * 2 * N * KPV + sizeof(int) * (KPV + 4) + kRowGroups * kListBytes, stream, d_preds,  \
                                 d_mask, d_out, d_status, tiles, static_cast<uint32_t>(chunks), K, N, S, C, sign_mode, nodes))
         switch (KP / 4) {
             case 1: return vec4 ? APPROXIFER_TILES(4, 8, false) : APPROXIFER_TILES(4, 8, true);
@@ -1169,7 +1186,7 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
         const dim3 tgrid(static_cast<unsigned>((G + kRowGroups / R - 1) / (kRowGroups / R))), tblock(kRowGroups * kRowLanes);
 #define APPROXIFER_TOP1_TILES(KPV, CHUNK, UNAL)                                                                        \
     launch_status(launch_kernel(decode_top1_tiles_kernel<KPV, CHUNK, UNAL>, tgrid, tblock,                              \
-                                sizeof(double) * (N + kRowGroups) * KPV + sizeof(int) * (kRowGroups * KPV + KPV + 4) +   \
+                                sizeof(double) * (2 * N + kRowGroups) * KPV + sizeof(int) * (kRowGroups * KPV + KPV + 4) +   \
                                     kRowGroups * kListBytes,                                                                 \
                                 stream, d_preds, d_mask, d_top1, d_score, d_status, G, static_cast<uint32_t>(chunks), R, K, \
                                 N, S, C, sign_mode, nodes))

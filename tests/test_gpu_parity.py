@@ -647,6 +647,33 @@ def test_decode_small_classes_four_rows_or_one_to_a_group(gpu, K, N, S, C):
     assert whole[1][3] == 1 and torch.all(whole[1][torch.arange(G, device=dev) != 3] == 0)
 
 
+@pytest.mark.parametrize("K,N,S,C,G", [(6, 9, 2, 10, 40), (15, 21, -1, 16, 2100), (6, 9, 2, 20, 2100), (10, 17, 7, 256, 256),
+                                       (13, 27, 11, 192, 400), (6, 9, 1, 77, 5500)])
+def test_decode_query_on_an_answered_workers_node_is_that_workers_row(gpu, K, N, S, C, G):
+    # .. bit for bit, and whatever the other workers returned: one of them returns NaN and infinities.
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(K * N + C)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    j_of, w_of = np.nonzero(alpha[:, None] == beta[None, :])
+    assert len(j_of) > 0
+    order = rng.random((G, N)).argsort(1).argsort(1)
+    late = np.full((G, 1), S) if S >= 0 else rng.integers(0, N - 2, (G, 1))
+    mask = (order >= late).astype(np.uint8)
+    Y = rng.standard_normal((G, N, C)).astype(np.float32)
+    other = int([w for w in range(N) if w not in set(w_of)][0])
+    Y[:, other, 0::3] = np.nan
+    Y[:, other, 1::3] = np.inf
+    out, st = binding.approxifer_decode(torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev), alpha, beta, S, 1)
+    top1, score, _ = binding.approxifer_decode_top1(torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev), alpha, beta, S, 1)
+    out, top1, score = out.cpu().numpy(), top1.cpu().numpy(), score.cpu().numpy()
+    assert torch.all(st == 0)
+    for j, w in zip(j_of, w_of):
+        came = mask[:, w] != 0
+        assert came.any()
+        assert np.array_equal(out[came, j], Y[came, w])
+        assert np.array_equal(top1[came, j], Y[came, w].argmax(-1)) and np.array_equal(score[came, j], Y[came, w].max(-1))
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
