@@ -31,6 +31,7 @@ constexpr int kDppQuadXor1 = 0xB1;       // quad_perm:[1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;       // quad_perm:[2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141; // lane i <-> 7-i inside each half row
 constexpr int kDppRowMirror = 0x140;     // lane i <-> 15-i inside each row
+constexpr int kDppWaveShr1 = 0x138;      // lane i takes lane i-1's, across rows
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_exchange(double v) {

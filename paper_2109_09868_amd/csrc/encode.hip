@@ -2,9 +2,10 @@
 //
 //   coded[g][i][d] = sum_j l_j(beta_i) * queries[g][j][d]
 //
-// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16 and 16-byte
-// rows, four waves (256 columns) otherwise; short ragged rows are tiled over the flattened (group, column)
-// index instead, so that no lane idles at a row end.  Each lane first issues the loads of its vector column of
+// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16 and rows of whole
+// 64-byte sectors, four waves (256 columns) otherwise; rows that leave lanes idle at their end are tiled over the
+// flattened (group, column) index instead, and rows that are not whole sectors go by tiles whose stores are
+// (encode_sectors_kernel, encode_mfma_sectors_kernel).  Each lane first issues the loads of its vector column of
 // all K queries (they stay in registers), and while those are in flight the workgroup
 // evaluates the N x K matrix l_j(beta_i) -- it depends on the nodes only -- in float64 (one
 // 16/32/64-lane group per worker row, the row's denominator by a DPP reduction) and keeps it
@@ -38,6 +39,8 @@ constexpr int kBlocksPerCuLargeK = 2;   // K > 16: four-wave workgroups
 constexpr int kMfmaMinK = 17;   // from this K on the matrix-core variant serves every shape
 constexpr int kMfmaWideMinK = 8;   // .. and from this K on the shapes with N >= 2K + 4
 constexpr int kMfmaBlocksPerCu = 4;   // matrix-core variant (four waves of 64 columns)
+constexpr int kSectorRowsMinD = 129;   // rows that are not whole 64-byte sectors: tiles of whole sectors from here on
+constexpr int kMfmaSectorsMinD = 300;   // K <= 16: .. on the matrix cores, where they pay, from here on
 constexpr int kScalarRowsMaxD = 128;   // ragged rows (D % 4 != 0) this short: 64-bit or 4-byte accesses only
 
 // Register type of VEC floats, and the type a lane loads and stores it through.  Rows that are only
@@ -64,6 +67,125 @@ __device__ __forceinline__ void store_stream(float *p, typename VecOf<VEC>::type
     __builtin_nontemporal_store(static_cast<M>(v), reinterpret_cast<M *>(p));
 }
 
+// ---- rows that do not begin on a 64-byte sector -------------------------------------------------------------------
+// A wave whose row segment begins or ends inside a sector writes that sector in part, and its neighbour the rest: the
+// memory pays for both as for two.  Where rows are not whole sectors (D % 16 != 0, or a base address that is none) a tile
+// therefore writes, of every coded row, the whole sectors that end inside it (tile [start, start + width) writes from the
+// sector of column `start` up to the one of column start + width), and loads sixteen columns more on its left for that.
+// Lane l of a wave holds columns start - 16 + 4 l .. + 3; a coded row whose phase is not a multiple of four floats is
+// shifted along the lanes first, so that every store is one aligned 16-byte piece.  Only a row's own first and last
+// sector are written in part, in single floats.
+constexpr int kSector = 16;                               // floats
+constexpr int kTileHalo = 4;                              // lanes on the left that a tile shares with its neighbour
+constexpr int kTileVecs = 64 - kTileHalo;                 // .. so that this many are its own; the row's last tile leaves one
+                                                          // lane more for what the shift pushes past the row's end
+
+struct RowTile {
+    int64_t g;                                            // group
+    int64_t start;                                        // first column, a multiple of four
+    int width;                                            // columns of a tile that is not the row's last
+    int left;                                             // last tile: columns up to the row's end
+    bool first, last;
+    // first column of the tile's vector v, relative to start: the row's first tile has no neighbour on the left
+    __device__ __forceinline__ int column(int v) const { return 4 * v - (first ? 0 : 4 * kTileHalo); }
+};
+// tile `id` of the batch, `per_row` tiles to a row
+__device__ __forceinline__ RowTile row_tile(uint32_t id, uint32_t per_row, int width, int64_t D) {
+    RowTile t;
+    const uint32_t g = id / per_row;
+    const uint32_t k = id - g * per_row;
+    t.g = g;
+    t.start = static_cast<int64_t>(k) * width;
+    t.width = width;
+    t.first = k == 0;
+    t.last = k + 1 == per_row;
+    t.left = t.last ? static_cast<int>(D - t.start) : width;
+    return t;
+}
+// Where lane-vector c (relative to the tile's start) of a query row is loaded from: always inside the row.  The vector over
+// the row's end is loaded from its last four columns; finish_vector() then moves its columns to their places.
+__device__ __forceinline__ int64_t load_column(const RowTile &t, int c, int64_t D) {
+    const int64_t col = t.start + c;
+    if (col < 0) return 0;
+    return col + 4 <= D ? col : D - 4;
+}
+__device__ __forceinline__ bool over_the_end(const RowTile &t, int c) { return t.last && c < t.left && c + 4 > t.left; }
+__device__ __forceinline__ v4f finish_vector(v4f x, bool over, int tail) {          // tail = D % 4, not 0
+    v4f y = x;
+    y[0] = tail == 1 ? x[3] : (tail == 2 ? x[2] : x[1]);
+    y[1] = tail == 2 ? x[3] : x[2];
+    y[2] = x[3];
+    return over ? y : x;
+}
+__device__ __forceinline__ float from_lane_below(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kDppWaveShr1, 0xF, 0xF, true));
+}
+// One coded row of the tile: v holds the lane's columns c .. c + 3 (c = 4 lane - 16, relative to the tile's start), `at` =
+// floats by which column `start` lies behind a sector's begin (the same for all lanes), row = address of column `start`.
+// Every lane of the wave calls it.
+__device__ __forceinline__ void store_sectors(float *row, v4f v, int c, int at, const RowTile &t) {
+    const int s = at & 3;
+    if (s & 2) {
+        const float p2 = from_lane_below(v[2]), p3 = from_lane_below(v[3]);
+        v = v4f{p2, p3, v[0], v[1]};
+    }
+    if (s & 1) {
+        const float p3 = from_lane_below(v[3]);
+        v = v4f{p3, v[0], v[1], v[2]};
+    }
+    const int q = c - s;
+    const int lo = t.first ? 0 : -at;
+    const int hi = t.last ? t.left - 3 : t.width - ((at + t.width) & (kSector - 1));
+    if (q >= lo && q < hi) store_stream<4>(row + q, v);
+    if (t.first || t.last) {
+        const bool part = (t.first && q < 0 && q > -4) || (t.last && q < t.left && q + 4 > t.left);
+        if (part) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (q + e >= lo && (!t.last || q + e < t.left)) __builtin_nontemporal_store(v[e], row + q + e);
+        }
+    }
+}
+
+// ---- l_j(beta_i) in float64, one group of LPR lanes per worker row ---------------------
+// The nodes are read with compile-time or wave-uniform indices only, i.e. through scalar
+// loads: a vector load here would queue behind the query loads above and make the wave
+// wait for all of them before it could evaluate a single weight.
+template <int K, int THREADS>
+__device__ __forceinline__ void encode_weights(float *wl, int N, const Nodes &nodes) {   // wl[N][KP]
+    constexpr int KP = (K + 3) & ~3;       // weight row padded to whole float4s
+    constexpr int LPR = K <= 16 ? 16 : (K <= 32 ? 32 : 64);   // lanes per weight row
+    constexpr int ROWS_PER_PASS = THREADS / LPR;
+    const int tid = threadIdx.x;
+    const int j = tid % LPR;
+    const int sub = tid / LPR;
+    const bool valid = j < K;
+    double xa = 0.0;
+#pragma unroll
+    for (int jj = 0; jj < K; ++jj) {
+        const double a = wave_uniform(nodes.alpha[jj]);
+        if (j == jj) xa = a;
+    }
+    const double sign = (j & 1) ? -1.0 : 1.0;
+    for (int i0 = 0; i0 < N; i0 += ROWS_PER_PASS) {   // i0 + ROWS_PER_PASS <= APPROXIFER_MAX_N always
+        double z = wave_uniform(nodes.beta[i0]);
+#pragma unroll
+        for (int r = 1; r < ROWS_PER_PASS; ++r) {
+            const double zr = wave_uniform(nodes.beta[i0 + r]);
+            if (sub == r) z = zr;
+        }
+        const int i = i0 + sub;
+        const bool row = i < N;
+        const BerrutTerm bt = berrut_term(z, xa, sign, valid && row);
+        const double den = group_sum<LPR>(bt.t);
+        const unsigned long long hits = __ballot(bt.hit);
+        const unsigned long long group_mask = (LPR == 64) ? ~0ull : ((1ull << (LPR & 63)) - 1ull) << ((tid & 63) / LPR * LPR);
+        const bool any_hit = (hits & group_mask) != 0ull;
+        const double w = any_hit ? (bt.hit ? 1.0 : 0.0) : bt.t * (1.0 / den);
+        if (row && j < KP) wl[i * KP + j] = valid ? static_cast<float>(w) : 0.0f;
+    }
+}
+
 // K: queries per group (compile time so that the K input columns stay in registers).
 // VEC: floats per lane per access.  THREADS: workgroup size.
 // FLAT: false -- a workgroup covers THREADS consecutive vector columns of ONE group (`chunks` workgroups per
@@ -78,9 +200,7 @@ __global__ __launch_bounds__(THREADS) void encode_kernel(
     const float *__restrict__ queries, float *__restrict__ coded, int N, int64_t D, int64_t Dv,
     int64_t chunks, int64_t col0, const Nodes nodes) {
     typedef typename VecOf<VEC>::type V;
-    constexpr int KP = (K + 3) & ~3;       // weight row padded to whole float4s
-    constexpr int LPR = K <= 16 ? 16 : (K <= 32 ? 32 : 64);   // lanes per weight row
-    constexpr int ROWS_PER_PASS = THREADS / LPR;
+    constexpr int KP = (K + 3) & ~3;
     extern __shared__ float wl[];          // [N][KP]
 
     const int tid = threadIdx.x;
@@ -112,39 +232,7 @@ __global__ __launch_bounds__(THREADS) void encode_kernel(
 #pragma unroll
     for (int j = 0; j < K; ++j) x[j] = load_stream<VEC, UNAL>(xg + static_cast<size_t>(j) * D);
 
-    // ---- l_j(beta_i) in float64, one group of LPR lanes per worker row ---------------------
-    // The nodes are read with compile-time or wave-uniform indices only, i.e. through scalar
-    // loads: a vector load here would queue behind the query loads above and make the wave
-    // wait for all of them before it could evaluate a single weight.
-    {
-        const int j = tid % LPR;
-        const int sub = tid / LPR;
-        const bool valid = j < K;
-        double xa = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < K; ++jj) {
-            const double a = wave_uniform(nodes.alpha[jj]);
-            if (j == jj) xa = a;
-        }
-        const double sign = (j & 1) ? -1.0 : 1.0;
-        for (int i0 = 0; i0 < N; i0 += ROWS_PER_PASS) {   // i0 + ROWS_PER_PASS <= APPROXIFER_MAX_N always
-            double z = wave_uniform(nodes.beta[i0]);
-#pragma unroll
-            for (int r = 1; r < ROWS_PER_PASS; ++r) {
-                const double zr = wave_uniform(nodes.beta[i0 + r]);
-                if (sub == r) z = zr;
-            }
-            const int i = i0 + sub;
-            const bool row = i < N;
-            const BerrutTerm bt = berrut_term(z, xa, sign, valid && row);
-            const double den = group_sum<LPR>(bt.t);
-            const unsigned long long hits = __ballot(bt.hit);
-            const unsigned long long group_mask = (LPR == 64) ? ~0ull : ((1ull << (LPR & 63)) - 1ull) << ((tid & 63) / LPR * LPR);
-            const bool any_hit = (hits & group_mask) != 0ull;
-            const double w = any_hit ? (bt.hit ? 1.0 : 0.0) : bt.t * (1.0 / den);
-            if (row && j < KP) wl[i * KP + j] = valid ? static_cast<float>(w) : 0.0f;
-        }
-    }
+    encode_weights<K, THREADS>(wl, N, nodes);
     __syncthreads();
 
     const v4f *wl4 = reinterpret_cast<const v4f *>(wl);
@@ -158,6 +246,53 @@ __global__ __launch_bounds__(THREADS) void encode_kernel(
                 if (4 * j4 + jj < K) acc = w[jj] * x[4 * j4 + jj] + acc;
         }
         if (ok) store_stream<VEC, UNAL>(og + static_cast<size_t>(i) * D, acc);
+    }
+}
+
+// The same on tiles of whole sectors (see store_sectors): a tile per wave, K <= 16.  An HBM stream as above; what the
+// unaligned stores cost it was a fifth (K = 8, N = 12, 64 groups of 3 x 299 x 299 floats: 270 -> 231 us, 5.1 -> 5.9 TB/s; rows of
+// 268288 floats, all sectors whole: 218 us).  Four waves to a workgroup, so that three of four halos are read through one L2:
+// with a wave each 250 us.
+template <int K, int THREADS>
+__global__ __launch_bounds__(THREADS) void encode_sectors_kernel(
+    const float *__restrict__ queries, float *__restrict__ coded, int N, int64_t D, uint32_t per_row, int width,
+    uint32_t tiles, const Nodes nodes) {
+    extern __shared__ float wl[];          // [N][KP]
+    constexpr int KP = (K + 3) & ~3;
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const uint32_t id = blockIdx.x * (THREADS / kWave) + __builtin_amdgcn_readfirstlane(wave_id());
+    const RowTile t = row_tile(id < tiles ? id : 0, per_row, width, D);
+    const int c = t.column(lane);
+    const float *xg = queries + static_cast<size_t>(t.g) * K * D + load_column(t, c, D);
+
+    v4f x[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) x[j] = load_stream<4, true>(xg + static_cast<size_t>(j) * D);
+    encode_weights<K, THREADS>(wl, N, nodes);
+    __syncthreads();
+    if (id >= tiles) return;               // no barrier left
+
+    if (t.last && D % 4 != 0) {
+        const bool over = over_the_end(t, c);
+#pragma unroll
+        for (int j = 0; j < K; ++j) x[j] = finish_vector(x[j], over, static_cast<int>(D % 4));
+    }
+    float *row = coded + static_cast<size_t>(t.g) * N * D + t.start;
+    int at = static_cast<int>(reinterpret_cast<uintptr_t>(row) / sizeof(float)) & (kSector - 1);
+    const v4f *wl4 = reinterpret_cast<const v4f *>(wl);
+    for (int i = 0; i < N; ++i) {
+        v4f acc = v4f(0.0f);
+#pragma unroll
+        for (int j4 = 0; j4 < KP / 4; ++j4) {
+            const v4f w = wl4[i * (KP / 4) + j4];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj)
+                if (4 * j4 + jj < K) acc = w[jj] * x[4 * j4 + jj] + acc;
+        }
+        store_sectors(row, acc, c, at, t);
+        row += D;
+        at = (at + static_cast<int>(D & (kSector - 1))) & (kSector - 1);
     }
 }
 
@@ -177,14 +312,50 @@ __global__ __launch_bounds__(THREADS) void encode_kernel(
 // The weights sit in LDS already in A-operand order, wA[(mt*KS + s)*64 + l].
 constexpr int kMfmaThreads = 256;
 
+// l_j(beta_i) in float64 (scalar node loads only, see encode_weights), stored in A order
+template <int KS>
+__device__ __forceinline__ void encode_mfma_weights(float *wA, int K, int N, const Nodes &nodes) {
+    constexpr int LPR = KS <= 8 ? 32 : 64;                    // lanes per weight row (K <= 32 / K <= 64)
+    constexpr int ROWS_PER_PASS = kMfmaThreads / LPR;
+    const int tid = threadIdx.x;
+    const int j = tid % LPR;
+    const int sub = tid / LPR;
+    const bool valid = j < K;
+    double xa = 0.0;
+#pragma unroll
+    for (int jj = 0; jj < 4 * KS; ++jj) {
+        const double a = wave_uniform(nodes.alpha[jj]);   // entries past K are zero-filled by the host
+        if (j == jj) xa = a;
+    }
+    const double sign = (j & 1) ? -1.0 : 1.0;
+    const int n16 = (N + 15) & ~15;
+    for (int i0 = 0; i0 < n16; i0 += ROWS_PER_PASS) {     // n16 <= 128 = APPROXIFER_MAX_N: reads stay in bounds
+        double z = wave_uniform(nodes.beta[i0]);
+#pragma unroll
+        for (int r = 1; r < ROWS_PER_PASS; ++r) {
+            const double zr = wave_uniform(nodes.beta[i0 + r]);
+            if (sub == r) z = zr;
+        }
+        const int i = i0 + sub;
+        const bool row = i < N;
+        const BerrutTerm bt = berrut_term(z, xa, sign, valid && row);
+        const double den = group_sum<LPR>(bt.t);
+        const unsigned long long hits = __ballot(bt.hit);
+        const unsigned long long group_mask =
+            (LPR == 64) ? ~0ull : ((1ull << (LPR & 63)) - 1ull) << ((tid & 63) / LPR * LPR);
+        const bool any_hit = (hits & group_mask) != 0ull;
+        const double w = any_hit ? (bt.hit ? 1.0 : 0.0) : bt.t * (1.0 / den);
+        if (j < 4 * KS)   // rows N..n16-1 and columns K..4KS-1 hold zeros
+            wA[((i >> 4) * KS + (j >> 2)) * 64 + (j & 3) * 16 + (i & 15)] = (valid && row) ? static_cast<float>(w) : 0.0f;
+    }
+}
+
 // KS = ceil(K / 4) k-steps; UNAL: rows only 4-byte aligned; FLAT: the 16-column wave tiles run over the flattened
 // (group, vector column) numbering of the batch (`chunks` = number of pairs), as in encode_kernel.
 template <int KS, bool UNAL, bool FLAT>
 __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
     const float *__restrict__ queries, float *__restrict__ coded, int K, int N, int64_t D, int64_t Dv,
     int64_t chunks, const Nodes nodes) {
-    constexpr int LPR = KS <= 8 ? 32 : 64;                    // lanes per weight row (K <= 32 / K <= 64)
-    constexpr int ROWS_PER_PASS = kMfmaThreads / LPR;
     extern __shared__ float wA[];                             // [ceil(N/16)][KS][64]
 
     const int tid = threadIdx.x;
@@ -222,39 +393,7 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
         x[s] = load_stream<4, UNAL>(xg + static_cast<size_t>(row) * D);
     }
 
-    // ---- l_j(beta_i) in float64 (scalar node loads only, see encode_kernel), stored in A order ----
-    {
-        const int j = tid % LPR;
-        const int sub = tid / LPR;
-        const bool valid = j < K;
-        double xa = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < 4 * KS; ++jj) {
-            const double a = wave_uniform(nodes.alpha[jj]);   // entries past K are zero-filled by the host
-            if (j == jj) xa = a;
-        }
-        const double sign = (j & 1) ? -1.0 : 1.0;
-        const int n16 = (N + 15) & ~15;
-        for (int i0 = 0; i0 < n16; i0 += ROWS_PER_PASS) {     // n16 <= 128 = APPROXIFER_MAX_N: reads stay in bounds
-            double z = wave_uniform(nodes.beta[i0]);
-#pragma unroll
-            for (int r = 1; r < ROWS_PER_PASS; ++r) {
-                const double zr = wave_uniform(nodes.beta[i0 + r]);
-                if (sub == r) z = zr;
-            }
-            const int i = i0 + sub;
-            const bool row = i < N;
-            const BerrutTerm bt = berrut_term(z, xa, sign, valid && row);
-            const double den = group_sum<LPR>(bt.t);
-            const unsigned long long hits = __ballot(bt.hit);
-            const unsigned long long group_mask =
-                (LPR == 64) ? ~0ull : ((1ull << (LPR & 63)) - 1ull) << ((tid & 63) / LPR * LPR);
-            const bool any_hit = (hits & group_mask) != 0ull;
-            const double w = any_hit ? (bt.hit ? 1.0 : 0.0) : bt.t * (1.0 / den);
-            if (j < 4 * KS)   // rows N..n16-1 and columns K..4KS-1 hold zeros
-                wA[((i >> 4) * KS + (j >> 2)) * 64 + (j & 3) * 16 + (i & 15)] = (valid && row) ? static_cast<float>(w) : 0.0f;
-        }
-    }
+    encode_mfma_weights<KS>(wA, K, N, nodes);
     __syncthreads();
 
     const int mtiles = (N + 15) >> 4;
@@ -284,6 +423,69 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
     }
 }
 
+// The same on tiles of whole sectors (see store_sectors), one tile of 64 vectors per workgroup: the waves compute sixteen
+// vectors each, as above, and exchange the sixteen coded rows of a round through LDS, from where each wave stores
+// four rows as they lie in memory.  (A wave's own sixteen vectors end inside a sector on both sides: five pieces for four.)
+// An HBM stream: K = 32, N = 48, 10003 floats, 93 groups 100 -> 65 us; K = 12, N = 28 87 -> 56 us (5.3 TB/s).
+// dynamic LDS: float wA[ceil(N/16)][KS][64] | stage[16][kStageRow]
+constexpr int kStageRow = 256 + 4;
+template <int KS>
+__global__ __launch_bounds__(kMfmaThreads) void encode_mfma_sectors_kernel(
+    const float *__restrict__ queries, float *__restrict__ coded, int K, int N, int64_t D, uint32_t per_row, int width,
+    const Nodes nodes) {
+    extern __shared__ __align__(16) float wA[];
+    const int mtiles = (N + 15) >> 4;
+    float *stage = wA + mtiles * KS * 64;
+    const int lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const RowTile t = row_tile(blockIdx.x, per_row, width, D);
+    const int krow = lane >> 4;
+    const int vec = wv * 16 + (lane & 15);                    // this lane's vector of the tile while computing
+    const int c = t.column(vec);
+    const float *xg = queries + static_cast<size_t>(t.g) * K * D + load_column(t, c, D);
+    v4f x[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int row = (4 * s + krow < K) ? 4 * s + krow : K - 1;
+        x[s] = load_stream<4, true>(xg + static_cast<size_t>(row) * D);
+    }
+    encode_mfma_weights<KS>(wA, K, N, nodes);
+    __syncthreads();
+    if (t.last && D % 4 != 0) {
+        const bool over = over_the_end(t, c);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) x[s] = finish_vector(x[s], over, static_cast<int>(D % 4));
+    }
+
+    float *og = coded + static_cast<size_t>(t.g) * N * D + t.start;
+    for (int mt = 0; mt < mtiles; ++mt) {
+        v4f acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = v4f(0.0f);
+        const float *wmt = wA + mt * KS * 64 + lane;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const float a = wmt[s * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, x[s][e], acc[e], 0, 0, 0);
+        }
+        if (mt > 0) __syncthreads();                          // the rows of the round before are stored
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<v4f *>(stage + (4 * krow + r) * kStageRow + 4 * vec) = v4f{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * mt + 4 * wv + r;
+            if (i < N) {
+                float *row = og + static_cast<size_t>(i) * D;
+                const int at = static_cast<int>(reinterpret_cast<uintptr_t>(row) / sizeof(float)) & (kSector - 1);
+                store_sectors(row, *reinterpret_cast<const v4f *>(stage + (4 * wv + r) * kStageRow + 4 * lane), t.column(lane), at, t);
+            }
+        }
+    }
+}
+
 template <int KS, bool UNAL, bool FLAT>
 int run_encode_mfma_shape(const float *d_queries, float *d_coded, int64_t tiles, int64_t chunks, int K, int N, int64_t D,
                           int64_t Dv, const Nodes &nodes, hipStream_t stream) {
@@ -306,20 +508,84 @@ int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, in
     const int64_t cols_per_block = (kMfmaThreads / 64) * 16;           // vector columns per workgroup
     const int64_t chunks = (Dv + cols_per_block - 1) / cols_per_block;
     const int64_t idle = chunks * cols_per_block - Dv;                  // columns without data at the row ends
-    if (idle * 100 > 3 * chunks * cols_per_block) {
+    if (UNAL || idle * 100 > 3 * chunks * cols_per_block) {   // UNAL: only short rows come here (sector_rows)
         const int64_t pairs = G * Dv;
         return run_encode_mfma_shape<KS, UNAL, true>(d_queries, d_coded, (pairs + cols_per_block - 1) / cols_per_block,
                                                      pairs, K, N, D, Dv, nodes, stream);
     }
-    return run_encode_mfma_shape<KS, UNAL, false>(d_queries, d_coded, G * chunks, chunks, K, N, D, Dv, nodes, stream);
+    if constexpr (UNAL) return APPROXIFER_ERR_LIMIT;                   // not reached
+    else return run_encode_mfma_shape<KS, false, false>(d_queries, d_coded, G * chunks, chunks, K, N, D, Dv, nodes, stream);
 }
 
-// Workgroup size.  K <= 16: one wave, but four for rows that are only 4-byte aligned.  There every wave's row segment
-// begins and ends inside a 128-byte line that the neighbouring wave's shares; in one workgroup the two meet in one L2
-// instead of two, and three of four such lines are moved once (K = 8, N = 12, 3 x 299 x 299 floats, 64 groups: 279 ->
-// 268 us; K = 4, N = 6, 50001 floats: 198 -> 174 us; K = 16, N = 24, 100001 floats: 225 -> 206 us).  K = 8..16 then have
-// eight waves, not six: over 500 shapes from 49 to 280000 floats they gained 4 % on average all the same.
+// Workgroup size.  K <= 16: one wave, but four for rows that are only 4-byte aligned (short ones: longer rows go by tiles of
+// whole sectors).
 constexpr int encode_threads(int K, bool UNAL) { return K <= 16 && !UNAL ? 64 : 256; }
+
+// Tiles of whole sectors: as many as it takes at kTileVecs vectors each, all of one width.
+struct SectorTiles {
+    int64_t per_row, total;
+    int width;                              // columns, a multiple of four
+};
+inline SectorTiles sector_tiles(int64_t G, int64_t D) {
+    const int64_t vecs = (D + 3) / 4;
+    SectorTiles t;
+    t.per_row = vecs <= 63 ? 1 : (vecs + 1 + kTileVecs - 1) / kTileVecs;
+    t.width = static_cast<int>(4 * ((vecs + t.per_row - 1) / t.per_row));
+    t.per_row = (vecs + t.width / 4 - 1) / (t.width / 4);
+    t.total = G * t.per_row;
+    return t;
+}
+
+// Workgroups per CU, where the stage and the weights leave room for them (six, eight and four at 300 MB: K = 12, N = 28,
+// 350 floats 77, 73, 82 us, 10003 floats 56, 59, 57; K = 8, N = 24, 350 floats 82, 74, 89, 10003 floats 56, 58, 60; with two
+// stages, a barrier less, and four 58 to 61 at 10003 floats).
+constexpr int mfma_sector_blocks(int64_t D) { return D < 2048 ? 8 : 6; }
+
+template <int KS>
+int run_encode_mfma_sectors(const float *d_queries, float *d_coded, int64_t G, int K, int N, int64_t D, const Nodes &nodes,
+                            hipStream_t stream) {
+    const SectorTiles t = sector_tiles(G, D);
+    if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+        const size_t lds_used = (static_cast<size_t>((N + 15) / 16) * KS * 64 + 16 * kStageRow) * sizeof(float);
+        size_t lds = (static_cast<size_t>(kLdsPerCu / mfma_sector_blocks(D)) / 512) * 512;
+    if (lds < lds_used) lds = lds_used;
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(encode_mfma_sectors_kernel<KS>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
+    return launch_status(launch_kernel(encode_mfma_sectors_kernel<KS>, dim3(static_cast<unsigned>(t.total)), dim3(kMfmaThreads),
+                                       lds, stream, d_queries, d_coded, K, N, D, static_cast<uint32_t>(t.per_row), t.width,
+                                       nodes));
+}
+
+// Workgroups of four waves per CU: with K <= 4 loads a wave, or rows of a few tiles that leave lanes idle, sixteen waves keep
+// enough bytes in flight; from five loads and 8 KB a row on, eight.  16 and 8 waves at N = K + 1 .. 1.5 K, 300 MB: K = 4, 1425
+// floats 52 and 59 us, 50001 floats 49 and 53; K = 8, 477 floats 66 and 80, 604 floats 58 and 59, 3075 floats 58 and 56.
+constexpr int sector_blocks(int K, int64_t D) {
+    if (K <= 2) return 6;
+    return K <= 4 || D < 2048 ? 4 : 2;
+}
+
+template <int K>
+int run_encode_sectors(const float *d_queries, float *d_coded, int64_t G, int N, int64_t D, const Nodes &nodes,
+                       hipStream_t stream) {
+    constexpr int KP = (K + 3) & ~3;
+    constexpr int THREADS = 256;
+    const SectorTiles t = sector_tiles(G, D);
+    if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    const int per_cu = sector_blocks(K, D);
+    const size_t lds_used = static_cast<size_t>(N) * KP * sizeof(float);
+    size_t lds = (static_cast<size_t>(kLdsPerCu / per_cu) / 512) * 512;
+    if (lds < lds_used) lds = lds_used;
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(encode_sectors_kernel<K, THREADS>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
+    return launch_status(launch_kernel(encode_sectors_kernel<K, THREADS>,
+                                       dim3(static_cast<unsigned>((t.total + THREADS / 64 - 1) / (THREADS / 64))), dim3(THREADS),
+                                       lds, stream, d_queries, d_coded, N, D, static_cast<uint32_t>(t.per_row), t.width,
+                                       static_cast<uint32_t>(t.total), nodes));
+}
 
 template <int K, int VEC, bool FLAT, bool UNAL>
 int run_encode_shape(const float *d_queries, float *d_coded, int64_t tiles, int64_t chunks, int N, int64_t D,
@@ -356,12 +622,13 @@ int run_encode(const float *d_queries, float *d_coded, int64_t G, int N, int64_t
     // lanes left idle at the row ends by the per-group tiling; above 3 % the flattened numbering pays for its
     // per-lane division and addresses
     const int64_t idle = chunks * THREADS - Dv;
-    if (idle * 100 > 3 * chunks * THREADS) {
+    if (UNAL || idle * 100 > 3 * chunks * THREADS) {          // UNAL: only short rows come here (sector_rows)
         const int64_t pairs = G * Dv;
         return run_encode_shape<K, VEC, true, UNAL>(d_queries, d_coded, (pairs + THREADS - 1) / THREADS, pairs, N, D, Dv,
                                                     col0, nodes, stream);
     }
-    return run_encode_shape<K, VEC, false, UNAL>(d_queries, d_coded, G * chunks, chunks, N, D, Dv, col0, nodes, stream);
+    if constexpr (UNAL) return APPROXIFER_ERR_LIMIT;          // not reached
+    else return run_encode_shape<K, VEC, false, false>(d_queries, d_coded, G * chunks, chunks, N, D, Dv, col0, nodes, stream);
 }
 
 // 128-bit columns: the matrix-core kernel or the vector kernel, by shape.
@@ -382,9 +649,29 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
     }
 }
 
+// Whether a call goes by tiles of whole sectors: rows that are no whole sectors, of kSectorRowsMinD floats or more.  Measured
+// against the kernels that move such rows as they come, 300 MB, 130 to 60000 floats: K <= 16 0.75 to 1.0 of the time (K = 8,
+// N = 12, 64 x 3 x 299 x 299 floats: 270 and 231 us), the matrix-core variant 0.62 to 1.0 (K = 32, N = 48, 10003 floats: 100 and 65
+// us), but K = 20, N = 24 with tiles of fewer than forty own vectors, 156 floats: 74 and 78 us, 258 floats: 86 and 98 us.
+inline bool sector_rows(const float *d_queries, const float *d_coded, int K, int N, int64_t D) {
+    const bool whole = reinterpret_cast<uintptr_t>(d_queries) % 64 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 64 == 0 &&
+                       D % kSector == 0;
+    if (whole || D < kSectorRowsMinD) return false;
+    return K < kMfmaMinK || 2 * N >= 3 * K || sector_tiles(1, D).width >= 4 * 40;
+}
+
 template <int K>
 int run_encode_k(const float *d_queries, float *d_coded, int64_t G, int N, int64_t D, const Nodes &nodes,
                  hipStream_t stream) {
+    if (sector_rows(d_queries, d_coded, K, N, D)) {
+        if constexpr (K >= kMfmaWideMinK) {
+            // as for whole rows (run_encode_wide), but rows of one or two tiles leave the matrix cores' workgroups less to
+            // do: K = 12, N = 28, 156 floats 85 us and 73 without matrix cores, 258 floats 107 and 90, 350 floats 73 and 77
+            if (K >= kMfmaMinK || (N >= 2 * K + 4 && D >= kMfmaSectorsMinD))
+                return run_encode_mfma_sectors<(K + 3) / 4>(d_queries, d_coded, G, K, N, D, nodes, stream);
+        }
+        if constexpr (K < kMfmaMinK) return run_encode_sectors<K>(d_queries, d_coded, G, N, D, nodes, stream);
+    }
     const bool aligned16 = (reinterpret_cast<uintptr_t>(d_queries) % 16 == 0) &&
                            (reinterpret_cast<uintptr_t>(d_coded) % 16 == 0) && (D % 4 == 0);
     if (aligned16) return run_encode_wide<K, false>(d_queries, d_coded, G, N, D, nodes, stream);

@@ -87,6 +87,28 @@ def test_encode_unaligned_pointers_and_canaries(gpu, K, N, D, G, off_in, off_out
     assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * N * D:] == 7.5)
 
 
+@pytest.mark.parametrize("K,N", [(1, 2), (5, 8), (16, 20), (8, 24), (12, 28), (20, 24), (33, 64)])
+@pytest.mark.parametrize("off_in,off_out", [(0, 0), (3, 0), (0, 6), (1, 13)])
+def test_encode_tiles_of_whole_sectors(gpu, K, N, off_in, off_out):
+    # rows that are no whole 64-byte sectors: one tile up to 63 vectors of a row, then 60 a tile less one for the last; row
+    # ends of every remainder, rows just above and below a tile more, phases of every row from the base's and the length's
+    torch, binding, dev = gpu
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    for D in (129, 130, 160, 250, 251, 252, 253, 254, 299, 300, 473, 475, 476, 477, 714, 717, 960, 2047, 2050):
+        G = 3
+        X = np.random.default_rng(D).uniform(0, 1, (G, K, D)).astype(np.float32)
+        flat_in = torch.full((G * K * D + off_in + 5,), float("nan"), dtype=torch.float32, device=dev)
+        flat_in[off_in:off_in + G * K * D] = torch.from_numpy(X).to(dev).reshape(-1)
+        flat_out = torch.full((G * N * D + off_out + 40,), 7.5, dtype=torch.float32, device=dev)
+        c = flat_out[off_out:off_out + G * N * D].view(G, N, D)
+        binding.approxifer_encode(flat_in[off_in:off_in + G * K * D].view(G, K, D), alpha, beta, coded=c)
+        got, ref = c.cpu().numpy(), orc.encode(X, alpha, beta)
+        # every element: K roundings of weights and products, the weights' absolute sum times the largest query (below 1)
+        bound = (K + 2) * 2.0 ** -23 * np.abs(orc.encode(np.eye(K)[None], alpha, beta)).sum(axis=2).max()
+        assert np.abs(got - ref).max() <= bound, (D, np.abs(got - ref).max(), bound)
+        assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * N * D:] == 7.5), D
+
+
 def test_encode_node_coincidence_passes_query_through(gpu):
     torch, binding, dev = gpu
     alpha, beta = orc.chebyshev_nodes(2, 5)
