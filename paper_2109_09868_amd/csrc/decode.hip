@@ -10,6 +10,7 @@
 //    row per group (up to sixteen classes) or per (group, 64 classes).
 #include "decode_common.h"
 #include "rows.h"
+#include "sectors.h"
 #include "survivors.h"
 
 namespace approxifer {
@@ -179,6 +180,138 @@ __global__ __launch_bounds__(kWave) void decode_stream_kernel(const float *__res
                 dst[0] = static_cast<float>(acc[j][0]);
                 if (floats > 1) dst[1] = static_cast<float>(acc[j][1]);
                 if (floats > 2) dst[2] = static_cast<float>(acc[j][2]);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// decoder on the float64 matrix cores
+// ------------------------------------------------------------------------------------
+// out = W (K x n) * Y (n x classes) with v_mfma_f64_16x16x4_f64, a workgroup of four waves per (group, tile of 64 vectors), the
+// tiles those of sectors.h: the waves compute sixteen vectors each and exchange sixteen output rows at a time through LDS,
+// from where they are stored as whole sectors.  Operand layout, lane l of the wave (c = l % 16, k = l / 16):
+//   A: element (row c, k)    B: element (k, column c)    D: register t holds element (row 4 t + k, column c)
+// so one 128-bit load of survivor 4 s + k gives the B operands of k-step s for four sets of columns, as in the encoder.
+// NS k-steps: up to 4 NS survivors; their rows stay in registers for all ceil(K / 16) rounds.  Four waves per SIMD (79 to 125
+// registers) hide the chain mask -> survivors -> rows and weights -> products; left to itself the compiler takes registers for
+// two (K = 32, 36 groups of 32000 classes 99 us, with four 79).  An HBM stream next to float64 matrix issue (half of it at K = 32);
+// two or four tiles to a workgroup that share their weights: 84 and 101 us where one each takes 81 (K = 20, 58 groups).
+// A query on the node of a worker that answered takes that worker's row as it is, whatever the others returned (coincide: the
+// call has such nodes; the search for them in every workgroup is a tenth of the time at K = 32, so the host looks first).
+// dynamic LDS: float stage[16][kStageRow] | double WdT[4 NS][KP] | alpha_s[K] | beta_s[N] | int F[N] | n | any hit | hit[64],
+// KP = matrix_stride(K)
+constexpr int kTileThreads = 256;
+constexpr int kStageRow = 256 + 4;
+// doubles between survivors in WdT: an odd number of 16-double lines, so that the four a wave reads lie in distinct banks
+__host__ __device__ constexpr int matrix_stride(int K) { return 16 * (((K + 15) / 16) | 1); }
+
+template <int NS>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(NS <= 9 ? 4 : 3))) void decode_matrix_kernel(
+    const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out, int32_t *__restrict__ status,
+    int K, int N, int S, int64_t C, uint32_t per_row, int width, int halo, int sign_mode, int coincide, const Nodes nodes) {
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    extern __shared__ double lds_d[];
+    const int KP = matrix_stride(K);
+    float *stage = reinterpret_cast<float *>(lds_d);
+    double *WdT = lds_d + 16 * kStageRow / 2;
+    double *alpha_s = WdT + 4 * NS * KP;
+    double *beta_s = alpha_s + K;
+    int *F = reinterpret_cast<int *>(beta_s + N);
+    int *n_sh = F + N;
+    int *hit = n_sh + 2;                                      // survivor whose node query j is, or -1; n_sh[1]: any
+    const int lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const RowTile t = row_tile(blockIdx.x, per_row, width, halo, C);
+
+    stage_nodes(nodes, K, N, alpha_s, beta_s);
+    for (int e = threadIdx.x; e < 4 * NS * KP; e += kTileThreads) WdT[e] = 0.0;
+    if (coincide && threadIdx.x < 64) hit[threadIdx.x] = -1;
+    if (wv == 0) {
+        const int n = survivors_from_mask(mask + t.g * N, N, F);
+        if (lane == 0) {
+            n_sh[0] = n;
+            n_sh[1] = 0;
+        }
+    }
+    __syncthreads();
+    const int nF = *n_sh;
+    const bool good = S < 0 ? nF >= 1 : nF == N - S;
+    if (t.first && threadIdx.x == 0 && status != nullptr) status[t.g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    if (!good) return;
+
+    const int krow = lane >> 4;
+    const int vec = wv * 16 + (lane & 15);                    // this lane's vector of the tile while computing
+    const int c = t.column(vec);
+    const float *pg = preds + static_cast<size_t>(t.g) * N * C + load_column(t, c, C);
+    v4f y[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int r = 4 * s + krow;
+        if (4 * s < nF)
+            y[s] = __builtin_nontemporal_load(reinterpret_cast<const v4f_dword_aligned *>(
+                pg + static_cast<size_t>(F[r < nF ? r : nF - 1]) * C));
+    }
+    for (int j = wv; coincide && j < K; j += kTileThreads / kWave)
+        if (lane < nF && alpha_s[j] == beta_s[F[lane]]) {     // nodes are distinct: at most one lane
+            hit[j] = lane;
+            n_sh[1] = 1;
+        }
+    decoder_weights(alpha_s, beta_s, F, nF, K, KP, sign_mode, WdT);
+    __syncthreads();
+    const bool over = over_the_end(t, c);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        if (t.last && C % 4 != 0) y[s] = finish_vector(y[s], over, static_cast<int>(C % 4));
+        if (4 * s + krow >= nF) y[s] = v4f(0.0f);             // no survivor: whatever the row holds counts for nothing
+    }
+
+    const bool hits = coincide && n_sh[1] != 0;
+    float *og = out + static_cast<size_t>(t.g) * K * C + t.start;
+    for (int j0 = 0; j0 < K; j0 += 16) {
+        v4d acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = v4d{0.0, 0.0, 0.0, 0.0};
+        const double *w = WdT + krow * KP + j0 + (lane & 15);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (4 * s < nF) {
+                const double a = w[4 * s * KP];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, static_cast<double>(y[s][e]), acc[e], 0, 0, 0);
+            }
+        }
+        if (j0 > 0) __syncthreads();                          // the rows of the round before are stored
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v4f v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = static_cast<float>(acc[e][r]);
+            *reinterpret_cast<v4f *>(stage + (4 * r + krow) * kStageRow + 4 * vec) = v;
+        }
+        if (hits) {
+            // behind this wave's own stores to the same columns; the row is read once more (kept, it costs all calls a fifth
+            // of their time: 100 registers for 79)
+            __builtin_amdgcn_wave_barrier();
+            for (int r = krow; r < 16; r += 4) {
+                const int h = hit[j0 + r];
+                if (h < 0) continue;
+                v4f v = *reinterpret_cast<const v4f_dword_aligned *>(preds + (static_cast<size_t>(t.g) * N + F[h]) * C +
+                                                                     load_column(t, c, C));
+                if (t.last && C % 4 != 0) v = finish_vector(v, over_the_end(t, c), static_cast<int>(C % 4));
+                *reinterpret_cast<v4f *>(stage + r * kStageRow + 4 * vec) = v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = j0 + 4 * wv + r;
+            if (j < K) {
+                float *row = og + static_cast<size_t>(j) * C;
+                const int at = static_cast<int>(reinterpret_cast<uintptr_t>(row) / sizeof(float)) & (kSector - 1);
+                store_sectors(row, *reinterpret_cast<const v4f *>(stage + (4 * wv + r) * kStageRow + 4 * lane), t.column(lane), at,
+                              t);
             }
         }
     }
@@ -1059,6 +1192,25 @@ bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
     if (vectors <= 25 && G >= 2048) return true;
     return K > 8 && S >= 0 && (K > 12 || N - S <= 12) && tiles >= 1024 && tiles <= kTilesOneRound;
 }
+// Whether decode_matrix_kernel decodes the call (more than eight queries, up to 64 workers, more than sixteen classes).  Its
+// tile takes four waves, whatever the row's length, so it is not for many groups of short rows; times without and with it:
+//  - K > 16, where the other kernel has a wave per four queries and 4-byte accesses for rows that are only 4-byte aligned: from 96
+//    classes on (K = 32, 1170 groups of 1001 classes 261 and 106 us, 1171 of 1000 150 and 106; K = 24, 15470 of 101 259 and 206) and in
+//    calls of few tiles (K = 24, 24 classes, 217 groups 14.9 and 8.6 us; K = 17, 17 classes, 432 groups 9.9 and 10.3);
+//  - K = 9..16 in rows that are only 4-byte aligned: from 96 classes on (K = 16, 2341 groups of 1001 classes 104 and 78 us, 78
+//    groups 16.3 and 7.5), with K = 9..11, which leave a third of the products' rows empty, up to 4096 tiles (K = 9, 832 groups of
+//    1001 classes 27.9 and 24.1, 4162 groups 98 and 103), and in calls of few tiles (K = 12, 50 classes, 208 groups 10.9 and
+//    5.8 us, 2083 groups 16.0 and 14.3);
+//  - K = 9..16 otherwise in calls of few tiles, whose time is one workgroup's chain: its weights are four waves' work (K = 12, ten
+//    groups of 1000 classes 7.2 and 5.3 us, 104 groups 7.1 and 7.0, 156 of 4000 classes 14.3 and 16.1; K = 13, 24 groups of 4000
+//    classes 8.1 and 6.3, 144 groups 20.4 and 17.2, 2884 of 1000 classes 68 and 83).
+bool matrix_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
+    if (K <= 8 || N > kWave || C <= kRowLanes) return false;
+    const int64_t tiles = G * ((C + 239) / 240);
+    if (K > 16) return C >= 96 || tiles <= 400;
+    if (!vec4) return C >= 96 ? K > 11 || tiles <= 4096 : tiles <= (C >= 48 ? 2048 : 400);
+    return tiles <= (K > 12 ? 1024 : 400) || (K > 12 && C >= 96 && tiles <= 4096 && !tiles_shape(K, N, S, C, G, vec4));
+}
 // Whether decode_top1_tiles_kernel decides the call: all of them (0.76 of the time of a workgroup per group over 1600
 // shapes), but for long rows that are only 4-byte aligned with few queries to make up for their ends (K = 3, 7900 groups of
 // 750 classes 48.8 and 79.5 us; K = 8 from 4096 groups on 3 to 8 % slower).
@@ -1101,6 +1253,30 @@ int run_rows(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t 
 #undef APPROXIFER_ROWS
 }
 
+bool nodes_coincide(const Nodes &nodes, int K, int N) {
+    int any = 0;
+    for (int j = 0; j < K; ++j)
+        for (int i = 0; i < N; ++i) any |= nodes.alpha[j] == nodes.beta[i];
+    return any != 0;
+}
+
+template <int NS>
+int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K, int N, int S,
+               int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
+    const int halo = whole_sectors(d_out, C) ? 0 : kTileHalo;
+    const SectorTiles t = sector_tiles(G, C, halo);
+    if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    const size_t lds = sizeof(float) * 16 * kStageRow + sizeof(double) * (static_cast<size_t>(4 * NS) * matrix_stride(K) + K + N) +
+                       sizeof(int) * (static_cast<size_t>(N) + 2 + APPROXIFER_MAX_K);
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(decode_matrix_kernel<NS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
+    return launch_status(launch_kernel(decode_matrix_kernel<NS>, dim3(static_cast<unsigned>(t.total)),
+                                       dim3(kTileThreads), lds, stream, d_preds, d_mask, d_out, d_status, K, N, S, C,
+                                       static_cast<uint32_t>(t.per_row), t.width, halo, sign_mode, nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
+}
+
 }  // namespace
 
 int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K,
@@ -1109,6 +1285,14 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
         return run_rows<false>(d_preds, d_mask, d_out, nullptr, nullptr, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     const int KP = (K + 3) & ~3;
     const bool vec4 = (C % 4 == 0) && aligned16(d_preds) && aligned16(d_out);
+    if (matrix_shape(K, N, S, C, G, vec4)) {
+        const int steps = ((S < 0 ? N : N - S) + 3) / 4;
+        if (steps <= 4) return run_matrix<4>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+        if (steps <= 6) return run_matrix<6>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+        if (steps <= 9) return run_matrix<9>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+        if (steps <= 12) return run_matrix<12>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+        return run_matrix<16>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
+    }
     const int64_t Cv = vec4 ? C / 4 : C;
     const int64_t ctiles = (Cv + kColsPerTile - 1) / kColsPerTile;
     const int64_t blocks = G * ctiles;

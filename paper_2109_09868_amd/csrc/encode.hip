@@ -25,6 +25,7 @@
 //    per CU by reserving LDS it does not use: each wave has all K of its 128-bit loads in flight,
 //    which is enough to cover latency (1.76 ms uncapped, 1.60 ms at 6 waves per CU).
 #include "common.h"
+#include "sectors.h"
 
 namespace approxifer {
 namespace {
@@ -65,86 +66,6 @@ template <int VEC, bool UNAL = false>
 __device__ __forceinline__ void store_stream(float *p, typename VecOf<VEC>::type v) {
     typedef typename MemOf<VEC, UNAL>::type M;
     __builtin_nontemporal_store(static_cast<M>(v), reinterpret_cast<M *>(p));
-}
-
-// ---- rows that do not begin on a 64-byte sector -------------------------------------------------------------------
-// A wave whose row segment begins or ends inside a sector writes that sector in part, and its neighbour the rest: the
-// memory pays for both as for two.  Where rows are not whole sectors (D % 16 != 0, or a base address that is none) a tile
-// therefore writes, of every coded row, the whole sectors that end inside it (tile [start, start + width) writes from the
-// sector of column `start` up to the one of column start + width), and loads sixteen columns more on its left for that.
-// Lane l of a wave holds columns start - 16 + 4 l .. + 3; a coded row whose phase is not a multiple of four floats is
-// shifted along the lanes first, so that every store is one aligned 16-byte piece.  Only a row's own first and last
-// sector are written in part, in single floats.
-constexpr int kSector = 16;                               // floats
-constexpr int kTileHalo = 4;                              // lanes on the left that a tile shares with its neighbour
-constexpr int kTileVecs = 64 - kTileHalo;                 // .. so that this many are its own; the row's last tile leaves one
-                                                          // lane more for what the shift pushes past the row's end
-
-struct RowTile {
-    int64_t g;                                            // group
-    int64_t start;                                        // first column, a multiple of four
-    int width;                                            // columns of a tile that is not the row's last
-    int left;                                             // last tile: columns up to the row's end
-    bool first, last;
-    // first column of the tile's vector v, relative to start: the row's first tile has no neighbour on the left
-    __device__ __forceinline__ int column(int v) const { return 4 * v - (first ? 0 : 4 * kTileHalo); }
-};
-// tile `id` of the batch, `per_row` tiles to a row
-__device__ __forceinline__ RowTile row_tile(uint32_t id, uint32_t per_row, int width, int64_t D) {
-    RowTile t;
-    const uint32_t g = id / per_row;
-    const uint32_t k = id - g * per_row;
-    t.g = g;
-    t.start = static_cast<int64_t>(k) * width;
-    t.width = width;
-    t.first = k == 0;
-    t.last = k + 1 == per_row;
-    t.left = t.last ? static_cast<int>(D - t.start) : width;
-    return t;
-}
-// Where lane-vector c (relative to the tile's start) of a query row is loaded from: always inside the row.  The vector over
-// the row's end is loaded from its last four columns; finish_vector() then moves its columns to their places.
-__device__ __forceinline__ int64_t load_column(const RowTile &t, int c, int64_t D) {
-    const int64_t col = t.start + c;
-    if (col < 0) return 0;
-    return col + 4 <= D ? col : D - 4;
-}
-__device__ __forceinline__ bool over_the_end(const RowTile &t, int c) { return t.last && c < t.left && c + 4 > t.left; }
-__device__ __forceinline__ v4f finish_vector(v4f x, bool over, int tail) {          // tail = D % 4, not 0
-    v4f y = x;
-    y[0] = tail == 1 ? x[3] : (tail == 2 ? x[2] : x[1]);
-    y[1] = tail == 2 ? x[3] : x[2];
-    y[2] = x[3];
-    return over ? y : x;
-}
-__device__ __forceinline__ float from_lane_below(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kDppWaveShr1, 0xF, 0xF, true));
-}
-// One coded row of the tile: v holds the lane's columns c .. c + 3 (c = 4 lane - 16, relative to the tile's start), `at` =
-// floats by which column `start` lies behind a sector's begin (the same for all lanes), row = address of column `start`.
-// Every lane of the wave calls it.
-__device__ __forceinline__ void store_sectors(float *row, v4f v, int c, int at, const RowTile &t) {
-    const int s = at & 3;
-    if (s & 2) {
-        const float p2 = from_lane_below(v[2]), p3 = from_lane_below(v[3]);
-        v = v4f{p2, p3, v[0], v[1]};
-    }
-    if (s & 1) {
-        const float p3 = from_lane_below(v[3]);
-        v = v4f{p3, v[0], v[1], v[2]};
-    }
-    const int q = c - s;
-    const int lo = t.first ? 0 : -at;
-    const int hi = t.last ? t.left - 3 : t.width - ((at + t.width) & (kSector - 1));
-    if (q >= lo && q < hi) store_stream<4>(row + q, v);
-    if (t.first || t.last) {
-        const bool part = (t.first && q < 0 && q > -4) || (t.last && q < t.left && q + 4 > t.left);
-        if (part) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (q + e >= lo && (!t.last || q + e < t.left)) __builtin_nontemporal_store(v[e], row + q + e);
-        }
-    }
 }
 
 // ---- l_j(beta_i) in float64, one group of LPR lanes per worker row ---------------------
@@ -262,7 +183,7 @@ __global__ __launch_bounds__(THREADS) void encode_sectors_kernel(
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const uint32_t id = blockIdx.x * (THREADS / kWave) + __builtin_amdgcn_readfirstlane(wave_id());
-    const RowTile t = row_tile(id < tiles ? id : 0, per_row, width, D);
+    const RowTile t = row_tile(id < tiles ? id : 0, per_row, width, kTileHalo, D);
     const int c = t.column(lane);
     const float *xg = queries + static_cast<size_t>(t.g) * K * D + load_column(t, c, D);
 
@@ -438,7 +359,7 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_sectors_kernel(
     float *stage = wA + mtiles * KS * 64;
     const int lane = lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(wave_id());
-    const RowTile t = row_tile(blockIdx.x, per_row, width, D);
+    const RowTile t = row_tile(blockIdx.x, per_row, width, kTileHalo, D);
     const int krow = lane >> 4;
     const int vec = wv * 16 + (lane & 15);                    // this lane's vector of the tile while computing
     const int c = t.column(vec);
@@ -521,21 +442,6 @@ int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, in
 // whole sectors).
 constexpr int encode_threads(int K, bool UNAL) { return K <= 16 && !UNAL ? 64 : 256; }
 
-// Tiles of whole sectors: as many as it takes at kTileVecs vectors each, all of one width.
-struct SectorTiles {
-    int64_t per_row, total;
-    int width;                              // columns, a multiple of four
-};
-inline SectorTiles sector_tiles(int64_t G, int64_t D) {
-    const int64_t vecs = (D + 3) / 4;
-    SectorTiles t;
-    t.per_row = vecs <= 63 ? 1 : (vecs + 1 + kTileVecs - 1) / kTileVecs;
-    t.width = static_cast<int>(4 * ((vecs + t.per_row - 1) / t.per_row));
-    t.per_row = (vecs + t.width / 4 - 1) / (t.width / 4);
-    t.total = G * t.per_row;
-    return t;
-}
-
 // Workgroups per CU, where the stage and the weights leave room for them (six, eight and four at 300 MB: K = 12, N = 28,
 // 350 floats 77, 73, 82 us, 10003 floats 56, 59, 57; K = 8, N = 24, 350 floats 82, 74, 89, 10003 floats 56, 58, 60; with two
 // stages, a barrier less, and four 58 to 61 at 10003 floats).
@@ -544,7 +450,7 @@ constexpr int mfma_sector_blocks(int64_t D) { return D < 2048 ? 8 : 6; }
 template <int KS>
 int run_encode_mfma_sectors(const float *d_queries, float *d_coded, int64_t G, int K, int N, int64_t D, const Nodes &nodes,
                             hipStream_t stream) {
-    const SectorTiles t = sector_tiles(G, D);
+    const SectorTiles t = sector_tiles(G, D, kTileHalo);
     if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
         const size_t lds_used = (static_cast<size_t>((N + 15) / 16) * KS * 64 + 16 * kStageRow) * sizeof(float);
         size_t lds = (static_cast<size_t>(kLdsPerCu / mfma_sector_blocks(D)) / 512) * 512;
@@ -571,7 +477,7 @@ int run_encode_sectors(const float *d_queries, float *d_coded, int64_t G, int N,
                        hipStream_t stream) {
     constexpr int KP = (K + 3) & ~3;
     constexpr int THREADS = 256;
-    const SectorTiles t = sector_tiles(G, D);
+    const SectorTiles t = sector_tiles(G, D, kTileHalo);
     if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const int per_cu = sector_blocks(K, D);
     const size_t lds_used = static_cast<size_t>(N) * KP * sizeof(float);
@@ -654,10 +560,8 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
 // N = 12, 64 x 3 x 299 x 299 floats: 270 and 231 us), the matrix-core variant 0.62 to 1.0 (K = 32, N = 48, 10003 floats: 100 and 65
 // us), but K = 20, N = 24 with tiles of fewer than forty own vectors, 156 floats: 74 and 78 us, 258 floats: 86 and 98 us.
 inline bool sector_rows(const float *d_queries, const float *d_coded, int K, int N, int64_t D) {
-    const bool whole = reinterpret_cast<uintptr_t>(d_queries) % 64 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 64 == 0 &&
-                       D % kSector == 0;
-    if (whole || D < kSectorRowsMinD) return false;
-    return K < kMfmaMinK || 2 * N >= 3 * K || sector_tiles(1, D).width >= 4 * 40;
+    if ((whole_sectors(d_queries, D) && whole_sectors(d_coded, D)) || D < kSectorRowsMinD) return false;
+    return K < kMfmaMinK || 2 * N >= 3 * K || sector_tiles(1, D, kTileHalo).width >= 4 * 40;
 }
 
 template <int K>

@@ -1487,6 +1487,49 @@ def test_paper_operating_point_workloads_full_size(gpu):
 # --------------------------------------------------------------------------------------
 # per-group straggler counts (S = APPROXIFER_S_FROM_MASK): ragged masks
 # --------------------------------------------------------------------------------------
+@pytest.mark.parametrize("K,N,S", [
+    (9, 9, 0), (9, 12, 2), (12, 20, 8), (13, 16, 0), (16, 20, 4), (16, 17, 1), (17, 17, 0), (17, 40, 3), (20, 26, 2), (31, 36, 3),
+    (32, 33, 0), (33, 40, 3), (48, 48, 0), (48, 64, 16), (64, 64, 0), (20, 50, -1), (16, 33, -1), (64, 64, -1),
+])
+def test_decode_on_the_matrix_cores(gpu, K, N, S):
+    # few tiles, so that every row length comes here: 4, 6, 9, 12 and 16 k-steps and remainders, one to four rounds of sixteen
+    # queries, tiles of whole and of ragged sectors (one up to 63 vectors, 60 a tile less one), row ends of every remainder,
+    # output rows of every phase, a rejected mask; predictions of workers that did not answer are NaN
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(100 * K + N)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    for C, off_in, off_out in [(17, 0, 0), (18, 1, 3), (96, 0, 0), (97, 0, 5), (240, 2, 0), (251, 0, 0), (252, 0, 2), (253, 3, 1),
+                               (256, 0, 0), (272, 0, 0), (476, 0, 0), (477, 1, 0), (1000, 0, 0), (1003, 0, 0)]:
+        G = 4
+        cnt = rng.integers(max(1, N // 2), N + 1, G) if S < 0 else np.full(G, N - S)
+        mask = np.zeros((G, N), np.uint8)
+        for g in range(G):
+            mask[g, rng.choice(N, cnt[g], replace=False)] = 1
+        Y = rng.standard_normal((G, N, C)).astype(np.float32)
+        ref, _ = orc.decode(Y, mask, alpha, beta, None if S < 0 else S, 1)
+        bad = mask.copy()
+        if S < 0:
+            bad[2] = 0
+        elif S > 0:
+            bad[2] = 1
+        else:
+            bad[2, 0] = 0
+        Yn = np.where(bad[:, :, None] != 0, Y, np.float32("nan"))
+        flat_in = torch.full((G * N * C + off_in + 3,), float("nan"), dtype=torch.float32, device=dev)
+        flat_in[off_in:off_in + G * N * C] = torch.from_numpy(Yn).to(dev).reshape(-1)
+        flat_out = torch.full((G * K * C + off_out + 40,), 7.5, dtype=torch.float32, device=dev)
+        out = flat_out[off_out:off_out + G * K * C].view(G, K, C)
+        _, st = binding.approxifer_decode(flat_in[off_in:off_in + G * N * C].view(G, N, C), torch.from_numpy(bad).to(dev), alpha, beta,
+                                          binding.S_FROM_MASK if S < 0 else S, 1, out=out)
+        assert st.cpu().tolist() == [0, 0, st.cpu().tolist()[2], 0] and st.cpu().tolist()[2] != 0
+        got = out.cpu().numpy()
+        good = [0, 1, 3]
+        # one rounding to float32; the float64 sums before it (weights of either sign, Lebesgue constant below 10) leave 1e-12
+        assert np.all(np.abs(got[good] - ref[good]) <= 2.0 ** -24 * np.abs(ref[good]) + 1e-12 * np.abs(Y).max()), C
+        assert np.all(got[2] == 7.5)
+        assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * K * C:] == 7.5), C
+
+
 @pytest.mark.parametrize("K,N,C,G", [(3, 9, 5, 12), (8, 12, 100, 40), (12, 20, 1000, 24), (16, 70, 36, 10), (5, 128, 3, 9),
                                      (10, 30, 10, 64), (16, 32, 16, 33)])
 @pytest.mark.parametrize("mode", [0, 1])
