@@ -1,4 +1,4 @@
-"""Compile the HIP sources into paper_2109_09868_amd/libapproxifer.so for gfx950."""
+"""Compile the HIP sources into paper_2109_09868_amd/libapproxifer.so for gfx950, and the binding's marshalling module."""
 from __future__ import annotations
 
 import os
@@ -26,6 +26,28 @@ def hipcc_path() -> str:
     if not os.path.exists(exe):
         raise RuntimeError("hipcc not found; the library cannot be built")
     return exe
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile csrc/marshal.cpp (host code on torch's C++ interface) into the module paper_2109_09868_amd._marshal."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    out = os.path.join(PKG_DIR, "_marshal.so")
+    include = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), sysconfig.get_paths()["include"],
+               os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path()))), "include")]
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *("-I" + p for p in include),
+           os.path.join(CSRC, "marshal.cpp"), "-o", out, *("-L" + p for p in cpp_extension.library_paths()),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s\n%s" % (r.stdout, r.stderr))
+    return out
 
 
 def build_library(verbose: bool = False, jobs: int = 4) -> str:
@@ -60,3 +82,4 @@ def build_library(verbose: bool = False, jobs: int = 4) -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_marshal(verbose=True))
