@@ -455,6 +455,132 @@ __device__ __forceinline__ void best_step(Best &b) {
 }
 
 // ------------------------------------------------------------------------------------
+// fused decoder + top-1 on the float64 matrix cores
+// ------------------------------------------------------------------------------------
+// One workgroup per group.  A wave takes stripes of sixteen vectors (64 classes), wave, wave + nwaves, .., multiplies as
+// decode_matrix_kernel does and keeps, per lane, the best (value, class) so far of the 4 R queries whose rows it holds
+// (R >= ceil(K / 16) rounds); the next stripe's rows are on their way meanwhile.  Nothing is stored until the end: sixteen
+// lanes merge by DPP, the waves through LDS.  Ties: the smaller class index; NaN never wins.
+// It is the chain load -> products -> best that bounds it, then float64 matrix issue (K = 32: see matrix_top1_shape).
+// dynamic LDS: double WdT[4 NS][KP] | alpha_s[K] | beta_s[N] | Best merged[waves][16 R] | int F[N] | n
+constexpr int top1_matrix_threads(int NS, int R) { return NS * R <= 8 ? 1024 : 512; }   // more registers: fewer waves
+
+template <int NS, int R>
+__global__ __launch_bounds__(top1_matrix_threads(NS, R)) void decode_top1_matrix_kernel(
+    const float *__restrict__ preds, const uint8_t *__restrict__ mask, int32_t *__restrict__ top1, float *__restrict__ score,
+    int32_t *__restrict__ status, int K, int N, int S, int64_t C, int sign_mode, const Nodes nodes) {
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    extern __shared__ double lds_d[];
+    const int KP = matrix_stride(K);
+    const int waves = blockDim.x / kWave;
+    double *WdT = lds_d;
+    double *alpha_s = WdT + 4 * NS * KP;
+    double *beta_s = alpha_s + K;
+    Best *merged = reinterpret_cast<Best *>(beta_s + N);
+    int *F = reinterpret_cast<int *>(merged + waves * 16 * R);
+    int *n_sh = F + N;
+    const int lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int64_t g = blockIdx.x;
+
+    stage_nodes(nodes, K, N, alpha_s, beta_s);
+    for (int e = threadIdx.x; e < 4 * NS * KP; e += blockDim.x) WdT[e] = 0.0;
+    if (wv == 0) {
+        const int n = survivors_from_mask(mask + g * N, N, F);
+        if (lane == 0) *n_sh = n;
+    }
+    __syncthreads();
+    const int nF = *n_sh;
+    const bool good = S < 0 ? nF >= 1 : nF == N - S;
+    if (threadIdx.x == 0 && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    if (!good) return;
+
+    const int krow = lane >> 4, c = lane & 15;
+    const float *pg = preds + static_cast<size_t>(g) * N * C;
+    const float *rows[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) rows[s] = pg + static_cast<size_t>(F[4 * s + krow < nF ? 4 * s + krow : nF - 1]) * C;
+    const int64_t stripes = (C + 63) / 64;
+    v4f y[NS], next[NS];
+    const auto load = [&](v4f(&to)[NS], int64_t stripe) {     // vectors past the row's end come from its last four columns
+        const int64_t col = 64 * stripe + 4 * c;
+        const int64_t at = col + 4 <= C ? col : C - 4;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (4 * s < nF) to[s] = __builtin_nontemporal_load(reinterpret_cast<const v4f_dword_aligned *>(rows[s] + at));
+    };
+    if (wv < stripes) load(y, wv);
+    decoder_weights(alpha_s, beta_s, F, nF, K, KP, sign_mode, WdT);
+    __syncthreads();
+
+    Best best[R][4];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) best[m][t] = Best{-__builtin_inf(), 0x7fffffff};
+    for (int64_t stripe = wv; stripe < stripes; stripe += waves) {
+        if (stripe + waves < stripes) load(next, stripe + waves);
+        const int64_t col = 64 * stripe + 4 * c;
+        const bool tail = stripe + 1 == stripes && C % 4 != 0;
+        const bool over = col < C && col + 4 > C;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (tail) y[s] = finish_vector(y[s], over, static_cast<int>(C % 4));
+            if (4 * s + krow >= nF) y[s] = v4f(0.0f);         // no survivor: whatever the row holds counts for nothing
+        }
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            if (16 * m >= K) break;
+            v4d acc[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = v4d{0.0, 0.0, 0.0, 0.0};
+            const double *w = WdT + krow * KP + 16 * m + c;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                if (4 * s < nF) {
+                    const double a = w[4 * s * KP];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, static_cast<double>(y[s][e]), acc[e], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in = col + e < C;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (in && acc[e][t] > best[m][t].v) best[m][t] = Best{acc[e][t], static_cast<int>(col + e)};
+            }
+        }
+        if (stripe + waves < stripes) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) y[s] = next[s];
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            Best b = best[m][t];
+            best_step<kDppQuadXor1>(b);
+            best_step<kDppQuadXor2>(b);
+            best_step<kDppRowHalfMirror>(b);
+            best_step<kDppRowMirror>(b);
+            if (c == 0) merged[wv * 16 * R + 16 * m + 4 * t + krow] = b;
+        }
+    __syncthreads();
+    for (int j = threadIdx.x; j < K; j += blockDim.x) {
+        Best b = merged[j];
+        for (int w = 1; w < waves; ++w) {
+            const Best o = merged[w * 16 * R + j];
+            if (better(o.v, o.i, b)) b = o;
+        }
+        top1[g * K + j] = b.i == 0x7fffffff ? 0 : b.i;
+        if (score != nullptr) score[g * K + j] = static_cast<float>(b.v);
+    }
+}
+
+// ------------------------------------------------------------------------------------
 // fused decoder + top-1 with all K accumulator rows in one wave (K <= 16, up to 64 survivors)
 // ------------------------------------------------------------------------------------
 // One workgroup per group; its waves take the column tiles wave, wave + nwaves, .. and each keeps, per lane, the
@@ -1277,6 +1403,55 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
                                        static_cast<uint32_t>(t.per_row), t.width, halo, sign_mode, nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
 }
 
+// Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes, not
+// few groups of thousands of classes: one workgroup's loads in flight are too few there, K = 32, one group of 32000 classes 104 and
+// 435 us).  Times without and with it: K = 32, 2341 groups of 1001 classes 644 and 172 us, 23205 of 101 1238 and 304, 2343 of
+// 1000 292 and 170; K = 12, 6243 of 1001 204 and 96, 6250 of 1000 133 and 98, 206 of 101 15.5 and 5.6; K = 16, 156 of 1000 12.2 and
+// 10.4.  K <= 8 leaves half of the products' rows empty (K = 8, 9375 of 1000 100 and 117).  K = 17..27 with few groups of whole
+// vectors stays with the waves that share no rows (K = 17, 147 of 1000 17.8 and 20.8).  Up to sixteen queries the other kernels
+// hand on the row of a worker whose node a query has, whatever the other workers returned; calls with such nodes stay there.
+bool top1_matrix_shape(int K, int N, int64_t C, int64_t G, bool vec4, const Nodes &nodes) {
+    if (K <= 8 || N > kWave || C <= kRowLanes) return false;
+    if (K <= 16) return !nodes_coincide(nodes, K, N);
+    return !vec4 || K >= 28 || G >= 256;
+}
+
+template <int NS, int R>
+int run_top1_matrix_shape(const float *d_preds, const uint8_t *d_mask, int32_t *d_top1, float *d_score, int32_t *d_status,
+                          int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
+    if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    // a wave per stripe, up to four; up to the kernel's most where there are few groups to fill the chip with, and then four at
+    // least: the weights are the whole workgroup's work
+    const int64_t stripes = (C + 63) / 64;
+    int64_t waves = G >= 1024 ? 4 : G >= 512 ? 8 : 16;
+    if (waves > top1_matrix_threads(NS, R) / kWave) waves = top1_matrix_threads(NS, R) / kWave;
+    if (waves > stripes) waves = G >= 1024 || stripes > 4 ? stripes : 4;
+    const size_t lds = sizeof(double) * (static_cast<size_t>(4 * NS) * matrix_stride(K) + K + N) + sizeof(Best) * waves * 16 * R +
+                       sizeof(int) * (static_cast<size_t>(N) + 2);
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(decode_top1_matrix_kernel<NS, R>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) != hipSuccess)
+        return APPROXIFER_ERR_LAUNCH;
+    return launch_status(launch_kernel(decode_top1_matrix_kernel<NS, R>, dim3(static_cast<unsigned>(G)),
+                                       dim3(static_cast<unsigned>(waves) * kWave), lds, stream, d_preds, d_mask, d_top1, d_score,
+                                       d_status, K, N, S, C, sign_mode, nodes));
+}
+
+int run_top1_matrix(const float *d_preds, const uint8_t *d_mask, int32_t *d_top1, float *d_score, int32_t *d_status, int64_t G,
+                    int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
+    const int steps = ((S < 0 ? N : N - S) + 3) / 4;
+#define APPROXIFER_TOP1_MATRIX(NS)                                                                                      \
+    (K <= 16 ? run_top1_matrix_shape<NS, 1>(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream) \
+     : K <= 32                                                                                                           \
+         ? run_top1_matrix_shape<NS, 2>(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream) \
+         : run_top1_matrix_shape<NS, 4>(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream))
+    if (steps <= 4) return APPROXIFER_TOP1_MATRIX(4);
+    if (steps <= 6) return APPROXIFER_TOP1_MATRIX(6);
+    if (steps <= 9) return APPROXIFER_TOP1_MATRIX(9);
+    return APPROXIFER_TOP1_MATRIX(16);
+#undef APPROXIFER_TOP1_MATRIX
+}
+
 }  // namespace
 
 int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K,
@@ -1363,6 +1538,8 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     // few groups with very many classes: the split below (K = 12, one group of 21844 classes 32 us, 92 with tiles; K = 4,
     // 4096 classes 10.5 and 9.3; K = 16, 128 groups of 50256 classes 269 and 307)
     const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;
+    if (!few_groups && top1_matrix_shape(K, N, C, G, vec4, nodes))
+        return run_top1_matrix(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     if (top1_tiles_shape(K, N, C, G, vec4) && !few_groups) {
         const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
         int R = 1;

@@ -1488,6 +1488,38 @@ def test_paper_operating_point_workloads_full_size(gpu):
 # per-group straggler counts (S = APPROXIFER_S_FROM_MASK): ragged masks
 # --------------------------------------------------------------------------------------
 @pytest.mark.parametrize("K,N,S", [
+    (9, 11, 1), (12, 20, 8), (13, 16, 0), (16, 17, 1), (16, 40, 4), (17, 17, 0), (20, 26, 2), (32, 33, 0), (28, 50, 20), (33, 40, 3),
+    (48, 64, 16), (64, 64, 0), (20, 50, -1), (16, 33, -1),
+])
+def test_decode_top1_on_the_matrix_cores(gpu, K, N, S):
+    # k-steps and rounds as above; one stripe of 64 classes, remainders of a stripe and of a vector, a stripe more than the
+    # waves take at once, a workgroup of one wave (G >= 1024) and of many; a rejected mask; workers without an answer are NaN
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(100 * K + N)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    for C, G in [(17, 3), (64, 1030), (66, 3), (101, 1030), (255, 3), (257, 300), (1001, 3), (1030, 256)]:
+        n = N - S if S >= 0 else N - 2
+        mask = (rng.random((G, N)).argsort(1).argsort(1) < n).astype(np.uint8)
+        Y = rng.standard_normal((G, N, C)).astype(np.float32)
+        Y[0, :, 5] = Y[0, :, 11] = 50.0                       # two classes tie: the smaller
+        mask[1] = 0
+        sent = np.where(mask[:, :, None] != 0, Y, np.float32("nan"))
+        t, s, st = binding.approxifer_decode_top1(torch.from_numpy(sent).to(dev), torch.from_numpy(mask).to(dev), alpha, beta,
+                                                  binding.S_FROM_MASK if S < 0 else S, 1)
+        t, s, st = t.cpu().numpy(), s.cpu().numpy(), st.cpu().numpy()
+        some = [0, 2, G - 1]
+        ref, _ = orc.decode(Y[some], mask[some], alpha, beta, None if S < 0 else S, 1)
+        assert st[1] != 0 and np.all(st[[0] + list(range(2, G))] == 0)
+        assert np.all(t[1] == -1) and np.all(s[1] == 0.0)
+        assert np.array_equal(t[0], np.full(K, 5))
+        for k, g in enumerate(some):
+            top = ref[k].max(axis=1)
+            # one rounding of the winner's value; float64 sums before it as in the decoder
+            assert np.all(np.abs(s[g] - top) <= 2.0 ** -24 * np.abs(top) + 1e-12 * 50.0)
+            assert np.all(ref[k][np.arange(K), t[g]] >= top - 1e-12 * 50.0)
+
+
+@pytest.mark.parametrize("K,N,S", [
     (9, 9, 0), (9, 12, 2), (12, 20, 8), (13, 16, 0), (16, 20, 4), (16, 17, 1), (17, 17, 0), (17, 40, 3), (20, 26, 2), (31, 36, 3),
     (32, 33, 0), (33, 40, 3), (48, 48, 0), (48, 64, 16), (64, 64, 0), (20, 50, -1), (16, 33, -1), (64, 64, -1),
 ])
