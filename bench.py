@@ -27,11 +27,12 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 
 # HBM traffic of one encode launch at the imagenet shape, from two rocprofv3 --pmc runs
 # (profiles/encode_imagenet_hbm_counters.md).  Valid only for the kernel sources hashed here.
-ENCODE_KERNEL_SOURCES = ("paper_2109_09868_amd/csrc/encode.hip", "paper_2109_09868_amd/csrc/common.h")
+ENCODE_KERNEL_SOURCES = ("paper_2109_09868_amd/csrc/encode.hip", "paper_2109_09868_amd/csrc/sectors.h",
+                         "paper_2109_09868_amd/csrc/common.h")
 ENCODE_TRAFFIC = {
-    "sources_sha256": "cdc1ee55fd11f8eb008bbf64033cf9affc7e836b7964cfa9a6d7c02888217384",
-    "fetch_size_kib": 1806373.4, "fetch_factor": 2.0000,     # counter reads half the bytes of a known copy
-    "write_size_kib": 6021171.4, "write_factor": 1.0000,
+    "sources_sha256": "3161c80caeab7bed89ccafadeffb75316ccc451605f507ea18d653d6fbfdee95",
+    "fetch_size_kib": 1806371.5, "fetch_factor": 2.0000,     # counter reads half the bytes of a known copy
+    "write_size_kib": 6021175.8, "write_factor": 1.0000,
 }
 
 

@@ -41,6 +41,7 @@ constexpr int kMfmaMinK = 17;   // from this K on the matrix-core variant serves
 constexpr int kMfmaWideMinK = 8;   // .. and from this K on the shapes with N >= 2K + 4
 constexpr int kMfmaBlocksPerCu = 4;   // matrix-core variant (four waves of 64 columns)
 constexpr int kSectorRowsMinD = 129;   // rows that are not whole 64-byte sectors: tiles of whole sectors from here on
+constexpr int kSectorMinTiles = 2048;   // .. if rows are 16-byte pieces, for calls of this many tiles or more
 constexpr int kMfmaSectorsMinD = 300;   // K <= 16: .. on the matrix cores, where they pay, from here on
 constexpr int kScalarRowsMaxD = 128;   // ragged rows (D % 4 != 0) this short: 64-bit or 4-byte accesses only
 
@@ -559,15 +560,20 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
 // against the kernels that move such rows as they come, 300 MB, 130 to 60000 floats: K <= 16 0.75 to 1.0 of the time (K = 8,
 // N = 12, 64 x 3 x 299 x 299 floats: 270 and 231 us), the matrix-core variant 0.62 to 1.0 (K = 32, N = 48, 10003 floats: 100 and 65
 // us), but K = 20, N = 24 with tiles of fewer than forty own vectors, 156 floats: 74 and 78 us, 258 floats: 86 and 98 us.
-inline bool sector_rows(const float *d_queries, const float *d_coded, int K, int N, int64_t D) {
+// Rows of 16-byte pieces in calls of fewer than kSectorMinTiles tiles, which are one workgroup's chain, stay too: they need no
+// second launch for their last columns, and the shift and the bounds lengthen the chain (K = 14, N = 16, two groups of 3836
+// floats 6.5 and 8.4 us; K = 18, N = 23, 1560 tiles of 24924 floats 15.9 and 17.3).
+inline bool sector_rows(const float *d_queries, const float *d_coded, int64_t G, int K, int N, int64_t D) {
     if ((whole_sectors(d_queries, D) && whole_sectors(d_coded, D)) || D < kSectorRowsMinD) return false;
+    const bool pieces = D % 4 == 0 && reinterpret_cast<uintptr_t>(d_queries) % 16 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 16 == 0;
+    if (pieces && sector_tiles(G, D, kTileHalo).total < kSectorMinTiles) return false;
     return K < kMfmaMinK || 2 * N >= 3 * K || sector_tiles(1, D, kTileHalo).width >= 4 * 40;
 }
 
 template <int K>
 int run_encode_k(const float *d_queries, float *d_coded, int64_t G, int N, int64_t D, const Nodes &nodes,
                  hipStream_t stream) {
-    if (sector_rows(d_queries, d_coded, K, N, D)) {
+    if (sector_rows(d_queries, d_coded, G, K, N, D)) {
         if constexpr (K >= kMfmaWideMinK) {
             // as for whole rows (run_encode_wide), but rows of one or two tiles leave the matrix cores' workgroups less to
             // do: K = 12, N = 28, 156 floats 85 us and 73 without matrix cores, 258 floats 107 and 90, 350 floats 73 and 77
