@@ -109,6 +109,34 @@ def test_encode_tiles_of_whole_sectors(gpu, K, N, off_in, off_out):
         assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * N * D:] == 7.5), D
 
 
+@pytest.mark.parametrize("rows", [14397, 14398, 14399, 14400, 14401, 16798, 47999])
+def test_rows_of_many_full_tiles_are_written_to_their_end(gpu, rows):
+    # from 60 tiles a row on a row can be whole tiles of sixty vectors, and the last one still has to keep a lane for the shift;
+    # the encoders' vector and matrix-core tiles and the decoder's, output rows of all four phases of a 16-byte piece
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(rows)
+    for K, N, S, off in [(3, 5, 1, 0), (3, 5, 1, 2), (12, 17, 4, 0), (12, 17, 4, 1), (20, 30, 6, 0), (20, 30, 6, 3)]:
+        alpha, beta = orc.chebyshev_nodes(K, N)
+        X = rng.uniform(0, 1, (2, K, rows)).astype(np.float32)
+        flat = torch.full((off + 2 * N * rows + 40,), float("nan"), dtype=torch.float32, device=dev)
+        c = flat[off:off + 2 * N * rows].view(2, N, rows)
+        binding.approxifer_encode(torch.from_numpy(X).to(dev), alpha, beta, coded=c)
+        # as for the short rows above: K roundings of weights and products
+        bound = (K + 2) * 2.0 ** -23 * np.abs(orc.encode(np.eye(K)[None], alpha, beta)).sum(axis=2).max()
+        assert np.all(np.abs(c.cpu().numpy() - orc.encode(X, alpha, beta)) <= bound), (K, off)
+        assert torch.isnan(flat[:off]).all() and torch.isnan(flat[off + 2 * N * rows:]).all()
+        Y = rng.standard_normal((2, N, rows)).astype(np.float32)
+        mask = np.ones((2, N), np.uint8)
+        mask[:, rng.choice(N, S, replace=False)] = 0
+        flat = torch.full((off + 2 * K * rows + 40,), float("nan"), dtype=torch.float32, device=dev)
+        out = flat[off:off + 2 * K * rows].view(2, K, rows)
+        binding.approxifer_decode(torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev), alpha, beta, S, 1, out=out)
+        ref, _ = orc.decode(Y, mask, alpha, beta, S, 1)
+        # one rounding to float32, float64 sums before it
+        assert np.all(np.abs(out.cpu().numpy() - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-12 * np.abs(Y).max()), (K, off)
+        assert torch.isnan(flat[:off]).all() and torch.isnan(flat[off + 2 * K * rows:]).all()
+
+
 def test_encode_node_coincidence_passes_query_through(gpu):
     torch, binding, dev = gpu
     alpha, beta = orc.chebyshev_nodes(2, 5)
