@@ -197,8 +197,10 @@ __global__ __launch_bounds__(kWave) void decode_stream_kernel(const float *__res
 // registers) hide the chain mask -> survivors -> rows and weights -> products; left to itself the compiler takes registers for
 // two (K = 32, 36 groups of 32000 classes 99 us, with four 79).  An HBM stream next to float64 matrix issue (half of it at K = 32);
 // two or four tiles to a workgroup that share their weights: 84 and 101 us where one each takes 81 (K = 20, 58 groups).
-// A query on the node of a worker that answered takes that worker's row as it is, whatever the others returned (coincide: the
-// call has such nodes; the search for them in every workgroup is a tenth of the time at K = 32, so the host looks first).
+// coincide: up to sixteen queries, one of them on a worker's node.  If that worker answered, the query takes its row as it is,
+// whatever the others returned, as in the tile kernels that serve those sizes too.  Beyond sixteen queries the other workers'
+// rows count with weight zero, as in decode_kernel and in both class decisions there (their NaN or infinities then show), so
+// that a group's answer does not depend on the size of the call.
 // dynamic LDS: float stage[16][kStageRow] | double WdT[4 NS][KP] | alpha_s[K] | beta_s[N] | int F[N] | n | any hit | hit[64],
 // KP = matrix_stride(K)
 constexpr int kTileThreads = 256;
@@ -1400,7 +1402,8 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
         return APPROXIFER_ERR_LAUNCH;
     return launch_status(launch_kernel(decode_matrix_kernel<NS>, dim3(static_cast<unsigned>(t.total)),
                                        dim3(kTileThreads), lds, stream, d_preds, d_mask, d_out, d_status, K, N, S, C,
-                                       static_cast<uint32_t>(t.per_row), t.width, halo, sign_mode, nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
+                                       static_cast<uint32_t>(t.per_row), t.width, halo, sign_mode,
+                                       K <= 16 && nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
 }
 
 // Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes, not

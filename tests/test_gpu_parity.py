@@ -724,6 +724,33 @@ def test_decode_query_on_an_answered_workers_node_is_that_workers_row(gpu, K, N,
         assert np.array_equal(top1[came, j], Y[came, w].argmax(-1)) and np.array_equal(score[came, j], Y[came, w].max(-1))
 
 
+@pytest.mark.parametrize("K,N,S,C,few,many", [(17, 18, 0, 50, 5, 450), (20, 41, 3, 50, 5, 450), (33, 34, 1, 90, 5, 450),
+                                              (27, 28, 0, 130, 5, 300)])
+def test_decode_beyond_sixteen_queries_is_the_same_in_calls_of_every_size(gpu, K, N, S, C, few, many):
+    # A query on an answered worker's node, while another worker returns NaN and infinities: a group's values and classes do
+    # not depend on how many groups the call has, nor on whether the classes are decided with the decoding or after it.
+    torch, binding, dev = gpu
+    rng = np.random.default_rng(K * N)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    if not np.isin(alpha, beta).any():
+        beta[N // 2] = alpha[K // 2]
+    mask = np.ones((many, N), np.uint8)
+    mask[:, 1:1 + S] = 0
+    Y = rng.standard_normal((many, N, C)).astype(np.float32)
+    Y[:, N - 1, 0::3] = np.nan
+    Y[:, N - 1, 1::3] = np.inf
+    Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
+    whole = binding.approxifer_decode(Yd, md, alpha, beta, S, 1)[0]
+    part = binding.approxifer_decode(Yd[:few], md[:few], alpha, beta, S, 1)[0]
+    # one rounding to float32 each, float64 sums before it
+    assert torch.allclose(whole[:few], part, rtol=2.0 ** -23, atol=1e-12 * 10, equal_nan=True)
+    for values in (whole, part):
+        fused = binding.approxifer_decode_top1(Yd[:len(values)], md[:len(values)], alpha, beta, S, 1)
+        after = binding.approxifer_top1(values)
+        assert torch.equal(fused[0], after[0])
+        assert torch.allclose(fused[1], after[1], rtol=2.0 ** -23, atol=1e-12 * 10)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
