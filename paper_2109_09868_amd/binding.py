@@ -16,6 +16,7 @@ import numpy as np
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG_DIR, "libapproxifer.so")
+MARSHAL_PATH = os.path.join(_PKG_DIR, "_marshal.so")
 
 MAX_K = 64
 MAX_N = 128
@@ -129,21 +130,44 @@ def _entry() -> ctypes.CDLL:
 _ordinary = None      # (library, the compiled marshalling module, its handle of the library)
 
 
+def marshal_target() -> str:
+    """The interpreter and torch that the marshalling module is compiled for."""
+    import sys
+
+    import torch
+    return "%s torch %s" % (sys.implementation.cache_tag, torch.__version__)
+
+
+def _marshal_module():
+    """The compiled marshalling module, or None.  One that is there but is not for this interpreter and torch, whose layouts
+    are compiled into it, is not used, and a warning says so."""
+    if not os.path.exists(MARSHAL_PATH):
+        return None
+    try:
+        import torch  # noqa: F401  (the module links its libraries)
+        from . import _marshal as module
+        if module.built_for == marshal_target():
+            return module
+        why = "it was built for %s" % module.built_for
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    import warnings
+    warnings.warn("%s is not used, calls take longer on the host: %s; build it again" % (MARSHAL_PATH, why), RuntimeWarning,
+                  stacklevel=2)
+    return None
+
+
 def _marshal():
     """The compiled marshalling module and its handle of the library, or (None, None) where it has not been built: the
-    calls then go through ctypes, 3 us more each on the host (a decode of 64 groups: 6.8 us to enqueue, 4 with it)."""
+    calls then go through ctypes, 3 us more each on the host (a decode of 64 groups: 6.8 us to enqueue, 3.4 with it)."""
     global _ordinary
     lib = load()
     if _ordinary is None or _ordinary[0] is not lib:
-        module = handle = None
-        try:
-            import torch  # noqa: F401  (the module links its libraries)
-            from . import _marshal as module
+        module, handle = _marshal_module(), None
+        if module is not None:
             names = ("encode", "decode", "decode_top1", "decode_byzantine", "decode_byzantine_homogeneous", "pad_last_group",
                      "top1", "wait_mask")
             handle = module.bind(*(ctypes.cast(getattr(lib, "approxifer_" + n), ctypes.c_void_p).value for n in names))
-        except ImportError:
-            module = handle = None
         _ordinary = (lib, module, handle)
     return _ordinary[1], _ordinary[2]
 

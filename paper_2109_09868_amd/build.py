@@ -28,25 +28,36 @@ def hipcc_path() -> str:
     return exe
 
 
-def build_marshal(verbose: bool = False) -> str:
+def host_compiler() -> str:
+    """g++, or where there is none the compiler that hipcc itself drives."""
+    exe = shutil.which("g++")
+    if exe is None:
+        rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+        exe = os.path.join(rocm, "llvm", "bin", "clang++")
+    return exe
+
+
+def build_marshal(verbose: bool = False, out: str = os.path.join(PKG_DIR, "_marshal.so")) -> str:
     """Compile csrc/marshal.cpp (host code on torch's C++ interface) into the module paper_2109_09868_amd._marshal."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
 
-    out = os.path.join(PKG_DIR, "_marshal.so")
+    from . import binding
+
     include = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), sysconfig.get_paths()["include"],
                os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path()))), "include")]
-    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *("-I" + p for p in include),
+    cmd = [host_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DAPPROXIFER_BUILT_FOR="%s"' % binding.marshal_target(), *("-I" + p for p in include),
            os.path.join(CSRC, "marshal.cpp"), "-o", out, *("-L" + p for p in cpp_extension.library_paths()),
            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("g++ failed on marshal.cpp:\n%s\n%s" % (r.stdout, r.stderr))
+        raise RuntimeError("%s failed on marshal.cpp:\n%s\n%s" % (cmd[0], r.stdout, r.stderr))
     return out
 
 

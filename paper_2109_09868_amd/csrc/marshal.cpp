@@ -281,4 +281,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module); }
+// built_for: the interpreter and the torch whose layouts are compiled in; the binding uses the module with no other.
+PyMODINIT_FUNC PyInit__marshal(void) {
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", APPROXIFER_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
