@@ -42,7 +42,8 @@ constexpr int kMfmaWideMinK = 8;   // .. and from this K on the shapes with N >=
 constexpr int kMfmaBlocksPerCu = 4;   // matrix-core variant (four waves of 64 columns)
 constexpr int kSectorRowsMinD = 129;   // rows that are not whole 64-byte sectors: tiles of whole sectors from here on
 constexpr int kSectorMinTiles = 2048;   // .. if rows are 16-byte pieces, for calls of this many tiles or more
-constexpr int kMfmaSectorsMinD = 300;   // K <= 16: .. on the matrix cores, where they pay, from here on
+constexpr int kSectorFewTiles = 640;   // calls whose time is the chain of one workgroup (see sector_rows)
+constexpr int kMfmaSectorsMinD = 300;   // K <= 16: .. on the matrix cores, where they pay, from here on; shorter rows: see sector_rows
 constexpr int kScalarRowsMaxD = 128;   // ragged rows (D % 4 != 0) this short: 64-bit or 4-byte accesses only
 
 // Register type of VEC floats, and the type a lane loads and stores it through.  Rows that are only
@@ -430,17 +431,16 @@ int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, in
     const int64_t cols_per_block = (kMfmaThreads / 64) * 16;           // vector columns per workgroup
     const int64_t chunks = (Dv + cols_per_block - 1) / cols_per_block;
     const int64_t idle = chunks * cols_per_block - Dv;                  // columns without data at the row ends
-    if (UNAL || idle * 100 > 3 * chunks * cols_per_block) {   // UNAL: only short rows come here (sector_rows)
-        const int64_t pairs = G * Dv;
-        return run_encode_mfma_shape<KS, UNAL, true>(d_queries, d_coded, (pairs + cols_per_block - 1) / cols_per_block,
-                                                     pairs, K, N, D, Dv, nodes, stream);
-    }
-    if constexpr (UNAL) return APPROXIFER_ERR_LIMIT;                   // not reached
-    else return run_encode_mfma_shape<KS, false, false>(d_queries, d_coded, G * chunks, chunks, K, N, D, Dv, nodes, stream);
+    const int64_t pairs = G * Dv;
+    const int64_t flat = (pairs + cols_per_block - 1) / cols_per_block;
+    if constexpr (!UNAL)                                                // UNAL: short rows, or few (sector_rows)
+        if (idle * 100 <= 3 * chunks * cols_per_block)
+            return run_encode_mfma_shape<KS, false, false>(d_queries, d_coded, G * chunks, chunks, K, N, D, Dv, nodes, stream);
+    return run_encode_mfma_shape<KS, UNAL, true>(d_queries, d_coded, flat, pairs, K, N, D, Dv, nodes, stream);
 }
 
-// Workgroup size.  K <= 16: one wave, but four for rows that are only 4-byte aligned (short ones: longer rows go by tiles of
-// whole sectors).
+// Workgroup size.  K <= 16: one wave, but four for rows that are only 4-byte aligned (short ones, or few: the others go by tiles
+// of whole sectors).
 constexpr int encode_threads(int K, bool UNAL) { return K <= 16 && !UNAL ? 64 : 256; }
 
 // Workgroups per CU, where the stage and the weights leave room for them (six, eight and four at 300 MB: K = 12, N = 28,
@@ -453,8 +453,8 @@ int run_encode_mfma_sectors(const float *d_queries, float *d_coded, int64_t G, i
                             hipStream_t stream) {
     const SectorTiles t = sector_tiles(G, D, kTileHalo);
     if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-        const size_t lds_used = (static_cast<size_t>((N + 15) / 16) * KS * 64 + 16 * kStageRow) * sizeof(float);
-        size_t lds = (static_cast<size_t>(kLdsPerCu / mfma_sector_blocks(D)) / 512) * 512;
+    const size_t lds_used = (static_cast<size_t>((N + 15) / 16) * KS * 64 + 16 * kStageRow) * sizeof(float);
+    size_t lds = (static_cast<size_t>(kLdsPerCu / mfma_sector_blocks(D)) / 512) * 512;
     if (lds < lds_used) lds = lds_used;
     if (lds > 64 * 1024 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(encode_mfma_sectors_kernel<KS>),
@@ -529,13 +529,12 @@ int run_encode(const float *d_queries, float *d_coded, int64_t G, int N, int64_t
     // lanes left idle at the row ends by the per-group tiling; above 3 % the flattened numbering pays for its
     // per-lane division and addresses
     const int64_t idle = chunks * THREADS - Dv;
-    if (UNAL || idle * 100 > 3 * chunks * THREADS) {          // UNAL: only short rows come here (sector_rows)
-        const int64_t pairs = G * Dv;
-        return run_encode_shape<K, VEC, true, UNAL>(d_queries, d_coded, (pairs + THREADS - 1) / THREADS, pairs, N, D, Dv,
-                                                    col0, nodes, stream);
-    }
-    if constexpr (UNAL) return APPROXIFER_ERR_LIMIT;          // not reached
-    else return run_encode_shape<K, VEC, false, false>(d_queries, d_coded, G * chunks, chunks, N, D, Dv, col0, nodes, stream);
+    const int64_t pairs = G * Dv;
+    const int64_t flat = (pairs + THREADS - 1) / THREADS;
+    if constexpr (!UNAL)                                      // UNAL: short rows, or few (sector_rows)
+        if (idle * 100 <= 3 * chunks * THREADS)
+            return run_encode_shape<K, VEC, false, false>(d_queries, d_coded, G * chunks, chunks, N, D, Dv, col0, nodes, stream);
+    return run_encode_shape<K, VEC, true, UNAL>(d_queries, d_coded, flat, pairs, N, D, Dv, col0, nodes, stream);
 }
 
 // 128-bit columns: the matrix-core kernel or the vector kernel, by shape.
@@ -556,18 +555,43 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
     }
 }
 
-// Whether a call goes by tiles of whole sectors: rows that are no whole sectors, of kSectorRowsMinD floats or more.  Measured
-// against the kernels that move such rows as they come, 300 MB, 130 to 60000 floats: K <= 16 0.75 to 1.0 of the time (K = 8,
-// N = 12, 64 x 3 x 299 x 299 floats: 270 and 231 us), the matrix-core variant 0.62 to 1.0 (K = 32, N = 48, 10003 floats: 100 and 65
-// us), but K = 20, N = 24 with tiles of fewer than forty own vectors, 156 floats: 74 and 78 us, 258 floats: 86 and 98 us.
-// Rows of 16-byte pieces in calls of fewer than kSectorMinTiles tiles, which are one workgroup's chain, stay too: they need no
-// second launch for their last columns, and the shift and the bounds lengthen the chain (K = 14, N = 16, two groups of 3836
-// floats 6.5 and 8.4 us; K = 18, N = 23, 1560 tiles of 24924 floats 15.9 and 17.3).
+// Whether a call goes by tiles of whole sectors: rows that are no whole sectors, of kSectorRowsMinD floats or more.  Both sides
+// timed over 5000 calls of 1 to 64 queries, 129 to 280000 floats, up to 1.2 GB; times without and with the tiles.
+//  - Rows that are only 4-byte aligned: nearly all calls gain (0.78 of the time on average; K = 8, N = 12, 64 x 3 x 299 x 299 floats 270
+//    and 231 us; K = 32, N = 48, 93 x 10003 95 and 72).  Not K = 20, N = 24 with tiles of fewer than forty own vectors (156
+//    floats 74 and 78 us, 258 floats 86 and 98); not K < 8 with sixteen or more workers in few short rows, whose time is one
+//    wave's chain of coded rows (K = 4, N = 16, 19 groups of 141 floats 7.6 and 8.7 us); not many small groups of a single query
+//    (12642 of 275 floats, N = 2 13.3 and 15.3).
+//  - Rows of 16-byte pieces lose only the sectors at the ends of a wave's segment, and only where HBM takes them:
+//    K > 32: none (K = 39, N = 54, 128 x 8132 floats 90 and 100 us; 1.05 times at K = 36, 1.2 times at K = 64).  K = 17..32: from 2048
+//    tiles on, rows of one tile of 45 vectors and more (K = 26, N = 31, 196 floats 166 and 127 us); tiles of more than forty own
+//    vectors where the coded rows are many (N >= 2 K: 0.82 of the time), of more than fifty from 1.5 K on (0.92), and with fewer
+//    yet of more than 54 and not for D % 8 = 0, which cuts fewer sectors (0.92; K = 17, N = 18, 20000 tiles of 1004 floats 132 and
+//    155 us).  K <= 16: calls of 8 MB a query and more (64 MB from eight on, and for K = 1), half that where N >= 2 K + 4, else twice
+//    that in tiles of fewer than fifty own vectors: 0.90 of the time above, 1.01 below (K = 4, N = 6, 2692 x 260 floats 7.4 and 8.9
+//    us; K = 6, N = 12, 193 x 2700 floats 9.4 and 10.9; K = 1, N = 9, 4 x 153684 floats 7.9 and 5.8).  From eight queries and N = 2 K + 4 on they
+//    stand against the matrix-core kernel: on the matrix cores in tiles of 48 vectors and more (K = 16, N = 40, 758 x 504 floats
+//    22 and 28 us), and for rows of one tile of up to 56 vectors (K = 14, N = 35, 11377 x 156 floats 114 and 88 us; K = 8, N = 23,
+//    9020 x 252 floats 53 and 67).
 inline bool sector_rows(const float *d_queries, const float *d_coded, int64_t G, int K, int N, int64_t D) {
     if ((whole_sectors(d_queries, D) && whole_sectors(d_coded, D)) || D < kSectorRowsMinD) return false;
     const bool pieces = D % 4 == 0 && reinterpret_cast<uintptr_t>(d_queries) % 16 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 16 == 0;
-    if (pieces && sector_tiles(G, D, kTileHalo).total < kSectorMinTiles) return false;
-    return K < kMfmaMinK || 2 * N >= 3 * K || sector_tiles(1, D, kTileHalo).width >= 4 * 40;
+    const SectorTiles t = sector_tiles(G, D, kTileHalo);
+    const int own = t.width / 4;
+    if (!pieces) {
+        if (K >= kMfmaMinK) return 2 * N >= 3 * K || own >= 40;
+        if (K == 1 && N <= 4 && own < 44 && t.total >= 8192) return false;
+        return K >= kMfmaWideMinK || N < 16 || D >= kMfmaSectorsMinD || t.total > kSectorFewTiles;
+    }
+    if (K >= kMfmaMinK) {
+        if (K > 32 || t.total < kSectorMinTiles) return false;
+        if (t.per_row == 1) return own >= 45;
+        return N >= 2 * K ? own > 40 : (2 * N >= 3 * K ? own > 50 : own > 54 && D % 8 != 0);
+    }
+    const bool many = N >= 2 * K + 4;
+    if (K >= kMfmaWideMinK && many && (D < kMfmaSectorsMinD ? own > 56 : own < 48)) return false;
+    const double least = 8e6 * (K == 1 || K > 8 ? 8 : K) * (many ? 0.5 : own < 50 ? 2.0 : 1.0);
+    return t.total >= kSectorMinTiles && 4.0 * static_cast<double>(G) * D * (K + N) >= least;
 }
 
 template <int K>
@@ -575,9 +599,12 @@ int run_encode_k(const float *d_queries, float *d_coded, int64_t G, int N, int64
                  hipStream_t stream) {
     if (sector_rows(d_queries, d_coded, G, K, N, D)) {
         if constexpr (K >= kMfmaWideMinK) {
-            // as for whole rows (run_encode_wide), but rows of one or two tiles leave the matrix cores' workgroups less to
-            // do: K = 12, N = 28, 156 floats 85 us and 73 without matrix cores, 258 floats 107 and 90, 350 floats 73 and 77
-            if (K >= kMfmaMinK || (N >= 2 * K + 4 && D >= kMfmaSectorsMinD))
+            // as for whole rows (run_encode_wide), but where rows of one or two tiles leave the matrix cores' workgroups less to
+            // do, only in few tiles (K = 12, N = 28, 300 MB, 156 floats 85 us and 73 without matrix cores,
+            // 258 floats 107 and 90, 350 floats 73 and 77).  A call of few tiles is one workgroup's chain, which four waves share: K = 11, N = 26,
+            // one row of 218 floats 7.7 and 13.5 us, K = 8, N = 9, 100 rows of 129 floats 0.6 of the time.
+            const bool few = sector_tiles(G, D, kTileHalo).total <= (N >= 2 * K + 4 ? 2 * kSectorFewTiles : kSectorFewTiles);
+            if (K >= kMfmaMinK || few || (N >= 2 * K + 4 && D >= kMfmaSectorsMinD))
                 return run_encode_mfma_sectors<(K + 3) / 4>(d_queries, d_coded, G, K, N, D, nodes, stream);
         }
         if constexpr (K < kMfmaMinK) return run_encode_sectors<K>(d_queries, d_coded, G, N, D, nodes, stream);
@@ -595,9 +622,8 @@ int run_encode_k(const float *d_queries, float *d_coded, int64_t G, int N, int64
     }
     if (D >= 4) {
         const int rc = run_encode_wide<K, true>(d_queries, d_coded, G, N, D, nodes, stream);
-        if (rc != APPROXIFER_OK) return rc;
+        if (rc != APPROXIFER_OK || tail == 0) return rc;
     }
-    if (tail == 0) return APPROXIFER_OK;
     return run_encode<K, 1, false>(d_queries, d_coded, G, N, D, tail, D - tail, nodes, stream);
 }
 

@@ -109,6 +109,28 @@ def test_encode_tiles_of_whole_sectors(gpu, K, N, off_in, off_out):
         assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * N * D:] == 7.5), D
 
 
+@pytest.mark.parametrize("K,N,D,G", [
+    (4, 6, 260, 6200), (8, 12, 1004, 900), (12, 28, 1004, 520), (14, 35, 156, 3000), (1, 9, 388, 2100),    # 16-byte pieces
+    (24, 48, 204, 2100), (20, 26, 2036, 240), (33, 40, 1004, 420),
+    (4, 16, 141, 700), (1, 2, 275, 4200), (9, 12, 203, 700), (11, 26, 218, 1400), (16, 20, 387, 330), (20, 24, 161, 40),   # ragged rows
+])
+def test_encode_gives_the_same_bits_in_calls_of_every_size(gpu, K, N, D, G):
+    # the number of groups decides between the tiles of whole sectors and the kernels that move rows as they come, and between
+    # vector and matrix cores: the same float32 multiply-adds in the same order everywhere
+    torch, binding, dev = gpu
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    X = torch.rand((G, K, D), generator=torch.Generator(device=dev).manual_seed(D), device=dev)
+    whole = torch.full((G, N, D), float("nan"), device=dev)
+    binding.approxifer_encode(X, alpha, beta, coded=whole)
+    for g0, n in [(0, 1), (1, 7), (G // 2, min(G // 4, 600)), (G - 1, 1)]:
+        part = torch.full((n, N, D), float("nan"), device=dev)
+        binding.approxifer_encode(X[g0:g0 + n].clone(), alpha, beta, coded=part)      # from a 16-byte address again
+        assert torch.equal(part, whole[g0:g0 + n]), (g0, n)
+    bound = (K + 2) * 2.0 ** -23 * np.abs(orc.encode(np.eye(K)[None], alpha, beta)).sum(axis=2).max()
+    for g in (0, G - 1):
+        assert np.abs(whole[g].cpu().numpy() - orc.encode(X[g:g + 1].cpu().numpy(), alpha, beta)[0]).max() <= bound
+
+
 @pytest.mark.parametrize("rows", [14397, 14398, 14399, 14400, 14401, 16798, 47999])
 def test_rows_of_many_full_tiles_are_written_to_their_end(gpu, rows):
     # from 60 tiles a row on a row can be whole tiles of sixty vectors, and the last one still has to keep a lane for the shift;
