@@ -1324,19 +1324,28 @@ bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
 // tile takes four waves, whatever the row's length, so it is not for many groups of short rows; times without and with it:
 //  - K > 16, where the other kernel has a wave per four queries and 4-byte accesses for rows that are only 4-byte aligned: from 96
 //    classes on (K = 32, 1170 groups of 1001 classes 261 and 106 us, 1171 of 1000 150 and 106; K = 24, 15470 of 101 259 and 206) and in
-//    calls of few tiles (K = 24, 24 classes, 217 groups 14.9 and 8.6 us; K = 17, 17 classes, 432 groups 9.9 and 10.3);
+//    calls of few tiles (K = 24, 24 classes, 217 groups 14.9 and 8.6 us; K = 17, 17 classes, 432 groups 9.9 and 10.3); fewer than 64
+//    classes in rows that are only 4-byte aligned from 25 queries or 33 survivors on (K = 21, 28 survivors, 33 classes, three
+//    groups 8.9 and 9.3; K = 18, 40 survivors, 19 classes, two groups 12.5 and 11.2);
 //  - K = 9..16 in rows that are only 4-byte aligned: from 96 classes on (K = 16, 2341 groups of 1001 classes 104 and 78 us, 78
 //    groups 16.3 and 7.5), with K = 9..11, which leave a third of the products' rows empty, up to 4096 tiles (K = 9, 832 groups of
-//    1001 classes 27.9 and 24.1, 4162 groups 98 and 103), and in calls of few tiles (K = 12, 50 classes, 208 groups 10.9 and
-//    5.8 us, 2083 groups 16.0 and 14.3);
+//    1001 classes 27.9 and 24.1, 4162 groups 98 and 103), up to 2048 with sixteen survivors or fewer (K = 10, ten survivors, 796 of
+//    1027 25.1 and 28.4) and not between one and a half rounds of the chip and two and a half where two tiles take a row of little
+//    more than one (K = 9, 1039 of 253 14.5 and 20.8), and in calls of few tiles (K = 12, 50 classes, 208 groups 10.9 and 5.8 us, 2083
+//    groups 16.0 and 14.3);
 //  - K = 9..16 otherwise in calls of few tiles, whose time is one workgroup's chain: its weights are four waves' work (K = 12, ten
 //    groups of 1000 classes 7.2 and 5.3 us, 104 groups 7.1 and 7.0, 156 of 4000 classes 14.3 and 16.1; K = 13, 24 groups of 4000
 //    classes 8.1 and 6.3, 144 groups 20.4 and 17.2, 2884 of 1000 classes 68 and 83).
 bool matrix_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
     if (K <= 8 || N > kWave || C <= kRowLanes) return false;
     const int64_t tiles = G * ((C + 239) / 240);
-    if (K > 16) return C >= 96 || tiles <= 400;
-    if (!vec4) return C >= 96 ? K > 11 || tiles <= 4096 : tiles <= (C >= 48 ? 2048 : 400);
+    const int survivors = S < 0 ? N : N - S;
+    if (K > 16) return C >= 96 || (tiles <= 400 && (vec4 || K > 24 || C >= 64 || survivors > 32));
+    if (!vec4 && C >= 96) {
+        const SectorTiles t = sector_tiles(G, C, kTileHalo);
+        return K > 11 || (t.total <= (survivors > 16 ? 4096 : 2048) && (t.width >= 4 * 38 || t.per_row == 1 || t.total <= 1536 || t.total > 2560));
+    }
+    if (!vec4) return tiles <= (C >= 48 ? 2048 : 400);
     return tiles <= (K > 12 ? 1024 : 400) || (K > 12 && C >= 96 && tiles <= 4096 && !tiles_shape(K, N, S, C, G, vec4));
 }
 // Whether decode_top1_tiles_kernel decides the call: all of them (0.76 of the time of a workgroup per group over 1600

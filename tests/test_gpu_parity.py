@@ -773,6 +773,27 @@ def test_decode_beyond_sixteen_queries_is_the_same_in_calls_of_every_size(gpu, K
         assert torch.allclose(fused[1], after[1], rtol=2.0 ** -23, atol=1e-12 * 10)
 
 
+@pytest.mark.parametrize("K,N,S,C,few,many", [
+    (10, 17, 7, 1027, 400, 800), (9, 14, 0, 253, 500, 1039), (11, 16, 2, 130, 2000, 2100), (13, 15, 1, 301, 20, 2500),
+    (21, 31, 2, 35, 3, 401), (24, 26, 1, 63, 3, 401), (26, 29, 0, 33, 5, 420), (18, 20, 2, 70, 5, 420),
+])
+def test_decode_is_the_same_in_calls_of_every_size(gpu, K, N, S, C, few, many):
+    # the number of groups decides which kernel decodes them
+    torch, binding, dev = gpu
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    gen = torch.Generator(device=dev).manual_seed(K * C)
+    Y = torch.randn((many, N, C), generator=gen, device=dev)
+    mask = (torch.rand((many, N), generator=gen, device=dev).argsort(1).argsort(1) >= S).to(torch.uint8)
+    whole, status = binding.approxifer_decode(Y, mask, alpha, beta, S, 1)
+    part, _ = binding.approxifer_decode(Y[:few].clone(), mask[:few].clone(), alpha, beta, S, 1)
+    assert torch.all(status == 0)
+    # one rounding to float32 each, float64 sums before it
+    assert torch.allclose(whole[:few], part, rtol=2.0 ** -23, atol=1e-12 * 10)
+    some = [0, few - 1, many - 1]
+    ref, _ = orc.decode(Y[some].cpu().numpy(), mask[some].cpu().numpy(), alpha, beta, S, 1)
+    assert np.all(np.abs(whole[some].cpu().numpy() - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-12 * 10)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
