@@ -1417,14 +1417,30 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
 
 // Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes, not
 // few groups of thousands of classes: one workgroup's loads in flight are too few there, K = 32, one group of 32000 classes 104 and
-// 435 us).  Times without and with it: K = 32, 2341 groups of 1001 classes 644 and 172 us, 23205 of 101 1238 and 304, 2343 of
-// 1000 292 and 170; K = 12, 6243 of 1001 204 and 96, 6250 of 1000 133 and 98, 206 of 101 15.5 and 5.6; K = 16, 156 of 1000 12.2 and
-// 10.4.  K <= 8 leaves half of the products' rows empty (K = 8, 9375 of 1000 100 and 117).  K = 17..27 with few groups of whole
-// vectors stays with the waves that share no rows (K = 17, 147 of 1000 17.8 and 20.8).  Up to sixteen queries the other kernels
+// 435 us).  Times without and with it, over 5000 calls:
+//  - K = 9..16 in rows that are only 4-byte aligned: always (0.2 to 0.96 of the time; K = 12, 6243 groups of 1001 classes 204 and 96, 206
+//    of 101 15.5 and 5.6);
+//  - K = 9..16 otherwise: against tiles that share a workgroup's sixteen rows of lanes.  Up to 256 classes in few groups (K = 16,
+//    4000 of 40 7.0 and 8.3, 20000 of 96 1.39 times); longer rows up to 24 survivors always (K = 12, 6250 of 1000 133 and 98), with more
+//    in one round of workgroups (G <= 256) and, up to 36 survivors, in many (N = 40, 384 to 1024 groups of 1000 classes 1.1 to 1.4 times);
+//  - K = 17..27 in whole vectors from 256 groups on (K = 17, 147 of 1000 17.8 and 20.8); K = 32, 2341 groups of 1001 classes 644 and 172,
+//    23205 of 101 1238 and 304, 2343 of 1000 292 and 170;
+//  - K > 16 in rows that are only 4-byte aligned: from 1024 classes on not in one round of the kernel below with a workgroup per
+//    quad of queries (K = 21, two groups of 1903 classes 20.9 and 29.7, K = 52, three of 1869 38 and 118);
+//  - K > 32: few groups of few classes stay with a wave per quad of queries (K = 48, 128 groups of 64 classes 1.24 times, of 33 1.44,
+//    500 of 33 25.5 and 30.5 us).
+// K <= 8 leaves half of the products' rows empty (K = 8, 9375 of 1000 100 and 117).  Up to sixteen queries the other kernels
 // hand on the row of a worker whose node a query has, whatever the other workers returned; calls with such nodes stay there.
-bool top1_matrix_shape(int K, int N, int64_t C, int64_t G, bool vec4, const Nodes &nodes) {
+bool top1_matrix_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4, const Nodes &nodes) {
     if (K <= 8 || N > kWave || C <= kRowLanes) return false;
-    if (K <= 16) return !nodes_coincide(nodes, K, N);
+    if (K <= 16) {
+        const int64_t stripes = (C + 63) / 64;
+        const int survivors = S < 0 ? N : N - S;
+        const bool faster = !vec4 || (stripes <= 4 ? G * (stripes + 1) <= 5120 : survivors <= 24 || G <= 256 || (survivors <= 36 && G > 1024));
+        return faster && !nodes_coincide(nodes, K, N);
+    }
+    if (!vec4 && C >= 1024 && G * ((K + 3) / 4) <= (K > 32 ? 512 : 256)) return false;
+    if (K > 32 && (vec4 ? C <= 400 && G <= 256 : C <= 64 && G <= 512)) return false;
     return !vec4 || K >= 28 || G >= 256;
 }
 
@@ -1432,12 +1448,14 @@ template <int NS, int R>
 int run_top1_matrix_shape(const float *d_preds, const uint8_t *d_mask, int32_t *d_top1, float *d_score, int32_t *d_status,
                           int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode, hipStream_t stream) {
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    // a wave per stripe, up to four; up to the kernel's most where there are few groups to fill the chip with, and then four at
-    // least: the weights are the whole workgroup's work
+    // a wave per stripe, up to four; more where there are few groups to fill the chip with, but all of them in one round: up to
+    // 256 groups the kernel's most, up to 512 half of it (K = 12, 500 groups of 1000 classes, eight waves 0.77 and sixteen 1.33 of the
+    // other kernel's time; N = 40, 400 groups, four waves 0.92 and eight 1.16).  Up to 512 groups at least four waves: the weights
+    // are the whole workgroup's work (beyond 48 queries up to 1023)
+    constexpr int most = top1_matrix_threads(NS, R) / kWave;
     const int64_t stripes = (C + 63) / 64;
-    int64_t waves = G >= 1024 ? 4 : G >= 512 ? 8 : 16;
-    if (waves > top1_matrix_threads(NS, R) / kWave) waves = top1_matrix_threads(NS, R) / kWave;
-    if (waves > stripes) waves = G >= 1024 || stripes > 4 ? stripes : 4;
+    int64_t waves = G <= 256 ? most : G <= 512 ? most / 2 : 4;
+    if (waves > stripes) waves = G > (K > 48 ? 1023 : 512) || stripes > 4 ? stripes : 4;
     const size_t lds = sizeof(double) * (static_cast<size_t>(4 * NS) * matrix_stride(K) + K + N) + sizeof(Best) * waves * 16 * R +
                        sizeof(int) * (static_cast<size_t>(N) + 2);
     if (lds > 64 * 1024 &&
@@ -1550,7 +1568,7 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     // few groups with very many classes: the split below (K = 12, one group of 21844 classes 32 us, 92 with tiles; K = 4,
     // 4096 classes 10.5 and 9.3; K = 16, 128 groups of 50256 classes 269 and 307)
     const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;
-    if (!few_groups && top1_matrix_shape(K, N, C, G, vec4, nodes))
+    if (!few_groups && top1_matrix_shape(K, N, S, C, G, vec4, nodes))
         return run_top1_matrix(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     if (top1_tiles_shape(K, N, C, G, vec4) && !few_groups) {
         const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;

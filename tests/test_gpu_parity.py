@@ -794,6 +794,30 @@ def test_decode_is_the_same_in_calls_of_every_size(gpu, K, N, S, C, few, many):
     assert np.all(np.abs(whole[some].cpu().numpy() - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-12 * 10)
 
 
+@pytest.mark.parametrize("K,N,S,C,few,many", [
+    (12, 16, 2, 1000, 200, 520), (12, 16, 0, 1000, 300, 1030), (10, 40, 2, 404, 250, 300), (10, 34, 0, 404, 700, 1030),
+    (16, 20, 1, 96, 1700, 1720), (14, 15, 1, 250, 1000, 1030), (21, 24, 1, 1903, 40, 50), (36, 40, 0, 1100, 50, 60),
+    (40, 44, 2, 50, 250, 520), (36, 45, 2, 360, 200, 300), (50, 60, 2, 18, 700, 1030), (20, 26, 0, 33, 500, 600),
+])
+def test_class_decision_is_the_same_in_calls_of_every_size(gpu, K, N, S, C, few, many):
+    # the number of groups decides which kernel decides the classes, and with how many waves to a group
+    torch, binding, dev = gpu
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    gen = torch.Generator(device=dev).manual_seed(K * C)
+    Y = torch.randn((many, N, C), generator=gen, device=dev)
+    Y[:, :, 7] = Y[:, :, 11] = 50.0 * (torch.arange(many, device=dev) % 2)[:, None]     # ties in every other group
+    mask = (torch.rand((many, N), generator=gen, device=dev).argsort(1).argsort(1) >= S).to(torch.uint8)
+    whole = binding.approxifer_decode_top1(Y, mask, alpha, beta, S, 1)
+    part = binding.approxifer_decode_top1(Y[:few].clone(), mask[:few].clone(), alpha, beta, S, 1)
+    assert torch.all(whole[2] == 0) and torch.all(whole[0][1::2] == 7)
+    assert torch.equal(whole[0][:few], part[0])
+    assert torch.allclose(whole[1][:few], part[1], rtol=2.0 ** -23, atol=1e-12 * 50)    # float64 sums, rounded once
+    some = [0, few - 1, many - 1]
+    ref, _ = orc.decode(Y[some].cpu().numpy(), mask[some].cpu().numpy(), alpha, beta, S, 1)
+    top = ref.max(axis=2)
+    assert np.all(np.abs(whole[1][some].cpu().numpy() - top) <= 2.0 ** -24 * np.abs(top) + 1e-12 * 50)
+
+
 # --------------------------------------------------------------------------------------
 # Byzantine decoder
 # --------------------------------------------------------------------------------------
