@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
     const float *xg = queries + static_cast<size_t>(g) * K * D + col * 4;
     float *og = coded + static_cast<size_t>(g) * N * D + col * 4;
 
-    // ---- query rows 4s + krow, columns 4*col..+3; rows past K are clamped (their weights are 0) ----
+    // ---- query rows 4s + krow, columns 4*col..+3; rows past K (KS = ceil(K / 4)) are clamped, and zeroed below ----
     v4f x[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -318,6 +318,7 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
 
     encode_mfma_weights<KS>(wA, K, N, nodes);
     __syncthreads();
+    if (4 * (KS - 1) + krow >= K) x[KS - 1] = v4f(0.0f);      // a clamped row: its infinities count for nothing either
 
     const int mtiles = (N + 15) >> 4;
     for (int mt = 0; mt < mtiles; ++mt) {
@@ -379,6 +380,7 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_sectors_kernel(
 #pragma unroll
         for (int s = 0; s < KS; ++s) x[s] = finish_vector(x[s], over, static_cast<int>(D % 4));
     }
+    if (4 * (KS - 1) + krow >= K) x[KS - 1] = v4f(0.0f);      // a clamped row, see encode_mfma_kernel
 
     float *og = coded + static_cast<size_t>(t.g) * N * D + t.start;
     for (int mt = 0; mt < mtiles; ++mt) {

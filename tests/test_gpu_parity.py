@@ -131,6 +131,28 @@ def test_encode_gives_the_same_bits_in_calls_of_every_size(gpu, K, N, D, G):
         assert np.abs(whole[g].cpu().numpy() - orc.encode(X[g:g + 1].cpu().numpy(), alpha, beta)[0]).max() <= bound
 
 
+@pytest.mark.parametrize("K,N,D,few,many", [(9, 12, 203, 3, 700), (11, 26, 1004, 2, 900), (14, 18, 141, 4, 800), (17, 23, 1008, 2, 40),
+                                            (22, 30, 501, 2, 40), (33, 41, 64, 2, 600)])
+def test_encode_of_an_infinity_in_the_last_query_is_that_infinity(gpu, K, N, D, few, many):
+    # numbers of queries that are no multiple of the matrix cores' four: what fills them up counts for nothing, and the kernels
+    # with and without matrix cores, between which the number of groups decides, answer the same
+    torch, binding, dev = gpu
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    weight = orc.encode(np.eye(K)[None], alpha, beta)[0][:, K - 1]
+    rows = np.abs(weight) > 1e-6
+    sign = torch.from_numpy(np.sign(weight[rows]).astype(np.float32)).to(dev)
+    for G in (few, many):
+        X = torch.rand((G, K, D), generator=torch.Generator(device=dev).manual_seed(G), device=dev)
+        plain = binding.approxifer_encode(X, alpha, beta)
+        X[:, K - 1, 5::7] = float("inf")
+        coded = binding.approxifer_encode(X, alpha, beta)
+        keep = torch.ones(D, dtype=torch.bool, device=dev)
+        keep[5::7] = False
+        assert torch.equal(coded[:, :, keep], plain[:, :, keep])
+        got = coded[:, torch.from_numpy(rows).to(dev)][:, :, 5::7]
+        assert bool((got == (sign * float("inf"))[None, :, None]).all()), G
+
+
 @pytest.mark.parametrize("rows", [14397, 14398, 14399, 14400, 14401, 16798, 47999])
 def test_rows_of_many_full_tiles_are_written_to_their_end(gpu, rows):
     # from 60 tiles a row on a row can be whole tiles of sixty vectors, and the last one still has to keep a lane for the shift;
