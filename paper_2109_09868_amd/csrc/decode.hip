@@ -1323,12 +1323,12 @@ bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
 // Whether decode_matrix_kernel decodes the call (more than eight queries, up to 64 workers, more than sixteen classes).  Its
 // tile takes four waves, whatever the row's length, so it is not for many groups of short rows; times without and with it:
 //  - K > 16, where the other kernel has a wave per four queries and 4-byte accesses for rows that are only 4-byte aligned: from 96
-//    classes on (K = 32, 1170 groups of 1001 classes 261 and 106 us, 1171 of 1000 150 and 106; K = 24, 15470 of 101 259 and 206) and in
+//    classes on (K = 32, 1170 groups of 1001 classes 241 and 96 us, 1171 of 1000 145 and 92; K = 24, 15470 of 101 259 and 206) and in
 //    calls of few tiles (K = 24, 24 classes, 217 groups 14.9 and 8.6 us; K = 17, 17 classes, 432 groups 9.9 and 10.3); fewer than 64
 //    classes in rows that are only 4-byte aligned from 25 queries or 33 survivors on (K = 21, 28 survivors, 33 classes, three
 //    groups 8.9 and 9.3; K = 18, 40 survivors, 19 classes, two groups 12.5 and 11.2);
-//  - K = 9..16 in rows that are only 4-byte aligned: from 96 classes on (K = 16, 2341 groups of 1001 classes 104 and 78 us, 78
-//    groups 16.3 and 7.5), with K = 9..11, which leave a third of the products' rows empty, up to 4096 tiles (K = 9, 832 groups of
+//  - K = 9..16 in rows that are only 4-byte aligned: from 96 classes on (K = 16, 2341 groups of 1001 classes 101 and 74 us, 78
+//    groups 15.9 and 7.7), with K = 9..11, which leave a third of the products' rows empty, up to 4096 tiles (K = 9, 832 groups of
 //    1001 classes 27.9 and 24.1, 4162 groups 98 and 103), up to 2048 with sixteen survivors or fewer (K = 10, ten survivors, 796 of
 //    1027 25.1 and 28.4) and not between one and a half rounds of the chip and two and a half where two tiles take a row of little
 //    more than one (K = 9, 1039 of 253 14.5 and 20.8), and in calls of few tiles (K = 12, 50 classes, 208 groups 10.9 and 5.8 us, 2083

@@ -2,10 +2,10 @@
 //
 //   coded[g][i][d] = sum_j l_j(beta_i) * queries[g][j][d]
 //
-// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16 and rows of whole
-// 64-byte sectors, four waves (256 columns) otherwise; rows that leave lanes idle at their end are tiled over the
-// flattened (group, column) index instead, and rows that are not whole sectors go by tiles whose stores are
-// (encode_sectors_kernel, encode_mfma_sectors_kernel).  Each lane first issues the loads of its vector column of
+// One workgroup per (group, tile of vector columns): a single wave (64 columns) for K <= 16 and rows of 16-byte
+// pieces, four waves (256 columns) otherwise; rows that leave lanes idle at their end are tiled over the
+// flattened (group, column) index instead, and rows that are not whole 64-byte sectors go by tiles whose stores are
+// (encode_sectors_kernel, encode_mfma_sectors_kernel) where that is the faster side (sector_rows).  Each lane first issues the loads of its vector column of
 // all K queries (they stay in registers), and while those are in flight the workgroup
 // evaluates the N x K matrix l_j(beta_i) -- it depends on the nodes only -- in float64 (one
 // 16/32/64-lane group per worker row, the row's denominator by a DPP reduction) and keeps it
@@ -350,7 +350,8 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
 // The same on tiles of whole sectors (see store_sectors), one tile of 64 vectors per workgroup: the waves compute sixteen
 // vectors each, as above, and exchange the sixteen coded rows of a round through LDS, from where each wave stores
 // four rows as they lie in memory.  (A wave's own sixteen vectors end inside a sector on both sides: five pieces for four.)
-// An HBM stream: K = 32, N = 48, 10003 floats, 93 groups 100 -> 65 us; K = 12, N = 28 87 -> 56 us (5.3 TB/s).
+// An HBM stream: K = 32, N = 48, 93 groups of 10003 floats 100 -> 65 us (4.6 TB/s; a quarter more is read than the queries hold);
+// K = 12, N = 28, 187 groups 87 -> 57 us (5.3 TB/s).  Launch after launch; the first on new buffers 74 and 68.
 // dynamic LDS: float wA[ceil(N/16)][KS][64] | stage[16][kStageRow]
 constexpr int kStageRow = 256 + 4;
 template <int KS>
@@ -446,7 +447,7 @@ int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, in
 constexpr int encode_threads(int K, bool UNAL) { return K <= 16 && !UNAL ? 64 : 256; }
 
 // Workgroups per CU, where the stage and the weights leave room for them (six, eight and four at 300 MB: K = 12, N = 28,
-// 350 floats 77, 73, 82 us, 10003 floats 56, 59, 57; K = 8, N = 24, 350 floats 82, 74, 89, 10003 floats 56, 58, 60; with two
+// 350 floats 76, 73, 79 us, 10003 floats 56, 58, 58; K = 8, N = 24, 350 floats 81, 75, 88, 10003 floats 57, 58, 60; with two
 // stages, a barrier less, and four 58 to 61 at 10003 floats).
 constexpr int mfma_sector_blocks(int64_t D) { return D < 2048 ? 8 : 6; }
 
@@ -469,10 +470,15 @@ int run_encode_mfma_sectors(const float *d_queries, float *d_coded, int64_t G, i
 
 // Workgroups of four waves per CU: with K <= 4 loads a wave, or rows of a few tiles that leave lanes idle, sixteen waves keep
 // enough bytes in flight; from five loads and 8 KB a row on, eight.  16 and 8 waves at N = K + 1 .. 1.5 K, 300 MB: K = 4, 1425
-// floats 52 and 59 us, 50001 floats 49 and 53; K = 8, 477 floats 66 and 80, 604 floats 58 and 59, 3075 floats 58 and 56.
-constexpr int sector_blocks(int K, int64_t D) {
+// floats 52 and 59 us, 50001 floats 49 and 53; K = 8, 477 floats 66 and 80, 604 floats 58 and 59, 3075 floats 58 and 56.  Calls
+// of up to 4096 tiles have sixteen, which is all of them at once, up to twelve queries (2049 tiles and more: K = 5 and 6 0.885 of
+// the time, 11 and 12 0.95, 15 and 16 0.99), and hardly more than one round of sixteen, up to 4800 tiles, are one of twenty-four (0.92 to
+// 0.98; beyond eight queries 1.02 where eight waves are the usual).
+constexpr int sector_blocks(int K, int64_t D, int64_t tiles) {
     if (K <= 2) return 6;
-    return K <= 4 || D < 2048 ? 4 : 2;
+    const int usual = K <= 4 || D < 2048 ? 4 : 2;
+    if (tiles <= 4096) return K <= 12 ? 4 : usual;
+    return tiles <= 4800 && (usual == 4 || K <= 8) ? 6 : usual;
 }
 
 template <int K>
@@ -482,7 +488,7 @@ int run_encode_sectors(const float *d_queries, float *d_coded, int64_t G, int N,
     constexpr int THREADS = 256;
     const SectorTiles t = sector_tiles(G, D, kTileHalo);
     if (t.total > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-    const int per_cu = sector_blocks(K, D);
+    const int per_cu = sector_blocks(K, D, t.total);
     const size_t lds_used = static_cast<size_t>(N) * KP * sizeof(float);
     size_t lds = (static_cast<size_t>(kLdsPerCu / per_cu) / 512) * 512;
     if (lds < lds_used) lds = lds_used;
@@ -507,7 +513,7 @@ int run_encode_shape(const float *d_queries, float *d_coded, int64_t tiles, int6
         if (per_cu < kWavesPerCuMin) per_cu = kWavesPerCuMin;
         if (per_cu > 24) per_cu = 24;
         if (THREADS > 64) per_cu = (per_cu + THREADS / 64 - 1) / (THREADS / 64);   // as many waves, up to whole workgroups
-        if (VEC == 1) per_cu = 7;       // 4-byte accesses (the last D % 4 columns, or D < 4): a sliver of the work
+        if (VEC == 1) per_cu = 7;       // 4-byte accesses: ragged rows of up to 128 floats, or the last D % 4 columns
     }
     if (tiles > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const size_t lds_used = static_cast<size_t>(N) * KP * sizeof(float);
@@ -560,7 +566,7 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
 // Whether a call goes by tiles of whole sectors: rows that are no whole sectors, of kSectorRowsMinD floats or more.  Both sides
 // timed over 5000 calls of 1 to 64 queries, 129 to 280000 floats, up to 1.2 GB; times without and with the tiles.
 //  - Rows that are only 4-byte aligned: nearly all calls gain (0.78 of the time on average; K = 8, N = 12, 64 x 3 x 299 x 299 floats 270
-//    and 231 us; K = 32, N = 48, 93 x 10003 95 and 72).  Not K = 20, N = 24 with tiles of fewer than forty own vectors (156
+//    and 231 us; K = 32, N = 48, 93 x 10003 100 and 65).  Not K = 20, N = 24 with tiles of fewer than forty own vectors (156
 //    floats 74 and 78 us, 258 floats 86 and 98); not K < 8 with sixteen or more workers in few short rows, whose time is one
 //    wave's chain of coded rows (K = 4, N = 16, 19 groups of 141 floats 7.6 and 8.7 us); not many small groups of a single query
 //    (12642 of 275 floats, N = 2 13.3 and 15.3).
@@ -571,10 +577,14 @@ int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, in
 //    yet of more than 54 and not for D % 8 = 0, which cuts fewer sectors (0.92; K = 17, N = 18, 20000 tiles of 1004 floats 132 and
 //    155 us).  K <= 16: calls of 8 MB a query and more (64 MB from eight on, and for K = 1), half that where N >= 2 K + 4, else twice
 //    that in tiles of fewer than fifty own vectors: 0.90 of the time above, 1.01 below (K = 4, N = 6, 2692 x 260 floats 7.4 and 8.9
-//    us; K = 6, N = 12, 193 x 2700 floats 9.4 and 10.9; K = 1, N = 9, 4 x 153684 floats 7.9 and 5.8).  From eight queries and N = 2 K + 4 on they
+//    us; K = 6, N = 12, 193 x 2700 floats 9.4 and 10.9; K = 1, N = 9, 4 x 153684 floats 7.9 and 5.8).  Not rows of 63
+//    vectors, which are one wave each as they come (252 floats: 1.0 to 1.17 times), nor many small tiles of a single query with two
+//    workers (8702 x 1484 floats 28.8 and 30.4), nor rows of whole 32-byte pieces (D % 8 = 0), which cut half as many sectors, in little
+//    more than one round of workgroups (three to five queries, N < 2 K; K = 3, N = 5, 1296 x 792 floats 7.5 and 8.9).  From eight queries and N = 2 K + 4 on they
 //    stand against the matrix-core kernel: on the matrix cores in tiles of 48 vectors and more (K = 16, N = 40, 758 x 504 floats
 //    22 and 28 us), and for rows of one tile of up to 56 vectors (K = 14, N = 35, 11377 x 156 floats 114 and 88 us; K = 8, N = 23,
-//    9020 x 252 floats 53 and 67).
+//    9020 x 252 floats 53 and 67), of whole 32-byte pieces only on the matrix cores and from 23 workers on (K = 14, N = 35, 4352 x 136
+//    floats 1.10 times; K = 8, N = 20, 1588 x 776 30.4 and 35.4; N = 23..28 0.87 to 0.99).
 inline bool sector_rows(const float *d_queries, const float *d_coded, int64_t G, int K, int N, int64_t D) {
     if ((whole_sectors(d_queries, D) && whole_sectors(d_coded, D)) || D < kSectorRowsMinD) return false;
     const bool pieces = D % 4 == 0 && reinterpret_cast<uintptr_t>(d_queries) % 16 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 16 == 0;
@@ -590,8 +600,14 @@ inline bool sector_rows(const float *d_queries, const float *d_coded, int64_t G,
         if (t.per_row == 1) return own >= 45;
         return N >= 2 * K ? own > 40 : (2 * N >= 3 * K ? own > 50 : own > 54 && D % 8 != 0);
     }
-    const bool many = N >= 2 * K + 4;
-    if (K >= kMfmaWideMinK && many && (D < kMfmaSectorsMinD ? own > 56 : own < 48)) return false;
+    const bool many = N >= 2 * K + 4, half = D % 8 == 0;
+    if (t.per_row == 1 && own == 63) return false;
+    if (K >= kMfmaWideMinK && many) {
+        if (half && (N <= 22 || D < kMfmaSectorsMinD)) return false;
+        if (D < kMfmaSectorsMinD ? own > 56 : own < 48) return false;
+    }
+    if (K == 1 && N <= 2 && own < 58 && t.total >= 16384) return false;
+    if (half && K > 2 && K <= 5 && N < 2 * K && t.total > 4800 && t.total <= 6144) return false;
     const double least = 8e6 * (K == 1 || K > 8 ? 8 : K) * (many ? 0.5 : own < 50 ? 2.0 : 1.0);
     return t.total >= kSectorMinTiles && 4.0 * static_cast<double>(G) * D * (K + N) >= least;
 }

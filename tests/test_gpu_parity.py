@@ -112,6 +112,7 @@ def test_encode_tiles_of_whole_sectors(gpu, K, N, off_in, off_out):
 @pytest.mark.parametrize("K,N,D,G", [
     (4, 6, 260, 6200), (8, 12, 1004, 900), (12, 28, 1004, 520), (14, 35, 156, 3000), (1, 9, 388, 2100),    # 16-byte pieces
     (24, 48, 204, 2100), (20, 26, 2036, 240), (33, 40, 1004, 420),
+    (6, 12, 252, 4000), (3, 5, 792, 1296), (8, 20, 776, 1600), (14, 35, 136, 2400), (5, 8, 2052, 500), (1, 2, 1484, 4000),
     (4, 16, 141, 700), (1, 2, 275, 4200), (9, 12, 203, 700), (11, 26, 218, 1400), (16, 20, 387, 330), (20, 24, 161, 40),   # ragged rows
 ])
 def test_encode_gives_the_same_bits_in_calls_of_every_size(gpu, K, N, D, G):
@@ -1629,14 +1630,14 @@ def test_paper_operating_point_workloads_full_size(gpu):
 
 
 # --------------------------------------------------------------------------------------
-# per-group straggler counts (S = APPROXIFER_S_FROM_MASK): ragged masks
+# decoders on the float64 matrix cores
 # --------------------------------------------------------------------------------------
 @pytest.mark.parametrize("K,N,S", [
     (9, 11, 1), (12, 20, 8), (13, 16, 0), (16, 17, 1), (16, 40, 4), (17, 17, 0), (20, 26, 2), (32, 33, 0), (28, 50, 20), (33, 40, 3),
     (48, 64, 16), (64, 64, 0), (20, 50, -1), (16, 33, -1),
 ])
 def test_decode_top1_on_the_matrix_cores(gpu, K, N, S):
-    # k-steps and rounds as above; one stripe of 64 classes, remainders of a stripe and of a vector, a stripe more than the
+    # k-steps and rounds as in the test below; one stripe of 64 classes, remainders of a stripe and of a vector, a stripe more than the
     # waves take at once, a workgroup of one wave (G >= 1024) and of many; a rejected mask; workers without an answer are NaN
     torch, binding, dev = gpu
     rng = np.random.default_rng(100 * K + N)
@@ -1668,7 +1669,7 @@ def test_decode_top1_on_the_matrix_cores(gpu, K, N, S):
     (32, 33, 0), (33, 40, 3), (48, 48, 0), (48, 64, 16), (64, 64, 0), (20, 50, -1), (16, 33, -1), (64, 64, -1),
 ])
 def test_decode_on_the_matrix_cores(gpu, K, N, S):
-    # few tiles, so that every row length comes here: 4, 6, 9, 12 and 16 k-steps and remainders, one to four rounds of sixteen
+    # few tiles, so that all but the shortest ragged rows of up to 24 queries come here: 4, 6, 9, 12 and 16 k-steps and remainders, one to four rounds of sixteen
     # queries, tiles of whole and of ragged sectors (one up to 63 vectors, 60 a tile less one), row ends of every remainder,
     # output rows of every phase, a rejected mask; predictions of workers that did not answer are NaN
     torch, binding, dev = gpu
@@ -1706,6 +1707,9 @@ def test_decode_on_the_matrix_cores(gpu, K, N, S):
         assert torch.all(flat_out[:off_out] == 7.5) and torch.all(flat_out[off_out + G * K * C:] == 7.5), C
 
 
+# --------------------------------------------------------------------------------------
+# per-group straggler counts (S = APPROXIFER_S_FROM_MASK): ragged masks
+# --------------------------------------------------------------------------------------
 @pytest.mark.parametrize("K,N,C,G", [(3, 9, 5, 12), (8, 12, 100, 40), (12, 20, 1000, 24), (16, 70, 36, 10), (5, 128, 3, 9),
                                      (10, 30, 10, 64), (16, 32, 16, 33)])
 @pytest.mark.parametrize("mode", [0, 1])
