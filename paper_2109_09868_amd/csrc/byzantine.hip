@@ -32,9 +32,11 @@
 // rounds of a DPP minimum in the others) vote in an LDS histogram, the A most voted workers (equal
 // counts: smaller index first) leave the available list, and the group is decoded over the rest.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
-#include "decode_common.h"
+#include "byzantine_common.h"
+#include "byzantine_pairs.h"
 #include "rows.h"
 
 // Built-in workspace of approxifer_decode_byzantine_static(): one copy per GPU the library runs on, held until
@@ -44,104 +46,6 @@ static __device__ __align__(256) unsigned char scratch[APPROXIFER_STATIC_WORKSPA
 
 namespace approxifer {
 namespace {
-
-// ------------------------------------------------------------------------------------------------
-// shared tail: vote -> located adversaries -> F -> decode
-// ------------------------------------------------------------------------------------------------
-// Decoder contraction of one group over every column tile, predictions read from global memory.
-template <int VEC>
-__device__ __forceinline__ void contract_group(const float *__restrict__ pg, float *__restrict__ og, const int *F, int nF,
-                                               int K, int KP, int64_t C, int64_t Cv, const double *WdT) {
-    for (int64_t cv0 = 0; cv0 < Cv; cv0 += kColsPerTile) {
-        const int64_t cv1 = (cv0 + kColsPerTile < Cv) ? cv0 + kColsPerTile : Cv;
-        typename PredVec<VEC>::type unused[kRowChunk];
-        contract_tile<VEC, false>(pg, og, F, nF, K, KP, C, cv0, cv1, WdT, unused);
-    }
-}
-
-// The A most voted workers (equal counts: smaller index first) go to adv_g in ascending order; F = the
-// available workers without them (ascending), Fpos = their positions in `avail`.  n <= 64, N <= 128.
-// One wave does it in registers: lane i ranks workers i and i + 64 by counting against the vote counts
-// (broadcast reads of LDS), ballots turn ranks into the ascending lists.
-// select_adversaries_wave: called by one whole wave after every vote has been added and a barrier; the lists are
-// visible after the next barrier.
-__device__ __forceinline__ void select_adversaries_wave(int32_t *__restrict__ adv_g, const int *avail, int n, int N,
-                                                        int A, const int *votes, int *F, int *Fpos) {
-    {
-        const int lane = lane_id();
-        const int mine0 = lane < N ? votes[lane] : -1;
-        const int mine1 = lane + kWave < N ? votes[lane + kWave] : -1;
-        int rank0 = 0, rank1 = 0;
-#pragma unroll 8
-        for (int o = 0; o < N; ++o) {
-            const int v = votes[o];
-            rank0 += (v > mine0 || (v == mine0 && o < lane)) ? 1 : 0;
-            rank1 += (v > mine1 || (v == mine1 && o < lane + kWave)) ? 1 : 0;
-        }
-        const bool s0 = lane < N && rank0 < A;
-        const bool s1 = lane + kWave < N && rank1 < A;
-        const unsigned long long m0 = __ballot(s0), m1 = __ballot(s1);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        if (s0) adv_g[__popcll(m0 & below)] = lane;
-        if (s1) adv_g[__popcll(m0) + __popcll(m1 & below)] = lane + kWave;
-        const int w = lane < n ? avail[lane] : 0;
-        const bool dropped = ((w < kWave ? m0 >> w : m1 >> (w - kWave)) & 1ull) != 0ull;
-        const bool keep = lane < n && !dropped;
-        const unsigned long long mk = __ballot(keep);
-        if (keep) {
-            const int pos = __popcll(mk & below);
-            F[pos] = w;
-            Fpos[pos] = lane;
-        }
-    }
-}
-
-// Called by the whole workgroup after every vote has been added and a barrier; ends with a barrier.
-__device__ __forceinline__ void select_adversaries(int32_t *__restrict__ adv_g, const int *avail, int n, int N, int A,
-                                                   const int *votes, int *F, int *Fpos) {
-    if (wave_id() == 0) select_adversaries_wave(adv_g, avail, n, N, A, votes, F, Fpos);
-    __syncthreads();
-}
-
-// Several workgroups share a group (few groups, many classes: each takes part of the classes).  They meet in the
-// group's N+1 words of the caller's workspace -- N vote counters and an arrival counter, cleared by
-// clear_workspace_kernel before the launch.  These words are touched by device-scope atomic read-modify-writes only,
-// which are carried out at the one place all workgroups of the device share.  A part's additions have been carried
-// out once their old values are back; only then does it count itself in, and the part that counts itself in last
-// reads the votes with the same kind of operation: no cache write-back or invalidation (a fence) is needed, and none
-// of the part's other memory traffic has to be ordered with this.  No part waits for another: whichever arrives last
-// gets every vote (into `votes`, LDS) and true, and finishes the group.
-// Called by the whole workgroup after a barrier that follows its last vote; ends with a barrier when it returns true.
-__device__ __forceinline__ bool pool_votes_last_arrival(int *gvotes, int *votes, int N, int splits, int *flag) {
-    const int tid = threadIdx.x;
-    int seen = 0;
-    for (int i = tid; i < N; i += blockDim.x)
-        if (votes[i] != 0) seen |= __hip_atomic_fetch_add(&gvotes[i], votes[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("" ::"v"(seen));                         // the returned values are waited for
-    __syncthreads();
-    if (tid == 0)
-        *flag = __hip_atomic_fetch_add(&gvotes[N], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == splits - 1 ? 1 : 0;
-    __syncthreads();
-    if (*flag == 0) return false;
-    for (int i = tid; i < N; i += blockDim.x)
-        votes[i] = __hip_atomic_fetch_add(&gvotes[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    return true;
-}
-
-// vec4: prediction rows are 16-byte aligned and C % 4 == 0, Cv = C / 4; else Cv = C.
-__device__ __forceinline__ void finish_group(const float *__restrict__ pg, float *__restrict__ og,
-                                             int32_t *__restrict__ adv_g, const int *avail, int n, int N, int A, int K,
-                                             int KP, int64_t C, int64_t Cv, bool vec4, int sign_mode,
-                                             const double *alpha_s, const double *beta_s, const int *votes,
-                                             int *F, int *Fpos, double *WdT) {
-    select_adversaries(adv_g, avail, n, N, A, votes, F, Fpos);
-    const int nF = n - A;
-    decoder_weights(alpha_s, beta_s, F, nF, K, KP, sign_mode, WdT);
-    __syncthreads();
-    if (vec4) contract_group<4>(pg, og, F, nF, K, KP, C, Cv, WdT);
-    else contract_group<1>(pg, og, F, nF, K, KP, C, Cv, WdT);
-}
 
 // Rank of |a_r| among the n rows of one class (LDS key[n]); the A smallest vote for their worker.
 // Called by the lanes of one class, lane j of `width` handling rows j, j+width, ..
@@ -174,39 +78,6 @@ constexpr int y_stride(int NB) { return (NB / 4) % 2 == 1 ? NB : NB + 4; }     /
 constexpr int hom_mt(int NB) { return NB / 2 < kProjMaxM ? NB / 2 : kProjMaxM; }
 constexpr int ush_rows(int RM) { return (RM + 3) & ~3; }
 constexpr int basis_stride(int NB) { return NB % 16 == 0 ? NB + 4 : NB; }      // of the basis kept in the workspace
-
-// Reciprocal and square root of a normal, positive-or-negative (rcp) / positive (sqrt) double to full
-// double precision: the hardware estimate refined by two Newton (Goldschmidt) steps and, for the root, one
-// residual correction.  No scaling for denormals or infinities and no final correctly-rounded fix-up, which
-// the factorisations here do not need: their operands are column norms and pivots, and a zero norm is
-// handled by the caller.
-__device__ __forceinline__ double rcp_normal(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return r;
-}
-__device__ __forceinline__ double sqrt_normal(double s) {
-    const double y = __builtin_amdgcn_rsq(s);
-    double g = s * y, h = 0.5 * y;
-    double r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    return fma(fma(-g, g, s), h, g);
-}
-
-__device__ __forceinline__ double rsqrt_normal(double s) {
-    const double y = __builtin_amdgcn_rsq(s);
-    double g = s * y, h = 0.5 * y;
-    double r = fma(-h, g, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    r = fma(-h, g, 0.5);
-    return 2.0 * fma(h, r, h);
-}
 
 // Householder reflector of a pivot column x (rows k..): returns alpha = -sign(x_k) ||x|| and the factor
 // f = 2 v^T a / (v^T v) for a column a, v = x - alpha e_k, given sigma = x^T x, d = x^T a.
@@ -1830,6 +1701,109 @@ int packed_groups(int64_t G, bool homogeneous) {
     return G <= 1280 ? 1 : (G <= 2560 ? 2 : 4);
 }
 
+// ---- two lanes to a class: the library's own nodes, few workers missing ------------------------------------------------
+// Most workers that can be missing from a group that is decoded.
+int most_missing(int N, int S, int M) { return S < 0 ? N - 2 * M : S; }
+
+// Whether the nodes are cos(i pi / (N - 1)) to a few roundings: the closed forms of locate_class_pair hold for these only.
+bool chebyshev_workers(const Nodes &nodes, int N) {
+    constexpr double kPi = 3.14159265358979323846;
+    constexpr double kClose = 16.0 / (1ull << 53);
+    for (int i = 0; 2 * i < N; ++i)
+        if (!(std::fabs(nodes.beta[i] - std::cos(i * kPi / (N - 1))) <= kClose) ||
+            !(std::fabs(nodes.beta[i] + nodes.beta[N - 1 - i]) <= kClose))
+            return false;
+    return true;
+}
+
+struct PairShape {
+    int mt, tt, extra, missing;                            // mt = 0: not for decode_byzantine_pairs_kernel
+};
+PairShape pair_shape(int K, int N, int S, int A, int64_t C) {
+    PairShape p = {0, 0, 0, 0};
+    const int M = K + A;
+    const int missing = most_missing(N, S, M);
+    if (M > 14 || A > kPairMaxAdversaries || missing > kPairMaxMissing || C > (1 << 24)) return p;
+    const int mt = std::max(4, (M + 1) & ~1);
+    const int sx = missing == 0 ? 0 : (missing <= 2 ? 2 : 4);
+    const int least = mt / 2 + sx / 2;
+    const int tt = std::max(least, (N - M + 1) / 2);
+    if (tt > least + 1) return p;
+    p.mt = mt;
+    p.tt = tt;
+    p.extra = tt - least;
+    p.missing = missing;
+    return p;
+}
+
+// The rank-one term's inverse root for the rows of parity h (locate_class_pair): sum of e^2 = c, of N - 1 = 2 / norm.
+double pair_lift(int N, int R, int h) {
+    const double c = h ? R / 2 : (R + 1) / 2 - 0.5;
+    return (1.0 / std::sqrt(1.0 - c / (N - 1)) - 1.0) / c;
+}
+
+int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv,
+                    int32_t *d_status, int64_t G, int K, int N, int S, int n, int A, int64_t C, bool vec4, const Nodes &nodes,
+                    int sign_mode, int32_t *votes, hipStream_t stream) {
+    PairCall call;
+    call.preds = d_preds;
+    call.mask = d_mask;
+    call.out = d_out;
+    call.adv = d_adv;
+    call.status = d_status;
+    call.votes = votes;
+    call.G = G;
+    call.C = C;
+    call.Cv = vec4 ? C / 4 : C;
+    call.K = K;
+    call.N = N;
+    call.S = S;
+    call.A = A;
+    call.n_cap = n;
+    call.vec4 = vec4 ? 1 : 0;
+    call.sign_mode = sign_mode;
+    call.lift0 = pair_lift(N, N - K - A, 0);
+    call.lift1 = pair_lift(N, N - K - A, 1);
+    call.gpw = 1;
+    call.parts = call.splits = 1;
+    int nw = kPairMaxWaves;
+    if (C > kPairPart) {
+        if ((C + kPairPart - 1) / kPairPart > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+        call.parts = static_cast<int>((C + kPairPart - 1) / kPairPart);
+        call.splits = votes != nullptr ? call.parts : 1;
+        if (G * call.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+        if (call.splits > 1) {
+            const int rc = clear_workspace(votes, G, N, stream);
+            if (rc != APPROXIFER_OK) return rc;
+        }
+    } else {
+        const int c = static_cast<int>(C);
+        nw = (c + kPairsPerWave - 1) / kPairsPerWave;
+        const char *env = getenv("APX_GPW");
+        const char *envw = getenv("APX_NW");
+        if (env) call.gpw = atoi(env), nw = atoi(envw);
+        else if (G * nw > 1024) {
+            // pack
+            int best = nw, bg = 1; double eff = 0;
+            for (int w = 1; w <= kPairMaxWaves; ++w) {
+                const int g = std::min(w * kPairsPerWave / c, 16 * w);
+                if (g < 1) continue;
+                const double e = double(g) * c / (w * kPairsPerWave);
+                if (e > eff + 0.02) eff = e, best = w, bg = g;
+            }
+            nw = best; call.gpw = bg;
+        }
+    }
+    switch (shape.mt) {
+        case 4: return run_pairs_4(shape.missing, shape.extra, call, nw, nodes, stream);
+        case 6: return run_pairs_6(shape.missing, shape.extra, call, nw, nodes, stream);
+        case 8: return run_pairs_8(shape.missing, shape.extra, call, nw, nodes, stream);
+        case 10: return run_pairs_10(shape.missing, shape.extra, call, nw, nodes, stream);
+        case 12: return run_pairs_12(shape.missing, shape.extra, call, nw, nodes, stream);
+        default: return run_pairs_14(shape.missing, shape.extra, call, nw, nodes, stream);
+    }
+}
+
 template <int NB, int RM, int NW, bool SHARED, bool HOMOG>
 int run_packed_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv, int32_t *d_status, int64_t G,
                      int K, int N, int S, int n, int A, int C, const Nodes &nodes, int sign_mode, const double *basis,
@@ -1993,6 +1967,14 @@ int launch_decode_byzantine(const float *d_preds, const uint8_t *d_mask, float *
     const int64_t Cv = vec4 ? C / 4 : C;
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
 
+    if (!homogeneous) {
+        const PairShape pair = pair_shape(K, N, S, A, C);
+        if (pair.mt != 0 && chebyshev_workers(nodes, N)) {
+            const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, C > kPairPart ? votes_bytes(G, N) : 0);
+            return run_pairs_shape(pair, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, vec4, nodes, sign_mode,
+                                   meet.votes, stream);
+        }
+    }
     if (homogeneous ? hom_proj_domain(M, n) : proj_domain(M, n)) {
         int rc = kNoFit;
 #define APPROXIFER_PROJ(T, NB, RM)                                                                                     \
