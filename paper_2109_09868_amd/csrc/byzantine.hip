@@ -1702,9 +1702,6 @@ int packed_groups(int64_t G, bool homogeneous) {
 }
 
 // ---- two lanes to a class: the library's own nodes, few workers missing ------------------------------------------------
-// Most workers that can be missing from a group that is decoded.
-int most_missing(int N, int S, int M) { return S < 0 ? N - 2 * M : S; }
-
 // Whether the nodes are cos(i pi / (N - 1)) to a few roundings: the closed forms of locate_class_pair hold for these only.
 bool chebyshev_workers(const Nodes &nodes, int N) {
     constexpr double kPi = 3.14159265358979323846;
@@ -1717,33 +1714,29 @@ bool chebyshev_workers(const Nodes &nodes, int N) {
 }
 
 struct PairShape {
-    int mt, tt, extra, missing;                            // mt = 0: not for decode_byzantine_pairs_kernel
+    int mt, tq;                                            // mt = 0: not for decode_byzantine_pairs_kernel
 };
-PairShape pair_shape(int K, int N, int S, int A, int64_t C) {
-    PairShape p = {0, 0, 0, 0};
+PairShape pair_shape(int64_t G, int K, int N, int S, int A, int64_t C) {
     const int M = K + A;
-    const int missing = most_missing(N, S, M);
-    if (M > 14 || A > kPairMaxAdversaries || missing > kPairMaxMissing || C > (1 << 24)) return p;
-    const int mt = std::max(4, (M + 1) & ~1);
-    const int sx = missing == 0 ? 0 : (missing <= 2 ? 2 : 4);
-    const int least = mt / 2 + sx / 2;
-    const int tt = std::max(least, (N - M + 1) / 2);
-    if (tt > least + 1) return p;
-    p.mt = mt;
-    p.tt = tt;
-    p.extra = tt - least;
-    p.missing = missing;
-    return p;
+    // A call of few classes is the chain of one wave, which the missing workers and registers beyond 256 lengthen most: up to
+    // 4000 classes in all the packed kernel, which gives a group several waves, is the faster one at the largest sizes (K = 11,
+    // A = 2, 28 of 32 workers, ten classes, 1 / 250 / 500 groups 17.1 / 18.6 / 22.2 us and here 18.5 / 19.7 / 21.1; K = 12,
+    // A = 3, 32 of 36, 20.0 / 21.9 / 27.8 and 23.1 / 24.9 / 26.2; K = 12, A = 2, 28 of 31 the same by either).
+    if (M >= 13 && S >= (M == 15 ? 2 : 3) && C < kClsLanes && G * C <= 4000) return {0, 0};
+    if (S < 0 || S > kPairMaxMissing || M > 15 || A > kPairMaxAdversaries || C > (1 << 24)) return {0, 0};
+    const int mt = std::max(4, (M + 1) & ~1), tq = std::max(mt / 2, (N - S - M + 1) / 2);
+    if (tq > mt / 2 + 1 || 2 * tq - (N - S - M) > 1) return {0, 0};      // the latter: K = A = 1
+    return {mt, tq};
 }
 
-// The rank-one term's inverse root for the rows of parity h (locate_class_pair): sum of e^2 = c, of N - 1 = 2 / norm.
+// The rank-one term's inverse root for the rows of parity h: 1 + lift e e^T, e^T e = c, of the Gram matrix 1 - e e^T / (N - 1).
 double pair_lift(int N, int R, int h) {
     const double c = h ? R / 2 : (R + 1) / 2 - 0.5;
     return (1.0 / std::sqrt(1.0 - c / (N - 1)) - 1.0) / c;
 }
 
 int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv,
-                    int32_t *d_status, int64_t G, int K, int N, int S, int n, int A, int64_t C, bool vec4, const Nodes &nodes,
+                    int32_t *d_status, int64_t G, int K, int N, int S, int A, int64_t C, bool vec4, const Nodes &nodes,
                     int sign_mode, int32_t *votes, hipStream_t stream) {
     PairCall call;
     call.preds = d_preds;
@@ -1759,17 +1752,15 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
     call.N = N;
     call.S = S;
     call.A = A;
-    call.n_cap = n;
     call.vec4 = vec4 ? 1 : 0;
     call.sign_mode = sign_mode;
     call.lift0 = pair_lift(N, N - K - A, 0);
     call.lift1 = pair_lift(N, N - K - A, 1);
     call.gpw = 1;
     call.parts = call.splits = 1;
-    int nw = kPairMaxWaves;
-    if (C > kPairPart) {
-        if ((C + kPairPart - 1) / kPairPart > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
-        call.parts = static_cast<int>((C + kPairPart - 1) / kPairPart);
+    if (C > kPairClasses) {
+        // more classes than a workgroup has pairs of lanes: a workgroup to every 128 of them, if they can meet
+        call.parts = static_cast<int>((C + kPairClasses - 1) / kPairClasses);
         call.splits = votes != nullptr ? call.parts : 1;
         if (G * call.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
         if (call.splits > 1) {
@@ -1777,30 +1768,19 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
             if (rc != APPROXIFER_OK) return rc;
         }
     } else {
-        const int c = static_cast<int>(C);
-        nw = (c + kPairsPerWave - 1) / kPairsPerWave;
-        const char *env = getenv("APX_GPW");
-        const char *envw = getenv("APX_NW");
-        if (env) call.gpw = atoi(env), nw = atoi(envw);
-        else if (G * nw > 1024) {
-            // pack
-            int best = nw, bg = 1; double eff = 0;
-            for (int w = 1; w <= kPairMaxWaves; ++w) {
-                const int g = std::min(w * kPairsPerWave / c, 16 * w);
-                if (g < 1) continue;
-                const double e = double(g) * c / (w * kPairsPerWave);
-                if (e > eff + 0.02) eff = e, best = w, bg = g;
-            }
-            nw = best; call.gpw = bg;
-        }
+        // as few groups to a workgroup as give every CU one, and no more than it has pairs for.  Ten classes, K = 8, A = 2, 20
+        // of 24 workers, 4 / 8 / 12 groups: 1000 groups 13.3 / 13.5 / 14.0 us, 2048 groups 18.6 / 13.7 / 14.2, 3000 groups
+        // 18.6 / 19.0 / 14.4; two classes, 8192 groups, 16 / 32 / 64 groups: 21 / 17.9 / 24 us.
+        call.gpw = static_cast<int>(std::min<int64_t>((G + 255) / 256, kPairClasses / C));
     }
     switch (shape.mt) {
-        case 4: return run_pairs_4(shape.missing, shape.extra, call, nw, nodes, stream);
-        case 6: return run_pairs_6(shape.missing, shape.extra, call, nw, nodes, stream);
-        case 8: return run_pairs_8(shape.missing, shape.extra, call, nw, nodes, stream);
-        case 10: return run_pairs_10(shape.missing, shape.extra, call, nw, nodes, stream);
-        case 12: return run_pairs_12(shape.missing, shape.extra, call, nw, nodes, stream);
-        default: return run_pairs_14(shape.missing, shape.extra, call, nw, nodes, stream);
+        case 4: return run_pairs_4(shape.tq, call, nodes, stream);
+        case 6: return run_pairs_6(shape.tq, call, nodes, stream);
+        case 8: return run_pairs_8(shape.tq, call, nodes, stream);
+        case 10: return run_pairs_10(shape.tq, call, nodes, stream);
+        case 12: return run_pairs_12(shape.tq, call, nodes, stream);
+        case 14: return run_pairs_14(shape.tq, call, nodes, stream);
+        default: return run_pairs_16(shape.tq, call, nodes, stream);
     }
 }
 
@@ -1968,10 +1948,10 @@ int launch_decode_byzantine(const float *d_preds, const uint8_t *d_mask, float *
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
 
     if (!homogeneous) {
-        const PairShape pair = pair_shape(K, N, S, A, C);
+        const PairShape pair = pair_shape(G, K, N, S, A, C);
         if (pair.mt != 0 && chebyshev_workers(nodes, N)) {
-            const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, C > kPairPart ? votes_bytes(G, N) : 0);
-            return run_pairs_shape(pair, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, n, A, C, vec4, nodes, sign_mode,
+            const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, C > kPairClasses ? votes_bytes(G, N) : 0);
+            return run_pairs_shape(pair, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, A, C, vec4, nodes, sign_mode,
                                    meet.votes, stream);
         }
     }

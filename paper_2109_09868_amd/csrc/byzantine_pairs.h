@@ -10,8 +10,9 @@ namespace approxifer {
 constexpr int kPairsPerWave = kWave / 2;
 constexpr int kPairMaxAdversaries = 3;
 constexpr int kPairMaxMissing = 4;
-constexpr int kPairMaxWaves = 4;
-constexpr int kPairPart = kPairMaxWaves * kPairsPerWave;   // classes of a workgroup that has part of a group's
+constexpr int kPairWaves = 4;                             // of a workgroup: one to a SIMD
+constexpr int kPairThreads = kPairWaves * kWave, kPairRows = kPairThreads / 16;
+constexpr int kPairClasses = kPairWaves * kPairsPerWave;  // of a workgroup
 
 // Launch arguments of decode_byzantine_pairs_kernel, by value.
 struct PairCall {
@@ -20,7 +21,7 @@ struct PairCall {
     float *out;
     int32_t *adv, *status, *votes;
     int64_t G, C, Cv;
-    int K, N, S, A, n_cap, vec4, sign_mode;
+    int K, N, S, A, vec4, sign_mode;
     int gpw;                 // groups of a workgroup (whole groups), or
     int parts, splits;       // parts > 1: parts of a group's classes, dealt to `splits` workgroups
     double lift0, lift1;     // see locate_class_pair
@@ -33,8 +34,17 @@ __device__ __forceinline__ double choose(bool first, double x, double y) {
     return first ? x : y;
 }
 __device__ __forceinline__ double pair_other(double v) { return dpp_exchange<kDppQuadXor1>(v); }
-__device__ __forceinline__ double rows_other(double v, int distance) {     // of lane ^ distance, 16 or 32
-    return __shfl_xor(v, distance);
+// v of this lane and of lane ^ DISTANCE, 16 or 32, added: the same bits in both
+template <int DISTANCE>
+__device__ __forceinline__ double rows_sum(double v) {
+    const unsigned lo = __double2loint(v), hi = __double2hiint(v);
+    if constexpr (DISTANCE == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    }
 }
 __device__ __forceinline__ double pair_sum(double v) { return v + pair_other(v); }
 // minimum and maximum of numbers (no NaN): the plain instruction, without the quieting that fmin and fmax bring
@@ -54,10 +64,28 @@ __device__ __forceinline__ double max_number(double a, double b) {
     return r;
 }
 
-// Tile: MT >= M columns (even), TT row slots to a lane, up to SX missing workers; 2 TT >= N - M.
-template <int MT, int TT>
+// A double held in accumulation registers: the vector ALUs cannot read them, but they are there.
+struct Parked {
+    int lo, hi;
+};
+__device__ __forceinline__ Parked park(double v) {
+    Parked p;
+    asm("v_accvgpr_write_b32 %0, %1" : "=a"(p.lo) : "v"(__double2loint(v)));
+    asm("v_accvgpr_write_b32 %0, %1" : "=a"(p.hi) : "v"(__double2hiint(v)));
+    return p;
+}
+__device__ __forceinline__ double parked(const Parked &p) {
+    int lo, hi;
+    asm("v_accvgpr_read_b32 %0, %1" : "=v"(lo) : "a"(p.lo));
+    asm("v_accvgpr_read_b32 %0, %1" : "=v"(hi) : "a"(p.hi));
+    return __hiloint2double(hi, lo);
+}
+
+// Tile: MT >= M columns (even), S missing workers, TQ row slots to a lane: 2 TQ >= N - S - M > 2 TQ - 2.
+template <int MT, int TQ, int S>
 struct PairTile {
     static constexpr int kMH = MT / 2;
+    static constexpr int TT = TQ + (S + 1) / 2;            // slots before the missing workers are taken out
     static constexpr int kLam = kMH + TT;                  // moments of one parity that the system is formed from
     static constexpr int kLamPad = (kLam + 1) & ~1;
     static constexpr int kNodes = (MT + 2 * TT + 1) / 2;   // most nodes that are not mirror images of others
@@ -66,36 +94,31 @@ struct PairTile {
 
 // The table tab[i][h][s] = w_i T_{2s+h}(beta_i) over the nodes i < ceil(N / 2), w_i = (-1)^i, halved at the end node and at
 // a node in the middle (its own mirror image, which is counted twice); zero for i up to kNodes.  T_t(cos x) = cos t x: the
-// values are nodes again.  A row of sixteen lanes takes every (rows)-th t of sixteen nodes; `beta`: LDS.
-template <int MT, int TT>
+// values are nodes again.  A row of sixteen lanes takes every sixteenth t of sixteen nodes; `beta`: LDS.
+template <int MT, int TQ, int S>
 __device__ __forceinline__ void pair_table(double *tab, int N, const double *beta) {
-    typedef PairTile<MT, TT> Tile;
-    constexpr int kTs = 2 * Tile::kLamPad, kSteps = (kTs + 3) / 4;
-    const int NH = (N + 1) / 2, period = 2 * (N - 1);
-    const int rows = blockDim.x / 16, r = threadIdx.x / 16;              // 4 to 16
+    typedef PairTile<MT, TQ, S> Tile;
+    constexpr int kTs = 2 * Tile::kLamPad;
+    const int period = 2 * (N - 1), r = threadIdx.x / 16;
 #pragma unroll
     for (int i0 = 0; i0 < Tile::kNodes; i0 += 16) {
         const int i = i0 + threadIdx.x % 16;
-        const bool node = i < NH;
+        const bool node = i < (N + 1) / 2;
         const double w = !node ? 0.0 : (i & 1 ? -1.0 : 1.0) * (i == 0 ? 0.5 : 1.0) * (2 * i == N - 1 ? 0.5 : 1.0);
-        int step = node ? i * rows : 0, k = node ? i * r : 0;            // modulo the period: i * 16 <= 4 periods
+        int step = node ? i * kPairRows : 0, k = node ? i * r : 0;       // modulo the period: i * 16 <= 4 periods
 #pragma unroll
         for (int m = 4; m > 0; m /= 2) {
             step = step >= m * period ? step - m * period : step;
             k = k >= m * period ? k - m * period : k;
         }
-        const auto entries = [&](int u0, int u1) {
 #pragma unroll
-            for (int u = u0; u < u1; ++u) {
-                const int t = r + u * rows;
-                const double v = beta[k < N ? k : period - k];
-                if (i < Tile::kNodes && t < kTs) tab[i * kTs + (t & 1) * Tile::kLamPad + t / 2] = w * v;
-                k += step;
-                k = k >= period ? k - period : k;
-            }
-        };
-        entries(0, 2);                                    // four waves need no more of these, or three
-        if (2 * rows < kTs) entries(2, kSteps);
+        for (int t0 = 0; t0 < kTs; t0 += kPairRows) {
+            const int t = t0 + r;
+            const double v = beta[k < N ? k : period - k];
+            if (i < Tile::kNodes && t < kTs) tab[i * kTs + (t & 1) * Tile::kLamPad + t / 2] = w * v;
+            k += step;
+            k = k >= period ? k - period : k;
+        }
     }
 }
 
@@ -119,12 +142,12 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
 // 2, 20 of 24 workers 1.4e-10 and 5e-10.
 //   y, ys: the class's predictions, y[i ys] for worker i (LDS), zero where there is no answer
 //   bits: workers that answered, missing: the others;  votes: the group's counters;  live: the pair has a class
-template <int MT, int TT, int SX>
+template <int MT, int TQ, int S>
 __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsigned long long bits, unsigned long long missing,
                                                   const double *tab, int N, int M, int A, double lift, bool live, int *votes) {
-    typedef PairTile<MT, TT> Tile;
+    typedef PairTile<MT, TQ, S> Tile;
     typedef double v2d __attribute__((ext_vector_type(2)));
-    constexpr int MH = Tile::kMH, kLam = Tile::kLam, kRow = 2 * Tile::kLamPad;
+    constexpr int TT = Tile::TT, MH = Tile::kMH, kLam = Tile::kLam, kRow = 2 * Tile::kLamPad;
     const int h = lane_id() & 1;
     const int NH = (N + 1) / 2;
     const int R = N - M;
@@ -136,16 +159,28 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 #pragma unroll
     for (int s = 0; s < Tile::kLamPad; ++s) p[s] = 0.0;
     {
-        const float *lo = y, *hi = y + (N - 1) * ys;
+        // a node's row is read while the one before it is multiplied: left to itself the compiler waits for every two reads
+        constexpr int kReads = Tile::kLamPad / 2;
+        v2d row[2][kReads];
+        float lo[2], hi[2];
+        const auto read = [&](int i) {
 #pragma unroll
-        for (int i = 0; i < Tile::kNodes; ++i, lo += ys, hi -= ys) {     // N >= kNodes; rows past NH of the table are zero
-            const double z = fma(mirror, static_cast<double>(*hi), static_cast<double>(*lo));
+            for (int s = 0; s < kReads; ++s) row[i & 1][s] = *reinterpret_cast<const v2d *>(own + i * kRow + 2 * s);
+            lo[i & 1] = y[i * ys];
+            hi[i & 1] = y[(N - 1 - i) * ys];
+        };
+        read(0);
 #pragma unroll
-            for (int s = 0; s < Tile::kLamPad; s += 2) {
-                const v2d t = *reinterpret_cast<const v2d *>(own + i * kRow + s);
-                p[s] = fma(t[0], z, p[s]);
-                p[s + 1] = fma(t[1], z, p[s + 1]);
+        for (int i = 0; i < Tile::kNodes; ++i) {          // N >= kNodes; rows past NH of the table are zero
+            if (i + 1 < Tile::kNodes) read(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const double z = fma(mirror, static_cast<double>(hi[i & 1]), static_cast<double>(lo[i & 1]));
+#pragma unroll
+            for (int s = 0; s < kReads; ++s) {
+                p[2 * s] = fma(row[i & 1][s][0], z, p[2 * s]);
+                p[2 * s + 1] = fma(row[i & 1][s][1], z, p[2 * s + 1]);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     double o[kLam], below[MH], ahead[kLam - 1];
@@ -156,73 +191,108 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 #pragma unroll
     for (int s = 0; s < kLam - 1; ++s) ahead[s] = choose(h, o[s + 1], o[s]); // lambda_{2s+1+h}
 
-    // ---- the system: a[e][t] = entry (2t + h, e), orthonormal rows --------------------------------------------------------
+    // ---- the system: a[e][t] = entry (2t + h, e), orthonormal rows, without the span of the missing workers' columns ------
     const double first = h ? 1.0 : 0.70710678118654752440;              // sqrt(1/2) for row 0
-    double a[MT][TT], x[SX > 0 ? SX : 1][TT];
-    const double there0 = 2 * (TT - 2) + h < R ? 1.0 : 0.0, there1 = 2 * (TT - 1) + h < R ? 1.0 : 0.0;   // of the last rows
-    const auto finish_column = [&](double (&c)[TT]) {
+    double there[2];                                      // 2t + h < R for the last two slots
+#pragma unroll
+    for (int t = TT - 2; t < TT; ++t) there[t - TT + 2] = 2 * t + h < R ? 1.0 : 0.0;
+    const auto orthonormal = [&](double (&c)[TT]) {
         c[0] *= first;
-        c[TT - 2] *= there0;
-        c[TT - 1] *= there1;
+        c[TT - 2] *= there[0];
+        c[TT - 1] *= there[1];
         double sum = first * c[0];
 #pragma unroll
         for (int t = 1; t < TT; ++t) sum += c[t];
         sum *= lift;
-        c[0] = fma(TT == 2 ? first * there0 : first, sum, c[0]);
+        c[0] = fma(TT == 2 ? first * there[0] : first, sum, c[0]);
 #pragma unroll
-        for (int t = 1; t < TT; ++t) c[t] = t < TT - 2 ? c[t] + sum : fma(t == TT - 2 ? there0 : there1, sum, c[t]);
+        for (int t = 1; t < TT; ++t) c[t] = t < TT - 2 ? c[t] + sum : fma(there[t - TT + 2], sum, c[t]);
+    };
+    // Reflections that take the missing workers' columns to the last S rows; the rows before these are then free of them.
+    double x[S > 0 ? S : 1][TT], scale[S > 0 ? S : 1];
+    const auto reflect = [&](double (&c)[TT], int s) {
+        double d = x[s][0] * c[0];
+#pragma unroll
+        for (int t = 1; t < TT; ++t) d = fma(x[s][t], c[t], d);
+        const double f = pair_sum(d) * scale[s];
+#pragma unroll
+        for (int t = 0; t < TT; ++t) c[t] = fma(f, x[s][t], c[t]);
+    };
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int w = __builtin_ctzll(missing);
+        missing &= missing - 1ull;
+        const double sign = 2 * w >= N ? mirror : 1.0;
+        const double *row = own + (2 * w >= N ? N - 1 - w : w) * kRow;
+#pragma unroll
+        for (int t = 0; t < TT; ++t) x[s][t] = sign * row[t];
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) orthonormal(x[s]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int r = R - 1 - s;
+        double sig = 0.0, at = 0.0;                       // over the rows up to r; row r itself.  R > 2 TT - 3
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+            if (2 * t + 1 > 2 * TT - 3 - s) {
+                x[s][t] = 2 * t + h <= r ? x[s][t] : 0.0;
+                at = 2 * t + h == r ? x[s][t] : at;
+            }
+            sig = fma(x[s][t], x[s][t], sig);
+        }
+        sig = pair_sum(sig);
+        at = pair_sum(at);
+        const double norm = sqrt_normal(sig), to = at >= 0.0 ? -norm : norm;
+        scale[s] = -rcp_normal(fma(-to, at, sig));
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (2 * t + 1 > 2 * TT - 3 - s) x[s][t] = 2 * t + h == r ? x[s][t] - to : x[s][t];
+#pragma unroll
+        for (int b = s + 1; b < S; ++b) reflect(x[b], s);
+    }
+    double a[MT][TQ];
+    const double kept = 2 * (TQ - 1) + h < R - S ? 1.0 : 0.0;
+    const auto column = [&](double (&c)[TT], double (&to)[TQ]) {
+        orthonormal(c);
+#pragma unroll
+        for (int s = 0; s < S; ++s) reflect(c, s);
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) to[t] = S > 0 && t == TQ - 1 ? kept * c[t] : c[t];
     };
     // odd columns first: the other lane's moments are then done with
+    constexpr bool kPark = MT * TQ + S * TT > 130;        // .. and their columns out of the way, where registers are short
+    Parked away[MH][TQ];
 #pragma unroll
     for (int u = 0; u < MH; ++u) {
+        double c[TT];
 #pragma unroll
-        for (int t = 0; t < TT; ++t) a[2 * u + 1][t] = ahead[t + u] + (t > u ? ahead[t > u ? t - u - 1 : 0] : o[t > u ? 0 : u - t]);
-        finish_column(a[2 * u + 1]);
+        for (int t = 0; t < TT; ++t) c[t] = ahead[t + u] + (t > u ? ahead[t > u ? t - u - 1 : 0] : o[t > u ? 0 : u - t]);
+        column(c, a[2 * u + 1]);
+        if constexpr (kPark) {
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) away[u][t] = park(a[2 * u + 1][t]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int u = 0; u < MH; ++u) {
+        double c[TT];
 #pragma unroll
-        for (int t = 0; t < TT; ++t) a[2 * u][t] = p[t + u] + (t >= u ? p[t >= u ? t - u : 0] : below[t >= u ? 1 : u - t]);
-        finish_column(a[2 * u]);
+        for (int t = 0; t < TT; ++t) c[t] = p[t + u] + (t >= u ? p[t >= u ? t - u : 0] : below[t >= u ? 1 : u - t]);
+        column(c, a[2 * u]);
         if (u > 0) {
 #pragma unroll
-            for (int t = 0; t < TT; ++t) a[2 * u][t] += u % 2 ? a[0][t] : -a[0][t];      // T_{2u}(0) = (-1)^u
+            for (int t = 0; t < TQ; ++t) a[2 * u][t] += u % 2 ? a[0][t] : -a[0][t];      // T_{2u}(0) = (-1)^u
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
 
-    // ---- missing workers out of every column ------------------------------------------------------------------------------
-    if constexpr (SX > 0) {
+    if constexpr (kPark) {
 #pragma unroll
-        for (int s = 0; s < SX; ++s) {
-            const bool there = missing != 0ull;
-            const int w = there ? __builtin_ctzll(missing) : 0;
-            missing &= missing - 1ull;
-            const double sign = there ? (2 * w >= N ? mirror : 1.0) : 0.0;
-            const double *row = own + (2 * w >= N ? N - 1 - w : w) * kRow;
+        for (int u = 0; u < MH; ++u)
 #pragma unroll
-            for (int t = 0; t < TT; ++t) x[s][t] = sign * row[t];
-            finish_column(x[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < SX; ++s) {
-            double sig = x[s][0] * x[s][0];
-#pragma unroll
-            for (int t = 1; t < TT; ++t) sig = fma(x[s][t], x[s][t], sig);
-            sig = pair_sum(sig);
-            const double rs = sig > 0.0 ? rcp_normal(sig) : 0.0;         // fewer are missing: nothing to take out
-            const auto take_out = [&](double (&c)[TT]) {
-                double d = x[s][0] * c[0];
-#pragma unroll
-                for (int t = 1; t < TT; ++t) d = fma(x[s][t], c[t], d);
-                const double f = -pair_sum(d) * rs;
-#pragma unroll
-                for (int t = 0; t < TT; ++t) c[t] = fma(f, x[s][t], c[t]);
-            };
-#pragma unroll
-            for (int r = s + 1; r < SX; ++r) take_out(x[r]);
-#pragma unroll
-            for (int e = 0; e < MT; ++e) take_out(a[e]);
-        }
+            for (int t = 0; t < TQ; ++t) a[2 * u + 1][t] = parked(away[u][t]);
     }
 
     // ---- elimination: nf[j][e / 2] = minus the share of column j in column e, lane e % 2 keeping it ------------------------
@@ -232,16 +302,16 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
         if (j < M) {
             double sig = a[j][0] * a[j][0];
 #pragma unroll
-            for (int t = 1; t < TT; ++t) sig = fma(a[j][t], a[j][t], sig);
+            for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
             const double rs = rcp_normal(pair_sum(sig));
-            const auto take_out = [&](double (&c)[TT]) {
+            const auto take_out = [&](double (&c)[TQ]) {
                 double d = a[j][0] * c[0];
 #pragma unroll
-                for (int t = 1; t < TT; ++t) d = fma(a[j][t], c[t], d);
+                for (int t = 1; t < TQ; ++t) d = fma(a[j][t], c[t], d);
                 const double f = -pair_sum(d) * rs;
                 if (j + 1 < MT) {                         // the right-hand side's remainder is not needed at the end
 #pragma unroll
-                    for (int t = 0; t < TT; ++t) c[t] = fma(f, a[j][t], c[t]);
+                    for (int t = 0; t < TQ; ++t) c[t] = fma(f, a[j][t], c[t]);
                 }
                 return f;
             };
@@ -284,17 +354,27 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
     double l0 = __builtin_inf(), l1 = __builtin_inf(), l2 = __builtin_inf();
     {
         const double side = h ? -1.0 : 1.0;
+        constexpr int kReads = (MH + 1) / 2, kAhead = 2;  // rows are read two nodes ahead
+        v2d row[kAhead + 1][kReads];
+        const auto read = [&](int i) {
+#pragma unroll
+            for (int s = 0; s < kReads; ++s) row[i % (kAhead + 1)][s] = *reinterpret_cast<const v2d *>(own + i * kRow + 2 * s);
+        };
+#pragma unroll
+        for (int i = 0; i < kAhead && i < Tile::kNodes; ++i) read(i);
 #pragma unroll
         for (int i = 0; i < Tile::kNodes; ++i) {
-            double v = own[i * kRow] * c[0];
+            if (i + kAhead < Tile::kNodes) read(i + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
+            double v = 0.0;
 #pragma unroll
-            for (int s = 1; s < MH; ++s) v = fma(own[i * kRow + s], c[s], v);
+            for (int s = 0; s < MH; ++s) v = fma(row[i % (kAhead + 1)][s / 2][s % 2], c[s], v);
             v = fma(side, pair_other(v), v);
             if (i == 0) v += v;                           // the table has half of these
             if (i >= Tile::kNodes - 4 && 2 * i == N - 1) v += v;
             v = min_magnitude(v, 1e300);                  // not a number: behind every number
             // nor does a worker that did not answer, or a row past the last node, come before any that did
-            const bool there = SX > 0 ? (mine & (1u << i)) != 0u : i < Tile::kNodes - 4 || (i < NH && !(h && 2 * i == N - 1));
+            const bool there = S > 0 ? (mine & (1u << i)) != 0u : i < Tile::kNodes - 4 || (i < NH && !(h && 2 * i == N - 1));
             const double k = __hiloint2double(there ? __double2hiint(v) : 0x7fe00000,
                                               (__double2loint(v) & ~63) | (h ? N - 1 - i : i));
             l2 = min_number(l2, max_number(l1, k));
@@ -319,38 +399,40 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 // s_i is the sign of worker i, 0 if it does not count.  A query node that is a worker's node has T = 0 there and takes that
 // worker's row.  More classes: `splits` workgroups take turns at 128 of them each, the last to finish decodes the group.
 // No row of a worker that did not answer is read.
-// dynamic LDS: double tab | whole groups: T[N][16] | sgn[4 nw][N] | beta_s[N]; parts: WdT[(n_cap - A) KP] | alpha_s[K] | beta_s[N]
+// dynamic LDS: double tab | whole groups: T[N][16] | sgn[16][N] | beta_s[N]; parts: WdT[(N - S - A) KP] | alpha_s[K] | beta_s[N]
 //              | float Ysh[groups][N][classes] | uint64 bits[gpw] | int votes[gpw][64] | hit[16]
 //              | parts: avail[N] | F[N] | Fpos[N] | flag
-__host__ __device__ constexpr int pair_decode_doubles(bool whole, int nw, int K, int N, int n_cap, int A) {
-    const int d = whole ? 16 * N + 4 * nw * N + N : (n_cap - A) * ((K + 3) & ~3) + K + N;
+__host__ __device__ constexpr int pair_decode_doubles(bool whole, int K, int N, int S, int A) {
+    const int d = whole ? 16 * N + kPairRows * N + N : (N - S - A) * ((K + 3) & ~3) + K + N;
     return (d + 1) & ~1;
 }
 __host__ __device__ constexpr int64_t pair_tile_floats(bool whole, int gpw, int N, int64_t C) {
-    return ((whole ? gpw * N * C : static_cast<int64_t>(N) * kPairPart) + 3) & ~static_cast<int64_t>(3);
+    return ((whole ? gpw * N * C : static_cast<int64_t>(N) * kPairClasses) + 3) & ~static_cast<int64_t>(3);
 }
-template <int MT, int TT>
-constexpr size_t pair_lds_bytes(bool whole, int gpw, int nw, int K, int N, int n_cap, int A, int64_t C) {
-    return sizeof(double) * (PairTile<MT, TT>::kTableDoubles + pair_decode_doubles(whole, nw, K, N, n_cap, A)) +
+template <int MT, int TQ, int S>
+constexpr size_t pair_lds_bytes(bool whole, int gpw, int K, int N, int A, int64_t C) {
+    return sizeof(double) * (PairTile<MT, TQ, S>::kTableDoubles + pair_decode_doubles(whole, K, N, S, A)) +
            sizeof(float) * pair_tile_floats(whole, gpw, N, C) + sizeof(uint64_t) * gpw +
            sizeof(int) * (kWave * gpw + 16 + (whole ? 0 : 3 * N + 2));
 }
 
-template <int MT, int TT, int SX, bool WHOLE>
-__global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_per_eu(MT * TT <= (WHOLE ? 100 : 50) ? 2 : 1))) void decode_byzantine_pairs_kernel(
+template <int MT, int TQ, int S, bool WHOLE>
+constexpr int kPairWavesPerSimd = MT * TQ + S * (TQ + (S + 1) / 2) <= (WHOLE ? 100 : 60) ? 2 : 1;
+
+template <int MT, int TQ, int S, bool WHOLE>
+__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kPairWavesPerSimd<MT, TQ, S, WHOLE>))) void decode_byzantine_pairs_kernel(
     const PairCall a, const Nodes nodes) {
-    typedef PairTile<MT, TT> Tile;
+    typedef PairTile<MT, TQ, S> Tile;
     extern __shared__ __align__(16) double lds_d[];
     constexpr bool whole = WHOLE;
     const int K = a.K, N = a.N, A = a.A, M = K + A;
-    const int nw = blockDim.x / kWave;
     const int tid = threadIdx.x, wv = wave_id(), lane = lane_id(), h = lane & 1;
     double *tab = lds_d;
     double *T = tab + Tile::kTableDoubles;
     double *sgn = T + 16 * N;
-    double *WdT = T, *alpha_s = WdT + (a.n_cap - A) * round_up4(K);
-    double *beta_s = whole ? sgn + 4 * nw * N : alpha_s + K;
-    float *Ysh = reinterpret_cast<float *>(T + pair_decode_doubles(whole, nw, K, N, a.n_cap, A));
+    double *WdT = T, *alpha_s = WdT + (N - S - A) * round_up4(K);
+    double *beta_s = whole ? sgn + kPairRows * N : alpha_s + K;
+    float *Ysh = reinterpret_cast<float *>(T + pair_decode_doubles(whole, K, N, S, A));
     unsigned long long *bits = reinterpret_cast<unsigned long long *>(Ysh + pair_tile_floats(whole, a.gpw, N, a.C));
     int *votes = reinterpret_cast<int *>(bits + a.gpw);
     int *hit = votes + kWave * a.gpw;
@@ -360,23 +442,23 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
     const int part0 = whole ? 0 : static_cast<int>(blockIdx.x - g0 * a.splits);
     const int here = !whole ? 1 : (a.G - g0 < a.gpw ? static_cast<int>(a.G - g0) : a.gpw);
 
-    // masks: a wave reads the rows of groups wv, wv + nw, .. (N < 64: one ballot each)
+    // masks: a wave reads the rows of groups wv, wv + 4, .. (N < 64: one ballot each)
     constexpr int kMaskRows = 4;
-    for (int q0 = wv; q0 < a.gpw; q0 += kMaskRows * nw) {
+    for (int q0 = wv; q0 < a.gpw; q0 += kMaskRows * kPairWaves) {
         uint8_t byte[kMaskRows];
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
-            const int q = q0 + u * nw;
+            const int q = q0 + u * kPairWaves;
             byte[u] = a.mask[q < here && lane < N ? (g0 + q) * N + lane : g0 * N];
         }
 #pragma unroll
         for (int u = 0; u < kMaskRows; ++u) {
-            const int q = q0 + u * nw;
+            const int q = q0 + u * kPairWaves;
             if (q >= here) break;
             const bool b = lane < N && byte[u] != 0;
             const unsigned long long m = __ballot(b);
             const int n = static_cast<int>(__popcll(m));
-            const bool good = a.S < 0 ? (n >= 2 * M && n <= a.n_cap) : n == a.n_cap;
+            const bool good = n == N - S;
             if (lane == 0) {
                 bits[q] = good ? m : 0ull;
                 if (part0 == 0 && a.status != nullptr) a.status[g0 + q] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
@@ -389,9 +471,9 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
         if (tid < N) beta_s[tid] = nodes.beta[tid];
     } else {
         stage_nodes(nodes, K, N, alpha_s, beta_s);
-        for (int e = tid; e < (a.n_cap - A) * round_up4(K); e += blockDim.x) WdT[e] = 0.0;
+        for (int e = tid; e < (N - S - A) * round_up4(K); e += kPairThreads) WdT[e] = 0.0;
     }
-    for (int e = tid; e < kWave * a.gpw; e += blockDim.x) votes[e] = 0;
+    for (int e = tid; e < kWave * a.gpw; e += kPairThreads) votes[e] = 0;
     if (tid < 16) hit[tid] = -1;
     __syncthreads();
     if (!whole && bits[0] == 0ull) return;
@@ -399,13 +481,13 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
     const unsigned long long all = (1ull << N) - 1ull;
     const double lift = h ? a.lift1 : a.lift0;
     const int slot = wv * kPairsPerWave + lane / 2;
-    const int Cs = whole ? static_cast<int>(a.C) : kPairPart;            // classes of a row of the tile
+    const int Cs = whole ? static_cast<int>(a.C) : kPairClasses;            // classes of a row of the tile
     const int C = static_cast<int>(a.C);
     const int q = whole ? slot / Cs : 0;
     const int c_rel = slot - q * Cs;                      // parts: slot < 128 = Cs
     const char *src = reinterpret_cast<const char *>(a.preds + static_cast<size_t>(g0) * N * a.C);
     for (int part = part0; part < (whole ? 1 : a.parts); part += whole ? 1 : a.splits) {
-        const int c = part * kPairPart + c_rel;
+        const int c = part * kPairClasses + c_rel;
         const bool in = q < here && c < C;
         const unsigned long long rows = in ? bits[q] : 0ull;
         const bool live = rows != 0ull;
@@ -422,23 +504,18 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
                 pf[u] = *reinterpret_cast<const float *>(src + ((own_rows & (1ull << (2 * u))) != 0ull ? at : first));
         }
         if (part == part0) {                              // meanwhile the tables
-            pair_table<MT, TT>(tab, N, beta_s);
+            pair_table<MT, TQ, S>(tab, N, beta_s);
             if (whole) {                                  // lane = query, a worker to each row of lanes
-                const int rows = blockDim.x / 16;
-                const auto workers = [&](int u0, int u1) {
 #pragma unroll
-                    for (int u = u0; u < u1; ++u) {
-                        const int i = u * rows + tid / 16;
-                        const double d = alpha - beta_s[i < N ? i : 0];
-                        const bool at = d == 0.0;         // nodes are distinct: one worker at most
-                        if (i < N) {
-                            T[i * 16 + (lane & 15)] = at ? 0.0 : rcp_normal(d);
-                            if (at && (lane & 15) < K) hit[lane & 15] = i;
-                        }
+                for (int u = 0; u < (2 * Tile::kNodes + kPairRows - 1) / kPairRows; ++u) {
+                    const int i = u * kPairRows + tid / 16;
+                    const double d = alpha - beta_s[i < N ? i : 0];
+                    const bool at = d == 0.0;             // nodes are distinct: one worker at most
+                    if (i < N) {
+                        T[i * 16 + (lane & 15)] = at ? 0.0 : rcp_normal(d);
+                        if (at && (lane & 15) < K) hit[lane & 15] = i;
                     }
-                };
-                workers(0, 3);
-                if (3 * rows < N) workers(3, (Tile::kNodes + 1) / 2);
+                }
             }
         }
         if (live) {
@@ -448,7 +525,11 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
         }
         if (part == part0) __syncthreads();
         else __builtin_amdgcn_wave_barrier();
-        locate_class_pair<MT, TT, SX>(y, Cs, rows, all & ~rows, tab, N, M, A, lift, live, votes + kWave * (in ? q : 0));
+        int Np = N, Mp = M, Ap = A, same = 0;
+        // parts: nothing of what follows is worth carrying from one to the next, registers being what is short
+        if (!whole) asm volatile("" : "+s"(Np), "+s"(Mp), "+s"(Ap), "+v"(same));
+        if (wv * kPairsPerWave < here * Cs)               // a wave without a class has its share in the rest
+            locate_class_pair<MT, TQ, S>(y, Cs, rows, all & ~rows, tab + same, Np, Mp, Ap, lift, live, votes + kWave * (in ? q : 0));
         __builtin_amdgcn_wave_barrier();                  // the next part's rows: this pair's own places again
     }
     __syncthreads();
@@ -465,10 +546,10 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
         // two or four rows share the workers of a unit (sixteen classes of a group) where the workgroup has that many to spare
         const int l = lane & 15;
         const int chunks = (Cs + 15) / 16, units = here * chunks;
-        const int share = units * 4 <= nw * 4 ? 2 : (units * 2 <= nw * 4 ? 1 : 0);           // log2
+        const int share = units * 4 <= kPairRows ? 2 : (units * 2 <= kPairRows ? 1 : 0);           // log2
         const int sub = (lane / 16) & ((1 << share) - 1), per_wave = 4 >> share;
         double *sg = sgn + (wv * 4 + lane / 16) * N;
-        for (int u0 = wv * per_wave; u0 < units; u0 += nw * per_wave) {
+        for (int u0 = wv * per_wave; u0 < units; u0 += kPairWaves * per_wave) {
             const int unit = u0 + ((lane / 16) >> share);
             const int q = unit < units ? unit / chunks : 0;
             const int c = (unit - q * chunks) * 16 + l;
@@ -482,7 +563,8 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
                 const int w = l + 16 * p;
                 key[p] = p < 2 || N > 32 ? (w < N ? (votes[q * kWave + w] << 6) | (kWave - 1 - w) : -1) : -1;
             }
-            unsigned long long drop = 0ull;
+            unsigned drop = 0u, drop_high = 0u;           // workers 0 .. 31, 32 ..
+            int located = 0;                              // lane k < A: the k-th of the located workers, in ascending order
 #pragma unroll
             for (int pick = 0; pick < kPairMaxAdversaries; ++pick) {
                 if (pick >= A) break;
@@ -491,20 +573,29 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
                 m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor2, 0xF, 0xF, true));
                 m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowHalfMirror, 0xF, 0xF, true));
                 m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowMirror, 0xF, 0xF, true));
-                drop |= 1ull << (kWave - 1 - (m & (kWave - 1)));
+                const int w = kWave - 1 - (m & (kWave - 1));
+                drop |= w < 32 ? 1u << w : 0u;
+                drop_high |= w < 32 ? 0u : 1u << (w - 32);
 #pragma unroll
                 for (int p = 0; p < 3; ++p) key[p] = key[p] == m ? -1 : key[p];          // keys of workers differ
             }
-            const unsigned long long left = there & ~drop;
-            const auto sign = [&](int w) {
-                const unsigned long long before = (1ull << w) - 1ull;
-                const int odd = a.sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK ? static_cast<int>(__popcll(left & before)) : w;
-                sg[w] = __hiloint2double((left >> w) & 1ull ? 0x3ff00000 | odd << 31 : 0, 0);              // 1, -1 or 0
-                if (live && c == l && sub == 0 && ((drop >> w) & 1ull)) a.adv[(g0 + q) * A + __popcll(drop & before)] = w;
+            {
+                unsigned long long rest = drop | static_cast<unsigned long long>(drop_high) << 32;
+#pragma unroll
+                for (int k = 0; k < kPairMaxAdversaries; ++k) {
+                    located = l == k ? __builtin_ctzll(rest | 1ull << 63) : located;
+                    rest &= rest - 1ull;
+                }
+                if (live && c < A && sub == 0) a.adv[(g0 + q) * A + l] = located;         // the group's first chunk: c = l
+            }
+            const unsigned left = static_cast<unsigned>(there) & ~drop, left_high = static_cast<unsigned>(there >> 32) & ~drop_high;
+            const auto sign = [&](int w, unsigned of, int before, int at) {              // w: bit of `of`; `before` are left ahead of it
+                const int odd = a.sign_mode == APPROXIFER_SIGN_SURVIVOR_RANK ? before + __popc(of & ((1u << w) - 1u)) : w;
+                sg[at] = __hiloint2double((of >> w) & 1u ? 0x3ff00000 | odd << 31 : 0, 0);                 // 1, -1 or 0
             };
-            if (l < N) sign(l);
-            if (l + 16 < N) sign(l + 16);
-            if (N > 32 && l + 32 < N) sign(l + 32);
+            if (l < N) sign(l, left, 0, l);
+            if (l + 16 < N) sign(l + 16, left, 0, l + 16);
+            if (N > 32 && l + 32 < N) sign(l, left_high, __popc(left), l + 32);
             __builtin_amdgcn_wave_barrier();
             const float *y = Ysh + q * N * Cs + (c < Cs ? c : 0);
             double acc[MT - 1], den = 0.0;                // K < M <= MT
@@ -545,10 +636,15 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
                 }
                 block(room);
             }
-            for (int d = 16; d < 16 << share; d *= 2) {
-                den += rows_other(den, d);
+            if (share > 0) {
+                den = rows_sum<16>(den);
 #pragma unroll
-                for (int j = 0; j < MT - 1; ++j) acc[j] += rows_other(acc[j], d);
+                for (int j = 0; j < MT - 1; ++j) acc[j] = rows_sum<16>(acc[j]);
+            }
+            if (share > 1) {
+                den = rows_sum<32>(den);
+#pragma unroll
+                for (int j = 0; j < MT - 1; ++j) acc[j] = rows_sum<32>(acc[j]);
             }
             const double rden = rcp_normal(den);
             const int on = hit[l];                            // query l's own worker, if it is one's node
@@ -561,7 +657,7 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
                     double v = acc[j] * row_bcast_dyn(rden, j);
                     if (hits) {
                         const int at = __builtin_amdgcn_readlane(on, j);
-                        if (at >= 0 && ((left >> at) & 1ull) != 0ull) v = static_cast<double>(y[at * Cs]);
+                        if (at >= 0 && ((at < 32 ? left >> at : left_high >> (at - 32)) & 1u) != 0u) v = static_cast<double>(y[at * Cs]);
                     }
                     if (mine && (j & ((1 << share) - 1)) == sub) og[j * Cs] = static_cast<float>(v);
                 }
@@ -571,30 +667,40 @@ __global__ __launch_bounds__(kPairMaxWaves *kWave) __attribute__((amdgpu_waves_p
     }
 }
 
-template <int MT, int TT, int SX>
-int run_pairs(PairCall call, int nw, const Nodes &nodes, hipStream_t stream) {
+template <int MT, int TQ, int S>
+int run_pairs(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     const bool whole = call.parts == 1;
-    const size_t lds = pair_lds_bytes<MT, TT>(whole, call.gpw, nw, call.K, call.N, call.n_cap, call.A, call.C);
-    const auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TT, SX, true> : decode_byzantine_pairs_kernel<MT, TT, SX, false>;
+    const size_t lds = pair_lds_bytes<MT, TQ, S>(whole, call.gpw, call.K, call.N, call.A, call.C);
+    const auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TQ, S, true> : decode_byzantine_pairs_kernel<MT, TQ, S, false>;
     if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                static_cast<int>(lds)) != hipSuccess)
         return APPROXIFER_ERR_LAUNCH;
     const int64_t blocks = whole ? (call.G + call.gpw - 1) / call.gpw : call.G * call.splits;
-    return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(nw * kWave), lds, stream, call, nodes));
+    return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kPairThreads), lds, stream, call, nodes));
 }
 
-// One function per M (rounded up to even), each in a source file of its own choosing: extra = TT - MT / 2 - SX / 2.
-template <int MT>
-int run_pairs_columns(int missing, int extra, const PairCall &call, int nw, const Nodes &nodes, hipStream_t stream) {
-    if (missing == 0) return extra ? run_pairs<MT, MT / 2 + 1, 0>(call, nw, nodes, stream) : run_pairs<MT, MT / 2, 0>(call, nw, nodes, stream);
-    if (missing <= 2) return extra ? run_pairs<MT, MT / 2 + 2, 2>(call, nw, nodes, stream) : run_pairs<MT, MT / 2 + 1, 2>(call, nw, nodes, stream);
-    return extra ? run_pairs<MT, MT / 2 + 3, 4>(call, nw, nodes, stream) : run_pairs<MT, MT / 2 + 2, 4>(call, nw, nodes, stream);
+// M rounded up to even, TQ = MT / 2 or one more.
+template <int MT, int TQ>
+int run_pairs_rows(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
+    switch (call.S) {
+        case 0: return run_pairs<MT, TQ, 0>(call, nodes, stream);
+        case 1: return run_pairs<MT, TQ, 1>(call, nodes, stream);
+        case 2: return run_pairs<MT, TQ, 2>(call, nodes, stream);
+        case 3: return run_pairs<MT, TQ, 3>(call, nodes, stream);
+        default: return run_pairs<MT, TQ, 4>(call, nodes, stream);
+    }
 }
-int run_pairs_4(int, int, const PairCall &, int, const Nodes &, hipStream_t);
-int run_pairs_6(int, int, const PairCall &, int, const Nodes &, hipStream_t);
-int run_pairs_8(int, int, const PairCall &, int, const Nodes &, hipStream_t);
-int run_pairs_10(int, int, const PairCall &, int, const Nodes &, hipStream_t);
-int run_pairs_12(int, int, const PairCall &, int, const Nodes &, hipStream_t);
-int run_pairs_14(int, int, const PairCall &, int, const Nodes &, hipStream_t);
+template <int MT>
+int run_pairs_columns(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream) {
+    return tq == MT / 2 ? run_pairs_rows<MT, MT / 2>(call, nodes, stream) : run_pairs_rows<MT, MT / 2 + 1>(call, nodes, stream);
+}
+// one function per MT, spread over source files for the build's sake
+int run_pairs_4(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_6(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_8(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_10(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_12(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_14(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_pairs_16(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 
 }  // namespace approxifer
