@@ -7,7 +7,11 @@
 // returns the A most voted workers.  The system is  V p + C_c q = y_c  with V the n x M Vandermonde
 // matrix of the nodes and C_c = -diag(y_c) V[:, 1:].
 //
-// Three kernels compute the same thing:
+// Four kernels compute the same thing:
+//
+//  * decode_byzantine_pairs_kernel (byzantine_pairs.h; the library's own worker nodes, a fixed number of at most four
+//    missing, K+A <= 15, up to two workers more than eq. (3) asks for: pair_shape).  Two lanes to a class; no factorisation,
+//    in the Chebyshev basis the projected system is sums of moments.
 //
 //  * decode_byzantine_proj_kernel (K+A <= 16, at most 48 available workers, n-M <= 32), one workgroup per
 //    group.  V is the same for every class of a group, so its Householder QR is done ONCE per group,
@@ -1535,6 +1539,39 @@ __global__ void clear_workspace_kernel(int32_t *__restrict__ workspace, int64_t 
     if (i < words) workspace[i] = 0;
 }
 
+// Decodes groups whose liars have been located (d_adv): a workgroup to 64 vector columns of a group.  The locating workgroups
+// leave this to a launch of its own where a group has many classes: one of them decoding all of a group, K = 8, A = 3, 26
+// workers, 55 groups of 787 classes took 116 us, 37 this way.
+// dynamic LDS: double WdT[nF KP] | alpha_s[K] | beta_s[N] | int F[N]
+size_t located_lds_bytes(int K, int N, int nF) {
+    return sizeof(double) * (static_cast<size_t>(nF) * ((K + 3) & ~3) + K + N) + sizeof(int) * N;
+}
+template <int VEC>
+__global__ __launch_bounds__(kPairThreads) void decode_located_kernel(const float *__restrict__ preds, const uint8_t *__restrict__ mask,
+                                                                      float *__restrict__ out, const int32_t *__restrict__ adv, int K,
+                                                                      int N, int S, int A, int64_t C, int64_t Cv, int64_t tiles,
+                                                                      int sign_mode, const Nodes nodes) {
+    extern __shared__ __align__(16) double lds_d[];
+    const int KP = round_up4(K), nF = N - S - A, lane = lane_id();
+    double *WdT = lds_d, *alpha_s = WdT + nF * KP, *beta_s = alpha_s + K;
+    int *F = reinterpret_cast<int *>(beta_s + N);
+    const int64_t g = blockIdx.x / tiles, tile = blockIdx.x - g * tiles;
+    bool left = lane < N && mask[g * N + lane] != 0;                      // N < 64
+    stage_nodes(nodes, K, N, alpha_s, beta_s);
+    if (static_cast<int>(__popcll(__ballot(left))) != N - S) return;      // a bad group: d_adv holds nothing
+    for (int e = threadIdx.x; e < nF * KP; e += kPairThreads) WdT[e] = 0.0;
+    for (int k = 0; k < A; ++k) left = left && adv[g * A + k] != lane;
+    const unsigned long long who = __ballot(left);
+    if (wave_id() == 0 && left) F[__popcll(who & ((1ull << lane) - 1ull))] = lane;
+    __syncthreads();
+    decoder_weights(alpha_s, beta_s, F, nF, K, KP, sign_mode, WdT);
+    __syncthreads();
+    const int64_t cv0 = tile * kColsPerTile;
+    typename PredVec<VEC>::type unused[kRowChunk];
+    contract_tile<VEC, false>(preds + static_cast<size_t>(g) * N * C, out + static_cast<size_t>(g) * K * C, F, nF, K, KP, C, cv0,
+                              cv0 + kColsPerTile < Cv ? cv0 + kColsPerTile : Cv, WdT, unused);
+}
+
 // ---- launch shapes (host) --------------------------------------------------------------------------
 constexpr int64_t kFillWaves = 4096;     // waves that put about four on every SIMD of the chip (256 CUs x 4 SIMDs)
 
@@ -1718,11 +1755,13 @@ struct PairShape {
 };
 PairShape pair_shape(int64_t G, int K, int N, int S, int A, int64_t C) {
     const int M = K + A;
-    // A call of few classes is the chain of one wave, which the missing workers and registers beyond 256 lengthen most: up to
-    // 4000 classes in all the packed kernel, which gives a group several waves, is the faster one at the largest sizes (K = 11,
-    // A = 2, 28 of 32 workers, ten classes, 1 / 250 / 500 groups 17.1 / 18.6 / 22.2 us and here 18.5 / 19.7 / 21.1; K = 12,
-    // A = 3, 32 of 36, 20.0 / 21.9 / 27.8 and 23.1 / 24.9 / 26.2; K = 12, A = 2, 28 of 31 the same by either).
-    if (M >= 13 && S >= (M == 15 ? 2 : 3) && C < kClsLanes && G * C <= 4000) return {0, 0};
+    // A call of few classes is the chain of one wave, which the missing workers, a column that an odd M leaves unused and
+    // registers beyond 256 lengthen most: up to 4000 classes in all the packed kernel, which gives a group several waves, is the
+    // faster one at the far sizes (K = 11, A = 2, 28 of 32 workers, ten classes, 1 / 250 / 500 groups 17.5 / 18.5 / 21.0 us and
+    // here 19.0 / 19.7 / 20.0; K = 12, A = 3, 32 of 36, 20.8 / 22.2 / 26.7 and 24.0 / 25.1 / 25.1; K = 8, A = 1, 20 of 24, 211 groups
+    // 12.6 and 13.4; K = 12, A = 2, 28 of 31, 17.1 / 18.1 / 20.5 and 16.6 / 17.6 / 17.7).
+    const int most = M == 15 ? 1 : (M >= 13 ? 2 : (M >= 9 && M % 2 == 1 ? 3 : kPairMaxMissing));
+    if (S > most && C < kClsLanes && G * C <= 4000) return {0, 0};
     if (S < 0 || S > kPairMaxMissing || M > 15 || A > kPairMaxAdversaries || C > (1 << 24)) return {0, 0};
     const int mt = std::max(4, (M + 1) & ~1), tq = std::max(mt / 2, (N - S - M + 1) / 2);
     if (tq > mt / 2 + 1 || 2 * tq - (N - S - M) > 1) return {0, 0};      // the latter: K = A = 1
@@ -1747,12 +1786,10 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
     call.votes = votes;
     call.G = G;
     call.C = C;
-    call.Cv = vec4 ? C / 4 : C;
     call.K = K;
     call.N = N;
     call.S = S;
     call.A = A;
-    call.vec4 = vec4 ? 1 : 0;
     call.sign_mode = sign_mode;
     call.lift0 = pair_lift(N, N - K - A, 0);
     call.lift1 = pair_lift(N, N - K - A, 1);
@@ -1773,15 +1810,24 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
         // 18.6 / 19.0 / 14.4; two classes, 8192 groups, 16 / 32 / 64 groups: 21 / 17.9 / 24 us.
         call.gpw = static_cast<int>(std::min<int64_t>((G + 255) / 256, kPairClasses / C));
     }
-    switch (shape.mt) {
-        case 4: return run_pairs_4(shape.tq, call, nodes, stream);
-        case 6: return run_pairs_6(shape.tq, call, nodes, stream);
-        case 8: return run_pairs_8(shape.tq, call, nodes, stream);
-        case 10: return run_pairs_10(shape.tq, call, nodes, stream);
-        case 12: return run_pairs_12(shape.tq, call, nodes, stream);
-        case 14: return run_pairs_14(shape.tq, call, nodes, stream);
-        default: return run_pairs_16(shape.tq, call, nodes, stream);
-    }
+    const auto run = [&] {
+        switch (shape.mt) {
+            case 4: return run_pairs_4(shape.tq, call, nodes, stream);
+            case 6: return run_pairs_6(shape.tq, call, nodes, stream);
+            case 8: return run_pairs_8(shape.tq, call, nodes, stream);
+            case 10: return run_pairs_10(shape.tq, call, nodes, stream);
+            case 12: return run_pairs_12(shape.tq, call, nodes, stream);
+            case 14: return run_pairs_14(shape.tq, call, nodes, stream);
+            default: return run_pairs_16(shape.tq, call, nodes, stream);
+        }
+    };
+    const int rc = run();
+    if (rc != APPROXIFER_OK || call.parts == 1) return rc;
+    const int64_t Cv = vec4 ? C / 4 : C, tiles = (Cv + kColsPerTile - 1) / kColsPerTile;
+    if (G * tiles > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    return launch_status(launch_kernel(vec4 ? decode_located_kernel<4> : decode_located_kernel<1>, dim3(static_cast<unsigned>(G * tiles)),
+                                       dim3(kPairThreads), located_lds_bytes(K, N, N - S - A), stream, d_preds, d_mask, d_out, d_adv, K,
+                                       N, S, A, C, Cv, tiles, sign_mode, nodes));
 }
 
 template <int NB, int RM, int NW, bool SHARED, bool HOMOG>

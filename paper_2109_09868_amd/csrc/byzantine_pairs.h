@@ -20,10 +20,10 @@ struct PairCall {
     const uint8_t *mask;
     float *out;
     int32_t *adv, *status, *votes;
-    int64_t G, C, Cv;
-    int K, N, S, A, vec4, sign_mode;
+    int64_t G, C;
+    int K, N, S, A, sign_mode;
     int gpw;                 // groups of a workgroup (whole groups), or
-    int parts, splits;       // parts > 1: parts of a group's classes, dealt to `splits` workgroups
+    int parts, splits;       // parts > 1: parts of a group's classes, each with a workgroup of its own (splits = parts) or one (1)
     double lift0, lift1;     // see locate_class_pair
 };
 
@@ -138,17 +138,17 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
 // part of Q are a lane's own, and a dot product over the rows is two short ones and an exchange.  The elimination is
 // modified Gram-Schmidt on [missing | columns 1 .. M-1 | column 0], as backward stable here as Householder reflections
 // with the right-hand side carried along (Bjorck 1967).  Next to the monomial basis its solutions are closer to the exact
-// ones: largest error of Q(x_i) relative to their maximum over 60 draws, K = 12, A = 2, 28 workers 2e-9 and 2e-8, K = 8, A =
+// ones: largest error of Q(x_i) relative to their maximum over 60 draws (both forms in numpy), K = 12, A = 2, 28 workers 2e-9 and 2e-8, K = 8, A =
 // 2, 20 of 24 workers 1.4e-10 and 5e-10.
 //   y, ys: the class's predictions, y[i ys] for worker i (LDS), zero where there is no answer
 //   bits: workers that answered, missing: the others;  votes: the group's counters;  live: the pair has a class
 template <int MT, int TQ, int S>
 __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsigned long long bits, unsigned long long missing,
-                                                  const double *tab, int N, int M, int A, double lift, bool live, int *votes) {
+                                                  const double *tab, int N, int M, int A, int h, double lift, bool live,
+                                                  int *votes) {
     typedef PairTile<MT, TQ, S> Tile;
     typedef double v2d __attribute__((ext_vector_type(2)));
     constexpr int TT = Tile::TT, MH = Tile::kMH, kLam = Tile::kLam, kRow = 2 * Tile::kLamPad;
-    const int h = lane_id() & 1;
     const int NH = (N + 1) / 2;
     const int R = N - M;
     const double mirror = ((N - 1 + h) & 1) ? -1.0 : 1.0;  // w_{N-1-i} T_t(beta_{N-1-i}) against node i, t of parity h
@@ -392,51 +392,50 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
     if (A > 2) vote(l2, m0);
 }
 
-// A workgroup of up to four waves takes `gpw` whole groups (C <= 128), a class to a pair of lanes, and decodes them, a row
+// A workgroup takes `gpw` whole groups (C <= 128), a class to a pair of lanes, and decodes them, a row
 // of sixteen lanes to sixteen classes of a group:
 //     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i),     T[j][i] = 1 / (alpha_j - beta_i),
 // lane j of the row holding T[j][i], which reaches the classes inside the multiply-add and sums the denominator of query j;
 // s_i is the sign of worker i, 0 if it does not count.  A query node that is a worker's node has T = 0 there and takes that
-// worker's row.  More classes: `splits` workgroups take turns at 128 of them each, the last to finish decodes the group.
-// No row of a worker that did not answer is read.
-// dynamic LDS: double tab | whole groups: T[N][16] | sgn[16][N] | beta_s[N]; parts: WdT[(N - S - A) KP] | alpha_s[K] | beta_s[N]
+// worker's row.  More classes: a workgroup to every 128 of a group's (kPart), or one that takes them all in turn (kParts: the
+// workgroups cannot meet without a workspace; the loop costs 50 registers, and with them the second wave of a SIMD); the
+// last to finish writes the located workers, and decode_located_kernel decodes.  No row of a worker that did not answer is read.
+// dynamic LDS: double tab | beta_s[N] | whole groups: T[N][16] | sgn[16][N]
 //              | float Ysh[groups][N][classes] | uint64 bits[gpw] | int votes[gpw][64] | hit[16]
-//              | parts: avail[N] | F[N] | Fpos[N] | flag
-__host__ __device__ constexpr int pair_decode_doubles(bool whole, int K, int N, int S, int A) {
-    const int d = whole ? 16 * N + kPairRows * N + N : (N - S - A) * ((K + 3) & ~3) + K + N;
+__host__ __device__ constexpr int pair_decode_doubles(bool whole, int N) {
+    const int d = whole ? 16 * N + kPairRows * N + N : N;
     return (d + 1) & ~1;
 }
 __host__ __device__ constexpr int64_t pair_tile_floats(bool whole, int gpw, int N, int64_t C) {
     return ((whole ? gpw * N * C : static_cast<int64_t>(N) * kPairClasses) + 3) & ~static_cast<int64_t>(3);
 }
 template <int MT, int TQ, int S>
-constexpr size_t pair_lds_bytes(bool whole, int gpw, int K, int N, int A, int64_t C) {
-    return sizeof(double) * (PairTile<MT, TQ, S>::kTableDoubles + pair_decode_doubles(whole, K, N, S, A)) +
-           sizeof(float) * pair_tile_floats(whole, gpw, N, C) + sizeof(uint64_t) * gpw +
-           sizeof(int) * (kWave * gpw + 16 + (whole ? 0 : 3 * N + 2));
+constexpr size_t pair_lds_bytes(bool whole, int gpw, int N, int64_t C) {
+    return sizeof(double) * (PairTile<MT, TQ, S>::kTableDoubles + pair_decode_doubles(whole, N)) +
+           sizeof(float) * pair_tile_floats(whole, gpw, N, C) + sizeof(uint64_t) * gpw + sizeof(int) * (kWave * gpw + 16);
 }
 
-template <int MT, int TQ, int S, bool WHOLE>
-constexpr int kPairWavesPerSimd = MT * TQ + S * (TQ + (S + 1) / 2) <= (WHOLE ? 100 : 60) ? 2 : 1;
+enum PairMode { kWhole, kPart, kParts };
 
-template <int MT, int TQ, int S, bool WHOLE>
-__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kPairWavesPerSimd<MT, TQ, S, WHOLE>))) void decode_byzantine_pairs_kernel(
+template <int MT, int TQ, int S, PairMode MODE>
+constexpr int kPairWavesPerSimd = MT * TQ + S * (TQ + (S + 1) / 2) <= (MODE == kParts ? 60 : 100) ? 2 : 1;
+
+template <int MT, int TQ, int S, PairMode MODE>
+__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kPairWavesPerSimd<MT, TQ, S, MODE>))) void decode_byzantine_pairs_kernel(
     const PairCall a, const Nodes nodes) {
     typedef PairTile<MT, TQ, S> Tile;
     extern __shared__ __align__(16) double lds_d[];
-    constexpr bool whole = WHOLE;
+    constexpr bool whole = MODE == kWhole;
     const int K = a.K, N = a.N, A = a.A, M = K + A;
     const int tid = threadIdx.x, wv = wave_id(), lane = lane_id(), h = lane & 1;
     double *tab = lds_d;
-    double *T = tab + Tile::kTableDoubles;
+    double *beta_s = tab + Tile::kTableDoubles;
+    double *T = beta_s + N;
     double *sgn = T + 16 * N;
-    double *WdT = T, *alpha_s = WdT + (N - S - A) * round_up4(K);
-    double *beta_s = whole ? sgn + kPairRows * N : alpha_s + K;
-    float *Ysh = reinterpret_cast<float *>(T + pair_decode_doubles(whole, K, N, S, A));
+    float *Ysh = reinterpret_cast<float *>(beta_s + pair_decode_doubles(whole, N));
     unsigned long long *bits = reinterpret_cast<unsigned long long *>(Ysh + pair_tile_floats(whole, a.gpw, N, a.C));
     int *votes = reinterpret_cast<int *>(bits + a.gpw);
     int *hit = votes + kWave * a.gpw;
-    int *avail = hit + 16, *F = avail + N, *Fpos = F + N, *flag = Fpos + N;
 
     const int64_t g0 = whole ? static_cast<int64_t>(blockIdx.x) * a.gpw : blockIdx.x / a.splits;
     const int part0 = whole ? 0 : static_cast<int>(blockIdx.x - g0 * a.splits);
@@ -463,16 +462,10 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
                 bits[q] = good ? m : 0ull;
                 if (part0 == 0 && a.status != nullptr) a.status[g0 + q] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
             }
-            if (!whole && b && good) avail[__popcll(m & ((1ull << lane) - 1ull))] = lane;
         }
     }
     const double alpha = nodes.alpha[(lane & 15) < K ? lane & 15 : 0];
-    if (whole) {
-        if (tid < N) beta_s[tid] = nodes.beta[tid];
-    } else {
-        stage_nodes(nodes, K, N, alpha_s, beta_s);
-        for (int e = tid; e < (N - S - A) * round_up4(K); e += kPairThreads) WdT[e] = 0.0;
-    }
+    if (tid < N) beta_s[tid] = nodes.beta[tid];
     for (int e = tid; e < kWave * a.gpw; e += kPairThreads) votes[e] = 0;
     if (tid < 16) hit[tid] = -1;
     __syncthreads();
@@ -486,7 +479,7 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     const int q = whole ? slot / Cs : 0;
     const int c_rel = slot - q * Cs;                      // parts: slot < 128 = Cs
     const char *src = reinterpret_cast<const char *>(a.preds + static_cast<size_t>(g0) * N * a.C);
-    for (int part = part0; part < (whole ? 1 : a.parts); part += whole ? 1 : a.splits) {
+    for (int part = part0; MODE == kParts ? part < a.parts : part == part0; ++part) {
         const int c = part * kPairClasses + c_rel;
         const bool in = q < here && c < C;
         const unsigned long long rows = in ? bits[q] : 0ull;
@@ -525,21 +518,33 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
         }
         if (part == part0) __syncthreads();
         else __builtin_amdgcn_wave_barrier();
-        int Np = N, Mp = M, Ap = A, same = 0;
+        int Np = N, Mp = M, Ap = A, hp = h;
         // parts: nothing of what follows is worth carrying from one to the next, registers being what is short
-        if (!whole) asm volatile("" : "+s"(Np), "+s"(Mp), "+s"(Ap), "+v"(same));
-        if (wv * kPairsPerWave < here * Cs)               // a wave without a class has its share in the rest
-            locate_class_pair<MT, TQ, S>(y, Cs, rows, all & ~rows, tab + same, Np, Mp, Ap, lift, live, votes + kWave * (in ? q : 0));
+        if (MODE == kParts) asm volatile("" : "+s"(Np), "+s"(Mp), "+s"(Ap), "+v"(hp));
+        if (whole ? wv * kPairsPerWave < here * Cs : part * kPairClasses + wv * kPairsPerWave < C)   // else: no class, the rest only
+            locate_class_pair<MT, TQ, S>(y, Cs, rows, all & ~rows, tab, Np, Mp, Ap, hp, lift, live, votes + kWave * (in ? q : 0));
         __builtin_amdgcn_wave_barrier();                  // the next part's rows: this pair's own places again
     }
     __syncthreads();
 
     if constexpr (!whole) {
-        float *og = a.out + static_cast<size_t>(g0) * K * a.C;
-        if (a.splits > 1 && !pool_votes_last_arrival(a.votes + g0 * (N + 1), votes, N, a.splits, flag)) return;
-        finish_group(a.preds + static_cast<size_t>(g0) * N * a.C, og, a.adv + g0 * A, avail,
-                     static_cast<int>(__popcll(bits[0])), N, A, K, round_up4(K), a.C, a.Cv, a.vec4 != 0, a.sign_mode, alpha_s,
-                     beta_s, votes, F, Fpos, WdT);
+        if (MODE == kPart && !pool_votes_last_arrival(a.votes + g0 * (N + 1), votes, N, a.splits, hit)) return;
+        if (wv != 0) return;
+        // as below, a lane to a worker
+        int key = lane < N ? (votes[lane] << 6) | (kWave - 1 - lane) : -1;
+        unsigned long long drop = 0ull;
+        for (int pick = 0; pick < A; ++pick) {
+            int m = key;
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor1, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor2, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowHalfMirror, 0xF, 0xF, true));
+            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowMirror, 0xF, 0xF, true));
+            m = max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                    max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+            drop |= 1ull << (kWave - 1 - (m & (kWave - 1)));
+            key = key == m ? -1 : key;
+        }
+        if ((drop >> lane) & 1ull) a.adv[g0 * A + __popcll(drop & ((1ull << lane) - 1ull))] = lane;
         return;
     } else {
 
@@ -670,8 +675,10 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
 template <int MT, int TQ, int S>
 int run_pairs(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     const bool whole = call.parts == 1;
-    const size_t lds = pair_lds_bytes<MT, TQ, S>(whole, call.gpw, call.K, call.N, call.A, call.C);
-    const auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TQ, S, true> : decode_byzantine_pairs_kernel<MT, TQ, S, false>;
+    const size_t lds = pair_lds_bytes<MT, TQ, S>(whole, call.gpw, call.N, call.C);
+    const auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TQ, S, kWhole>
+                              : (call.splits > 1 ? decode_byzantine_pairs_kernel<MT, TQ, S, kPart>
+                                                 : decode_byzantine_pairs_kernel<MT, TQ, S, kParts>);
     if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                static_cast<int>(lds)) != hipSuccess)
         return APPROXIFER_ERR_LAUNCH;
