@@ -232,10 +232,10 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const int r = R - 1 - s;
-        double sig = 0.0, at = 0.0;                       // over the rows up to r; row r itself.  R > 2 TT - 3
+        double sig = 0.0, at = 0.0;                       // over the rows up to r; row r itself.  R >= 2 TT - 2
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
-            if (2 * t + 1 > 2 * TT - 3 - s) {
+            if (2 * t + 1 >= 2 * TT - 3 - s) {
                 x[s][t] = 2 * t + h <= r ? x[s][t] : 0.0;
                 at = 2 * t + h == r ? x[s][t] : at;
             }
@@ -247,7 +247,7 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
         scale[s] = -rcp_normal(fma(-to, at, sig));
 #pragma unroll
         for (int t = 0; t < TT; ++t)
-            if (2 * t + 1 > 2 * TT - 3 - s) x[s][t] = 2 * t + h == r ? x[s][t] - to : x[s][t];
+            if (2 * t + 1 >= 2 * TT - 3 - s) x[s][t] = 2 * t + h == r ? x[s][t] - to : x[s][t];
 #pragma unroll
         for (int b = s + 1; b < S; ++b) reflect(x[b], s);
     }

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import approxifer_oracle as orc
-from parity_cases import TOL, group_err
+from parity_cases import TOL, assert_rounding_ties, group_err
 
 pytestmark = pytest.mark.gpu
 
@@ -71,6 +71,27 @@ def test_located_and_decoded_as_by_the_oracle(gpu, K, A, S, ex):
     ref, _ = orc.decode(np.where(left[:, :, None] != 0, Y[good], 0.0).astype(np.float32), left, alpha, beta, S + A, mode)
     ok = np.abs(ref).max(axis=(1, 2)) < 1e6                    # printed signs can meet a pole
     assert group_err(out[good][ok], ref[ok]).max() <= TOL
+
+
+@pytest.mark.parametrize("K,A,S,ex", SHAPES)
+def test_fits_of_predictions_that_are_not_rational(gpu, K, A, S, ex):
+    # Noise, one class to a group: every equation of the fits counts, where rational predictions satisfy them all.  The located
+    # workers are the oracle's but where its two closest candidates agree to rounding.
+    torch, binding, dev = gpu
+    N, G = 2 * (K + A) + S + ex, 40
+    rng = np.random.default_rng(10 * N + K)
+    alpha, beta = orc.chebyshev_nodes(K, N)
+    Y = rng.standard_normal((G, N, 1)).astype(np.float32)
+    mask = np.zeros((G, N), np.uint8)
+    for g in range(G):
+        mask[g, rng.permutation(N)[S:]] = 1
+    Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
+    for locator, entry in ((orc.LOCATOR_ALGORITHM_2, binding.approxifer_decode_byzantine),
+                           (orc.LOCATOR_ALGORITHM_1, binding.approxifer_decode_byzantine_homogeneous)):
+        adv = entry(Yd, md, alpha, beta, S, A, 1)[1].cpu().numpy()
+        _, adv_ref, _ = orc.decode_byzantine(Y, mask, alpha, beta, S, A, 1, locator)
+        assert np.all(adv == adv_ref, axis=1).sum() >= (0.95 if K + A <= 12 else 0.8) * G
+        assert_rounding_ties(Y, mask, beta, K, A, adv, adv_ref, locator)
 
 
 @pytest.mark.parametrize("K,A,S,N,C", [(8, 2, 4, 24, 10), (4, 1, 1, 12, 2), (2, 1, 0, 7, 1), (6, 2, 0, 16, 40), (8, 2, 2, 22, 128),
