@@ -9,8 +9,9 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libapproxifer.so")
-SOURCES = ["api.hip", "encode.hip", "decode.hip", "byzantine.hip", "byzantine_pairs_small.hip",
-           "byzantine_pairs_medium.hip", "byzantine_pairs_large.hip"]
+SOURCES = ["api.hip", "encode.hip", "decode.hip", "byzantine.hip", "byzantine_pairs_large.hip",
+           "byzantine_null_pairs_large.hip", "byzantine_pairs_medium.hip", "byzantine_null_pairs_medium.hip",
+           "byzantine_pairs_small.hip", "byzantine_null_pairs_small.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -62,7 +63,7 @@ def build_marshal(verbose: bool = False, out: str = os.path.join(PKG_DIR, "_mars
     return out
 
 
-def build_library(verbose: bool = False, jobs: int = 7) -> str:
+def build_library(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every source (in parallel, one hipcc per file) and link the shared library."""
     from concurrent.futures import ThreadPoolExecutor
 

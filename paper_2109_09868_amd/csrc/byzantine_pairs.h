@@ -1,8 +1,8 @@
-// Algorithm 2 on the library's own worker nodes, beta_i = cos(i pi / (N - 1)), with at most four workers missing: two
+// Algorithms 2 and 1 on the library's own worker nodes, beta_i = cos(i pi / (N - 1)), with at most four workers missing: two
 // lanes to a class.
 #pragma once
 
-#include "byzantine_common.h"
+#include "byzantine_general.h"
 #include "rows.h"
 
 namespace approxifer {
@@ -122,7 +122,328 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
     }
 }
 
-// Algorithm 2, steps 1-5, for the class of this pair of lanes; h = lane % 2.
+// Algorithm 1 (HOMOG below): the unit vector (P, Q) of monomial coefficients that minimises sum_i (P(x_i) + y_i Q(x_i))^2 (the
+// sign of y only flips that of Q), for the class of this pair of lanes.  With p, q the coefficients in the Chebyshev basis, D
+// the matrix that takes them to monomials (T_e has terms of e's parity only, so it is a lane's own business), T the basis at
+// the nodes that answered, G = T^T T and K = T^T diag(y) T, a round of the inverse iteration
+//     [ G  K              ] [p']   [D^T D p]
+//     [ K  T^T diag(y)^2 T ] [q'] = [D^T D q]
+// is solved by eliminating p', which leaves B^T B for q', B the projected system of Algorithm 2 with all M columns, through its
+// triangular factor (B is never squared):
+//     u = G^-1 D^T D p,   B^T B q' = D^T D q - K u,   p' = u - G^-1 K q'.
+// G^-1 is in closed form (diagonal and a rank-one term per parity, less the missing workers' rows), K's entries are sums of two
+// moments as the system's are.  Start vector, settling rule, extrapolation of a slowly decaying mode and the floor under
+// vanishing pivots are those of homogeneous_q, which is the fallback for a class that has not settled after kPairRounds.
+// Against the monomial QR (numpy, both): largest error of Q(x_i) relative to their maximum 1.6e-10 and 3e-8 at K = 12, A = 2,
+// 28 workers, 3e-12 and 2e-11 at K = 8, A = 2, 20 of 24; the same number of rounds, two to four on rational data.
+//   a: the system's columns (destroyed), k[s]: half the moment sum_i y_i T_{2s+h}(beta_i), square: sum_i y_i^2
+//   c: coefficients of T_{2s+h} in Q.  Returns whether the class settled: the same in both lanes
+constexpr int kPairRounds = 64;
+
+// T_{2s+h} = sum_k c[h][k][s] x^{2k+h}
+struct ChebyshevToMonomial {
+    double c[2][8][8];
+    constexpr ChebyshevToMonomial() : c() {
+        double t[16][16] = {};
+        t[0][0] = 1.0;
+        t[1][1] = 1.0;
+        for (int e = 2; e < 16; ++e)
+            for (int d = 0; d <= e; ++d) t[e][d] = (d > 0 ? 2.0 * t[e - 1][d - 1] : 0.0) - t[e - 2][d];
+        for (int h = 0; h < 2; ++h)
+            for (int k = 0; k < 8; ++k)
+                for (int s = 0; s < 8; ++s) c[h][k][s] = t[2 * s + h][2 * k + h];
+    }
+};
+static __constant__ constexpr ChebyshevToMonomial kChebyshev;
+
+template <int LANE>
+__device__ __forceinline__ double pair_bcast(double v) {   // lane LANE of the pair's, to both
+    return dpp_exchange<LANE == 0 ? 0xA0 : 0xF5>(v);      // quad_perm:[0,0,2,2], [1,1,3,3]
+}
+
+template <int MT, int TQ, int S>
+__device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const double (&k)[MT], double square, const double *own,
+                                                 const double *basis, unsigned long long absent, int N, int M, int h, bool live,
+                                                 double (&c)[MT / 2]) {
+    constexpr int MH = MT / 2, kRow = 2 * PairTile<MT, TQ, S>::kLamPad;
+    // ---- elimination, all columns in their order: nf as for Algorithm 2, rs[s] = 1 / pivot^2 of column 2s + h ---------------
+    const double floor = 1e-48 * square;
+    double nf[MT][MH], rs[MH], even = 0.0;
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+        double r = 0.0;
+        if (j < M) {
+            double sig = a[j][0] * a[j][0];
+#pragma unroll
+            for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
+            sig = pair_sum(sig);
+            r = rcp_normal(sig > floor ? sig : floor);
+            const auto take_out = [&](double (&to)[TQ]) {
+                double d = a[j][0] * to[0];
+#pragma unroll
+                for (int t = 1; t < TQ; ++t) d = fma(a[j][t], to[t], d);
+                const double f = -pair_sum(d) * r;
+#pragma unroll
+                for (int t = 0; t < TQ; ++t) to[t] = fma(f, a[j][t], to[t]);
+                return f;
+            };
+#pragma unroll
+            for (int s = (j + 1) / 2; s < MH; ++s) {
+                double fe = 0.0;
+                if (2 * s > j) fe = take_out(a[2 * s]);
+                nf[j][s] = choose(h, take_out(a[2 * s + 1]), fe);
+            }
+        } else {
+#pragma unroll
+            for (int s = (j + 1) / 2; s < MH; ++s) nf[j][s] = 0.0;
+        }
+        r *= 2 * (N - 1);                                 // the rows of a[] are 2 ((N - 1) / 2)^1/2 times orthonormal ones'
+        if (j % 2 == 0) even = r;
+        else rs[j / 2] = choose(h, r, even);
+    }
+    const bool last = 2 * (MH - 1) + h < M;               // an odd M: lane 1 has no last entry
+
+    // ---- G^-1 v = v / d - scale (sum v / d) / d + W W^T v -----------------------------------------------------------------
+    const double over = 2.0 / (N - 1), over0 = h ? over : 0.5 * over;    // 1 / d_0, the others; d = 0 of no entry: none
+    double inv[MH], sum_inv = 0.0;
+#pragma unroll
+    for (int s = 0; s < MH; ++s) {
+        inv[s] = s == 0 ? over0 : (s < MH - 1 || last ? over : 0.0);
+        sum_inv += inv[s];
+    }
+    const double scale = rcp_normal(1.0 + sum_inv);
+    double w[S > 0 ? S : 1][MH];
+    const auto full_inverse = [&](const double (&v)[MH], double (&to)[MH]) {
+        double sum = 0.0;
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            to[s] = v[s] * inv[s];
+            sum += to[s];
+        }
+        sum *= -scale;
+#pragma unroll
+        for (int s = 0; s < MH; ++s) to[s] = fma(sum, inv[s], to[s]);
+    };
+    const auto dot = [](const double (&v)[MH], const double (&z)[MH]) {
+        double d = v[0] * z[0];
+#pragma unroll
+        for (int s = 1; s < MH; ++s) d = fma(v[s], z[s], d);
+        return pair_sum(d);
+    };
+    const auto inverse = [&](const double (&v)[MH], double (&to)[MH]) {
+        full_inverse(v, to);
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            const double d = dot(w[b], v);
+#pragma unroll
+            for (int s = 0; s < MH; ++s) to[s] = fma(d, w[b][s], to[s]);
+        }
+    };
+    if constexpr (S > 0) {                                // (G - X X^T)^-1 = G^-1 + W W^T, W = G^-1 X L^-T, L L^T = 1 - X^T G^-1 X
+        double x[S][MH], l[S][S], rd[S];
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            const int i0 = __builtin_ctzll(absent), i = 2 * i0 >= N ? N - 1 - i0 : i0;
+            absent &= absent - 1ull;
+            const double back = (i & 1 ? -1.0 : 1.0) * (i == 0 || 2 * i == N - 1 ? 2.0 : 1.0) * (2 * i0 >= N && h ? -1.0 : 1.0);
+#pragma unroll
+            for (int s = 0; s < MH; ++s) x[b][s] = s < MH - 1 || last ? back * own[i * kRow + s] : 0.0;
+        }
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            full_inverse(x[b], w[b]);
+#pragma unroll
+            for (int r = 0; r <= b; ++r) {
+                l[b][r] = r < b ? 0.0 : 1.0;
+                l[b][r] -= r < b ? dot(x[r], w[b]) : dot(x[b], w[b]);
+            }
+        }
+        // rows of L in turn; w[b] becomes column b of W
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+#pragma unroll
+            for (int r = 0; r <= b; ++r) {
+#pragma unroll
+                for (int m = 0; m < r; ++m) l[b][r] = fma(-l[b][m], l[r][m], l[b][r]);
+                if (r < b) l[b][r] *= rd[r];
+            }
+            rd[b] = rsqrt_normal(l[b][b]);
+#pragma unroll
+            for (int s = 0; s < MH; ++s) {
+#pragma unroll
+                for (int r = 0; r < b; ++r) w[b][s] = fma(-l[b][r], w[r][s], w[b][s]);
+                w[b][s] *= rd[b];
+            }
+        }
+    }
+
+    // ---- K v: row 2t + h from own and the other lane's half moments, as the system's columns are formed ---------------------
+    double ko[MT], below[MH], ahead[MT - 1];
+#pragma unroll
+    for (int s = 0; s < MT; ++s) ko[s] = pair_other(k[s]);
+#pragma unroll
+    for (int d = 1; d < MH; ++d) below[d] = choose(h, k[d - 1], k[d]);
+#pragma unroll
+    for (int s = 0; s < MT - 1; ++s) ahead[s] = choose(h, ko[s + 1], ko[s]);
+    const auto multiply = [&](const double (&v)[MH], double (&to)[MH]) { // to -= K v
+        double ve[MH], vo[MH];
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            ve[s] = -pair_bcast<0>(v[s]);
+            vo[s] = -pair_bcast<1>(v[s]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < MH; ++t) {
+            double sum = to[t];
+#pragma unroll
+            for (int u = 0; u < MH; ++u) {
+                sum = fma(k[t + u], ve[u], sum);
+                sum = fma(t >= u ? k[t >= u ? t - u : 0] : below[t >= u ? 1 : u - t], ve[u], sum);
+                sum = fma(ahead[t + u], vo[u], sum);
+                sum = fma(t > u ? ahead[t > u ? t - u - 1 : 0] : ko[t > u ? 0 : u - t], vo[u], sum);
+            }
+            to[t] = t < MH - 1 || last ? sum : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    const double *mono = basis;
+    // ---- inverse iteration; mp, mq: the monomial coefficients of the unit vector ----------------------------------------------
+    const auto to_monomials = [&](const double (&v)[MH], double (&m)[MH]) {
+#pragma unroll
+        for (int d = 0; d < MH; ++d) {
+            m[d] = 0.0;
+#pragma unroll
+            for (int s = d; s < MH; ++s) m[d] = fma(mono[d * MH + s], v[s], m[d]);
+        }
+    };
+    const auto transposed = [&](const double (&m)[MH], double (&v)[MH]) {
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            v[s] = 0.0;
+#pragma unroll
+            for (int d = 0; d <= s; ++d) v[s] = fma(mono[d * MH + s], m[d], v[s]);
+            if (s == MH - 1 && !last) v[s] = 0.0;
+        }
+    };
+    double mp[MH], mq[MH];
+#pragma unroll
+    for (int s = 0; s < MH; ++s) {
+        const bool in = s < MH - 1 || last;
+        mp[s] = in ? 1.0 + 0.25 * ((2 * s + h) % 3) : 0.0;
+        mq[s] = in ? 1.0 + 0.25 * ((M + 2 * s + h) % 3) : 0.0;
+    }
+    {
+        double nn = 0.0;
+#pragma unroll
+        for (int s = 0; s < MH; ++s) nn = fma(mp[s], mp[s], fma(mq[s], mq[s], nn));
+        const double unit = rsqrt_normal(pair_sum(nn));
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            mp[s] *= unit;
+            mq[s] *= unit;
+        }
+    }
+    double dd_prev = __builtin_inf(), quotient = 0.0;
+    int since_jump = 0;
+    bool settled = false;
+    for (int round = 0; round < kPairRounds; ++round) {
+        // read again in every round: carried along it would take the registers that the rest of the round needs
+        int offset = 0;
+        asm volatile("" : "+v"(offset));
+        mono = basis + offset;
+        double f[MH], u[MH], t[MH];
+        transposed(mp, f);
+        __builtin_amdgcn_sched_barrier(0);
+        inverse(f, u);
+        __builtin_amdgcn_sched_barrier(0);
+        transposed(mq, t);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(u, t);
+        // (1 + N)^T, the pivots, (1 + N), N = -nf above the diagonal
+#pragma unroll
+        for (int j = 0; j < MT - 1; ++j) {
+            const double tj = j % 2 == 0 ? pair_bcast<0>(t[j / 2]) : pair_bcast<1>(t[j / 2]);
+#pragma unroll
+            for (int s = (j + 1) / 2; s < MH; ++s) t[s] = fma(nf[j][s], tj, t[s]);
+        }
+        double part[MT];
+#pragma unroll
+        for (int j = 0; j < MT; ++j) part[j] = 0.0;
+#pragma unroll
+        for (int s = MH - 1; s >= 0; --s) {
+            t[s] *= rs[s];
+            const double odd = pair_sum(part[2 * s + 1]);
+            part[2 * s] = fma(nf[2 * s][s], t[s] + odd, part[2 * s]);    // lane 1's; zero in lane 0
+            c[s] = t[s] + choose(h, odd, pair_sum(part[2 * s]));
+#pragma unroll
+            for (int j = 0; j < 2 * s; ++j) part[j] = fma(nf[j][s], c[s], part[j]);
+        }
+#pragma unroll
+        for (int s = 0; s < MH; ++s) f[s] = 0.0;
+        multiply(c, f);
+        inverse(f, t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < MH; ++s) u[s] += t[s];
+        double np[MH], nq[MH];
+        to_monomials(u, np);
+        __builtin_amdgcn_sched_barrier(0);
+        to_monomials(c, nq);
+        __builtin_amdgcn_sched_barrier(0);
+        double nn = 0.0;
+#pragma unroll
+        for (int s = 0; s < MH; ++s) nn = fma(np[s], np[s], fma(nq[s], nq[s], nn));
+        const double unit = rsqrt_normal(pair_sum(nn));   // zero, inf or NaN: NaN, the class does not settle
+        double dd = 0.0;
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            const double ep = fma(np[s], unit, -mp[s]), eq = fma(nq[s], unit, -mq[s]);   // z' . z > 0 always: no sign to align
+            dd = fma(ep, ep, fma(eq, eq, dd));
+        }
+        dd = pair_sum(dd);
+        const double dd_before = dd_prev;
+        settled = settled || dd <= 1e-22 || (dd_prev <= 1e-16 && dd >= 0.25 * dd_prev);
+        dd_prev = dd;
+        ++since_jump;
+        double old = 0.0, next = 1.0;                     // what of z and z' the next round starts from
+        if (round == 0) {
+            quotient = unit * fma(-0.5, dd, 1.0);         // z'^T A z', A z' = unit z
+        } else if (round == 1 && !settled && dd > 1e-18 && dd < 1.0) {
+            // The best vector of span(z, z') once: by now two modes are left, and the slow one is gone with it.  20480
+            // rational classes at K = 8, A = 2, 20 of 24 workers take up to ten rounds without this and five with it; K = 12, A = 2, 28
+            // workers, seven and four.
+            const double g = fma(-0.5, dd, 1.0), across2 = dd * fma(-0.25, dd, 1.0), across = sqrt_normal(across2);
+            const double r = rcp_normal(across), mixed = fma(-g, quotient, unit) * r, other = g * fma(g, quotient, -unit) * r * r;
+            const double half = 0.5 * (other - quotient);
+            const double tangent = -mixed * rcp_normal(half + sqrt_normal(fma(half, half, mixed * mixed))), tau = tangent * r;
+            if (half > 0.0 && tau > 0.0) {
+                const double norm = rsqrt_normal(fma(tangent, tangent, 1.0));
+                old = fma(-tau, g, 1.0) * norm;
+                next = tau * norm;
+                if (!(next > 0.95 && next < 1.05)) dd_prev = __builtin_inf();
+            }
+        } else if (!settled && since_jump >= 3 && dd < 1e-4 && dd_before < __builtin_inf()) {
+            const double r = sqrt(dd / dd_before);
+            if (r > 0.05 && r < 0.97) {
+                old = -r / (1.0 - r);
+                next = 1.0 - old;
+                since_jump = 0;
+                dd_prev = __builtin_inf();
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < MH; ++s) {
+            mp[s] = fma(old, mp[s], next * unit * np[s]);
+            mq[s] = fma(old, mq[s], next * unit * nq[s]);
+        }
+        if (__all((settled || !live) ? 1 : 0)) break;
+    }
+    return settled;
+}
+
+// Algorithm 2 (HOMOG: Algorithm 1), steps 1-5, for the class of this pair of lanes; h = lane % 2.
 //
 // The polynomial P is eliminated in closed form.  With omega = (1/2, 1, .., 1, 1/2) the Chebyshev polynomials are orthogonal
 // on the nodes, so the rows u_r = omega T_{N-1-r} = w T_r, r < R = N - M, are orthogonal to every polynomial of degree
@@ -132,20 +453,21 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
 //     u_r diag(y) T_e = (lambda_{r+e} + lambda_|r-e|) / 2,     lambda_t = sum_i w_i y_i T_t(beta_i),
 // and the mirror images beta_{N-1-i} = -beta_i halve the work for the moments: no factorisation of the nodes, and a sixth
 // of the multiply-adds of forming U diag(y) V entry by entry.  A missing worker's prediction counts as a free unknown (its
-// column u_r e_i is eliminated ahead of the class's own, y_i = 0).  Q_0 = 1 is sum_e q_e T_e(0) = 1, which takes the even
+// column u_r e_i is reflected out ahead, y_i = 0).  Q_0 = 1 is sum_e q_e T_e(0) = 1, which takes the even
 // columns to T_e - T_e(0).
 // Rows of parity h live in lane h (row 2t + h in slot t): the moments of a parity, the rank-one term and the even and odd
 // part of Q are a lane's own, and a dot product over the rows is two short ones and an exchange.  The elimination is
-// modified Gram-Schmidt on [missing | columns 1 .. M-1 | column 0], as backward stable here as Householder reflections
-// with the right-hand side carried along (Bjorck 1967).  Next to the monomial basis its solutions are closer to the exact
+// modified Gram-Schmidt on [columns 1 .. M-1 | column 0], with the right-hand side carried along as backward stable as
+// reflections (Bjorck 1967).  Next to the monomial basis its solutions are closer to the exact
 // ones: largest error of Q(x_i) relative to their maximum over 60 draws (both forms in numpy), K = 12, A = 2, 28 workers 2e-9 and 2e-8, K = 8, A =
 // 2, 20 of 24 workers 1.4e-10 and 5e-10.
 //   y, ys: the class's predictions, y[i ys] for worker i (LDS), zero where there is no answer
 //   bits: workers that answered, missing: the others;  votes: the group's counters;  live: the pair has a class
-template <int MT, int TQ, int S>
-__device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsigned long long bits, unsigned long long missing,
-                                                  const double *tab, int N, int M, int A, int h, double lift, bool live,
-                                                  int *votes) {
+// Returns whether the class has voted (Algorithm 1 may not have settled).
+template <int MT, int TQ, int S, bool HOMOG>
+__device__ __forceinline__ bool locate_class_pair(const float *y, int ys, unsigned long long bits, unsigned long long missing,
+                                                  const double *tab, const double *mono, int N, int M, int A, int h, double lift,
+                                                  bool live, int *votes) {
     typedef PairTile<MT, TQ, S> Tile;
     typedef double v2d __attribute__((ext_vector_type(2)));
     constexpr int TT = Tile::TT, MH = Tile::kMH, kLam = Tile::kLam, kRow = 2 * Tile::kLamPad;
@@ -154,10 +476,15 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
     const double mirror = ((N - 1 + h) & 1) ? -1.0 : 1.0;  // w_{N-1-i} T_t(beta_{N-1-i}) against node i, t of parity h
     const double *own = tab + h * Tile::kLamPad;
 
+    const unsigned long long absent = missing;
+
     // ---- moments: p[s] = lambda_{2s+h}, o[s] = lambda_{2s+1-h} -----------------------------------------------------------
     double p[Tile::kLamPad];
 #pragma unroll
     for (int s = 0; s < Tile::kLamPad; ++s) p[s] = 0.0;
+    double k[HOMOG ? MT : 1], square = 0.0;               // HOMOG: k[s] = sum_i y_i T_{2s+h}(beta_i) / 2; sum y^2
+#pragma unroll
+    for (int s = 0; s < (HOMOG ? MT : 1); ++s) k[s] = 0.0;
     {
         // a node's row is read while the one before it is multiplied: left to itself the compiler waits for every two reads
         constexpr int kReads = Tile::kLamPad / 2;
@@ -174,14 +501,26 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
         for (int i = 0; i < Tile::kNodes; ++i) {          // N >= kNodes; rows past NH of the table are zero
             if (i + 1 < Tile::kNodes) read(i + 1);
             __builtin_amdgcn_sched_barrier(0);
-            const double z = fma(mirror, static_cast<double>(hi[i & 1]), static_cast<double>(lo[i & 1]));
+            const double near = lo[i & 1], far = hi[i & 1];
+            const double z = fma(mirror, far, near);
 #pragma unroll
             for (int s = 0; s < kReads; ++s) {
                 p[2 * s] = fma(row[i & 1][s][0], z, p[2 * s]);
                 p[2 * s + 1] = fma(row[i & 1][s][1], z, p[2 * s + 1]);
             }
+            if constexpr (HOMOG) {
+                const double v = (i & 1 ? -0.5 : 0.5) * (i == 0 ? 2.0 : 1.0) * fma(h ? -1.0 : 1.0, far, near);
+#pragma unroll
+                for (int s = 0; s < MT; ++s) k[s] = fma(row[i & 1][s / 2][s % 2], v, k[s]);
+                square = fma(near, near, fma(far, far, square));
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    if constexpr (HOMOG) {                                // here and not where they are used, with the table's rows kept until then
+#pragma unroll
+        for (int s = 0; s < MT; ++s) asm volatile("" : "+v"(k[s]));
+        asm volatile("" : "+v"(square));
     }
     double o[kLam], below[MH], ahead[kLam - 1];
 #pragma unroll
@@ -281,7 +620,7 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 #pragma unroll
         for (int t = 0; t < TT; ++t) c[t] = p[t + u] + (t >= u ? p[t >= u ? t - u : 0] : below[t >= u ? 1 : u - t]);
         column(c, a[2 * u]);
-        if (u > 0) {
+        if (!HOMOG && u > 0) {
 #pragma unroll
             for (int t = 0; t < TQ; ++t) a[2 * u][t] += u % 2 ? a[0][t] : -a[0][t];      // T_{2u}(0) = (-1)^u
         }
@@ -295,56 +634,62 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
             for (int t = 0; t < TQ; ++t) a[2 * u + 1][t] = parked(away[u][t]);
     }
 
-    // ---- elimination: nf[j][e / 2] = minus the share of column j in column e, lane e % 2 keeping it ------------------------
-    double nf[MT][MH];
-#pragma unroll
-    for (int j = 1; j < MT; ++j) {
-        if (j < M) {
-            double sig = a[j][0] * a[j][0];
-#pragma unroll
-            for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
-            const double rs = rcp_normal(pair_sum(sig));
-            const auto take_out = [&](double (&c)[TQ]) {
-                double d = a[j][0] * c[0];
-#pragma unroll
-                for (int t = 1; t < TQ; ++t) d = fma(a[j][t], c[t], d);
-                const double f = -pair_sum(d) * rs;
-                if (j + 1 < MT) {                         // the right-hand side's remainder is not needed at the end
-#pragma unroll
-                    for (int t = 0; t < TQ; ++t) c[t] = fma(f, a[j][t], c[t]);
+    double c[MH];                                         // c[s]: coefficient of T_{2s+h} in Q
+    bool settled = true;
+    if constexpr (HOMOG) {
+        settled = null_vector_pair<MT, TQ, S>(a, k, square, own, mono, absent, N, M, h, live, c);
+    } else {
+        // ---- elimination: nf[j][e / 2] = minus the share of column j in column e, lane e % 2 keeping it ------------------------
+        double nf[MT][MH];
+    #pragma unroll
+        for (int j = 1; j < MT; ++j) {
+            if (j < M) {
+                double sig = a[j][0] * a[j][0];
+    #pragma unroll
+                for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
+                const double rs = rcp_normal(pair_sum(sig));
+                const auto take_out = [&](double (&c)[TQ]) {
+                    double d = a[j][0] * c[0];
+    #pragma unroll
+                    for (int t = 1; t < TQ; ++t) d = fma(a[j][t], c[t], d);
+                    const double f = -pair_sum(d) * rs;
+                    if (j + 1 < MT) {                         // the right-hand side's remainder is not needed at the end
+    #pragma unroll
+                        for (int t = 0; t < TQ; ++t) c[t] = fma(f, a[j][t], c[t]);
+                    }
+                    return f;
+                };
+                nf[j][0] = choose(h, 0.0, take_out(a[0]));
+    #pragma unroll
+                for (int s = (j + 1) / 2; s < MH; ++s) {      // columns 2s (if behind j) and 2s + 1
+                    double fe = 0.0;
+                    if (2 * s > j) fe = take_out(a[2 * s]);
+                    nf[j][s] = choose(h, take_out(a[2 * s + 1]), fe);
                 }
-                return f;
-            };
-            nf[j][0] = choose(h, 0.0, take_out(a[0]));
-#pragma unroll
-            for (int s = (j + 1) / 2; s < MH; ++s) {      // columns 2s (if behind j) and 2s + 1
-                double fe = 0.0;
-                if (2 * s > j) fe = take_out(a[2 * s]);
-                nf[j][s] = choose(h, take_out(a[2 * s + 1]), fe);
+            } else {
+    #pragma unroll
+                for (int s = 0; s < MH; ++s) nf[j][s] = 0.0;
             }
-        } else {
-#pragma unroll
-            for (int s = 0; s < MH; ++s) nf[j][s] = 0.0;
         }
-    }
 
-    // ---- back substitution: c[s] = coefficient of T_{2s+h} in Q ---------------------------------------------------------------
-    double c[MH], part[MT];
-#pragma unroll
-    for (int j = 1; j < MT; ++j) part[j] = nf[j][0];
-    double q0 = 1.0;
-#pragma unroll
-    for (int s = MH - 1; s >= 0; --s) {
-        const double qo = 2 * s + 1 < M ? pair_sum(part[2 * s + 1]) : 0.0;
-        double qe = 0.0;
-        if (s > 0) {
-            part[2 * s] = fma(nf[2 * s][s], qo, part[2 * s]);            // lane 1's; zero in lane 0
-            qe = 2 * s < M ? pair_sum(part[2 * s]) : 0.0;
-            q0 += s % 2 ? qe : -qe;                       // Q_0 = 1: minus T_{2s}(0) of every even column
+        // ---- back substitution: c[s] = coefficient of T_{2s+h} in Q ---------------------------------------------------------------
+        double part[MT];
+    #pragma unroll
+        for (int j = 1; j < MT; ++j) part[j] = nf[j][0];
+        double q0 = 1.0;
+    #pragma unroll
+        for (int s = MH - 1; s >= 0; --s) {
+            const double qo = 2 * s + 1 < M ? pair_sum(part[2 * s + 1]) : 0.0;
+            double qe = 0.0;
+            if (s > 0) {
+                part[2 * s] = fma(nf[2 * s][s], qo, part[2 * s]);            // lane 1's; zero in lane 0
+                qe = 2 * s < M ? pair_sum(part[2 * s]) : 0.0;
+                q0 += s % 2 ? qe : -qe;                       // Q_0 = 1: minus T_{2s}(0) of every even column
+            }
+            c[s] = h ? qo : (s > 0 ? qe : q0);
+    #pragma unroll
+            for (int j = 1; j < 2 * s; ++j) part[j] = fma(nf[j][s], c[s], part[j]);
         }
-        c[s] = h ? qo : (s > 0 ? qe : q0);
-#pragma unroll
-        for (int j = 1; j < 2 * s; ++j) part[j] = fma(nf[j][s], c[s], part[j]);
     }
 
     // ---- a_i = Q(beta_i), up to sign: lane 0 node i, lane 1 its mirror image; the A smallest vote --------------------------
@@ -385,11 +730,12 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
     // of two ascending lists of A, the A smallest are those where own k-th < the other's (A - 1 - k)-th, from either side
     const double m0 = pair_other(l0), m1 = pair_other(l1), m2 = pair_other(l2);
     const auto vote = [&](double k, double against) {
-        if (live && k < against) atomicAdd(&votes[__double2loint(k) & 63], 1);
+        if (live && settled && k < against) atomicAdd(&votes[__double2loint(k) & 63], 1);
     };
     vote(l0, A == 1 ? m0 : (A == 2 ? m1 : m2));
     if (A > 1) vote(l1, A == 2 ? m0 : m1);
     if (A > 2) vote(l2, m0);
+    return settled;
 }
 
 // A workgroup takes `gpw` whole groups (C <= 128), a class to a pair of lanes, and decodes them, a row
@@ -402,6 +748,7 @@ __device__ __forceinline__ void locate_class_pair(const float *y, int ys, unsign
 // last to finish writes the located workers, and decode_located_kernel decodes.  No row of a worker that did not answer is read.
 // dynamic LDS: double tab | beta_s[N] | whole groups: T[N][16] | sgn[16][N]
 //              | float Ysh[groups][N][classes] | uint64 bits[gpw] | int votes[gpw][64] | hit[16]
+//              | HOMOG: double mono[2][MT / 2][MT / 2] | scratch[4][pair_scratch_doubles]
 __host__ __device__ constexpr int pair_decode_doubles(bool whole, int N) {
     const int d = whole ? 16 * N + kPairRows * N + N : N;
     return (d + 1) & ~1;
@@ -409,19 +756,23 @@ __host__ __device__ constexpr int pair_decode_doubles(bool whole, int N) {
 __host__ __device__ constexpr int64_t pair_tile_floats(bool whole, int gpw, int N, int64_t C) {
     return ((whole ? gpw * N * C : static_cast<int64_t>(N) * kPairClasses) + 3) & ~static_cast<int64_t>(3);
 }
+__host__ __device__ constexpr int pair_scratch_doubles(int N, int n, int M) {     // of a wave (HOMOG): xs, see locate_classes_wave, avail
+    return N + n * (2 * M + 1) + M + n + (N + 1) / 2;
+}
 template <int MT, int TQ, int S>
-constexpr size_t pair_lds_bytes(bool whole, int gpw, int N, int64_t C) {
+constexpr size_t pair_lds_bytes(bool whole, int gpw, int N, int M, int64_t C, bool homogeneous) {
     return sizeof(double) * (PairTile<MT, TQ, S>::kTableDoubles + pair_decode_doubles(whole, N)) +
-           sizeof(float) * pair_tile_floats(whole, gpw, N, C) + sizeof(uint64_t) * gpw + sizeof(int) * (kWave * gpw + 16);
+           sizeof(float) * pair_tile_floats(whole, gpw, N, C) + sizeof(uint64_t) * gpw + sizeof(int) * (kWave * gpw + 16) +
+           (homogeneous ? sizeof(double) * (MT * MT / 2 + kPairWaves * pair_scratch_doubles(N, N - S, M)) : 0);
 }
 
 enum PairMode { kWhole, kPart, kParts };
 
-template <int MT, int TQ, int S, PairMode MODE>
-constexpr int kPairWavesPerSimd = MT * TQ + S * (TQ + (S + 1) / 2) <= (MODE == kParts ? 60 : 100) ? 2 : 1;
+template <int MT, int TQ, int S, PairMode MODE, bool HOMOG>
+constexpr int kPairWavesPerSimd = MT * TQ + S * (TQ + (S + 1) / 2) + (HOMOG ? 2 * MT : 0) <= (MODE == kParts ? 60 : 100) ? 2 : 1;
 
-template <int MT, int TQ, int S, PairMode MODE>
-__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kPairWavesPerSimd<MT, TQ, S, MODE>))) void decode_byzantine_pairs_kernel(
+template <int MT, int TQ, int S, PairMode MODE, bool HOMOG>
+__global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kPairWavesPerSimd<MT, TQ, S, MODE, HOMOG>))) void decode_byzantine_pairs_kernel(
     const PairCall a, const Nodes nodes) {
     typedef PairTile<MT, TQ, S> Tile;
     extern __shared__ __align__(16) double lds_d[];
@@ -436,6 +787,9 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     unsigned long long *bits = reinterpret_cast<unsigned long long *>(Ysh + pair_tile_floats(whole, a.gpw, N, a.C));
     int *votes = reinterpret_cast<int *>(bits + a.gpw);
     int *hit = votes + kWave * a.gpw;
+    // HOMOG: the basis change, and a scratch for each wave's classes that do not settle
+    double *mono = reinterpret_cast<double *>(hit + 16);
+    double *scratch = mono + 2 * Tile::kMH * Tile::kMH;
 
     const int64_t g0 = whole ? static_cast<int64_t>(blockIdx.x) * a.gpw : blockIdx.x / a.splits;
     const int part0 = whole ? 0 : static_cast<int>(blockIdx.x - g0 * a.splits);
@@ -466,6 +820,10 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     }
     const double alpha = nodes.alpha[(lane & 15) < K ? lane & 15 : 0];
     if (tid < N) beta_s[tid] = nodes.beta[tid];
+    if constexpr (HOMOG) {
+        constexpr int MH = Tile::kMH;
+        if (tid < 2 * MH * MH) mono[tid] = kChebyshev.c[tid / (MH * MH)][tid / MH % MH][tid % MH];
+    }
     for (int e = tid; e < kWave * a.gpw; e += kPairThreads) votes[e] = 0;
     if (tid < 16) hit[tid] = -1;
     __syncthreads();
@@ -479,7 +837,7 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     const int q = whole ? slot / Cs : 0;
     const int c_rel = slot - q * Cs;                      // parts: slot < 128 = Cs
     const char *src = reinterpret_cast<const char *>(a.preds + static_cast<size_t>(g0) * N * a.C);
-    for (int part = part0; MODE == kParts ? part < a.parts : part == part0; ++part) {
+    for (int part = part0; MODE == kParts ? part < a.parts : part == part0; part += MODE == kParts ? a.splits : 1) {
         const int c = part * kPairClasses + c_rel;
         const bool in = q < here && c < C;
         const unsigned long long rows = in ? bits[q] : 0ull;
@@ -521,14 +879,37 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
         int Np = N, Mp = M, Ap = A, hp = h;
         // parts: nothing of what follows is worth carrying from one to the next, registers being what is short
         if (MODE == kParts) asm volatile("" : "+s"(Np), "+s"(Mp), "+s"(Ap), "+v"(hp));
-        if (whole ? wv * kPairsPerWave < here * Cs : part * kPairClasses + wv * kPairsPerWave < C)   // else: no class, the rest only
-            locate_class_pair<MT, TQ, S>(y, Cs, rows, all & ~rows, tab, Np, Mp, Ap, hp, lift, live, votes + kWave * (in ? q : 0));
+        if (whole ? wv * kPairsPerWave < here * Cs : part * kPairClasses + wv * kPairsPerWave < C) {   // else: no class, the rest only
+            const bool settled = locate_class_pair<MT, TQ, S, HOMOG>(y, Cs, rows, all & ~rows, tab, mono + hp * Tile::kMH * Tile::kMH, Np,
+                                                                     Mp, Ap, hp, lift, live, votes + kWave * (in ? q : 0));
+            if constexpr (HOMOG) {
+                unsigned long long open = __ballot(live && !settled && h == 0);
+                const int n = N - S, per_wave = pair_scratch_doubles(N, n, M);
+                double *xs = scratch + wv * per_wave, *mat = xs + N;
+                int *avail = reinterpret_cast<int *>(mat + n * (2 * M + 1) + M + n);
+                while (open != 0ull) {                    // the whole wave on one class
+                    const int from = __builtin_ctzll(open);
+                    open &= open - 1ull;
+                    const int qf = __builtin_amdgcn_readlane(in ? q : 0, from), cf = __builtin_amdgcn_readlane(c, from);
+                    const unsigned long long there = bits[qf];
+                    if (lane < N && ((there >> lane) & 1ull)) {
+                        const int at = __popcll(there & ((1ull << lane) - 1ull));
+                        avail[at] = lane;
+                        xs[at] = beta_s[lane];
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    locate_classes_wave<true>(a.preds + static_cast<size_t>(g0 + qf) * N * a.C, a.C, cf, 1, avail, xs, n, M, A, mat,
+                                              votes + kWave * qf);
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        }
         __builtin_amdgcn_wave_barrier();                  // the next part's rows: this pair's own places again
     }
     __syncthreads();
 
     if constexpr (!whole) {
-        if (MODE == kPart && !pool_votes_last_arrival(a.votes + g0 * (N + 1), votes, N, a.splits, hit)) return;
+        if (a.splits > 1 && !pool_votes_last_arrival(a.votes + g0 * (N + 1), votes, N, a.splits, hit)) return;
         if (wv != 0) return;
         // as below, a lane to a worker
         int key = lane < N ? (votes[lane] << 6) | (kWave - 1 - lane) : -1;
@@ -672,13 +1053,14 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     }
 }
 
-template <int MT, int TQ, int S>
+template <int MT, int TQ, int S, bool HOMOG>
 int run_pairs(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     const bool whole = call.parts == 1;
-    const size_t lds = pair_lds_bytes<MT, TQ, S>(whole, call.gpw, call.N, call.C);
-    const auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TQ, S, kWhole>
-                              : (call.splits > 1 ? decode_byzantine_pairs_kernel<MT, TQ, S, kPart>
-                                                 : decode_byzantine_pairs_kernel<MT, TQ, S, kParts>);
+    const size_t lds = pair_lds_bytes<MT, TQ, S>(whole, call.gpw, call.N, call.K + call.A, call.C, HOMOG);
+    auto kernel = whole ? decode_byzantine_pairs_kernel<MT, TQ, S, kWhole, HOMOG> : decode_byzantine_pairs_kernel<MT, TQ, S, kParts, HOMOG>;
+    if constexpr (!HOMOG) {
+        if (call.splits > 1) kernel = decode_byzantine_pairs_kernel<MT, TQ, S, kPart, HOMOG>;
+    }
     if (lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                static_cast<int>(lds)) != hipSuccess)
         return APPROXIFER_ERR_LAUNCH;
@@ -686,22 +1068,24 @@ int run_pairs(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kPairThreads), lds, stream, call, nodes));
 }
 
-// M rounded up to even, TQ = MT / 2 or one more.
-template <int MT, int TQ>
+// M rounded up to even, TQ = MT / 2 or one more.  Algorithm 1 with three missing is not built (pair_shape).
+template <int MT, int TQ, bool HOMOG>
 int run_pairs_rows(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     switch (call.S) {
-        case 0: return run_pairs<MT, TQ, 0>(call, nodes, stream);
-        case 1: return run_pairs<MT, TQ, 1>(call, nodes, stream);
-        case 2: return run_pairs<MT, TQ, 2>(call, nodes, stream);
-        case 3: return run_pairs<MT, TQ, 3>(call, nodes, stream);
-        default: return run_pairs<MT, TQ, 4>(call, nodes, stream);
+        case 0: return run_pairs<MT, TQ, 0, HOMOG>(call, nodes, stream);
+        case 1: return run_pairs<MT, TQ, 1, HOMOG>(call, nodes, stream);
+        case 2: return run_pairs<MT, TQ, 2, HOMOG>(call, nodes, stream);
+        case 3:
+            if constexpr (!HOMOG) return run_pairs<MT, TQ, 3, HOMOG>(call, nodes, stream);
+            return APPROXIFER_ERR_LIMIT;
+        default: return run_pairs<MT, TQ, 4, HOMOG>(call, nodes, stream);
     }
 }
-template <int MT>
+template <int MT, bool HOMOG>
 int run_pairs_columns(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream) {
-    return tq == MT / 2 ? run_pairs_rows<MT, MT / 2>(call, nodes, stream) : run_pairs_rows<MT, MT / 2 + 1>(call, nodes, stream);
+    return tq == MT / 2 ? run_pairs_rows<MT, MT / 2, HOMOG>(call, nodes, stream) : run_pairs_rows<MT, MT / 2 + 1, HOMOG>(call, nodes, stream);
 }
-// one function per MT, spread over source files for the build's sake
+// one function per MT and locator, spread over source files for the build's sake
 int run_pairs_4(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 int run_pairs_6(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 int run_pairs_8(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
@@ -709,5 +1093,11 @@ int run_pairs_10(int tq, const PairCall &call, const Nodes &nodes, hipStream_t s
 int run_pairs_12(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 int run_pairs_14(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 int run_pairs_16(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_4(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_6(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_8(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_10(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_12(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
+int run_null_pairs_14(int tq, const PairCall &call, const Nodes &nodes, hipStream_t stream);
 
 }  // namespace approxifer

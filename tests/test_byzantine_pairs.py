@@ -1,4 +1,4 @@
-"""Algorithm 2 on the library's own worker nodes with at most four workers missing (csrc/byzantine_pairs.h), at the edges of its
+"""Algorithms 2 and 1 on the library's own worker nodes with at most four workers missing (csrc/byzantine_pairs.h), at the edges of its
 tiles: K + A odd and even, the fewest workers of eq. (3) and up to two more, none to four missing, a node in the middle and a
 query node on a worker's, one class to several workgroups of them, and group counts that fill workgroups in part."""
 import numpy as np
@@ -94,20 +94,22 @@ def test_fits_of_predictions_that_are_not_rational(gpu, K, A, S, ex):
         assert_rounding_ties(Y, mask, beta, K, A, adv, adv_ref, locator)
 
 
+@pytest.mark.parametrize("entry", ["approxifer_decode_byzantine", "approxifer_decode_byzantine_homogeneous"])
 @pytest.mark.parametrize("K,A,S,N,C", [(8, 2, 4, 24, 10), (4, 1, 1, 12, 2), (2, 1, 0, 7, 1), (6, 2, 0, 16, 40), (8, 2, 2, 22, 128),
                                        (3, 1, 0, 9, 129), (8, 2, 1, 23, 260)])
-def test_a_group_has_the_same_bits_in_calls_of_every_size(gpu, K, A, S, N, C):
+def test_a_group_has_the_same_bits_in_calls_of_every_size(gpu, K, A, S, N, C, entry):
     # groups to a workgroup, and rows of lanes to a group, by the number of groups; with and without a workspace
     torch, binding, dev = gpu
     G = 1100 if C <= 40 else 270
     alpha, beta, Y, mask, _ = _inputs(K, A, S, N, C, G, 7 * K + N + C)
+    decode = getattr(binding, entry)
     Yd, md = torch.from_numpy(Y).to(dev), torch.from_numpy(mask).to(dev)
-    whole = [t.cpu().numpy() for t in binding.approxifer_decode_byzantine(Yd, md, alpha, beta, S, A, 1)]
+    whole = [t.cpu().numpy() for t in decode(Yd, md, alpha, beta, S, A, 1)]
     for n in (1, 3, 255, 257, 700):
         if n > G:
             continue
         for ws in (None, binding.NO_WORKSPACE):
-            part = binding.approxifer_decode_byzantine(Yd[:n], md[:n], alpha, beta, S, A, 1, workspace=ws)
+            part = decode(Yd[:n], md[:n], alpha, beta, S, A, 1, workspace=ws)
             for a, b in zip(whole, part):
                 assert np.array_equal(a[:n], b.cpu().numpy())
 
