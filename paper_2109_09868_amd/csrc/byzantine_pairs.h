@@ -408,12 +408,12 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
         dd_prev = dd;
         ++since_jump;
         double old = 0.0, next = 1.0;                     // what of z and z' the next round starts from
-        if (round == 0) {
-            quotient = unit * fma(-0.5, dd, 1.0);         // z'^T A z', A z' = unit z
-        } else if (round == 1 && !settled && dd > 1e-18 && dd < 1.0) {
-            // The best vector of span(z, z') once: by now two modes are left, and the slow one is gone with it.  20480
-            // rational classes at K = 8, A = 2, 20 of 24 workers take up to ten rounds without this and five with it; K = 12, A = 2, 28
-            // workers, seven and four.
+        if (round % 2 == 0) {
+            quotient = round == 0 || dd > 1e-12 ? unit * fma(-0.5, dd, 1.0) : 0.0;   // z'^T A z', A z' = unit z
+        } else if (quotient > 0.0 && !settled && dd > (round == 1 ? 1e-18 : 1e-12) && dd < 1.0) {
+            // The best vector of span(z, z') in every other round while the steps are large: where two modes are left the slow one
+            // is gone with it.  The slowest of 20480 rational classes, in each of eight sets, needs 4 to 8 rounds with it at K = 8,
+            // A = 2, 20 of 24 workers and 5 to 8 at K = 9, A = 3, 24 workers; with it in round 1 alone 4 to 15 and 5 to 13.
             const double g = fma(-0.5, dd, 1.0), across2 = dd * fma(-0.25, dd, 1.0), across = sqrt_normal(across2);
             const double r = rcp_normal(across), mixed = fma(-g, quotient, unit) * r, other = g * fma(g, quotient, -unit) * r * r;
             const double half = 0.5 * (other - quotient);
@@ -424,10 +424,11 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
                 next = tau * norm;
                 if (!(next > 0.95 && next < 1.05)) dd_prev = __builtin_inf();
             }
-        } else if (!settled && since_jump >= 3 && dd < 1e-4 && dd_before < __builtin_inf()) {
-            const double r = sqrt(dd / dd_before);
+        }
+        if (round > 1 && !settled && since_jump >= 3 && dd <= 1e-12 && dd_before < __builtin_inf()) {
+            const double r = sqrt_normal(dd * rcp_normal(dd_before));
             if (r > 0.05 && r < 0.97) {
-                old = -r / (1.0 - r);
+                old = -r * rcp_normal(1.0 - r);
                 next = 1.0 - old;
                 since_jump = 0;
                 dd_prev = __builtin_inf();
