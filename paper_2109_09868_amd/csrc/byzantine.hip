@@ -1439,14 +1439,13 @@ struct PairShape {
 PairShape pair_shape(int64_t G, int K, int N, int S, int A, int64_t C, bool homogeneous) {
     const int M = K + A;
     // Algorithm 1 adds rounds of inverse iteration, serial in the wave that has the slowest class, and the moments of a second
-    // half: wide tiles leave their registers for scratch, and A = 3 draws tails of twenty rounds and more, which at K + A = 15
-    // do not settle in as many classes.  1200 drawn calls, the former kernels' time over this one's: K + A <= 10 1.03 to 7, mean
-    // 1.5; K + A = 11 to 14 with S <= 2 and A <= 2 0.94 (S = 2 at 13) to 5.5, mean 1.5; S = 4 up to 2000 classes 0.83 to 1.2 from
-    // K + A = 11 to 13, beyond 1.06 to 2.5, at 14 at most 1.0; A = 3 up to 12 0.85 (one call in sixty, a class that takes
-    // more rounds than there) to 3.8, mean 1.6, at 13 with S <= 1 0.96 to 1.8 and with S = 2 down to 0.76, at 14 from 0.85 (0.52 with
-    // S = 4); K + A = 15 0.22 to 2.3, mean 0.6.  S = 3 is not built.
-    if (homogeneous && (S == 3 || M == 15 || (A == 3 && (M == 14 || (M == 13 && S > 1))) || (S == 4 && M == 14) ||
-                        (G * C <= 2000 && ((S == 4 && M > 10) || (S == 2 && M == 13)))))
+    // half: wide tiles leave their registers for scratch, and A = 3 draws longer tails of rounds, which at K + A = 15 do not settle
+    // in as many classes.  The former kernels' time over this one's in 1600 drawn calls: K + A <= 10 1.1 to 7, mean 1.5;
+    // K + A = 11 to 14 with S <= 2 and A <= 2 0.94 (S = 2 at 13) to 5.5, mean 1.5; S = 3, 4 from K + A = 11 to 13, up to 2000
+    // classes 0.83 to 1.2 (S = 4), beyond 1.06 to 3, at 14 at most 1.0; A = 3 up to 12 0.97 to 3.8, mean 1.6, at 13 with S <= 1 0.96
+    // to 1.8 and with S = 2 down to 0.76, at 14 from 0.85 (0.52 with S = 4); K + A = 15 0.22 to 2.3, mean 0.6.
+    if (homogeneous && (M == 15 || (A == 3 && (M == 14 || (M == 13 && S > 1))) || (S > 2 && M == 14) ||
+                        (G * C <= 2000 && ((S > 2 && M > 10) || (S == 2 && M == 13)))))
         return {0, 0};
     // A call of few classes is the chain of one wave, which the missing workers, a column that an odd M leaves unused and
     // registers beyond 256 lengthen most: up to 4000 classes in all the packed kernel, which gives a group several waves, is the

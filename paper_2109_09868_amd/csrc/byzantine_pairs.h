@@ -1076,9 +1076,7 @@ int run_pairs_rows(const PairCall &call, const Nodes &nodes, hipStream_t stream)
         case 0: return run_pairs<MT, TQ, 0, HOMOG>(call, nodes, stream);
         case 1: return run_pairs<MT, TQ, 1, HOMOG>(call, nodes, stream);
         case 2: return run_pairs<MT, TQ, 2, HOMOG>(call, nodes, stream);
-        case 3:
-            if constexpr (!HOMOG) return run_pairs<MT, TQ, 3, HOMOG>(call, nodes, stream);
-            return APPROXIFER_ERR_LIMIT;
+        case 3: return run_pairs<MT, TQ, 3, HOMOG>(call, nodes, stream);
         default: return run_pairs<MT, TQ, 4, HOMOG>(call, nodes, stream);
     }
 }
