@@ -8,6 +8,8 @@
 //  * node table: T[i][j] = 1 / (alpha_j - beta_i), the same for all groups, is evaluated once per
 //    workgroup; numerators and denominators are summed over F and divided at the end.  A 16-lane
 //    row per group (up to sixteen classes) or per (group, 64 classes).
+#include <algorithm>
+
 #include "decode_common.h"
 #include "rows.h"
 #include "sectors.h"
@@ -339,7 +341,7 @@ template <int VEC>
 __global__ void decode_top1_kernel(const float *__restrict__ preds, const uint8_t *__restrict__ mask,
                                    int32_t *__restrict__ top1, float *__restrict__ score,
                                    int32_t *__restrict__ status, int K, int N, int S, int64_t C, int64_t Cv,
-                                   int sign_mode, int qsplit, const Nodes nodes) {
+                                   int sign_mode, const Nodes nodes) {
     typedef typename PredVec<VEC>::type V;
     extern __shared__ double lds_d[];
     const int KP = round_up4(K);
@@ -349,9 +351,7 @@ __global__ void decode_top1_kernel(const float *__restrict__ preds, const uint8_
     double *beta_s = alpha_s + K;
     int *F = reinterpret_cast<int *>(beta_s + N);
     int *n_sh = F + N;
-    // qsplit > 1 (few groups, very many classes): qsplit = KP/4 workgroups share a group, one quad of queries each
-    const int64_t g = blockIdx.x / qsplit;
-    const int qpart = static_cast<int>(blockIdx.x - g * qsplit);
+    const int64_t g = blockIdx.x;
 
     stage_nodes(nodes, K, N, alpha_s, beta_s);
     for (int e = threadIdx.x; e < nF_cap * KP; e += blockDim.x) WdT[e] = 0.0;
@@ -371,12 +371,11 @@ __global__ void decode_top1_kernel(const float *__restrict__ preds, const uint8_
     const int lane = lane_id();
     const int KQ = KP / 4;
     const int nwaves = blockDim.x / kWave;
-    const bool one_quad = qsplit > 1;                           // this workgroup: quad qpart only, every wave a slice
-    const int slices = one_quad ? nwaves : (nwaves >= KQ ? nwaves / KQ : 1);   // waves that share one quad split its columns
-    const int qwaves = one_quad ? 1 : (nwaves >= KQ ? KQ : nwaves);            // quads processed concurrently
+    const int slices = nwaves >= KQ ? nwaves / KQ : 1;          // waves that share one quad split its columns
+    const int qwaves = nwaves >= KQ ? KQ : nwaves;              // quads processed concurrently
     const int slice = wave_id() / qwaves;
     Best *merged = reinterpret_cast<Best *>((reinterpret_cast<uintptr_t>(n_sh + 1) + 15) & ~static_cast<uintptr_t>(15));   // [KP][slices]
-    for (int q = one_quad ? qpart : wave_id() % qwaves; q < KQ && slice < slices; q += one_quad ? KQ : qwaves) {
+    for (int q = wave_id() % qwaves; q < KQ && slice < slices; q += qwaves) {
         Best best[4];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
@@ -432,9 +431,7 @@ __global__ void decode_top1_kernel(const float *__restrict__ preds, const uint8_
         }
     }
     __syncthreads();
-    const int j_first = one_quad ? 4 * qpart : 0;
-    const int j_end = one_quad ? (4 * qpart + 4 < K ? 4 * qpart + 4 : K) : K;
-    for (int j = j_first + threadIdx.x; j < j_end; j += blockDim.x) {
+    for (int j = threadIdx.x; j < K; j += blockDim.x) {
         Best b = merged[j * slices];
         for (int sl = 1; sl < slices; ++sl) {
             const Best o = merged[j * slices + sl];
@@ -453,6 +450,148 @@ __device__ __forceinline__ void best_step(Best &b) {
     if (better(ov, oi, b)) {
         b.v = ov;
         b.i = oi;
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// fused decoder + top-1, few groups of thousands of classes
+// ------------------------------------------------------------------------------------
+// A workgroup of up to sixteen waves per (group, QN queries).  Every lane walks vectors of four classes with the queries'
+// accumulators and bests in registers; the next eight rows are on their way while the last eight are multiplied, across the end of
+// a vector too.  The parts of a group read the same rows, from the caches.  What one CU has in flight bounds it (128 KB and 2 us a chunk
+// of eight rows: 45 GB/s): K = 9, eight groups of 22613 classes, rows only 4-byte aligned, 72 us with a workgroup per quad of
+// queries and 4-byte loads one chunk at a time, 26 this way; without a hint against the caches, and without loads for the rows
+// that the last chunk lacks, which took 39.  A group's classes over several workgroups would need a place for their bests.
+// dynamic LDS: double WdT[(N-S) QN] | alpha_s[K] | beta_s[N] | int F[N] | int n | pad to 16 bytes | Best merged[QN][waves].
+constexpr int kSplitThreads = 1024;
+
+template <int QN, bool UNAL>
+__global__ __launch_bounds__(kSplitThreads) void decode_top1_split_kernel(const float *__restrict__ preds,
+                                                                           const uint8_t *__restrict__ mask,
+                                                                           int32_t *__restrict__ top1, float *__restrict__ score,
+                                                                           int32_t *__restrict__ status, int K, int N, int S,
+                                                                           int64_t C, int sign_mode, int parts, const Nodes nodes) {
+    extern __shared__ double lds_d[];
+    const int nF_cap = S < 0 ? N : N - S;
+    double *WdT = lds_d;
+    double *alpha_s = WdT + nF_cap * QN;
+    double *beta_s = alpha_s + K;
+    int *F = reinterpret_cast<int *>(beta_s + N);
+    int *n_sh = F + N;
+    Best *merged = reinterpret_cast<Best *>((reinterpret_cast<uintptr_t>(n_sh + 1) + 15) & ~static_cast<uintptr_t>(15));
+    const int64_t g = blockIdx.x / parts;
+    const int j0 = static_cast<int>(blockIdx.x - g * parts) * QN;
+    const int own = K - j0 < QN ? K - j0 : QN;
+    const int lane = lane_id();
+    const int nwaves = blockDim.x / kWave;
+
+    stage_nodes(nodes, K, N, alpha_s, beta_s);
+    for (int e = threadIdx.x; e < nF_cap * QN; e += blockDim.x) WdT[e] = 0.0;
+    if (wave_id() == 0) {
+        const int n = survivors_from_mask(mask + g * N, N, F);
+        if (lane == 0) *n_sh = n;
+    }
+    __syncthreads();
+    const int nF = __builtin_amdgcn_readfirstlane(*n_sh);
+    const bool good = S < 0 ? nF >= 1 : nF == nF_cap;
+    if (j0 == 0 && threadIdx.x == 0 && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    if (!good) return;
+
+    const float *pgroup = preds + static_cast<size_t>(g) * N * C;
+    const int Cv = static_cast<int>((C + 3) / 4);
+    const auto floats_of = [&](int cv) { return UNAL && C - 4ll * cv < 4 ? static_cast<int>(C - 4ll * cv) : 4; };
+    const auto load_rows = [&](int cv, int r0, v4f (&y)[kRowChunk]) {        // the parts of a group share them: no hint to the caches
+        const int floats = floats_of(cv);
+#pragma unroll
+        for (int u = 0; u < kRowChunk; ++u) {
+            if (r0 + u < nF) {
+                const float *p = pgroup + static_cast<size_t>(__builtin_amdgcn_readfirstlane(F[r0 + u])) * C + 4ll * cv;
+                if (!UNAL) {
+                    y[u] = *reinterpret_cast<const v4f *>(p);
+                } else if (floats >= 4) {
+                    y[u] = *reinterpret_cast<const v4f_dword_aligned *>(p);
+                } else {
+                    y[u][0] = p[0];
+                    if (floats > 1) y[u][1] = p[1];
+                    if (floats > 2) y[u][2] = p[2];
+                }
+            }
+        }
+    };
+    v4f ahead[kRowChunk];
+    int cv = threadIdx.x;
+    load_rows(cv < Cv ? cv : 0, 0, ahead);                  // in flight while the weights are evaluated
+    decoder_weights(alpha_s + j0, beta_s, F, nF, own, QN, sign_mode, WdT);
+    __syncthreads();
+
+    Best best[QN];
+#pragma unroll
+    for (int j = 0; j < QN; ++j) {
+        best[j].v = -__builtin_inf();
+        best[j].i = 0x7fffffff;
+    }
+    for (; cv < Cv; cv += blockDim.x) {
+        double acc[QN][4];
+#pragma unroll
+        for (int j = 0; j < QN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[j][e] = 0.0;
+        for (int r0 = 0; r0 < nF; r0 += kRowChunk) {
+            v4f y[kRowChunk];
+#pragma unroll
+            for (int u = 0; u < kRowChunk; ++u) y[u] = ahead[u];
+            const bool more = r0 + kRowChunk < nF;
+            const int next = more ? cv : cv + static_cast<int>(blockDim.x);
+            if (next < Cv) load_rows(next, more ? r0 + kRowChunk : 0, ahead);
+#pragma unroll
+            for (int u = 0; u < kRowChunk; ++u) {
+                if (r0 + u < nF) {
+                    const double *w = WdT + (r0 + u) * QN;
+                    const double y0 = y[u][0], y1 = y[u][1], y2 = y[u][2], y3 = y[u][3];
+#pragma unroll
+                    for (int j = 0; j < QN; ++j) {
+                        const double wj = w[j];
+                        acc[j][0] = fma(wj, y0, acc[j][0]);
+                        acc[j][1] = fma(wj, y1, acc[j][1]);
+                        acc[j][2] = fma(wj, y2, acc[j][2]);
+                        acc[j][3] = fma(wj, y3, acc[j][3]);
+                    }
+                }
+            }
+        }
+        const int floats = floats_of(cv);
+#pragma unroll
+        for (int j = 0; j < QN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < floats && better(acc[j][e], 4 * cv + e, best[j])) {
+                    best[j].v = acc[j][e];
+                    best[j].i = 4 * cv + e;
+                }
+    }
+#pragma unroll
+    for (int j = 0; j < QN; ++j) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const double ov = __shfl_xor(best[j].v, off, kWave);
+            const int oi = __shfl_xor(best[j].i, off, kWave);
+            if (better(ov, oi, best[j])) {
+                best[j].v = ov;
+                best[j].i = oi;
+            }
+        }
+        if (lane == 0) merged[j * nwaves + wave_id()] = best[j];
+    }
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < own) {
+        Best b = merged[threadIdx.x * nwaves];
+        for (int w2 = 1; w2 < nwaves; ++w2) {
+            const Best o = merged[threadIdx.x * nwaves + w2];
+            if (better(o.v, o.i, b)) b = o;
+        }
+        const int64_t at = g * K + j0 + threadIdx.x;
+        top1[at] = b.i == 0x7fffffff ? 0 : b.i;
+        if (score != nullptr) score[at] = static_cast<float>(b.v);
     }
 }
 
@@ -1356,6 +1495,36 @@ bool top1_tiles_shape(int K, int N, int64_t C, int64_t G, bool vec4) {
     return vec4 || C <= 128 || K > 8 || (K > 4 && G < 4096);
 }
 
+int64_t top1_split_waves(int64_t C) { return std::min<int64_t>((C + 4 * kWave - 1) / (4 * kWave), kSplitThreads / kWave); }
+
+// Queries to a workgroup of decode_top1_split_kernel, 0: not the call's kernel.  For up to 512 quads of queries, whose other kernels
+// leave most of the chip idle and wait for one chunk of rows after the other.  Times without and with it, 680 calls:
+//  - rows of whole vectors: K > 16 always (K = 28, 15 groups of 2520 classes 38.6 and 11.7 us, K = 64, 19 of 3844 345 and 55, K = 24,
+//    20 classes, 36 quads 15.3 and 8.4); K = 9..16 from 384 classes on (one group of 21844 32 and 25; K = 16, 40 of 288 7.7 and
+//    8.0), up to 240 quads where they are shorter than 2000 (K = 14, 77 of 688 8.3 and 9.8); K <= 8 from 256 (K = 6, 4 of 6176 14.0 and
+//    9.7), shorter than 4096 while a CU has one workgroup or two queries to each (K = 4, 336 of 2156 11.1 and 16.0, 449 of 420 6.5 and 8.3);
+//  - rows that are only 4-byte aligned: always from 4096 classes on (K = 9, 8 groups of 22613 72 and 26); K > 32 always (214
+//    classes, 32 quads 54 and 18), K = 17..32 from 64 (874 classes, 8 quads 22.6 and 12.0; 43 classes, 180 quads 11.0 and 11.4);
+//    K = 9..16 from 1900 up to 200 quads (2125 classes, 90 quads 12.6 and 9.6; 1597, 396 quads 14.1 and 17.2; 511, one group 7.7
+//    and 10.6), K <= 8 from 100, while a CU has one workgroup or the waves are few (K = 8, 152 of 1178 18.5 and 11.3; K = 5, 163 of
+//    2351 14.0 and 17.1).
+// Two queries to a workgroup while that gives each CU one workgroup, or all of them together 1600 waves (K = 20, 76 of 260 10.0 with
+// four and 8.1; K = 7, 184 of 372 7.6 and 6.1; K = 20, 35 of 2168 12.9 and 18.9); with more than 12000 classes up to 176, from
+// where on the rows that the parts read again cost more (K = 28, 11 of 23540 59 and 48; K = 12, 39 of 25640 40 and 48).
+int top1_split(int K, int64_t C, int64_t G, bool vec4) {
+    const int64_t quads = G * ((K + 3) / 4), pairs = G * ((K + 1) / 2), waves = top1_split_waves(C);
+    if (quads > 512 || C <= kRowLanes || C > 0x7fffffff) return 0;
+    const int queries = K <= 2 || pairs <= (C <= 12000 ? 256 : 176) || pairs * waves <= 1600 ? 2 : 4;
+    const int64_t blocks = G * ((K + queries - 1) / queries);
+    bool faster;
+    if (K > 32) faster = true;
+    else if (K > 16) faster = vec4 || C >= 64;
+    else if (K > 8) faster = vec4 ? C >= 384 && (C >= 2000 || quads <= 240) : C >= 4093 || (C >= 1900 && quads <= 200);
+    else if (vec4) faster = C >= 256 && (C >= 4096 || blocks <= 256 || queries == 2);
+    else faster = C >= 100 && (C >= 4093 || blocks <= 256 || queries == 2 || blocks * waves <= 2000);
+    return faster ? queries : 0;
+}
+
 template <bool TOP1, int KP, int QS>
 int run_rows_shape(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_top1, float *d_score,
                    int32_t *d_status, int64_t G, int K, int N, int S, int64_t C, const Nodes &nodes, int sign_mode,
@@ -1415,9 +1584,8 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
                                        K <= 16 && nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
 }
 
-// Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes, not
-// few groups of thousands of classes: one workgroup's loads in flight are too few there, K = 32, one group of 32000 classes 104 and
-// 435 us).  Times without and with it, over 5000 calls:
+// Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes) that
+// top1_split leaves.  Times without and with it, over 5000 calls:
 //  - K = 9..16 in rows that are only 4-byte aligned: always (0.2 to 0.96 of the time; K = 12, 6243 groups of 1001 classes 204 and 96, 206
 //    of 101 15.5 and 5.6);
 //  - K = 9..16 otherwise: against tiles that share a workgroup's sixteen rows of lanes.  Up to 256 classes in few groups (K = 16,
@@ -1425,8 +1593,6 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
 //    in one round of workgroups (G <= 256) and, up to 36 survivors, in many (N = 40, 384 to 1024 groups of 1000 classes 1.1 to 1.4 times);
 //  - K = 17..27 in whole vectors from 256 groups on (K = 17, 147 of 1000 17.8 and 20.8); K = 32, 2341 groups of 1001 classes 644 and 172,
 //    23205 of 101 1238 and 304, 2343 of 1000 292 and 170;
-//  - K > 16 in rows that are only 4-byte aligned: from 1024 classes on not in one round of the kernel below with a workgroup per
-//    quad of queries (K = 21, two groups of 1903 classes 20.9 and 29.7, K = 52, three of 1869 38 and 118);
 //  - K > 32: few groups of few classes stay with a wave per quad of queries (K = 48, 128 groups of 64 classes 1.24 times, of 33 1.44,
 //    500 of 33 25.5 and 30.5 us).
 // K <= 8 leaves half of the products' rows empty (K = 8, 9375 of 1000 100 and 117).  Up to sixteen queries the other kernels
@@ -1439,7 +1605,6 @@ bool top1_matrix_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4, con
         const bool faster = !vec4 || (stripes <= 4 ? G * (stripes + 1) <= 5120 : survivors <= 24 || G <= 256 || (survivors <= 36 && G > 1024));
         return faster && !nodes_coincide(nodes, K, N);
     }
-    if (!vec4 && C >= 1024 && G * ((K + 3) / 4) <= (K > 32 ? 512 : 256)) return false;
     if (K > 32 && (vec4 ? C <= 400 && G <= 256 : C <= 64 && G <= 512)) return false;
     return !vec4 || K >= 28 || G >= 256;
 }
@@ -1565,12 +1730,24 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     const int64_t Cv = vec4 ? C / 4 : C;
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
     const int KQ = KP / 4;
-    // few groups with very many classes: the split below (K = 12, one group of 21844 classes 32 us, 92 with tiles; K = 4,
-    // 4096 classes 10.5 and 9.3; K = 16, 128 groups of 50256 classes 269 and 307)
-    const bool few_groups = G * KQ <= 512 && (C + 3) / 4 >= 64 * 16;
-    if (!few_groups && top1_matrix_shape(K, N, S, C, G, vec4, nodes))
+    const int split = top1_split(K, C, G, vec4);
+    // up to sixteen queries the tile kernel hands on the row of a worker whose node a query has; calls that it used to serve stay
+    if (split > 0 && (K > 16 || N > kWave || C >= 4093 || !nodes_coincide(nodes, K, N))) {
+        const int parts = (K + split - 1) / split;
+        const int64_t waves = top1_split_waves(C);
+        const size_t slds = sizeof(double) * (static_cast<size_t>(S < 0 ? N : N - S) * split + K + N) +
+                            sizeof(int) * (static_cast<size_t>(N) + 1) + 16 + sizeof(Best) * split * waves;
+        const dim3 sgrid(static_cast<unsigned>(G * parts)), sblock(static_cast<unsigned>(waves) * kWave);
+#define APPROXIFER_TOP1_SPLIT(QN, UNAL)                                                                                 \
+    launch_status(launch_kernel(decode_top1_split_kernel<QN, UNAL>, sgrid, sblock, slds, stream, d_preds, d_mask, d_top1,  \
+                                d_score, d_status, K, N, S, C, sign_mode, parts, nodes))
+        if (split == 2) return vec4 ? APPROXIFER_TOP1_SPLIT(2, false) : APPROXIFER_TOP1_SPLIT(2, true);
+        return vec4 ? APPROXIFER_TOP1_SPLIT(4, false) : APPROXIFER_TOP1_SPLIT(4, true);
+#undef APPROXIFER_TOP1_SPLIT
+    }
+    if (top1_matrix_shape(K, N, S, C, G, vec4, nodes))
         return run_top1_matrix(d_preds, d_mask, d_top1, d_score, d_status, G, K, N, S, C, nodes, sign_mode, stream);
-    if (top1_tiles_shape(K, N, C, G, vec4) && !few_groups) {
+    if (top1_tiles_shape(K, N, C, G, vec4)) {
         const int64_t chunks = ((C + 3) / 4 + kRowLanes - 1) / kRowLanes;
         int R = 1;
         while (R < kRowGroups && R < chunks) R *= 2;
@@ -1589,9 +1766,8 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
         }
 #undef APPROXIFER_TOP1_TILES
     }
-    // K <= 16, up to 64 survivors, enough groups to fill the chip: a workgroup per group whose waves keep all K
-    // accumulator rows (few groups with very many classes stay with the quad-per-workgroup split below)
-    if (K <= 16 && (S < 0 ? N : N - S) <= 64 && C >= 4 && !few_groups) {
+    // K <= 16, up to 64 survivors: a workgroup per group whose waves keep all K accumulator rows
+    if (K <= 16 && (S < 0 ? N : N - S) <= 64 && C >= 4) {
         const int64_t sCv = (C + 3) / 4;
         const int64_t stiles = (sCv + kColsPerTile - 1) / kColsPerTile;
         const int nwaves = stiles < 4 ? static_cast<int>(stiles) : 4;
@@ -1614,20 +1790,12 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
     if (slices > most) slices = most;
     if (slices * KQ > 16) slices = 16 / KQ;
     if (slices < 1) slices = 1;
-    int waves = KQ <= 16 ? KQ * slices : 16;
-    // Few groups and very many classes (vocabulary-sized predictions in a small batch): a workgroup per quad of
-    // queries, all sixteen waves slicing the columns.  Every workgroup reads all surviving rows; with so few
-    // groups they come from the cache.
-    int qsplit = 1;
-    if (G * KQ <= 512 && KQ >= 2 && Cv >= 64 * 16) {
-        qsplit = KQ;
-        waves = 16;
-    }
-    const int lds_slices = qsplit > 1 ? waves : (waves >= KQ ? waves / KQ : 1);
+    const int waves = KQ <= 16 ? KQ * slices : 16;
+    const int lds_slices = waves >= KQ ? waves / KQ : 1;
     // int F[N] | int n | 1 pad int  keeps the Best array that follows 16-byte aligned when N is even; round up
     size_t lds = sizeof(double) * (static_cast<size_t>(S < 0 ? N : N - S) * KP + K + N) + sizeof(int) * (static_cast<size_t>(N) + 3);
     lds += 16 + sizeof(double) * 2 * static_cast<size_t>(KP) * lds_slices;
-    const dim3 grid(static_cast<unsigned>(G * qsplit)), block(waves * kWave);
+    const dim3 grid(static_cast<unsigned>(G)), block(waves * kWave);
     if (lds > 64 * 1024) {
         const void *fn = vec4 ? reinterpret_cast<const void *>(decode_top1_kernel<4>)
                               : reinterpret_cast<const void *>(decode_top1_kernel<1>);
@@ -1635,7 +1803,7 @@ int launch_decode_top1(const float *d_preds, const uint8_t *d_mask, int32_t *d_t
             return APPROXIFER_ERR_LAUNCH;
     }
     return launch_status(launch_kernel(vec4 ? decode_top1_kernel<4> : decode_top1_kernel<1>, grid, block, lds, stream,
-                                       d_preds, d_mask, d_top1, d_score, d_status, K, N, S, C, Cv, sign_mode, qsplit, nodes));
+                                       d_preds, d_mask, d_top1, d_score, d_status, K, N, S, C, Cv, sign_mode, nodes));
 }
 
 int launch_argmax_rows(const float *d_values, int32_t *d_top1, float *d_score, int64_t rows, int64_t C,
