@@ -322,6 +322,150 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(NS
 }
 
 // ------------------------------------------------------------------------------------
+// decoder on the float64 matrix cores, short rows, more than sixteen queries
+// ------------------------------------------------------------------------------------
+// A wave per group, four to a workgroup, which walk the groups with the grid's stride: a tile of decode_matrix_kernel takes four
+// waves and a set of weights, K |F| divisions, whatever the row's length.  Here T[i][j] = 1 / (alpha_j - beta_i), the same for all
+// groups, is evaluated once per workgroup; the products of a wave are sums of T s_i y_i, s_i the alternating sign of survivor i, and
+// the queries' denominators, one to a lane, divide them at the end.  A lane's D rows 4 t + k of consecutive k are neighbouring
+// rows of out: sixteen lanes store vectors of one row, the next sixteen of the next.  Operand layout as in decode_matrix_kernel.
+// R >= ceil(K / 16) rounds; rows of up to eight k-steps at a time stay in registers for all rounds and stripes of sixteen vectors
+// come one after the other.  Float64 matrix issue and the chain of one group per wave at two waves a SIMD: 31 of 34 workers, K = 31, 14070
+// groups of 36 classes 273 us with decode_kernel and 72 here (20 for the bytes); K = 48, 6851 of 60 307 and 78; K = 20, 487 of 40
+// 13.4 and 8.2; K = 18, 7818 of 50 53 and 40.
+// COINCIDE: some query has a worker's node.
+// dynamic LDS: double T[N][short_stride(R)] | rden[4][16 R] | int F[4][64] | node[16 R].
+constexpr int kShortWaves = 4;
+constexpr int kShortClasses = 128;                            // two stripes
+__host__ __device__ constexpr int short_stride(int R) { return 16 * (R | 1); }
+
+template <int R, bool UNAL, bool COINCIDE>
+__global__ __launch_bounds__(kShortWaves *kWave) __attribute__((amdgpu_waves_per_eu(2))) void decode_short_kernel(
+    const float *__restrict__ preds, const uint8_t *__restrict__ mask, float *__restrict__ out, int32_t *__restrict__ status,
+    int64_t G, int K, int N, int S, int C, int sign_mode, const Nodes nodes) {
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    constexpr int TS = short_stride(R), kSteps = 8;
+    extern __shared__ double lds_d[];
+    double *T = lds_d;
+    double *rden = T + N * TS;
+    int *F = reinterpret_cast<int *>(rden + kShortWaves * 16 * R);
+    int *node = F + kShortWaves * kWave;                      // the worker whose node query j is, or -1
+    const int lane = lane_id(), c = lane & 15, k = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    rden += wv * 16 * R;
+    F += wv * kWave;
+
+    if (COINCIDE) {
+        if (static_cast<int>(threadIdx.x) < 16 * R) node[threadIdx.x] = -1;
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < N * 16 * R; e += kShortWaves * kWave) {
+        const int i = e / (16 * R), j = e % (16 * R);
+        const double d = j < K ? nodes.alpha[j] - nodes.beta[i] : 0.0;
+        T[i * TS + j] = d != 0.0 ? 1.0 / d : 0.0;
+        if (COINCIDE && j < K && d == 0.0) node[j] = i;       // nodes are distinct: one worker at most
+    }
+    __syncthreads();
+
+    const int Cv = (C + 3) / 4;
+    for (int64_t g = static_cast<int64_t>(blockIdx.x) * kShortWaves + wv; g < G; g += static_cast<int64_t>(gridDim.x) * kShortWaves) {
+        __builtin_amdgcn_wave_barrier();                      // the group before has been through the list
+        const bool in = lane < N && mask[g * N + lane] != 0;
+        const unsigned long long bits = __ballot(in);
+        const int nF = __popcll(bits);
+        if (in) F[__popcll(bits & ((1ull << lane) - 1ull))] = lane;
+        __builtin_amdgcn_wave_barrier();
+        const bool good = S < 0 ? nF >= 1 : nF == N - S;
+        if (lane == 0 && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+        if (!good) continue;
+        const float *pg = preds + static_cast<size_t>(g) * N * C;
+        float *og = out + static_cast<size_t>(g) * K * C;
+        // A query on the node of a worker that answered: weight one for it, zero for the others (whose NaN or infinities show, as
+        // in decode_kernel)
+        const auto on_node = [&](int j) {
+            const int i = node[j];
+            return i >= 0 && ((bits >> i) & 1ull) != 0 ? i : -1;
+        };
+        int own[R];
+        if (COINCIDE)
+#pragma unroll
+            for (int q = 0; q < R; ++q) own[q] = on_node(16 * q + c);
+        for (int c0 = 0; c0 < Cv; c0 += 16) {
+            const int cv = c0 + c;
+            const int floats = cv >= Cv ? 0 : (UNAL && C - 4 * cv < 4 ? C - 4 * cv : 4);
+            v4d acc[R][4];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[r][e] = v4d{0.0, 0.0, 0.0, 0.0};
+            for (int s0 = 0; s0 < nF; s0 += 4 * kSteps) {
+                v4f y[kSteps];
+                int at[kSteps];
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) {
+                    const int r = s0 + 4 * s + k;
+                    y[s] = v4f(0.0f);
+                    at[s] = F[r < nF ? r : nF - 1];
+                    if (s0 + 4 * s < nF && r < nF && floats > 0)
+                        y[s] = load_pred_vector<UNAL>(pg + static_cast<size_t>(at[s]) * C + 4 * cv, floats);
+                }
+                if (c0 == 0 && s0 == 0) {                     // while the first rows are on their way
+                    double den = 0.0;
+                    for (int r = 0; r < nF; ++r) {
+                        const int i = __builtin_amdgcn_readfirstlane(F[r]);
+                        const double t = T[i * TS + (lane < 16 * R ? lane : 0)];
+                        den += ((sign_mode == APPROXIFER_SIGN_WORKER_INDEX ? i : r) & 1) ? -t : t;
+                    }
+                    if (lane < 16 * R) rden[lane] = COINCIDE && on_node(lane) >= 0 ? 1.0 : 1.0 / den;
+                }
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) {
+                    if (s0 + 4 * s < nF) {
+                        const int r = s0 + 4 * s + k;
+                        const int odd = (sign_mode == APPROXIFER_SIGN_WORKER_INDEX ? at[s] : r) & 1;
+                        double a[R];
+#pragma unroll
+                        for (int q = 0; q < R; ++q) {
+                            a[q] = T[at[s] * TS + 16 * q + c];
+                            if (COINCIDE && own[q] >= 0) a[q] = at[s] != own[q] ? 0.0 : (odd ? -1.0 : 1.0);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const double v = static_cast<double>(y[s][e]), b = odd ? -v : v;
+#pragma unroll
+                            for (int q = 0; q < R; ++q) acc[q][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b, acc[q][e], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int j = 16 * q + 4 * t + k;
+                    if (j < K && floats > 0) {
+                        const double rd = rden[j];
+                        v4f v;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = static_cast<float>(acc[q][e][t] * rd);
+                        float *dst = og + static_cast<size_t>(j) * C + 4 * cv;
+                        if (!UNAL) {
+                            __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(dst));
+                        } else if (floats >= 4) {
+                            __builtin_nontemporal_store(static_cast<v4f_dword_aligned>(v), reinterpret_cast<v4f_dword_aligned *>(dst));
+                        } else {
+                            dst[0] = v[0];
+                            if (floats > 1) dst[1] = v[1];
+                            if (floats > 2) dst[2] = v[2];
+                        }
+                    }
+                }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------
 // fused decoder + top-1 kernel
 // ------------------------------------------------------------------------------------
 struct Best {
@@ -1461,10 +1605,10 @@ bool tiles_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
 }
 // Whether decode_matrix_kernel decodes the call (more than eight queries, up to 64 workers, more than sixteen classes).  Its
 // tile takes four waves, whatever the row's length, so it is not for many groups of short rows; times without and with it:
-//  - K > 16, where the other kernel has a wave per four queries and 4-byte accesses for rows that are only 4-byte aligned: from 96
-//    classes on (K = 32, 1170 groups of 1001 classes 241 and 96 us, 1171 of 1000 145 and 92; K = 24, 15470 of 101 259 and 206) and in
-//    calls of few tiles (K = 24, 24 classes, 217 groups 14.9 and 8.6 us; K = 17, 17 classes, 432 groups 9.9 and 10.3); fewer than 64
-//    classes in rows that are only 4-byte aligned from 25 queries or 33 survivors on (K = 21, 28 survivors, 33 classes, three
+//  - K > 16: from 96 classes on (K = 32, 1170 groups of 1001 classes 241 and 96 us, 1171 of 1000 145 and 92), up to kShortClasses against
+//    decode_short_kernel while tiles are few (100 classes: K = 21, 975 groups 17.6 there and 13.7 in decode_short_kernel, K = 21, 443 of
+//    122 13.3 and 17.9; K = 40, 6009 of 100 171 and 105), and in calls of few tiles (84 classes: K = 31, seven groups
+//    9.8 and 12.8; up to 64 even with it, K = 32, 250 of 32 10.0 and 11.1, K = 20, 36 of 20 9.1 and 8.6); fewer than 64 classes in rows that are only 4-byte aligned from 25 queries or 33 survivors on (K = 21, 28 survivors, 33 classes, three
 //    groups 8.9 and 9.3; K = 18, 40 survivors, 19 classes, two groups 12.5 and 11.2);
 //  - K = 9..16 in rows that are only 4-byte aligned: from 96 classes on (K = 16, 2341 groups of 1001 classes 101 and 74 us, 78
 //    groups 15.9 and 7.7), with K = 9..11, which leave a third of the products' rows empty, up to 4096 tiles (K = 9, 832 groups of
@@ -1479,7 +1623,7 @@ bool matrix_shape(int K, int N, int S, int64_t C, int64_t G, bool vec4) {
     if (K <= 8 || N > kWave || C <= kRowLanes) return false;
     const int64_t tiles = G * ((C + 239) / 240);
     const int survivors = S < 0 ? N : N - S;
-    if (K > 16) return C >= 96 || (tiles <= 400 && (vec4 || K > 24 || C >= 64 || survivors > 32));
+    if (K > 16) return C > kShortClasses || (C >= 96 && tiles <= 500) || (tiles <= 400 && (vec4 || K > 24 || C >= 64 || survivors > 32));
     if (!vec4 && C >= 96) {
         const SectorTiles t = sector_tiles(G, C, kTileHalo);
         return K > 11 || (t.total <= (survivors > 16 ? 4096 : 2048) && (t.width >= 4 * 38 || t.per_row == 1 || t.total <= 1536 || t.total > 2560));
@@ -1584,6 +1728,20 @@ int run_matrix(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_
                                        K <= 16 && nodes_coincide(nodes, K, N) ? 1 : 0, nodes));
 }
 
+template <int R>
+int run_short(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K, int N, int S,
+              int64_t C, bool vec4, const Nodes &nodes, int sign_mode, hipStream_t stream) {
+    const int64_t blocks = std::min<int64_t>((G + kShortWaves - 1) / kShortWaves, 1024);
+    const size_t lds = sizeof(double) * (static_cast<size_t>(N) * short_stride(R) + kShortWaves * 16 * R) +
+                       sizeof(int) * (kShortWaves * kWave + 16 * R);
+    const auto run = [&](auto *kernel) {
+        return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kShortWaves * kWave), lds, stream, d_preds,
+                                           d_mask, d_out, d_status, G, K, N, S, static_cast<int>(C), sign_mode, nodes));
+    };
+    if (nodes_coincide(nodes, K, N)) return run(vec4 ? decode_short_kernel<R, false, true> : decode_short_kernel<R, true, true>);
+    return run(vec4 ? decode_short_kernel<R, false, false> : decode_short_kernel<R, true, false>);
+}
+
 // Whether decode_top1_matrix_kernel decides the call (more than eight queries, up to 64 workers, more than sixteen classes) that
 // top1_split leaves.  Times without and with it, over 5000 calls:
 //  - K = 9..16 in rows that are only 4-byte aligned: always (0.2 to 0.96 of the time; K = 12, 6243 groups of 1001 classes 204 and 96, 206
@@ -1663,6 +1821,11 @@ int launch_decode(const float *d_preds, const uint8_t *d_mask, float *d_out, int
         if (steps <= 12) return run_matrix<12>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
         return run_matrix<16>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, nodes, sign_mode, stream);
     }
+    // what matrix_shape leaves of these, otherwise a workgroup per group with a wave for every four queries (figures at the kernel);
+    // beyond two stripes the third is mostly empty (K = 28, 2362 groups of 132 classes 46.6 and 55.4 us)
+    if (K > 16 && N <= kWave && C <= kShortClasses)
+        return K <= 32 ? run_short<2>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, vec4, nodes, sign_mode, stream)
+                       : run_short<4>(d_preds, d_mask, d_out, d_status, G, K, N, S, C, vec4, nodes, sign_mode, stream);
     const int64_t Cv = vec4 ? C / 4 : C;
     const int64_t ctiles = (Cv + kColsPerTile - 1) / kColsPerTile;
     const int64_t blocks = G * ctiles;
