@@ -305,7 +305,11 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
         if (!ok) col = 0;
     }
     const int krow = lane >> 4;                               // row offset inside a k-step
-    const float *xg = queries + static_cast<size_t>(g) * K * D + col * 4;
+    // a row's last, partial vector is loaded as the last four floats of the row and shifted down below (a launch of its own for the
+    // last columns costs its weights again: K = 40, N = 88, four rows of 73 floats 29.5 and 18.3 us)
+    const int tail = UNAL ? static_cast<int>(D & 3) : 0;
+    const bool over = tail != 0 && col == Dv - 1;
+    const float *xg = queries + static_cast<size_t>(g) * K * D + (over ? D - 4 : col * 4);
     float *og = coded + static_cast<size_t>(g) * N * D + col * 4;
 
     // ---- query rows 4s + krow, columns 4*col..+3; rows past K (KS = ceil(K / 4)) are clamped, and zeroed below ----
@@ -318,6 +322,10 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
 
     encode_mfma_weights<KS>(wA, K, N, nodes);
     __syncthreads();
+    if (UNAL && tail != 0) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) x[s] = finish_vector(x[s], over, tail);
+    }
     if (4 * (KS - 1) + krow >= K) x[KS - 1] = v4f(0.0f);      // a clamped row: its infinities count for nothing either
 
     const int mtiles = (N + 15) >> 4;
@@ -341,7 +349,14 @@ __global__ __launch_bounds__(kMfmaThreads) void encode_mfma_kernel(
                 v[1] = acc[1][r];
                 v[2] = acc[2][r];
                 v[3] = acc[3][r];
-                store_stream<4, UNAL>(og + static_cast<size_t>(i) * D, v);
+                float *row = og + static_cast<size_t>(i) * D;
+                if (!UNAL || !over) {
+                    store_stream<4, UNAL>(row, v);
+                } else {
+                    row[0] = v[0];
+                    if (tail > 1) row[1] = v[1];
+                    if (tail > 2) row[2] = v[2];
+                }
             }
         }
     }
@@ -430,7 +445,7 @@ int run_encode_mfma_shape(const float *d_queries, float *d_coded, int64_t tiles,
 template <int KS, bool UNAL>
 int run_encode_mfma(const float *d_queries, float *d_coded, int64_t G, int K, int N, int64_t D, const Nodes &nodes,
                     hipStream_t stream) {
-    const int64_t Dv = D / 4;
+    const int64_t Dv = UNAL ? (D + 3) / 4 : D / 4;                      // counts a partial last vector
     const int64_t cols_per_block = (kMfmaThreads / 64) * 16;           // vector columns per workgroup
     const int64_t chunks = (Dv + cols_per_block - 1) / cols_per_block;
     const int64_t idle = chunks * cols_per_block - Dv;                  // columns without data at the row ends
@@ -545,21 +560,21 @@ int run_encode(const float *d_queries, float *d_coded, int64_t G, int N, int64_t
     return run_encode_shape<K, VEC, true, UNAL>(d_queries, d_coded, flat, pairs, N, D, Dv, col0, nodes, stream);
 }
 
-// 128-bit columns: the matrix-core kernel or the vector kernel, by shape.
-template <int K, bool UNAL>
+// 16-byte-aligned rows: the matrix-core kernel or the vector kernel, by shape.
+template <int K>
 int run_encode_wide(const float *d_queries, float *d_coded, int64_t G, int N, int64_t D, const Nodes &nodes,
                     hipStream_t stream) {
     if constexpr (K >= kMfmaMinK) {
-        return run_encode_mfma<(K + 3) / 4, UNAL>(d_queries, d_coded, G, K, N, D, nodes, stream);
+        return run_encode_mfma<(K + 3) / 4, false>(d_queries, d_coded, G, K, N, D, nodes, stream);
     } else {
         if constexpr (K >= kMfmaWideMinK) {
             // Many more coded than plain queries (the Byzantine worker counts, N = 2 (K + A) + S): a one-wave
             // tile would keep K + N >= 3K + 4 row streams open, and the matrix-core variant, whose waves work on
             // 256-byte row segments, measures 4..14 % faster (K=8, N=24: 5.7 -> 6.2 TB/s; K=12, N=36: 5.5 -> 6.0).
             if (N >= 2 * K + 4)
-                return run_encode_mfma<(K + 3) / 4, UNAL>(d_queries, d_coded, G, K, N, D, nodes, stream);
+                return run_encode_mfma<(K + 3) / 4, false>(d_queries, d_coded, G, K, N, D, nodes, stream);
         }
-        return run_encode<K, 4, UNAL>(d_queries, d_coded, G, N, D, D / 4, 0, nodes, stream);
+        return run_encode<K, 4, false>(d_queries, d_coded, G, N, D, D / 4, 0, nodes, stream);
     }
 }
 
@@ -629,20 +644,35 @@ int run_encode_k(const float *d_queries, float *d_coded, int64_t G, int N, int64
     }
     const bool aligned16 = (reinterpret_cast<uintptr_t>(d_queries) % 16 == 0) &&
                            (reinterpret_cast<uintptr_t>(d_coded) % 16 == 0) && (D % 4 == 0);
-    if (aligned16) return run_encode_wide<K, false>(d_queries, d_coded, G, N, D, nodes, stream);
+    if (aligned16) return run_encode_wide<K>(d_queries, d_coded, G, N, D, nodes, stream);
     // rows only 4-byte aligned: 128-bit accesses on the first 4 * (D / 4) columns, 4-byte accesses on the rest;
     // short ragged rows: aligned 64-bit accesses throughout where the rows allow them, else 4-byte accesses
     const int64_t tail = D % 4;
+    if constexpr (K >= kMfmaWideMinK) {
+        // The matrix-core kernel takes a row's partial last vector along, in rows of any length.  Over 260 calls (where the rows had
+        // 4-byte accesses, or a launch of their own for the last columns): K > 16 1.0 to 2.6 times as fast (K = 40, N = 46, 7 x 151 floats
+        // 28.7 and 11.2 us; K = 23, N = 57, 15397 x 5 32.9 and 18.6; K = 37, N = 41, 16384 x 151 266 and 248), but for short rows of K < 20
+        // queries and hardly more workers in many groups (K = 17, N = 18, 1749 x 49 7.4 and 8.2); K = 9..16 with N >= 2 K + 4 0.97 to 1.7 (K =
+        // 16, N = 44, 11677 x 9 27.3 and 16.0; not many rows of 5 to 7, K = 14, N = 37, 9611 x 6 12.9 and 13.9), K = 8 in short rows 0.93
+        // to 1.07.
+        const bool scalar = tail != 0 && D <= kScalarRowsMaxD && (K == 8 || (K < 20 && 4 * N < 5 * K && G * D > 65536) ||
+                                                                   (K < kMfmaMinK && D < 8 && G > 4096));
+        if (D >= 4 && !scalar && (K >= kMfmaMinK || N >= 2 * K + 4))
+            return run_encode_mfma<(K + 3) / 4, true>(d_queries, d_coded, G, K, N, D, nodes, stream);
+    }
     if (tail != 0 && D <= kScalarRowsMaxD) {
         if (D % 2 == 0 && reinterpret_cast<uintptr_t>(d_queries) % 8 == 0 && reinterpret_cast<uintptr_t>(d_coded) % 8 == 0)
             return run_encode<K, 2, false>(d_queries, d_coded, G, N, D, D / 2, 0, nodes, stream);
         return run_encode<K, 1, false>(d_queries, d_coded, G, N, D, D, 0, nodes, stream);
     }
-    if (D >= 4) {
-        const int rc = run_encode_wide<K, true>(d_queries, d_coded, G, N, D, nodes, stream);
-        if (rc != APPROXIFER_OK || tail == 0) return rc;
+    if constexpr (K < kMfmaMinK) {
+        if (D >= 4) {
+            const int rc = run_encode<K, 4, true>(d_queries, d_coded, G, N, D, D / 4, 0, nodes, stream);
+            if (rc != APPROXIFER_OK || tail == 0) return rc;
+        }
+        return run_encode<K, 1, false>(d_queries, d_coded, G, N, D, tail, D - tail, nodes, stream);
     }
-    return run_encode<K, 1, false>(d_queries, d_coded, G, N, D, tail, D - tail, nodes, stream);
+    return APPROXIFER_ERR_LIMIT;                              // not reached: from kMfmaMinK on every row has gone one of the ways above
 }
 
 }  // namespace
