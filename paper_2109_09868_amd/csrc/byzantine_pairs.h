@@ -34,6 +34,9 @@ __device__ __forceinline__ double choose(bool first, double x, double y) {
     return first ? x : y;
 }
 __device__ __forceinline__ double pair_other(double v) { return dpp_exchange<kDppQuadXor1>(v); }
+__device__ __forceinline__ int bits_of_other(unsigned mask) {             // ones in the other lane's mask
+    return __builtin_amdgcn_update_dpp(0, static_cast<int>(__popc(mask)), kDppQuadXor1, 0xF, 0xF, true);
+}
 // v of this lane and of lane ^ DISTANCE, 16 or 32, added: the same bits in both
 template <int DISTANCE>
 __device__ __forceinline__ double rows_sum(double v) {
@@ -694,9 +697,11 @@ __device__ __forceinline__ bool locate_class_pair(const float *y, int ys, unsign
     }
 
     // ---- a_i = Q(beta_i), up to sign: lane 0 node i, lane 1 its mirror image; the A smallest vote --------------------------
-    // The three smallest so far, worker in the low six bits: equal magnitudes, and what agrees to 46 bits, in worker order.
+    // A lane keeps its magnitudes and its three smallest; with the other lane's these give the A-th smallest of all, and who is
+    // not above it votes.  All bits of a magnitude count: of equal ones alone the smaller worker index comes first.
     const unsigned answered = static_cast<unsigned>(h ? __brevll(bits) >> (64 - N) : bits);
     const unsigned mine = answered & ((1u << (h ? N / 2 : NH)) - 1u);    // bit i: this lane's node i; a middle one is lane 0's
+    double size[Tile::kNodes];
     double l0 = __builtin_inf(), l1 = __builtin_inf(), l2 = __builtin_inf();
     {
         const double side = h ? -1.0 : 1.0;
@@ -718,24 +723,45 @@ __device__ __forceinline__ bool locate_class_pair(const float *y, int ys, unsign
             v = fma(side, pair_other(v), v);
             if (i == 0) v += v;                           // the table has half of these
             if (i >= Tile::kNodes - 4 && 2 * i == N - 1) v += v;
-            v = min_magnitude(v, 1e300);                  // not a number: behind every number
+            v = min_magnitude(v, __builtin_inf());        // not a number: behind every number
             // nor does a worker that did not answer, or a row past the last node, come before any that did
             const bool there = S > 0 ? (mine & (1u << i)) != 0u : i < Tile::kNodes - 4 || (i < NH && !(h && 2 * i == N - 1));
-            const double k = __hiloint2double(there ? __double2hiint(v) : 0x7fe00000,
-                                              (__double2loint(v) & ~63) | (h ? N - 1 - i : i));
-            l2 = min_number(l2, max_number(l1, k));
-            l1 = min_number(l1, max_number(l0, k));
-            l0 = min_number(l0, k);
+            v = there ? v : __builtin_inf();
+            size[i] = v;
+            l2 = min_number(l2, max_number(l1, v));
+            l1 = min_number(l1, max_number(l0, v));
+            l0 = min_number(l0, v);
         }
     }
-    // of two ascending lists of A, the A smallest are those where own k-th < the other's (A - 1 - k)-th, from either side
     const double m0 = pair_other(l0), m1 = pair_other(l1), m2 = pair_other(l2);
-    const auto vote = [&](double k, double against) {
-        if (live && settled && k < against) atomicAdd(&votes[__double2loint(k) & 63], 1);
-    };
-    vote(l0, A == 1 ? m0 : (A == 2 ? m1 : m2));
-    if (A > 1) vote(l1, A == 2 ? m0 : m1);
-    if (A > 2) vote(l2, m0);
+    const double last = A == 1 ? min_number(l0, m0)
+                               : (A == 2 ? min_number(min_number(l1, m1), max_number(l0, m0))
+                                         : min_number(min_number(l2, m2), min_number(max_number(l0, m1), max_number(l1, m0))));
+    unsigned picks = 0u;
+#pragma unroll
+    for (int i = 0; i < Tile::kNodes; ++i) picks |= size[i] <= last ? 1u << i : 0u;
+    picks &= mine;
+    if (static_cast<int>(__popc(picks)) + bits_of_other(picks) > A) {   // of those that equal the A-th the first workers, lane 0's in ascending order
+        unsigned less = 0u;
+#pragma unroll
+        for (int i = 0; i < Tile::kNodes; ++i) less |= size[i] < last ? 1u << i : 0u;
+        less &= mine;
+        unsigned equal = picks & ~less;
+        const int ahead = bits_of_other(equal);           // both lanes are here: the sum above is the same in either
+        int room = A - static_cast<int>(__popc(less)) - bits_of_other(less) - (h ? ahead : 0);
+        picks = less;
+        for (; room > 0 && equal != 0u; --room) {
+            const unsigned next = h ? 1u << (31 - __builtin_clz(equal)) : equal & -equal;
+            picks |= next;
+            equal &= ~next;
+        }
+    }
+    if (live && settled) {
+        for (; picks != 0u; picks &= picks - 1u) {
+            const int i = __builtin_ctz(picks);
+            atomicAdd(&votes[h ? N - 1 - i : i], 1);
+        }
+    }
     return settled;
 }
 
