@@ -135,13 +135,18 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
 // triangular factor (B is never squared):
 //     u = G^-1 D^T D p,   B^T B q' = D^T D q - K u,   p' = u - G^-1 K q'.
 // G^-1 is in closed form (diagonal and a rank-one term per parity, less the missing workers' rows), K's entries are sums of two
-// moments as the system's are.  Start vector, settling rule, extrapolation of a slowly decaying mode and the floor under
-// vanishing pivots are those of homogeneous_q, which is the fallback for a class that has not settled after kPairRounds.
+// moments as the system's are.  Start vector, settling rule and the floor under vanishing pivots are those of homogeneous_q, which
+// is the fallback for a class that has not settled after kPairRounds.
 // Against the monomial QR (numpy, both): largest error of Q(x_i) relative to their maximum 1.6e-10 and 3e-8 at K = 12, A = 2,
 // 28 workers, 3e-12 and 2e-11 at K = 8, A = 2, 20 of 24; the same number of rounds, two to four on rational data.
 //   a: the system's columns (destroyed), k[s]: half the moment sum_i y_i T_{2s+h}(beta_i), square: sum_i y_i^2
 //   c: coefficients of T_{2s+h} in Q.  Returns whether the class settled: the same in both lanes
 constexpr int kPairRounds = 64;
+// Rounds with a Ritz step, further and further apart: done often it keeps stirring up the third mode, and classes whose smallest
+// singular values are within 5 % of each other never settle.  Of 550000 classes (six shapes; linear, ReLU and softmax answers and
+// noise, liars or none; the iteration in numpy) all settle; every sixth round from the fifth on leaves 3 of them, every other
+// round 1 of 8000.
+constexpr unsigned long long kRitzRounds = 1ull << 1 | 1ull << 3 | 1ull << 5 | 1ull << 11 | 1ull << 19 | 1ull << 29 | 1ull << 41 | 1ull << 55;
 
 // T_{2s+h} = sum_k c[h][k][s] x^{2k+h}
 struct ChebyshevToMonomial {
@@ -348,10 +353,11 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
             mq[s] *= unit;
         }
     }
-    double dd_prev = __builtin_inf(), quotient = 0.0;
+    double dd_prev = __builtin_inf(), ratio_before = dd_prev, quotient = 0.0;
     int since_jump = 0;
     bool settled = false;
-    for (int round = 0; round < kPairRounds; ++round) {
+    unsigned long long ritz = kRitzRounds;
+    for (int round = 0; round < kPairRounds; ++round, ritz >>= 1) {
         // read again in every round: carried along it would take the registers that the rest of the round needs
         int offset = 0;
         asm volatile("" : "+v"(offset));
@@ -411,32 +417,35 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
         dd_prev = dd;
         ++since_jump;
         double old = 0.0, next = 1.0;                     // what of z and z' the next round starts from
-        if (round % 2 == 0) {
+        if (ritz & 2ull) {                                // in the next round
             quotient = round == 0 || dd > 1e-12 ? unit * fma(-0.5, dd, 1.0) : 0.0;   // z'^T A z', A z' = unit z
-        } else if (quotient > 0.0 && !settled && dd > (round == 1 ? 1e-18 : 1e-12) && dd < 1.0) {
-            // The best vector of span(z, z') in every other round while the steps are large: where two modes are left the slow one
-            // is gone with it.  The slowest of 20480 rational classes, in each of eight sets, needs 4 to 8 rounds with it at K = 8,
-            // A = 2, 20 of 24 workers and 5 to 8 at K = 9, A = 3, 24 workers; with it in round 1 alone 4 to 15 and 5 to 13.
+        } else if ((ritz & 1ull) && quotient > 0.0 && !settled && dd > (round == 1 ? 1e-18 : 1e-12) && dd < 1.0) {
+            // The best vector of span(z, z') while the steps are large: where two modes are left the slow one is gone with it, also
+            // where the iterate still lies by the wrong one of them (half < 0).
             const double g = fma(-0.5, dd, 1.0), across2 = dd * fma(-0.25, dd, 1.0), across = sqrt_normal(across2);
             const double r = rcp_normal(across), mixed = fma(-g, quotient, unit) * r, other = g * fma(g, quotient, -unit) * r * r;
-            const double half = 0.5 * (other - quotient);
-            const double tangent = -mixed * rcp_normal(half + sqrt_normal(fma(half, half, mixed * mixed))), tau = tangent * r;
-            if (half > 0.0 && tau > 0.0) {
-                const double norm = rsqrt_normal(fma(tangent, tangent, 1.0));
-                old = fma(-tau, g, 1.0) * norm;
-                next = tau * norm;
+            const double half = 0.5 * (other - quotient), root = fabs(half) + sqrt_normal(fma(half, half, mixed * mixed));
+            const double norm = rsqrt_normal(fma(root, root, mixed * mixed));          // of (root, -mixed) or (-mixed, root)
+            const double along = (half > 0.0 ? root : -mixed) * norm, tau = (half > 0.0 ? -mixed : root) * norm * r;
+            if (tau > 0.0) {
+                old = fma(-tau, g, along);
+                next = tau;
                 if (!(next > 0.95 && next < 1.05)) dd_prev = __builtin_inf();
             }
         }
-        if (round > 1 && !settled && since_jump >= 3 && dd <= 1e-12 && dd_before < __builtin_inf()) {
-            const double r = sqrt_normal(dd * rcp_normal(dd_before));
-            if (r > 0.05 && r < 0.97) {
-                old = -r * rcp_normal(1.0 - r);
+        // A slow decay is followed to its limit once it is steady: two ratios of successive steps that differ by a tenth of their
+        // distance from 1 (a third mode that still decays makes them differ, and the jump would bring it back).
+        double ratio = __builtin_inf();
+        if (round > 1 && !settled && dd <= 1e-10 && dd_before < __builtin_inf()) {
+            ratio = sqrt_normal(dd * rcp_normal(dd_before));
+            if (since_jump >= 3 && ratio > 0.05 && ratio < 0.9995 && fabs(ratio - ratio_before) <= 0.1 * (1.0 - ratio)) {
+                old = -ratio * rcp_normal(1.0 - ratio);
                 next = 1.0 - old;
                 since_jump = 0;
                 dd_prev = __builtin_inf();
             }
         }
+        ratio_before = ratio;
 #pragma unroll
         for (int s = 0; s < MH; ++s) {
             mp[s] = fma(old, mp[s], next * unit * np[s]);
