@@ -260,11 +260,12 @@ __device__ __forceinline__ void factor_class_system(double *mat, int LD, int n, 
 //   scratch  this wave's LDS: per class  mat[n][W2] | coef[M] | key[n]
 // Lane (cl, j) = (lane / W2, lane % W2) works on class c0 + cl; lanes beyond cpw classes idle.
 // HOMOG: Algorithm 1's fit instead (Q_0 free).  The last column, y, then is one more column of the homogeneous
-// system [V | -y x^1 .. -y x^(M-1) | y] whose coefficient is -Q_0; (P, Q) is its null vector of unit length.
+// system [V | -y x^1 .. -y x^(M-1) | y] whose coefficient is -Q_0; (P, Q) is its null vector of unit length.  jacobi_only: see
+// homogeneous_q.
 template <bool HOMOG>
 __device__ __forceinline__ void locate_classes_wave(const float *__restrict__ pg, int64_t C, int64_t c0, int cpw,
                                                     const int *avail, const double *xs, int n, int M, int A,
-                                                    double *scratch, int *votes) {
+                                                    double *scratch, int *votes, bool jacobi_only = false) {
     const int lane = lane_id();
     const int W2 = 2 * M;
     const int cols = W2 - 1;                 // unknowns P_0..P_{M-1}, Q_1..Q_{M-1}; column `cols` is the rhs
@@ -283,7 +284,7 @@ __device__ __forceinline__ void locate_classes_wave(const float *__restrict__ pg
 
     if (HOMOG) {
         // ---- the null vector, then a_r = Q(x_r): Q_k = coef[k-1] for k >= 1, Q_0 = -coef[M-1] ----------------------
-        homogeneous_q(mat, LD, coef, key, W2, M, j, live);
+        homogeneous_q(mat, LD, coef, key, W2, M, j, live, jacobi_only);
         if (live) {
             for (int r = j; r < n; r += W2) {
                 const double x = xs[r];
