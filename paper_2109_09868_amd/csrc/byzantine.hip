@@ -1222,16 +1222,17 @@ __global__ void clear_workspace_kernel(int32_t *__restrict__ workspace, int64_t 
     if (i < words) workspace[i] = 0;
 }
 
-// Decodes groups whose liars have been located (d_adv): a workgroup to 64 vector columns of a group.  The locating workgroups
-// leave this to a launch of its own where a group has many classes: one of them decoding all of a group, K = 8, A = 3, 26
-// workers, 55 groups of 787 classes took 116 us, 37 this way.
+// Locates the liars of groups by the votes of their classes (`votes`: N counters of N + 1 words a group, from the launch before) and
+// decodes: a workgroup to 64 vector columns of a group.  A launch of its own where a group has many classes: one workgroup decoding
+// all of a group, K = 8, A = 3, 26 workers, 55 groups of 787 classes took 116 us, 37 this way.
 // dynamic LDS: double WdT[nF KP] | alpha_s[K] | beta_s[N] | int F[N]
 size_t located_lds_bytes(int K, int N, int nF) {
     return sizeof(double) * (static_cast<size_t>(nF) * ((K + 3) & ~3) + K + N) + sizeof(int) * N;
 }
 template <int VEC>
 __global__ __launch_bounds__(kPairThreads) void decode_located_kernel(const float *__restrict__ preds, const uint8_t *__restrict__ mask,
-                                                                      float *__restrict__ out, const int32_t *__restrict__ adv, int K,
+                                                                      const int32_t *__restrict__ votes, float *__restrict__ out,
+                                                                      int32_t *__restrict__ adv, int32_t *__restrict__ status, int K,
                                                                       int N, int S, int A, int64_t C, int64_t Cv, int64_t tiles,
                                                                       int sign_mode, const Nodes nodes) {
     extern __shared__ __align__(16) double lds_d[];
@@ -1239,13 +1240,15 @@ __global__ __launch_bounds__(kPairThreads) void decode_located_kernel(const floa
     double *WdT = lds_d, *alpha_s = WdT + nF * KP, *beta_s = alpha_s + K;
     int *F = reinterpret_cast<int *>(beta_s + N);
     const int64_t g = blockIdx.x / tiles, tile = blockIdx.x - g * tiles;
-    bool left = lane < N && mask[g * N + lane] != 0;                      // N < 64
+    const unsigned long long there = __ballot(lane < N && mask[g * N + lane] != 0);       // N < 64
+    const unsigned long long drop = most_voted(votes + g * (N + 1), N, A), left = there & ~drop, below = (1ull << lane) - 1ull;
     stage_nodes(nodes, K, N, alpha_s, beta_s);
-    if (static_cast<int>(__popcll(__ballot(left))) != N - S) return;      // a bad group: d_adv holds nothing
+    const bool good = static_cast<int>(__popcll(there)) == N - S;
+    if (tile == 0 && threadIdx.x == 0 && status != nullptr) status[g] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+    if (!good) return;
+    if (tile == 0 && wave_id() == 0 && ((drop >> lane) & 1ull)) adv[g * A + __popcll(drop & below)] = lane;
     for (int e = threadIdx.x; e < nF * KP; e += kPairThreads) WdT[e] = 0.0;
-    for (int k = 0; k < A; ++k) left = left && adv[g * A + k] != lane;
-    const unsigned long long who = __ballot(left);
-    if (wave_id() == 0 && left) F[__popcll(who & ((1ull << lane) - 1ull))] = lane;
+    if (wave_id() == 0 && ((left >> lane) & 1ull)) F[__popcll(left & below)] = lane;
     __syncthreads();
     decoder_weights(alpha_s, beta_s, F, nF, K, KP, sign_mode, WdT);
     __syncthreads();
@@ -1487,12 +1490,14 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
     call.lift1 = pair_lift(N, N - K - A, 1);
     call.gpw = 1;
     call.parts = call.splits = 1;
+    call.vec4 = vec4;
+    const int64_t Cv = vec4 ? C / 4 : C, tiles = (Cv + kColsPerTile - 1) / kColsPerTile;
     if (C > kPairClasses) {
-        // more classes than a workgroup has pairs of lanes: a workgroup to every 128 of them, if they can meet
+        // more classes than a workgroup has pairs of lanes: a workgroup to every 128 of them, if there is a place for their votes
         call.parts = static_cast<int>((C + kPairClasses - 1) / kPairClasses);
         call.splits = votes != nullptr ? call.parts : 1;
-        if (G * call.splits > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
         if (call.splits > 1) {
+            if (G * std::max<int64_t>(call.splits, tiles) > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
             const int rc = clear_workspace(votes, G, N, stream);
             if (rc != APPROXIFER_OK) return rc;
         }
@@ -1515,12 +1520,10 @@ int run_pairs_shape(const PairShape &shape, const float *d_preds, const uint8_t 
         }
     };
     const int rc = run();
-    if (rc != APPROXIFER_OK || call.parts == 1) return rc;
-    const int64_t Cv = vec4 ? C / 4 : C, tiles = (Cv + kColsPerTile - 1) / kColsPerTile;
-    if (G * tiles > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
+    if (rc != APPROXIFER_OK || call.splits == 1) return rc;
     return launch_status(launch_kernel(vec4 ? decode_located_kernel<4> : decode_located_kernel<1>, dim3(static_cast<unsigned>(G * tiles)),
-                                       dim3(kPairThreads), located_lds_bytes(K, N, N - S - A), stream, d_preds, d_mask, d_out, d_adv, K,
-                                       N, S, A, C, Cv, tiles, sign_mode, nodes));
+                                       dim3(kPairThreads), located_lds_bytes(K, N, N - S - A), stream, d_preds, d_mask, votes, d_out,
+                                       d_adv, d_status, K, N, S, A, C, Cv, tiles, sign_mode, nodes));
 }
 
 template <int NB, int RM, int NW, bool SHARED, bool HOMOG>

@@ -19,11 +19,12 @@ struct PairCall {
     const float *preds;
     const uint8_t *mask;
     float *out;
-    int32_t *adv, *status, *votes;
+    int32_t *adv, *status, *votes;   // votes: the workspace, splits > 1
     int64_t G, C;
     int K, N, S, A, sign_mode;
     int gpw;                 // groups of a workgroup (whole groups), or
     int parts, splits;       // parts > 1: parts of a group's classes, each with a workgroup of its own (splits = parts) or one (1)
+    bool vec4;               // as finish_group; parts > 1
     double lift0, lift1;     // see locate_class_pair
 };
 
@@ -779,14 +780,34 @@ __device__ __forceinline__ bool locate_class_pair(const float *y, int ys, unsign
     return settled;
 }
 
+// The A most voted workers (equal counts: smaller index first), a lane to a worker (N < 64): bit w is worker w.  By a whole wave.
+__device__ __forceinline__ unsigned long long most_voted(const int *votes, int N, int A) {
+    const int lane = lane_id();
+    int key = lane < N ? (votes[lane] << 6) | (kWave - 1 - lane) : -1;
+    unsigned long long drop = 0ull;
+    for (int pick = 0; pick < A; ++pick) {
+        int m = key;
+        m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor1, 0xF, 0xF, true));
+        m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor2, 0xF, 0xF, true));
+        m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowHalfMirror, 0xF, 0xF, true));
+        m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowMirror, 0xF, 0xF, true));
+        m = max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
+                max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
+        drop |= 1ull << (kWave - 1 - (m & (kWave - 1)));
+        key = key == m ? -1 : key;
+    }
+    return drop;
+}
+
 // A workgroup takes `gpw` whole groups (C <= 128), a class to a pair of lanes, and decodes them, a row
 // of sixteen lanes to sixteen classes of a group:
 //     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i),     T[j][i] = 1 / (alpha_j - beta_i),
 // lane j of the row holding T[j][i], which reaches the classes inside the multiply-add and sums the denominator of query j;
 // s_i is the sign of worker i, 0 if it does not count.  A query node that is a worker's node has T = 0 there and takes that
-// worker's row.  More classes: a workgroup to every 128 of a group's (kPart), or one that takes them all in turn (kParts: the
-// workgroups cannot meet without a workspace; the loop costs 50 registers, and with them the second wave of a SIMD); the
-// last to finish writes the located workers, and decode_located_kernel decodes.  No row of a worker that did not answer is read.
+// worker's row.  More classes: a workgroup to every 128 of a group's (kPart) that leaves its votes in the workspace, from where
+// decode_located_kernel goes on: that launch alone writes outputs, so that one which fails leaves all of them as they were.  Without a
+// workspace one workgroup takes all classes in turn (kParts: the loop costs 50 registers, and with them the second wave of a SIMD) and
+// decodes its group itself.  No row of a worker that did not answer is read.
 // dynamic LDS: double tab | beta_s[N] | whole groups: T[N][16] | sgn[16][N]
 //              | float Ysh[groups][N][classes] | uint64 bits[gpw] | int votes[gpw][64] | hit[16]
 //              | HOMOG: double mono[2][MT / 2][MT / 2] | scratch[4][pair_scratch_doubles]
@@ -855,7 +876,7 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
             const bool good = n == N - S;
             if (lane == 0) {
                 bits[q] = good ? m : 0ull;
-                if (part0 == 0 && a.status != nullptr) a.status[g0 + q] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
+                if ((whole || a.splits == 1) && a.status != nullptr) a.status[g0 + q] = good ? APPROXIFER_GROUP_OK : APPROXIFER_GROUP_BAD_MASK;
             }
         }
     }
@@ -950,23 +971,28 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
     __syncthreads();
 
     if constexpr (!whole) {
-        if (a.splits > 1 && !pool_votes_last_arrival(a.votes + g0 * (N + 1), votes, N, a.splits, hit)) return;
-        if (wv != 0) return;
-        // as below, a lane to a worker
-        int key = lane < N ? (votes[lane] << 6) | (kWave - 1 - lane) : -1;
-        unsigned long long drop = 0ull;
-        for (int pick = 0; pick < A; ++pick) {
-            int m = key;
-            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor1, 0xF, 0xF, true));
-            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppQuadXor2, 0xF, 0xF, true));
-            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowHalfMirror, 0xF, 0xF, true));
-            m = max(m, __builtin_amdgcn_update_dpp(0, m, kDppRowMirror, 0xF, 0xF, true));
-            m = max(max(__builtin_amdgcn_readlane(m, 0), __builtin_amdgcn_readlane(m, 16)),
-                    max(__builtin_amdgcn_readlane(m, 32), __builtin_amdgcn_readlane(m, 48)));
-            drop |= 1ull << (kWave - 1 - (m & (kWave - 1)));
-            key = key == m ? -1 : key;
+        if (MODE == kPart || a.splits > 1) {              // the words are read by the next launch
+            if (tid < N && votes[tid] != 0)
+                __hip_atomic_fetch_add(&a.votes[g0 * (N + 1) + tid], votes[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
         }
-        if ((drop >> lane) & 1ull) a.adv[g0 * A + __popcll(drop & ((1ull << lane) - 1ull))] = lane;
+        if constexpr (MODE == kParts) {
+            const int KP = round_up4(K), nF = N - S - A;
+            double *WdT = reinterpret_cast<double *>(Ysh), *alpha_s = WdT + nF * KP;      // located_lds_bytes <= the tile's N x 128 floats
+            int *F = reinterpret_cast<int *>(alpha_s + K);
+            const unsigned long long drop = most_voted(votes, N, A), left = bits[0] & ~drop, below = (1ull << lane) - 1ull;
+            if (wv == 0 && ((drop >> lane) & 1ull)) a.adv[g0 * A + __popcll(drop & below)] = lane;
+            if (wv == 0 && ((left >> lane) & 1ull)) F[__popcll(left & below)] = lane;
+            if (tid < K) alpha_s[tid] = nodes.alpha[tid];
+            for (int e = tid; e < nF * KP; e += kPairThreads) WdT[e] = 0.0;
+            __syncthreads();
+            decoder_weights(alpha_s, beta_s, F, nF, K, KP, a.sign_mode, WdT);
+            __syncthreads();
+            const float *pg = a.preds + static_cast<size_t>(g0) * N * a.C;
+            float *og = a.out + static_cast<size_t>(g0) * K * a.C;
+            if (a.vec4) contract_group<4>(pg, og, F, nF, K, KP, a.C, a.C / 4, WdT);
+            else contract_group<1>(pg, og, F, nF, K, KP, a.C, a.C, WdT);
+        }
         return;
     } else {
 
