@@ -448,6 +448,10 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
             }
         }
         ratio_before = ratio;
+        if (settled) {                                    // it stays: how often the wave's other classes still go round is not to show
+            old = 1.0;
+            next = 0.0;
+        }
 #pragma unroll
         for (int s = 0; s < MH; ++s) {
             mp[s] = fma(old, mp[s], next * unit * np[s]);
