@@ -28,6 +28,13 @@ struct PairCall {
     double lift0, lift1;     // see locate_class_pair
 };
 
+// A column whose square is below this part of the largest before it (Algorithm 1: of sum y^2) is rounding: it depends on the ones before it,
+// as most do where only liars answer anything but zero or a constant.  The nodes are rational angles, so that such a column can also be
+// zero to the last bit, or a rounding of roundings, and may not serve as a pivot next to others that are merely rounded.  K = 6, A = 1, 16
+// workers, one liar's answers alone not zero: found in 0.79 of the classes without this, in all with it.  Liars' answers 1e14 times the others'
+// are still found (both in numpy); honest float32 data leave nothing of use below 1e-14 of a column.
+constexpr double kRoundingPart = 1e-28;
+
 // x or y by a condition, as values: the compiler otherwise turns a choice between neighbouring elements of an array into
 // one element at an address of its own, and keeps the array in memory for it.
 __device__ __forceinline__ double choose(bool first, double x, double y) {
@@ -136,8 +143,9 @@ __device__ __forceinline__ void pair_table(double *tab, int N, const double *bet
 // triangular factor (B is never squared):
 //     u = G^-1 D^T D p,   B^T B q' = D^T D q - K u,   p' = u - G^-1 K q'.
 // G^-1 is in closed form (diagonal and a rank-one term per parity, less the missing workers' rows), K's entries are sums of two
-// moments as the system's are.  Start vector, settling rule and the floor under vanishing pivots are those of homogeneous_q, which
-// is the fallback for a class that has not settled after kPairRounds.
+// moments as the system's are.  Start vector and settling rule are those of homogeneous_q, which is the fallback for a class that has not
+// settled after kPairRounds; pivots of columns that depend on others are all raised to one floor, so that the null vector is a mixture of
+// such columns (a single one has zeros at nodes of its own).
 // Against the monomial QR (numpy, both): largest error of Q(x_i) relative to their maximum 1.6e-10 and 3e-8 at K = 12, A = 2,
 // 28 workers, 3e-12 and 2e-11 at K = 8, A = 2, 20 of 24; the same number of rounds, two to four on rational data.
 //   a: the system's columns (destroyed), k[s]: half the moment sum_i y_i T_{2s+h}(beta_i), square: sum_i y_i^2
@@ -176,7 +184,7 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
                                                  double (&c)[MT / 2]) {
     constexpr int MH = MT / 2, kRow = 2 * PairTile<MT, TQ, S>::kLamPad;
     // ---- elimination, all columns in their order: nf as for Algorithm 2, rs[s] = 1 / pivot^2 of column 2s + h ---------------
-    const double floor = 1e-48 * square;
+    const double floor = kRoundingPart * square;
     const bool fits = square > 0.0 && square < __builtin_inf();
     double nf[MT][MH], rs[MH], even = 0.0;
 #pragma unroll
@@ -187,12 +195,13 @@ __device__ __forceinline__ bool null_vector_pair(double (&a)[MT][TQ], const doub
 #pragma unroll
             for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
             sig = pair_sum(sig);
-            r = rcp_normal(sig > floor ? sig : floor);
+            r = rcp_normal(sig > floor ? sig : floor);    // the pivot; nothing is taken out along a column of rounding
+            const double share = sig > floor ? r : 0.0;
             const auto take_out = [&](double (&to)[TQ]) {
                 double d = a[j][0] * to[0];
 #pragma unroll
                 for (int t = 1; t < TQ; ++t) d = fma(a[j][t], to[t], d);
-                const double f = -pair_sum(d) * r;
+                const double f = -pair_sum(d) * share;
 #pragma unroll
                 for (int t = 0; t < TQ; ++t) to[t] = fma(f, a[j][t], to[t]);
                 return f;
@@ -663,14 +672,16 @@ __device__ __forceinline__ bool locate_class_pair(const float *y, int ys, unsign
         settled = null_vector_pair<MT, TQ, S>(a, k, square, own, mono, absent, N, M, h, live, c);
     } else {
         // ---- elimination: nf[j][e / 2] = minus the share of column j in column e, lane e % 2 keeping it ------------------------
-        double nf[MT][MH];
+        double nf[MT][MH], most = 0.0;                        // the largest sig so far
     #pragma unroll
         for (int j = 1; j < MT; ++j) {
             if (j < M) {
                 double sig = a[j][0] * a[j][0];
     #pragma unroll
                 for (int t = 1; t < TQ; ++t) sig = fma(a[j][t], a[j][t], sig);
-                const double rs = rcp_normal(pair_sum(sig));
+                sig = pair_sum(sig);
+                most = max_number(most, sig);
+                const double rs = sig > kRoundingPart * most ? rcp_normal(sig) : 0.0;      // a column of rounding: coefficient zero
                 const auto take_out = [&](double (&c)[TQ]) {
                     double d = a[j][0] * c[0];
     #pragma unroll
