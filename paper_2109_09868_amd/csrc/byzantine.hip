@@ -1439,24 +1439,20 @@ bool chebyshev_workers(const Nodes &nodes, int N) {
 struct PairShape {
     int mt, tq;                                            // mt = 0: not for decode_byzantine_pairs_kernel
 };
-PairShape pair_shape(int64_t G, int K, int N, int S, int A, int64_t C, bool homogeneous) {
+PairShape pair_shape(int K, int N, int S, int A, int64_t C, bool homogeneous) {
     const int M = K + A;
-    // Algorithm 1 adds rounds of inverse iteration, serial in the wave that has the slowest class, and the moments of a second
-    // half: wide tiles leave their registers for scratch, and A = 3 draws longer tails of rounds, which at K + A = 15 do not settle
-    // in as many classes.  The former kernels' time over this one's in 1600 drawn calls: K + A <= 10 1.1 to 7, mean 1.5;
-    // K + A = 11 to 14 with S <= 2 and A <= 2 0.94 (S = 2 at 13) to 5.5, mean 1.5; S = 3, 4 from K + A = 11 to 13, up to 2000
-    // classes 0.83 to 1.2 (S = 4), beyond 1.06 to 3, at 14 at most 1.0; A = 3 up to 12 0.97 to 3.8, mean 1.6, at 13 with S <= 1 0.96
-    // to 1.8 and with S = 2 down to 0.76, at 14 from 0.85 (0.52 with S = 4); K + A = 15 0.22 to 2.3, mean 0.6.
-    if (homogeneous && (M == 15 || (A == 3 && (M == 14 || (M == 13 && S > 1))) || (S > 2 && M == 14) ||
-                        (G * C <= 2000 && ((S > 2 && M > 10) || (S == 2 && M == 13)))))
-        return {0, 0};
-    // A call of few classes is the chain of one wave, which the missing workers, a column that an odd M leaves unused and
-    // registers beyond 256 lengthen most: up to 4000 classes in all the packed kernel, which gives a group several waves, is the
-    // faster one at the far sizes (K = 11, A = 2, 28 of 32 workers, ten classes, 1 / 250 / 500 groups 17.5 / 18.5 / 21.0 us and
-    // here 19.0 / 19.7 / 20.0; K = 12, A = 3, 32 of 36, 20.8 / 22.2 / 26.7 and 24.0 / 25.1 / 25.1; K = 8, A = 1, 20 of 24, 211 groups
-    // 12.6 and 13.4; K = 12, A = 2, 28 of 31, 17.1 / 18.1 / 20.5 and 16.6 / 17.6 / 17.7).
-    const int most = M == 15 ? 1 : (M >= 13 ? 2 : (M >= 9 && M % 2 == 1 ? 3 : kPairMaxMissing));
-    if (!homogeneous && S > most && C < kClsLanes && G * C <= 4000) return {0, 0};
+    // By the shape alone, never by the number of groups: the kernels round differently, and where fewer workers lie than A the
+    // last bits decide who else goes, so that a group must not change kernels with the size of its call.  Where a line costs
+    // small calls something the large ones decide: the chain of one wave is longer here than in the packed kernel, which gives a
+    // group several waves.  Former kernels and this one, ten classes, 1 / 200 / 600 / 2000 groups, in us.  Algorithm 2, the far sizes:
+    // K = 12, A = 3, 32 of 36 workers 23.4 / 24.0 / 33.9 / 75.3 and 27.2 / 27.7 / 27.5 / 30.1; K = 11, A = 2, 28 of 32 20.1 / 20.6 / 25.5 /
+    // 46.3 and 21.9 / 22.3 / 22.3 / 24.4; K = 8, A = 1, 20 of 24 14.5 / 15.1 / 17.8 / 23.2 and 15.3 / 15.6 / 15.5 / 16.6.
+    // Algorithm 1 adds rounds of inverse iteration, serial in the wave that has the slowest class: K = 10, A = 2, 24 of 28, a linear
+    // model's answers 27.7 / 32.4 / 41.4 / 78.5 and 27.4 / 30.3 / 32.5 / 37.5, softmax answers 37 / 61 / 79 / 570 and 43 / 66 / 66 / 76; K = 11,
+    // A = 2, 26 of 28, softmax 38 / 68 / 72 / 641 and 60 / 82 / 82 / 85.  It does not take wide tiles that leave their registers for scratch
+    // and where A = 3 draws longer tails of rounds (the former kernels' time over this one's in 1600 drawn calls: A = 3 at K + A = 13
+    // with S = 2 down to 0.76, at 14 from 0.85, 0.52 with S = 4; S > 2 at 14 at most 1.0; K + A = 15 0.22 to 2.3, mean 0.6).
+    if (homogeneous && (M == 15 || (A == 3 && (M == 14 || (M == 13 && S > 1))) || (S > 2 && M == 14))) return {0, 0};
     if (S < 0 || S > kPairMaxMissing || M > 15 || A > kPairMaxAdversaries || C > (1 << 24)) return {0, 0};
     const int mt = std::max(4, (M + 1) & ~1), tq = std::max(mt / 2, (N - S - M + 1) / 2);
     if (tq > mt / 2 + 1 || 2 * tq - (N - S - M) > 1) return {0, 0};      // the latter: K = A = 1
@@ -1689,7 +1685,7 @@ int launch_decode_byzantine(const float *d_preds, const uint8_t *d_mask, float *
     const int64_t Cv = vec4 ? C / 4 : C;
     if (G > 0x7fffffffLL) return APPROXIFER_ERR_LIMIT;
 
-    const PairShape pair = pair_shape(G, K, N, S, A, C, homogeneous);
+    const PairShape pair = pair_shape(K, N, S, A, C, homogeneous);
     if (pair.mt != 0 && chebyshev_workers(nodes, N)) {
         const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, C > kPairClasses ? votes_bytes(G, N) : 0);
         return run_pairs_shape(pair, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, A, C, vec4, nodes, sign_mode, homogeneous,
