@@ -2,6 +2,8 @@
 // lanes to a class.
 #pragma once
 
+#include <type_traits>
+
 #include "byzantine_general.h"
 #include "rows.h"
 
@@ -1066,54 +1068,64 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
             if (N > 32 && l + 32 < N) sign(l, left_high, __popc(left), l + 32);
             __builtin_amdgcn_wave_barrier();
             const float *y = Ysh + q * N * Cs + (c < Cs ? c : 0);
-            double acc[MT - 1], den = 0.0;                // K < M <= MT
+            // Four sums, over the workers 4 m + r of each r, added as (0 + 1) + (2 + 3) whichever rows of lanes have taken them: how many
+            // groups lie in a workgroup is not to show in a group's bits.
+            double acc[MT - 1], den;                      // K < M <= MT
+            const auto contract = [&](auto rows) {        // 1, 2 or 4 rows to a unit, each with 4, 2 or 1 of the sums
+                constexpr int kRows = decltype(rows)::value, kSums = 4 / kRows, kAhead = 4;
+                double part[kSums][MT - 1], dens[kSums];
 #pragma unroll
-            for (int j = 0; j < MT - 1; ++j) acc[j] = 0.0;
-            const double *sp = sg + sub, *tp = T + sub * 16 + l;
-            const float *yp = y + sub * Cs;
-            constexpr int kAhead = 4;
-            const int stride = 1 << share, ystride = Cs << share;
-            const auto block = [&](int room) {            // the next four workers of this row, `room` of them and more there
-                double s[kAhead], ti[kAhead];
-                float yi[kAhead];
+                for (int r = 0; r < kSums; ++r) {
+                    dens[r] = 0.0;
 #pragma unroll
-                for (int b = 0; b < kAhead; ++b) {
-                    const int at = b < room ? b : 0;
-                    s[b] = b < room ? sp[at * stride] : 0.0;
-                    ti[b] = tp[at * 16 * stride];
-                    yi[b] = yp[at * ystride];
+                    for (int j = 0; j < MT - 1; ++j) part[r][j] = 0.0;
                 }
+                const double *sp = sg + sub, *tp = T + sub * 16 + l;
+                const float *yp = y + sub * Cs;
+                const int ystride = Cs * kRows;
+                const auto block = [&](int room) {        // the next four workers of this row, `room` of them and more there
+                    double s[kAhead], ti[kAhead];
+                    float yi[kAhead];
 #pragma unroll
-                for (int b = 0; b < kAhead; ++b) {
-                    const double v = s[b] * static_cast<double>(s[b] != 0.0 ? yi[b] : 0.0f);   // who is out may hold anything
-                    row_outer<0, 0, MT - 1>(acc, ti[b], v);
-                    den = fma(ti[b], s[b], den);
+                    for (int b = 0; b < kAhead; ++b) {
+                        const int at = b < room ? b : 0;
+                        s[b] = b < room ? sp[at * kRows] : 0.0;
+                        ti[b] = tp[at * 16 * kRows];
+                        yi[b] = yp[at * ystride];
+                    }
+#pragma unroll
+                    for (int b = 0; b < kAhead; ++b) {
+                        const double v = s[b] * static_cast<double>(s[b] != 0.0 ? yi[b] : 0.0f);   // who is out may hold anything
+                        row_outer<0, 0, MT - 1>(part[b % kSums], ti[b], v);
+                        dens[b % kSums] = fma(ti[b], s[b], dens[b % kSums]);
+                    }
+                    sp += kAhead * kRows;
+                    tp += kAhead * 16 * kRows;
+                    yp += kAhead * ystride;
+                };
+                const int full = N / (kRows * kAhead);    // blocks that every row of the unit has whole
+                for (int b = 0; b < full; ++b) block(kAhead);
+                for (int i = sub + full * kAhead * kRows; i - sub < N; i += kAhead * kRows) {
+                    const int room = (N - i + kRows - 1) / kRows;           // none, for the last rows: 0
+                    if (room <= 0) {
+                        sp = sg;
+                        tp = T + l;
+                        yp = y;
+                    }
+                    block(room);
                 }
-                sp += kAhead * stride;
-                tp += kAhead * 16 * stride;
-                yp += kAhead * ystride;
+                const auto total = [&](auto of) {
+                    if constexpr (kRows == 1) return (of(0) + of(1)) + (of(2) + of(3));
+                    else if constexpr (kRows == 2) return rows_sum<16>(of(0)) + rows_sum<16>(of(1));
+                    else return rows_sum<32>(rows_sum<16>(of(0)));
+                };
+                den = total([&](int r) { return dens[r]; });
+#pragma unroll
+                for (int j = 0; j < MT - 1; ++j) acc[j] = total([&](int r) { return part[r][j]; });
             };
-            const int full = (N >> share) / kAhead;       // blocks that every row of the unit has whole
-            for (int b = 0; b < full; ++b) block(kAhead);
-            for (int i = sub + full * kAhead * stride; i - sub < N; i += kAhead * stride) {
-                const int room = (N - i + stride - 1) >> share;          // none, for the last rows: 0
-                if (room <= 0) {
-                    sp = sg;
-                    tp = T + l;
-                    yp = y;
-                }
-                block(room);
-            }
-            if (share > 0) {
-                den = rows_sum<16>(den);
-#pragma unroll
-                for (int j = 0; j < MT - 1; ++j) acc[j] = rows_sum<16>(acc[j]);
-            }
-            if (share > 1) {
-                den = rows_sum<32>(den);
-#pragma unroll
-                for (int j = 0; j < MT - 1; ++j) acc[j] = rows_sum<32>(acc[j]);
-            }
+            if (share == 0) contract(std::integral_constant<int, 1>());
+            else if (share == 1) contract(std::integral_constant<int, 2>());
+            else contract(std::integral_constant<int, 4>());
             const double rden = rcp_normal(den);
             const int on = hit[l];                            // query l's own worker, if it is one's node
             const bool hits = __ballot(on >= 0) != 0ull;
