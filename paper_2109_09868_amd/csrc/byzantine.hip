@@ -1425,13 +1425,25 @@ int packed_groups(int64_t G, bool homogeneous) {
 }
 
 // ---- two lanes to a class: the library's own nodes, few workers missing ------------------------------------------------
+constexpr int kPairMostWorkers = 2 * 15 + 3 + kPairMaxMissing;            // of pair_shape
+
+// cos(i pi / (N - 1)), N up to kPairMostWorkers; evaluated once, by the first call (N / 2 cosines took 0.2 us of each call's 2.3 on the host).
+struct WorkerNodes {
+    double x[kPairMostWorkers + 1][(kPairMostWorkers + 1) / 2];
+    WorkerNodes() : x() {
+        constexpr double kPi = 3.14159265358979323846;
+        for (int N = 2; N <= kPairMostWorkers; ++N)
+            for (int i = 0; 2 * i < N; ++i) x[N][i] = std::cos(i * kPi / (N - 1));
+    }
+};
+
 // Whether the nodes are cos(i pi / (N - 1)) to a few roundings: the closed forms of locate_class_pair hold for these only.
 bool chebyshev_workers(const Nodes &nodes, int N) {
-    constexpr double kPi = 3.14159265358979323846;
+    static const WorkerNodes table;
     constexpr double kClose = 16.0 / (1ull << 53);
+    if (N > kPairMostWorkers) return false;
     for (int i = 0; 2 * i < N; ++i)
-        if (!(std::fabs(nodes.beta[i] - std::cos(i * kPi / (N - 1))) <= kClose) ||
-            !(std::fabs(nodes.beta[i] + nodes.beta[N - 1 - i]) <= kClose))
+        if (!(std::fabs(nodes.beta[i] - table.x[N][i]) <= kClose) || !(std::fabs(nodes.beta[i] + nodes.beta[N - 1 - i]) <= kClose))
             return false;
     return true;
 }
