@@ -816,6 +816,48 @@ __device__ __forceinline__ unsigned long long most_voted(const int *votes, int N
     return drop;
 }
 
+// The decoder contraction of one group by a workgroup of few waves: a wave takes all queries of 64 vector columns, so that it reads every row
+// once, and the next rows are on their way while it multiplies the last ones.
+template <int VEC, int QUADS>
+__device__ __forceinline__ void contract_columns(const float *__restrict__ pg, float *__restrict__ og, const int *F, int nF, int K, int KP,
+                                                 int64_t C, int64_t Cv, const double *WdT) {
+    typedef typename PredVec<VEC>::type V;
+    for (int64_t cv = static_cast<int64_t>(wave_id()) * kColsPerTile + lane_id(); cv < Cv; cv += kPairWaves * kColsPerTile) {
+        double acc[4 * QUADS][VEC];
+#pragma unroll
+        for (int j = 0; j < 4 * QUADS; ++j)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[j][e] = 0.0;
+        V ahead[kRowChunk];
+        load_row_chunk<VEC>(pg, F, nF, 0, C, cv, ahead);
+        for (int r0 = 0; r0 < nF; r0 += kRowChunk) {
+            V y[kRowChunk];
+#pragma unroll
+            for (int u = 0; u < kRowChunk; ++u) y[u] = ahead[u];
+            if (r0 + kRowChunk < nF) load_row_chunk<VEC>(pg, F, nF, r0 + kRowChunk, C, cv, ahead);
+#pragma unroll
+            for (int u = 0; u < kRowChunk; ++u) {
+                if (r0 + u < nF) {
+#pragma unroll
+                    for (int q = 0; q < QUADS; ++q) {
+                        if (4 * q < KP) {
+                            const double *w = WdT + (r0 + u) * KP + 4 * q;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                                for (int e = 0; e < VEC; ++e)
+                                    acc[4 * q + j][e] = fma(w[j], static_cast<double>(vec_get<VEC>(y[u], e)), acc[4 * q + j][e]);
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4 * QUADS; ++j)
+            if (j < K) store_row<VEC>(og + static_cast<size_t>(j) * C + cv * VEC, acc[j]);
+    }
+}
+
 // A workgroup takes `gpw` whole groups (C <= 128), a class to a pair of lanes, and decodes them, a row
 // of sixteen lanes to sixteen classes of a group:
 //     out[j][c] = (sum_i T[j][i] s_i y_ic) / (sum_i T[j][i] s_i),     T[j][i] = 1 / (alpha_j - beta_i),
@@ -1007,8 +1049,8 @@ __global__ __launch_bounds__(kPairThreads) __attribute__((amdgpu_waves_per_eu(kP
             __syncthreads();
             const float *pg = a.preds + static_cast<size_t>(g0) * N * a.C;
             float *og = a.out + static_cast<size_t>(g0) * K * a.C;
-            if (a.vec4) contract_group<4>(pg, og, F, nF, K, KP, a.C, a.C / 4, WdT);
-            else contract_group<1>(pg, og, F, nF, K, KP, a.C, a.C, WdT);
+            if (a.vec4) contract_columns<4, (MT + 2) / 4>(pg, og, F, nF, K, KP, a.C, a.C / 4, WdT);     // K < MT
+            else contract_columns<1, (MT + 2) / 4>(pg, og, F, nF, K, KP, a.C, a.C, WdT);
         }
         return;
     } else {
