@@ -154,12 +154,13 @@ int approxifer_decode(const float *d_preds, const uint8_t *d_mask, float *d_out,
  *             device scratch memory owned by the caller, 8-byte aligned, or NULL / 0; contents on entry and exit
  *             are meaningless, the call initialises what it uses.  Two things live there.
  *             (1) The vote of Algorithm 2's return step is the one place where the classes of a group meet.  With
- *             few groups and many classes the library spreads a group's classes over several workgroups, which
- *             pool their per-class picks in N vote counters and an arrival counter per group.
+ *             many classes the library spreads a group's over several workgroups, which pool their per-class
+ *             picks in N vote counters and an arrival counter per group.
  *             (2) Without stragglers (S = 0, the setting of the paper's Byzantine experiments, or
  *             APPROXIFER_S_FROM_MASK) every group whose mask is full fits the same node set: the part of
  *             Algorithm 2's system that does not depend on the predictions is then factorised once per call
- *             instead of once per group, and kept in the workspace.
+ *             instead of once per group, and kept in the workspace.  On the Chebyshev worker nodes with S = 0 most
+ *             shapes need no factorisation; the bytes are asked for all the same, for nodes of the caller's own.
  *             approxifer_workspace_bytes() gives the size that allows both.  With NULL, fewer bytes or a
  *             misaligned pointer the call uses what fits and is just as correct: d_out, d_adv and d_status hold
  *             the same bits; only time is lost (every group stays with one workgroup and repeats the
@@ -203,7 +204,8 @@ size_t approxifer_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t
  *   - A shape for which approxifer_workspace_bytes() exceeds APPROXIFER_STATIC_WORKSPACE_BYTES is refused
  *     with APPROXIFER_ERR_WORKSPACE_LIMIT before anything is enqueued (4 (N + 1) G bytes are needed when
  *     few groups bring hundreds of classes or more, up to 13 KiB when no stragglers are asked for; shapes
- *     that need no workspace are never refused).
+ *     that need no workspace are never refused, nor are more groups than fill the GPU with one workgroup each:
+ *     their votes are counted without the workspace where it has no room for them).
  *   - The device of `stream` must be the current device.  The first call on a device looks up the address
  *     of that device's copy of the array (no allocation, no synchronisation).
  *   - All calls on one GPU share that GPU's array.  Each call clears the part it uses with a kernel of
@@ -230,7 +232,7 @@ int approxifer_decode_byzantine_static(const float *d_preds, const uint8_t *d_ma
  * defined up to one factor, which the order of the |a_i| does not see.  Unlike Algorithm 2
  * this locator can find a worker whose node is exactly 0.  It costs a singular value
  * decomposition per class where Algorithm 2 costs a least-squares solve.
- * The iterations are bounded (24 rounds of inverse iteration, then at most 30 Jacobi sweeps); a
+ * The iterations are bounded (24 or 64 rounds of inverse iteration, then at most 30 Jacobi sweeps); a
  * class whose columns are still not orthogonal to rounding after that -- not observed on finite
  * data -- votes with the shortest column found so far, best effort, and no status reports it.
  * Arguments, requirements and error behaviour as approxifer_decode_byzantine().

@@ -182,11 +182,21 @@ int approxifer_decode_rational(const float *d_preds, const uint8_t *d_mask, floa
                                               static_cast<hipStream_t>(stream));
 }
 
+static size_t workspace_bytes_of(int64_t G, int K, int N, int S, int A, int64_t C, bool pairs) {
+    // the shapes the Byzantine decoders accept; anything else needs no workspace because the call is refused
+    if (G <= 0 || C <= 0 || K < 1 || K > APPROXIFER_MAX_K || N < 2 || N > APPROXIFER_MAX_N) return 0;
+    if (S < APPROXIFER_S_FROM_MASK || S >= N || A < 1) return 0;
+    const int most_available = S < 0 ? N : N - S;
+    if (most_available < 2 * (K + A) || (S >= 0 && N - S > APPROXIFER_MAX_AVAIL_BYZ)) return 0;
+    return approxifer::byzantine_workspace_bytes(G, K, N, S, A, C, pairs);
+}
+
 int approxifer_decode_byzantine_static(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_adv,
                                        int32_t *d_status, int64_t G, int K, int N, int S, int A, int64_t C,
                                        const double *h_alpha, const double *h_beta, int sign_mode, void *stream) {
     // shapes the decoder refuses are refused by the checked call below with their own codes (need is 0 for them)
-    const size_t need = approxifer_workspace_bytes(G, K, N, S, A, C);
+    size_t need = workspace_bytes_of(G, K, N, S, A, C, true);
+    if (need > APPROXIFER_STATIC_WORKSPACE_BYTES) need = workspace_bytes_of(G, K, N, S, A, C, false);
     if (need > APPROXIFER_STATIC_WORKSPACE_BYTES) return APPROXIFER_ERR_WORKSPACE_LIMIT;
     void *d_scratch = nullptr;
     if (need > 0) {
@@ -198,12 +208,7 @@ int approxifer_decode_byzantine_static(const float *d_preds, const uint8_t *d_ma
 }
 
 size_t approxifer_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t C) {
-    // the shapes the Byzantine decoders accept; anything else needs no workspace because the call is refused
-    if (G <= 0 || C <= 0 || K < 1 || K > APPROXIFER_MAX_K || N < 2 || N > APPROXIFER_MAX_N) return 0;
-    if (S < APPROXIFER_S_FROM_MASK || S >= N || A < 1) return 0;
-    const int most_available = S < 0 ? N : N - S;
-    if (most_available < 2 * (K + A) || (S >= 0 && N - S > APPROXIFER_MAX_AVAIL_BYZ)) return 0;
-    return approxifer::byzantine_workspace_bytes(G, K, N, S, A, C);
+    return workspace_bytes_of(G, K, N, S, A, C, true);
 }
 
 int approxifer_top1(const float *d_values, int32_t *d_top1, float *d_score, int64_t rows, int64_t C, void *stream) {

@@ -1471,6 +1471,14 @@ PairShape pair_shape(int K, int N, int S, int A, int64_t C, bool homogeneous) {
     return {mt, tq};
 }
 
+// Whether a call of many classes that pair_shape takes has a use for votes' cells in the workspace: a workgroup to every 128 classes then,
+// else one to a group that goes through them in turn.  Up to 512 groups, where one to each leaves places free (K = 8, A = 2, 20 of 24 workers, 300 of
+// 1000 classes 86 us with and 111 without, 900 of 300 89 and 85), and for Algorithm 2 with K + A = 13 and 14 and nobody missing, where the
+// split form alone has two waves to a SIMD (K = 12, A = 2, 513 groups of 130 55 and 81, 4000 of 130 282 and 418; K + A = 12: 224 and 177).
+bool pair_votes(int64_t G, int M, int S, int64_t C, bool homogeneous) {
+    return C > kPairClasses && (G <= 512 || (!homogeneous && S == 0 && (M == 13 || M == 14)));
+}
+
 // The rank-one term's inverse root for the rows of parity h: 1 + lift e e^T, e^T e = c, of the Gram matrix 1 - e e^T / (N - 1).
 double pair_lift(int N, int R, int h) {
     const double c = h ? R / 2 : (R + 1) / 2 - 0.5;
@@ -1672,7 +1680,7 @@ int launch_decode_rational(const float *d_preds, const uint8_t *d_mask, float *d
                                        nodes));
 }
 
-size_t byzantine_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t C) {
+size_t byzantine_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t C, bool pairs) {
     const int n = avail_capacity(N, S);
     const int M = K + A;
     bool splits = false;
@@ -1684,6 +1692,9 @@ size_t byzantine_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t 
         splits = general_shape(G, K, N, n, A, C, false, true).splits > 1;
     }
     splits = splits || general_shape(G, K, N, n, A, C, true, true).splits > 1;       // Algorithm 1's locator
+    // on the library's nodes, which this query is not told
+    for (const bool homogeneous : {false, true})
+        splits = splits || (pairs && pair_votes(G, M, S, C, homogeneous) && pair_shape(K, N, S, A, C, homogeneous).mt != 0);
     return basis + (splits ? votes_bytes(G, N) : 0);
 }
 
@@ -1699,7 +1710,7 @@ int launch_decode_byzantine(const float *d_preds, const uint8_t *d_mask, float *
 
     const PairShape pair = pair_shape(K, N, S, A, C, homogeneous);
     if (pair.mt != 0 && chebyshev_workers(nodes, N)) {
-        const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, C > kPairClasses ? votes_bytes(G, N) : 0);
+        const Carved meet = carve_workspace(d_workspace, workspace_bytes, 0, pair_votes(G, M, S, C, homogeneous) ? votes_bytes(G, N) : 0);
         return run_pairs_shape(pair, d_preds, d_mask, d_out, d_adv, d_status, G, K, N, S, A, C, vec4, nodes, sign_mode, homogeneous,
                                meet.votes, stream);
     }

@@ -132,7 +132,8 @@ int launch_decode_byzantine(const float *d_preds, const uint8_t *d_mask, float *
                             size_t workspace_bytes, hipStream_t stream);
 int launch_decode_rational(const float *d_preds, const uint8_t *d_mask, float *d_out, int32_t *d_status, int64_t G, int K,
                            int N, int S, int A, int64_t C, const Nodes &nodes, hipStream_t stream);
-size_t byzantine_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t C);
+// pairs: with what only the library's own nodes have a use for
+size_t byzantine_workspace_bytes(int64_t G, int K, int N, int S, int A, int64_t C, bool pairs);
 int static_workspace(void **d_ptr);
 
 int launch_argmax_rows(const float *d_values, int32_t *d_top1, float *d_score, int64_t rows, int64_t C,

@@ -94,6 +94,7 @@ def open_library(shim, path):
     lib.approxifer_workspace_bytes.restype = ctypes.c_size_t
     for name in ("approxifer_decode_byzantine", "approxifer_decode_byzantine_homogeneous"):
         getattr(lib, name).argtypes = [p, p, p, p, p, q, i, i, i, i, q, dp, dp, i, p, ctypes.c_size_t, p]
+    lib.approxifer_decode_byzantine_static.argtypes = [p, p, p, p, p, q, i, i, i, i, q, dp, dp, i, p]
     return lib, log
 
 
@@ -107,8 +108,8 @@ def _main():
         lib.approxifer_chebyshev_nodes(K, N, alpha, beta)
         need = lib.approxifer_workspace_bytes(c["G"], K, N, c["S"], c["A"], c["C"]) if c["workspace"] else 0
         log.launch_log_start(-1, 0)
-        rc = getattr(lib, c["entry"])(at, at, at, at, at, c["G"], K, N, c["S"], c["A"], c["C"], alpha, beta, 1, at if need else None,
-                                      need, None)
+        scratch = () if c["entry"].endswith("_static") else (at if need else None, need)
+        rc = getattr(lib, c["entry"])(at, at, at, at, at, c["G"], K, N, c["S"], c["A"], c["C"], alpha, beta, 1, *scratch, None)
         print(json.dumps([rc, log.launch_log().decode().split()]))
 
 

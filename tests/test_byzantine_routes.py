@@ -23,3 +23,23 @@ def test_the_number_of_groups_does_not_choose_the_locator(tmp_path, entry):
         assert len(tiles) == 1, (shape, tiles)
         taken += tiles != {None}
     assert taken > len(shapes) // 4
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_the_size_asked_for_is_the_size_that_is_used(tmp_path, entry):
+    # more than 128 classes: a workgroup to every 128 of them, and the launches that clear and read their votes, or one workgroup to a group
+    calls = [dict(entry=entry, G=G, K=K, A=A, S=S, N=2 * (K + A) + S, C=C, workspace=True)
+             for G in (3, 512, 513, 5000) for K, A, S in ((8, 2, 4), (8, 2, 0), (12, 2, 0), (12, 1, 0), (12, 1, 1), (4, 1, 1)) for C in (257, 1000)]
+    for c, (rc, names) in zip(calls, launch_log.launches(tmp_path, calls)):
+        split = c["G"] <= 512 or (entry == ENTRIES[0] and c["S"] == 0 and c["K"] == 12)
+        assert rc == 0 and [launch_log.pairs_tile(n) is not None for n in names] == ([False, True, False] if split else [True]), (c, names)
+
+
+def test_the_built_in_workspace_refuses_what_it_refused(tmp_path):
+    # votes that only the library's nodes have a use for are done without where they do not fit
+    entry = "approxifer_decode_byzantine_static"
+    refused = [dict(entry=entry, G=512, K=8, A=2, S=4, N=36, C=1000, workspace=False)]
+    accepted = [dict(entry=entry, G=G, K=8, A=2, S=4, N=24, C=C, workspace=False) for G, C in ((1000, 300), (1024, 1000), (5000, 129), (2048, 10))]
+    got = launch_log.launches(tmp_path, refused + accepted)
+    assert [rc for rc, _ in got] == [-8, 0, 0, 0, 0]
+    assert not got[0][1] and all(names for _, names in got[1:])
