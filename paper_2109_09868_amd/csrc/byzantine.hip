@@ -10,7 +10,7 @@
 // Four kernels compute the same thing:
 //
 //  * decode_byzantine_pairs_kernel (byzantine_pairs.h; the library's own worker nodes, a fixed number of at most four
-//    missing, K+A <= 15, up to two workers more than eq. (3) asks for: pair_shape).  Two lanes to a class; no factorisation,
+//    missing, K+A <= 15, up to two workers more than eq. (3) asks for, three with K+A odd: pair_shape).  Two lanes to a class; no factorisation,
 //    in the Chebyshev basis the projected system is sums of moments.
 //
 //  * decode_byzantine_proj_kernel (K+A <= 16, at most 48 available workers, n-M <= 32), one workgroup per

@@ -1204,7 +1204,7 @@ int run_pairs(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     return launch_status(launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kPairThreads), lds, stream, call, nodes));
 }
 
-// M rounded up to even, TQ = MT / 2 or one more.  Algorithm 1 with three missing is not built (pair_shape).
+// M rounded up to even, TQ = MT / 2 or one more.
 template <int MT, int TQ, bool HOMOG>
 int run_pairs_rows(const PairCall &call, const Nodes &nodes, hipStream_t stream) {
     switch (call.S) {

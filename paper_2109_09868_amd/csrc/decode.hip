@@ -603,7 +603,7 @@ __device__ __forceinline__ void best_step(Best &b) {
 // A workgroup of up to sixteen waves per (group, QN queries).  Every lane walks vectors of four classes with the queries'
 // accumulators and bests in registers; the next eight rows are on their way while the last eight are multiplied, across the end of
 // a vector too.  The parts of a group read the same rows, from the caches.  What one CU has in flight bounds it (128 KB and 2 us a chunk
-// of eight rows: 45 GB/s): K = 9, eight groups of 22613 classes, rows only 4-byte aligned, 72 us with a workgroup per quad of
+// of eight rows: 65 GB/s): K = 9, eight groups of 22613 classes, rows only 4-byte aligned, 72 us with a workgroup per quad of
 // queries and 4-byte loads one chunk at a time, 26 this way; without a hint against the caches, and without loads for the rows
 // that the last chunk lacks, which took 39.  A group's classes over several workgroups would need a place for their bests.
 // dynamic LDS: double WdT[(N-S) QN] | alpha_s[K] | beta_s[N] | int F[N] | int n | pad to 16 bytes | Best merged[QN][waves].
